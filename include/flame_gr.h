@@ -34,7 +34,7 @@
  *     pointer is INVALID_ARGUMENT.
  *
  * Arithmetic of the two element types
- *   - FLAME_GR_F32: fp32 operands, fp32 accumulation, plain FMA kernels.
+ *   - FLAME_GR_F32: fp32 operands, fp32 accumulation (fp32 matrix instructions).
  *   - FLAME_GR_BF16 names the STORAGE type at this boundary: embeddings, W1, b1, ln_g, ln_b, W2, b2 and w_s
  *     arrive as bf16.  Inside, the matrix instructions run on IEEE binary16 (fp16) operands with fp32
  *     accumulation: embeddings and projection matrices are converted bf16 -> fp16 once, and the
@@ -312,7 +312,7 @@ int flame_gr_host_plan(const flame_gr_config *cfg, const int32_t *history_offset
  * is CAPACITY_EXCEEDED, which can only happen when max_seq_tokens splits requests (every chunk repeats the
  * history).  Device memory per row with FLAME_GR_BF16: 14*d bytes (the residual as two
  * fp16 words, four fp16 planes, the attention output; 16*d for model widths whose output projection is not fused),
- * 28*d with FLAME_GR_F32, plus 4*d*n_layers with kv_cache. */
+ * 24*d with FLAME_GR_F32, plus 4*d*n_layers with kv_cache. */
 int flame_gr_host_workspace_rows(const flame_gr_config *cfg, int64_t *rows);
 
 /* Plan of the two-stage path: as flame_gr_host_plan, but with candidate rows reserved for

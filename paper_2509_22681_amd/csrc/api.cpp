@@ -250,7 +250,7 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, const voi
       if (mode == PASS_HISTORY) { it = hitems + G.hitem_begin; n_it = G.hitem_end - G.hitem_begin; }
       else if (mode == PASS_CANDIDATES || last) { it = citems + G.citem_begin; n_it = G.citem_end - G.citem_begin; }
       if (dt == FLAME_GR_BF16) launch_attn_bf16(pp, bias_l, tscale_l, h->O, it, n_it, sh, s);
-      else launch_attn_f32((const float *)planes, bias_l, tscale_l, (float *)h->O, it, n_it, h->q_tile, sh, s);
+      else launch_attn_f32((const float *)planes, bias_l, tscale_l, (float *)h->O, it, n_it, sh, s);
     }
     const int32_t *bl = mode == PASS_FULL ? (last ? cl : nullptr) : pass_list;
     const int nb = mode == PASS_FULL ? (last ? n_cblk : n_blk) : pass_n;
@@ -258,14 +258,17 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, const voi
     if (dt == FLAME_GR_BF16 && k3_fused_supported(d)) {
       Timed t(h, KIND_OUTPROJ, s);
       launch_k3_fused(h->O, planes, lg, lb, (const char *)h->W2p + (size_t)l * d * d * e, b2, h->Xb, h->Xl, l == 0, blocks, bl, nb, bf, sh, s);
-    } else {
+    } else if (dt == FLAME_GR_BF16) {
       {
         Timed t(h, KIND_LNGATE, s);
-        launch_ln_gate(dt, h->O, planes, lg, lb, h->G, blocks, bl, nb, bf, d, sh.eps, s);
+        launch_ln_gate(h->O, planes, lg, lb, h->G, blocks, bl, nb, bf, d, sh.eps, s);
       }
       Timed t(h, KIND_OUTPROJ, s);
-      if (dt == FLAME_GR_BF16) launch_outproj_bf16(h->G, w2, b2, h->Xb, h->Xl, l == 0, bl, nb, bf, sh, s);
-      else launch_outproj_f32((const float *)h->G, (const float *)w2, (const float *)b2, h->X, bl, nb, bf, sh, s);
+      launch_outproj_bf16(h->G, w2, b2, h->Xb, h->Xl, l == 0, bl, nb, bf, sh, s);
+    } else {
+      Timed t(h, KIND_OUTPROJ, s);
+      launch_outproj_f32((const float *)h->O, (const float *)planes, (const float *)lg, (const float *)lb, (const float *)w2, (const float *)b2, h->X,
+                         blocks, bl, nb, bf, sh, s);
     }
     if (capture && h->cap_planes) {
       const size_t r0 = (size_t)G.row_begin * d, nr = (size_t)(G.row_end - G.row_begin) * d;
@@ -451,7 +454,7 @@ int flame_gr_create(const flame_gr_config *cfg_in, flame_gr_t **out) {
   CR(hipMalloc(&h->planes, 4 * h->plane_bytes));
   if (cfg.kv_cache) CR(hipMalloc((void **)&h->kv, (size_t)cfg.n_layers * 2 * h->plane_bytes));
   CR(hipMalloc(&h->O, rows * d * e));
-  const bool need_g = !mfma_path || !k3_fused_supported(cfg.d_model);      // the fused K3 keeps the gated rows in LDS
+  const bool need_g = mfma_path && !k3_fused_supported(cfg.d_model);       // otherwise the gated rows stay in LDS
   if (need_g) CR(hipMalloc(&h->G, rows * d * e));
   if (mfma_path) {
     CR(hipMalloc(&h->Xb, rows * d * e));

@@ -29,9 +29,9 @@ void launch_bf16_to_f16(const void *in, void *out, int64_t rows, int K, bool blo
 // MFMA path, whose attention kernel works on halved logits; 1 in the fp32 path).
 void launch_expand_bias(const float *rab, const int32_t *bucket_tab, float *bias, int n_lh,
                         int n_buckets, int D, float scale, hipStream_t s);
-// G = (LayerNorm(O) * gamma + beta) * U, one row at a time (element type of O, U, G = dtype);
+// G = (LayerNorm(O) * gamma + beta) * U, one row at a time (MFMA path, for widths whose output projection is not fused with it);
 // padding rows of a block get G = 0 so that they stay finite through the layers.
-void launch_ln_gate(int dtype, const void *O, const void *U, const void *gamma, const void *beta,
+void launch_ln_gate(const void *O, const void *U, const void *gamma, const void *beta,
                     void *G, const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first, int d,
                     float eps, hipStream_t s);
 // scores[src_row + i] = <X[row], w_s> + b_s for the valid rows of every candidate block (MFMA path: X = Xh + Xl).
@@ -60,17 +60,18 @@ void launch_clear_spare(void *K, void *Vt, int d, int64_t ws_rows, int64_t row0,
 void launch_debug_mask(int L, int M, const int32_t *bucket_tab, int D, uint8_t *mask, int32_t *bucket,
                        hipStream_t s);
 
-// ---- fp32 path (kernels_f32.hip): plain FMA kernels, correctness first ------------------------
+// ---- fp32 path (kernels_f32.hip): the fp32 matrix instruction ----------------------------------
 // planes[p][row][n] = silu(X W1^T + b1), p = U,V,Q,K; rows = 64-row blocks [blk_first, blk_first+n_blk)
 void launch_uvqk_f32(const float *X, const float *W1, const float *b1, float *planes, int blk_first,
                      int n_blk, const Shape &sh, hipStream_t s);
 // tscale_h (softmax only): per head, the factor from the logit the kernel forms to the exponent it feeds to
 // its exponential: 1 / tau here (natural exponential of the full logit).
 void launch_attn_f32(const float *planes, const float *bias_lh, const float *tscale_h, float *O, const AttnItem *items,
-                     int n_items, int q_tile, const Shape &sh, hipStream_t s);
-// X[row] += G[row] W2^T + b2 for the rows of the listed blocks (blk_list == nullptr: contiguous)
-void launch_outproj_f32(const float *G, const float *W2, const float *b2, float *X,
-                        const int32_t *blk_list, int n_blk, int blk_first, const Shape &sh, hipStream_t s);
+                     int n_items, const Shape &sh, hipStream_t s);
+// X[row] += ((LayerNorm(O[row]) * gamma + beta) * U[row]) W2^T + b2 for the rows of the listed blocks (blk_list == nullptr:
+// contiguous); padding rows of a block get the bias only, so that they stay finite through the layers.
+void launch_outproj_f32(const float *O, const float *U, const float *gamma, const float *beta, const float *W2, const float *b2, float *X,
+                        const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first, const Shape &sh, hipStream_t s);
 
 // The four activation planes of a layer (MFMA path), each [ws_rows][d] fp16 (V feature-major [d][ws_rows]).  The
 // one-pass forward keeps them in one allocation; the two-stage path points v and k at the layer's cache.

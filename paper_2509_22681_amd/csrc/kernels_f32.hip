@@ -1,155 +1,486 @@
-// fp32 instantiation of the GR block: plain FMA kernels with LDS tiling.  This path exists for
-// the 1e-4 parity case and for any shape the MFMA path does not cover; it is not tuned.
+// fp32 instantiation of the GR block, on the fp32 matrix instruction (32 x 32 x 2: fp32 operands and accumulator, the
+// arithmetic of a chain of FMAs).  It serves the 1e-4 parity case and every shape the fp16 kernels do not cover.
+//
+// Operand layout of that instruction, used throughout: acc[i][j] += sum over two k slots of A[i][k] B[j][k]; lane l
+// supplies row l & 31 of either operand for k slot l >> 5.  A lane reads four consecutive floats of its row at offset
+// 4 (l >> 5) of every group of eight, which feeds four instructions (slots {8 g + t, 8 g + 4 + t}) from one 16-byte load.
+// Accumulator element e of a lane is row 8 (e / 4) + 4 (l >> 5) + e % 4 of A, row l & 31 of B.
 #include "device_common.h"
 #include "kernels.h"
 
 namespace flame {
 
+namespace {
+
+__device__ __forceinline__ void mfma_f32_k8(const f32x4 a, const f32x4 b, f32x16 &acc) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t], b[t], acc, 0, 0, 0);
+}
+
+// Four consecutive floats p[k..k+3], zero where k >= K.  VEC: rows are 16-byte aligned and K is a multiple of 4.
+template <bool VEC>
+__device__ __forceinline__ f32x4 load4(const float *p, int k, int K) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (VEC) {
+    if (k < K) v = *(const f32x4 *)(p + k);
+  } else {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      if (k + t < K) v[t] = p[k + t];
+  }
+  return v;
+}
+
+// Sum over the 16 lanes of a row of lanes, delivered to all of them.
+__device__ __forceinline__ float row16_sum(float v) {
+  v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x128, 0xf, 0xf, false));  // row_ror:8
+  v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x124, 0xf, 0xf, false));  // row_ror:4
+  v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x122, 0xf, 0xf, false));  // row_ror:2
+  v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x121, 0xf, 0xf, false));  // row_ror:1
+  return v;
+}
+
+}  // namespace
+
 // ---------------------------------------------------------------------------------------------
-// C[m][n] = sum_k A[m][k] W[n][k] + bias[n] over 64-row blocks, 64x64 tile, 16-deep k chunks,
-// 256 threads each owning a 4x4 patch.  EPI 0: silu -> planes[n / d][m][n % d].
-// EPI 1: X[m][n] += value (residual update in place).
+// C[m][n] = sum_k A[m][k] W[n][k] + bias[n] on 64-row blocks.  256 threads = 2 x 2 wavefronts of 32 T x 32 T outputs, so a
+// (64 T)^2 tile per workgroup; k in chunks of 32 through two LDS stages (one barrier per chunk, the next chunk's loads in
+// flight under the current one's matrix work).  LDS rows are 128 bytes, 16-byte chunks XOR-swizzled by row / 2, which the
+// fragment reads take without bank conflicts.
+// EPI 0: planes[n / d][m][n % d] = silu(C) with A = X.
+// EPI 1: X[m][n] += C with A = (LayerNorm(O) * gamma + beta) * U, made while the chunk is staged: the statistics of the 64
+//        rows come first (mean, then the centred second moment), and the gated rows never travel through memory.
+// The matrix rate is the bound for large batches (64 cycles per instruction), latency for small ones.  20 480 rows, d = 256:
+// K1 260 -> 106 us (10.7 GFLOP at 101 TFLOP/s; the instruction alone reaches 157), LN, gate and output projection 71 + 11 -> 47 us,
+// against plain FMA kernels on 64 x 64 tiles with a LayerNorm pass of its own.
 // ---------------------------------------------------------------------------------------------
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W,
-                                                       const float *__restrict__ bias, float *__restrict__ out,
-                                                       const int32_t *__restrict__ blk_list, int blk_first,
-                                                       int K, int Ncols, int d, int64_t plane_stride) {
-  __shared__ float sA[16][64 + 1];
-  __shared__ float sW[16][64 + 1];
-  const int blk = blk_list ? blk_list[blockIdx.x] : blk_first + blockIdx.x;
-  const int64_t row0 = (int64_t)blk * kRowAlign;
-  const int n0 = blockIdx.y * 64;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int i = threadIdx.x; i < 64 * 16; i += 256) {
-      const int r = i >> 4, k = i & 15;
-      sA[k][r] = (k0 + k < K) ? A[(row0 + r) * K + k0 + k] : 0.f;
-      sW[k][r] = (k0 + k < K && n0 + r < Ncols) ? W[(int64_t)(n0 + r) * K + k0 + k] : 0.f;
-    }
-    __syncthreads();
+// NI (EPI 1): 16-byte loads per lane and row that the statistics keep in registers, ceil(K / 64) at least; 0: any K, in two reads of the rows.
+template <int EPI, int T, bool VEC, int NI>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ U, const float *__restrict__ gamma,
+                                                       const float *__restrict__ beta, const RowBlock *__restrict__ blocks, float eps,
+                                                       const float *__restrict__ W, const float *__restrict__ bias, float *__restrict__ out,
+                                                       const int32_t *__restrict__ blk_list, int blk_first, int n_blk, int K, int Ncols, int d,
+                                                       int64_t plane_stride) {
+  constexpr int BT = 64 * T, BK = 32, LPT = BT / 32;      // tile side, k chunk, 16-byte loads per thread and operand
+  __shared__ __attribute__((aligned(256))) float sA[2][BT * BK];
+  __shared__ __attribute__((aligned(256))) float sW[2][BT * BK];
+  __shared__ float s_mu[EPI == 1 ? 64 : 1], s_rstd[EPI == 1 ? 64 : 1];
+  static_assert(EPI == 0 || T == 1, "row statistics are kept for one block of rows");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, lhalf = lane >> 5;
+  const int n0 = blockIdx.y * BT;
+  int64_t row0[T];
+  bool present[T];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float a[4], w[4];
+  for (int t = 0; t < T; ++t) {
+    const int i = blockIdx.x * T + t;
+    present[t] = i < n_blk;
+    const int ic = present[t] ? i : n_blk - 1;
+    row0[t] = (int64_t)(blk_list ? blk_list[ic] : blk_first + ic) * kRowAlign;
+  }
+  int n_valid = kRowAlign;
+  if constexpr (EPI == 1) {
+    n_valid = blocks[row0[0] / kRowAlign].n_valid;
+    if constexpr (NI > 0) {
+      // statistics: 16 lanes per row, four rows of a wavefront at a time, all of its rows' loads in flight together
+      // (up to 16 x 16 bytes per lane), so that the memory latency is paid once or twice and not once per row
+      constexpr int RB = NI > 4 ? 2 : 4;             // row groups per round
+      const int c16 = lane & 15, rq = lane >> 4;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) { a[i] = sA[k][ty * 4 + i]; w[i] = sW[k][tx * 4 + i]; }
+      for (int g0 = 0; g0 < 4; g0 += RB) {
+        f32x4 v[RB][NI];
+        float mu[RB], sq[RB];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+        for (int g = 0; g < RB; ++g)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
+          for (int i = 0; i < NI; ++i)
+            v[g][i] = load4<true>(A + (row0[0] + wave * 16 + 4 * (g0 + g) + rq) * K, 4 * (c16 + 16 * i), K);
+#pragma unroll
+        for (int g = 0; g < RB; ++g) {
+          mu[g] = 0.f;
+#pragma unroll
+          for (int i = 0; i < NI; ++i) mu[g] += (v[g][i][0] + v[g][i][1]) + (v[g][i][2] + v[g][i][3]);
+        }
+#pragma unroll
+        for (int g = 0; g < RB; ++g) mu[g] = row16_sum(mu[g]) / (float)K;
+#pragma unroll
+        for (int g = 0; g < RB; ++g) {
+          sq[g] = 0.f;
+#pragma unroll
+          for (int i = 0; i < NI; ++i)
+            if (4 * (c16 + 16 * i) < K) {
+#pragma unroll
+              for (int t = 0; t < 4; ++t) { const float c = v[g][i][t] - mu[g]; sq[g] += c * c; }
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < RB; ++g) {
+          const float rstd = rsqrtf(row16_sum(sq[g]) / (float)K + eps);
+          const int r = wave * 16 + 4 * (g0 + g) + rq;
+          if (c16 == 0) { s_mu[r] = mu[g]; s_rstd[r] = rstd; }
+        }
+      }
+    } else {
+      for (int b = 0; b < 4; ++b) {
+        const int r = wave * 16 + 4 * b;
+        const float *o = A + (row0[0] + r) * K;
+        float s[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int k = lane; k < K; k += 64)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) s[q] += o[(int64_t)q * K + k];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s[q] = wave_sum(s[q]) / (float)K;
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int k = lane; k < K; k += 64)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) { const float c = o[(int64_t)q * K + k] - s[q]; v[q] += c * c; }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          v[q] = rsqrtf(wave_sum(v[q]) / (float)K + eps);
+          if (lane == 0) { s_mu[r + q] = s[q]; s_rstd[r + q] = v[q]; }
+        }
+      }
     }
     __syncthreads();
   }
+  // staging: thread (row = tid / 8 + 32 i, chunk = tid % 8) brings 16 bytes of either operand
+  const int sr = tid >> 3, sc = tid & 7;
+  f32x4 ra[LPT], rw[LPT];
+  auto fetch = [&](int k0) {
+    const int k = k0 + 4 * sc;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < LPT; ++i) {
+      const int r = sr + 32 * i;
+      const int64_t m = row0[T == 1 ? 0 : r >> 6] + (r & 63);
+      ra[i] = load4<VEC>(A + m * K, k, K);
+      if constexpr (EPI == 1) {
+        const f32x4 u = load4<VEC>(U + m * K, k, K), g = load4<VEC>(gamma, k, K), b = load4<VEC>(beta, k, K);
+        const float mu = s_mu[r], rstd = s_rstd[r];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      const int64_t m = row0 + ty * 4 + i;
-      if (n >= Ncols) continue;
-      const float v = acc[i][j] + bias[n];
-      if (EPI == 0) out[(int64_t)(n / d) * plane_stride + m * d + (n % d)] = silu_f32(v);
-      else out[m * Ncols + n] += v;
+        for (int t = 0; t < 4; ++t) ra[i][t] = r < n_valid ? ((ra[i][t] - mu) * rstd * g[t] + b[t]) * u[t] : 0.f;
+      }
+      const int n = n0 + r;
+      rw[i] = n < Ncols ? load4<VEC>(W + (int64_t)n * K, k, K) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
+  };
+  auto store = [&](int st) {
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) {
+      const int r = sr + 32 * i, off = r * BK + ((sc ^ ((r >> 1) & 7)) << 2);
+      *(f32x4 *)(sA[st] + off) = ra[i];
+      *(f32x4 *)(sW[st] + off) = rw[i];
+    }
+  };
+  f32x16 acc[T][T];
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int j = 0; j < T; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  fetch(0);
+  store(0);
+  __syncthreads();
+  const int nk = (K + BK - 1) / BK;
+  for (int kc = 0; kc < nk; ++kc) {
+    const int st = kc & 1;
+    if (kc + 1 < nk) fetch((kc + 1) * BK);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      f32x4 fa[T], fw[T];
+#pragma unroll
+      for (int i = 0; i < T; ++i) {
+        const int r = wm * 32 * T + 32 * i + l32, q = wn * 32 * T + 32 * i + l32;
+        fa[i] = *(const f32x4 *)(sA[st] + r * BK + (((2 * s + lhalf) ^ ((r >> 1) & 7)) << 2));
+        fw[i] = *(const f32x4 *)(sW[st] + q * BK + (((2 * s + lhalf) ^ ((q >> 1) & 7)) << 2));
+      }
+#pragma unroll
+      for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = 0; j < T; ++j) mfma_f32_k8(fa[i], fw[j], acc[i][j]);
+    }
+    if (kc + 1 < nk) store(st ^ 1);       // the other stage: everybody left it at the barrier that opened this chunk
+    __syncthreads();
+  }
+  // a lane holds one output column and 16 rows: 32 lanes write 128 contiguous bytes of a row
+#pragma unroll
+  for (int j = 0; j < T; ++j) {
+    const int n = n0 + wn * 32 * T + 32 * j + l32;
+    if (n >= Ncols) continue;
+    const float bn = bias[n];
+    float *col = EPI == 0 ? out + (int64_t)(n / d) * plane_stride + n % d : out + n;
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+      const int rb = wm * 32 * T + 32 * i, blk = T == 1 ? 0 : rb >> 6;
+      if (!present[blk]) continue;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int64_t m = row0[blk] + (rb & 63) + 8 * (e >> 2) + 4 * lhalf + (e & 3);
+        const float v = acc[i][j][e] + bn;
+        if (EPI == 0) col[m * d] = silu_f32(v);
+        else col[m * d] += v;
+      }
+    }
+  }
 }
+
+// 16-byte loads of the operands: rows of the workspaces start on 16 bytes when d does; weights where the caller put them
+static bool vec4_rows(int d, const void *p) { return d % 4 == 0 && (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 void launch_uvqk_f32(const float *X, const float *W1, const float *b1, float *planes, int blk_first, int n_blk,
                      const Shape &sh, hipStream_t s) {
   if (n_blk <= 0) return;
-  dim3 grid(n_blk, (4 * sh.d + 63) / 64);
-  gemm_f32_kernel<0><<<grid, 256, 0, s>>>(X, W1, b1, planes, nullptr, blk_first, sh.d, 4 * sh.d, sh.d, sh.ws_rows * sh.d);
+  const int N = 4 * sh.d;
+  const bool vec = vec4_rows(sh.d, W1);
+#define UVQK_CASE(TT, VV) gemm_f32_kernel<0, TT, VV, 0><<<dim3((n_blk + TT - 1) / TT, (N + 64 * TT - 1) / (64 * TT)), 256, 0, s>>>( \
+      X, nullptr, nullptr, nullptr, nullptr, 0.f, W1, b1, planes, nullptr, blk_first, n_blk, sh.d, N, sh.d, sh.ws_rows * sh.d)
+  // 128 x 128 tiles halve the operand traffic; a launch needs enough of them for two per compute unit
+  const bool big = (int64_t)((n_blk + 1) / 2) * ((N + 127) / 128) >= 512;
+  if (vec) { if (big) UVQK_CASE(2, true); else UVQK_CASE(1, true); }
+  else UVQK_CASE(1, false);
+#undef UVQK_CASE
 }
 
-void launch_outproj_f32(const float *G, const float *W2, const float *b2, float *X, const int32_t *blk_list,
-                        int n_blk, int blk_first, const Shape &sh, hipStream_t s) {
+void launch_outproj_f32(const float *O, const float *U, const float *gamma, const float *beta, const float *W2, const float *b2, float *X,
+                        const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first, const Shape &sh, hipStream_t s) {
   if (n_blk <= 0) return;
-  dim3 grid(n_blk, (sh.d + 63) / 64);
-  gemm_f32_kernel<1><<<grid, 256, 0, s>>>(G, W2, b2, X, blk_list, blk_first, sh.d, sh.d, sh.d, 0);
+  const dim3 grid(n_blk, (sh.d + 63) / 64);
+#define OUT_CASE(VV, NI) gemm_f32_kernel<1, 1, VV, NI><<<grid, 256, 0, s>>>(O, U, gamma, beta, blocks, sh.eps, W2, b2, X, blk_list, blk_first, n_blk, sh.d, sh.d, sh.d, 0)
+  if (vec4_rows(sh.d, W2) && vec4_rows(sh.d, gamma) && vec4_rows(sh.d, beta)) {
+    if (sh.d <= 64) OUT_CASE(true, 1);
+    else if (sh.d <= 128) OUT_CASE(true, 2);
+    else if (sh.d <= 256) OUT_CASE(true, 4);
+    else if (sh.d <= 512) OUT_CASE(true, 8);
+    else OUT_CASE(true, 0);
+  } else {
+    OUT_CASE(false, 0);
+  }
+#undef OUT_CASE
 }
 
 // ---------------------------------------------------------------------------------------------
-// Attention, one wavefront per query row.  Keys are taken 64 at a time: lane c computes
-// silu(alpha <Q_r,K_c> + bias[p_r - p_c]) for its key, the 64 weights go through LDS, then lane j
-// accumulates sum_c weight_c V_c[j].  Fixed summation order: results are run-to-run identical.
+// Attention.  One workgroup = 64 query rows of one head, four wavefronts: two groups of 32 rows, each served by two wavefronts
+// that take every other block of 32 keys and add up at the end (in a fixed order).  Transposed products as in the fp16
+// kernel: S^T = K Q^T puts 16 keys of one query into a lane, in the very slots that O^T += V^T P^T takes as its B operand
+// (instruction e of a block multiplies keys 8 (e / 4) + e % 4 and + 4), so the weights never leave their registers.
+// Operands come straight from global memory: a block of 32 keys is 64 matrix instructions of 64 cycles (head width 64) against 16 KB
+// of K and V, which L1 and L2 deliver many times over, and no barrier ties the wavefronts together.  The matrix rate bounds it.
+// DB = 32-wide blocks of the head; EXACT: the head is exactly 32 DB wide (vector loads), else elements past it count as zero.
+// A lane's V operand of block b is feature DB * row + b, so that one load brings a lane's features of all blocks.
 // ---------------------------------------------------------------------------------------------
-template <bool SOFTMAX>
+template <int DB, bool EXACT, bool SOFTMAX>
 __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__ U_V_Q_K, const float *__restrict__ bias_lh,
                                                        const float *__restrict__ tscale_h,
                                                        float *__restrict__ O, const AttnItem *__restrict__ items,
-                                                       int q_tile, int d, int dh, int D, float alpha, int64_t plane_stride) {
-  __shared__ float sQ[4][256];
-  __shared__ float sP[4][64];
-  const AttnItem it = items[blockIdx.x];
-  const int h = blockIdx.y;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+                                                       int d, int dh, int D, float alpha, int64_t plane_stride) {
+  constexpr int NG = 4 * DB;                         // groups of eight features
+  constexpr int DBR = DB < 4 ? DB : 4;               // head blocks that leave per round at the end
+  constexpr int PITCH = 32 * DBR + 4;                // floats per row of the output patch of 32 query rows
+  __shared__ __attribute__((aligned(16))) float s_patch[2][32 * PITCH];
+  __shared__ float s_state[2][2][64], s_row[2][2][32];
+  const AttnItem it = items[blockIdx.y];             // heads of an item side by side: the longest items of all heads start first
+  const int h = blockIdx.x;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l32 = lane & 31, lhalf = lane >> 5;
+  const int qg = wave & 1, split = wave >> 1;
   const float *Vp = U_V_Q_K + 1 * plane_stride + h * dh;
   const float *Qp = U_V_Q_K + 2 * plane_stride + h * dh;
   const float *Kp = U_V_Q_K + 3 * plane_stride + h * dh;
   const float *bias = bias_lh + (int64_t)h * D;
-  for (int qi = wave; qi < it.n_q; qi += 4) {
-    const int64_t qrow = it.q_row + qi;
-    const int q_index = it.is_cand ? it.L : it.q_pos + qi;
-    const int n_vis = visible_history(it.is_cand, q_index, it.L);
-    for (int k = lane; k < dh; k += 64) sQ[wave][k] = Qp[qrow * d + k];
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    // softmax: running maximum and sum of the row (in units of the scaled logit), a finite stand-in for -inf
-    constexpr float kNeg = -1.0e30f;
-    const float ts = SOFTMAX ? tscale_h[h] : 0.f;
-    float m_run = kNeg, l_run = 0.f;
-    // history keys, then (candidates only) the row itself as one more key at distance 0
-    const int n_keys = n_vis + (it.is_cand ? 1 : 0);
-    for (int c0 = 0; c0 < n_keys; c0 += 64) {
-      const int c = c0 + lane;
-      float p = 0.f, z = kNeg;
-      if (c < n_keys) {
-        const bool self = c >= n_vis;
-        const int64_t krow = self ? qrow : (int64_t)it.kv_row + c;
-        const int delta = self ? 0 : q_index - c;
-        float dot = 0.f;
-        for (int k = 0; k < dh; ++k) dot = fmaf(sQ[wave][k], Kp[krow * d + k], dot);
-        const float logit = alpha * dot + bias[delta < D ? delta : D - 1];
-        if (SOFTMAX) z = logit * ts;
-        else p = silu_f32(logit);
-      }
-      if (SOFTMAX) {
-        const float m_new = fmaxf(m_run, wave_max(z));
-        const float sc = expf(m_run - m_new);
-        p = c < n_keys ? expf(z - m_new) : 0.f;
-        l_run = l_run * sc + wave_sum(p);
+  const int q0 = qg * 32;
+  const bool active = q0 < it.n_q;
+  const int q_local = q0 + l32;
+  const bool row_valid = q_local < it.n_q;
+  const int64_t qrow = it.q_row + (row_valid ? q_local : it.n_q - 1);        // clamped for the loads
+  const int q_index = it.is_cand ? it.L : it.q_pos + q_local;
+  const int n_vis = row_valid ? visible_history(it.is_cand, q_index, it.L) : 0;
+  const int vis_max = active ? (it.is_cand ? it.L : min(it.q_pos + q0 + 32, it.n_kv)) : 0;
+  constexpr float kNeg = -1.0e30f;                   // a finite stand-in for -inf
+  const float ts = SOFTMAX ? tscale_h[h] : 0.f;
+  float m_run = kNeg, l_run = 0.f;                   // softmax: running maximum of my row, and the sum over this lane's keys
+  // features 8 g + 4 lhalf + 0..3 of a row
+  auto row4 = [&](const float *row, int g) {
+    const int k = 8 * g + 4 * lhalf;
+    if constexpr (EXACT) return *(const f32x4 *)(row + k);
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j] *= sc;
-        m_run = m_new;
-      }
-      sP[wave][lane] = p;
-      const int cn = min(64, n_keys - c0);
-      for (int cc = 0; cc < cn; ++cc) {
-        const bool self = c0 + cc >= n_vis;
-        const int64_t vrow = self ? qrow : (int64_t)it.kv_row + c0 + cc;
-        const float pw = sP[wave][cc];
+    for (int t = 0; t < 4; ++t)
+      if (k + t < dh) v[t] = row[k + t];
+    return v;
+  };
+  f32x4 fq[NG];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int k = lane + j * 64;
-          if (k < dh) acc[j] = fmaf(pw, Vp[vrow * d + k], acc[j]);
-        }
+  for (int g = 0; g < NG; ++g) fq[g] = row4(Qp + qrow * d, g);
+  f32x16 oacc[DB];
+#pragma unroll
+  for (int b = 0; b < DB; ++b)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) oacc[b][e] = 0.f;
+  f32x4 fk[NG];
+  auto load_k = [&](int k0) {
+#pragma unroll
+    for (int g = 0; g < NG; ++g) fk[g] = row4(Kp + ((int64_t)it.kv_row + k0 + l32) * d, g);
+  };
+  const int first = split * 32, pitch = 64;
+  if (first < vis_max) load_k(first);
+  for (int k0 = first; k0 < vis_max; k0 += pitch) {
+    // V and the bias of this block are requested ahead of its S, K of the next block ahead of its V^T P
+    float fv[16][DB], bz[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int c = k0 + 8 * (e >> 2) + 4 * lhalf + (e & 3);
+      const float *vr = Vp + ((int64_t)it.kv_row + c) * d + DB * l32;
+      if constexpr (EXACT && DB == 2) { const float2 v = *(const float2 *)vr; fv[e][0] = v.x; fv[e][1] = v.y; }
+      else if constexpr (EXACT && DB == 4) { const f32x4 v = *(const f32x4 *)vr; for (int b = 0; b < DB; ++b) fv[e][b] = v[b]; }
+      else {
+#pragma unroll
+        for (int b = 0; b < DB; ++b) fv[e][b] = EXACT || DB * l32 + b < dh ? vr[b] : 0.f;
+      }
+      bz[e] = bias[max(0, min(D - 1, q_index - c))];
+    }
+    f32x16 sacc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) sacc[e] = 0.f;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) mfma_f32_k8(fk[g], fq[g], sacc);
+    if (k0 + pitch < vis_max) load_k(k0 + pitch);
+    float p[16];
+    if constexpr (SOFTMAX) {
+      float mt = kNeg;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int c = k0 + 8 * (e >> 2) + 4 * lhalf + (e & 3);
+        p[e] = c < n_vis ? (alpha * sacc[e] + bz[e]) * ts : kNeg;
+        mt = fmaxf(mt, p[e]);
+      }
+      const float m_new = fmaxf(m_run, pair_max(mt));
+      const float sc = expf(m_run - m_new);
+      m_run = m_new;
+      l_run *= sc;
+#pragma unroll
+      for (int b = 0; b < DB; ++b)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) oacc[b][e] *= sc;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int c = k0 + 8 * (e >> 2) + 4 * lhalf + (e & 3);
+        p[e] = c < n_vis ? expf(p[e] - m_new) : 0.f;
+        l_run += p[e];
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int c = k0 + 8 * (e >> 2) + 4 * lhalf + (e & 3);
+        p[e] = c < n_vis ? silu_f32(alpha * sacc[e] + bz[e]) : 0.f;
       }
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int k = lane + j * 64;
-      if (k < dh) O[qrow * d + h * dh + k] = SOFTMAX ? acc[j] / l_run : acc[j];
+    for (int e = 0; e < 16; ++e)
+#pragma unroll
+      for (int b = 0; b < DB; ++b) oacc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fv[e][b], p[e], oacc[b], 0, 0, 0);
+  }
+  // ---- the two wavefronts of a row group add up, and the rows leave as whole lines: a lane holds scattered features of one
+  // query, so the sums pass through a patch of rows in LDS.
+  float s_mine = 1.f, s_other = 1.f;
+  if constexpr (SOFTMAX) {
+    if (split == 1) { s_state[qg][0][lane] = m_run; s_state[qg][1][lane] = l_run; }
+    __syncthreads();
+    if (split == 0) {
+      const float m_o = s_state[qg][0][lane], l_o = s_state[qg][1][lane];
+      const float m_new = fmaxf(m_run, m_o);
+      s_mine = expf(m_run - m_new);
+      s_other = expf(m_o - m_new);
+      m_run = m_new;
+      l_run = l_run * s_mine + l_o * s_other;
+    }
+  }
+  if (split == 0) {
+    // what a row's sum is multiplied by, and the weight of its own V row: a candidate is one more key for itself, at distance
+    // 0.  (By vector arithmetic on its own rows only: no other candidate's values come near it.)
+    float p = 0.f;
+    if (it.is_cand) {
+      float dot = 0.f;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        const f32x4 k = row4(Kp + qrow * d, g);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) dot = fmaf(fq[g][t], k[t], dot);
+      }
+      const float logit = alpha * pair_sum(dot) + bias[0];
+      if constexpr (SOFTMAX) {
+        const float z = logit * ts, m_new = fmaxf(m_run, z), sc = expf(m_run - m_new);
+        p = expf(z - m_new);
+        l_run = l_run * sc + (lhalf == 0 ? p : 0.f);
+        s_mine *= sc;
+        s_other *= sc;
+      } else {
+        p = silu_f32(logit);
+      }
+    }
+    float inv = 1.f;
+    if constexpr (SOFTMAX) inv = 1.0f / pair_sum(l_run);
+    if (lhalf == 0) { s_row[qg][0][l32] = p; s_row[qg][1][l32] = inv; }
+  }
+  float *patch = s_patch[qg];
+#pragma unroll
+  for (int b0 = 0; b0 < DB; b0 += DBR) {
+    if (b0 > 0) __syncthreads();                     // the round before has left
+    if (split == 1) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+#pragma unroll
+        for (int b = 0; b < DBR; ++b) patch[l32 * PITCH + DBR * (8 * (e >> 2) + 4 * lhalf + (e & 3)) + b] = oacc[b0 + b][e];
+    }
+    __syncthreads();
+    if (split == 0) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+#pragma unroll
+        for (int b = 0; b < DBR; ++b) {
+          float *o = patch + l32 * PITCH + DBR * (8 * (e >> 2) + 4 * lhalf + (e & 3)) + b;
+          *o = SOFTMAX ? oacc[b0 + b][e] * s_mine + *o * s_other : oacc[b0 + b][e] + *o;
+        }
+    }
+    __syncthreads();
+    // 128 threads write the 32 rows of their group, 16 bytes each
+    const int rows = min(32, it.n_q - q0);
+    for (int i = split * 64 + lane; i < rows * 8 * DBR; i += 128) {
+      const int r = i / (8 * DBR), c = 4 * (i % (8 * DBR));                 // floats c .. c + 3 of the patch row
+      const int f = DB == DBR ? c : (c / DBR) * DB + b0 + c % DBR;          // the features they are
+      const int64_t at = (int64_t)(it.q_row + q0 + r) * d + f;
+      f32x4 v = *(const f32x4 *)(patch + r * PITCH + c);
+      const float p = s_row[qg][0][r], inv = s_row[qg][1][r];
+      if (it.is_cand) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] = fmaf(p, EXACT || f + t < dh ? Vp[at + t] : 0.f, v[t]);
+      }
+      if constexpr (SOFTMAX) v *= inv;
+      float *o = O + h * dh + at;
+      if constexpr (EXACT) *(f32x4 *)o = v;
+      else {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          if (f + t < dh) o[t] = v[t];
+      }
     }
   }
 }
 
 void launch_attn_f32(const float *planes, const float *bias_lh, const float *tscale_h, float *O, const AttnItem *items,
-                     int n_items, int q_tile, const Shape &sh, hipStream_t s) {
+                     int n_items, const Shape &sh, hipStream_t s) {
   if (n_items <= 0) return;
-  dim3 grid(n_items, sh.H);
-  if (sh.softmax)
-    attn_f32_kernel<true><<<grid, 256, 0, s>>>(planes, bias_lh, tscale_h, O, items, q_tile, sh.d, sh.dh, sh.D, sh.alpha, sh.ws_rows * sh.d);
-  else
-    attn_f32_kernel<false><<<grid, 256, 0, s>>>(planes, bias_lh, tscale_h, O, items, q_tile, sh.d, sh.dh, sh.D, sh.alpha, sh.ws_rows * sh.d);
+  const dim3 grid(sh.H, n_items);
+#define ATTN_CASE(DBV, EX, SM) attn_f32_kernel<DBV, EX, SM><<<grid, 256, 0, s>>>(planes, bias_lh, tscale_h, O, items, sh.d, sh.dh, sh.D, sh.alpha, sh.ws_rows * sh.d)
+#define ATTN_WIDTH(DBV) do { const bool ex = sh.dh == 32 * DBV; \
+    if (sh.softmax) { if (ex) ATTN_CASE(DBV, true, true); else ATTN_CASE(DBV, false, true); } \
+    else { if (ex) ATTN_CASE(DBV, true, false); else ATTN_CASE(DBV, false, false); } } while (0)
+  if (sh.dh <= 32) ATTN_WIDTH(1);
+  else if (sh.dh <= 64) ATTN_WIDTH(2);
+  else if (sh.dh <= 128) ATTN_WIDTH(4);
+  else ATTN_WIDTH(8);
+#undef ATTN_WIDTH
+#undef ATTN_CASE
 }
 
 }  // namespace flame

@@ -13,21 +13,26 @@ namespace flame {
 // projection's operand) and Xl = fp16(X - Xh); embeddings are exact in Xh, so assembly writes Xh only and the first layer
 // treats Xl as zero.
 // ---------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void assemble_kernel(const RowBlock *__restrict__ blocks, const int32_t *__restrict__ list, int blk_begin,
-                                                       const T *__restrict__ hist, const T *__restrict__ cand,
-                                                       float *__restrict__ X, half_t *__restrict__ Xh, int d) {
+// VEC: 16 bytes per lane (d % 4 == 0, embeddings on 16-byte boundaries).  Each 64-row block is cut into gridDim.y row slices.
+template <bool VEC>
+__global__ __launch_bounds__(256) void assemble_f32_kernel(const RowBlock *__restrict__ blocks, const int32_t *__restrict__ list, int blk_begin,
+                                                           const float *__restrict__ hist, const float *__restrict__ cand,
+                                                           float *__restrict__ X, int d) {
   const int b = list ? list[blockIdx.x] : blk_begin + blockIdx.x;
   const RowBlock rb = blocks[b];
-  const T *src = rb.kind ? cand : hist;
-  const int64_t dst0 = (int64_t)b * kRowAlign * d;
-  const int n = kRowAlign * d;
-  const int nv = rb.n_valid * d;
-  for (int i = threadIdx.x; i < n; i += 256) {
-    float v = 0.f;
-    if (i < nv) v = to_f32(src[(int64_t)rb.src_row * d + i]);
-    X[dst0 + i] = v;
-    if (Xh) Xh[blocked_index((int64_t)b * kRowAlign + i / d, i % d, d)] = to_f16_sat(v);
+  const int rows = kRowAlign / gridDim.y, r0 = blockIdx.y * rows;
+  const float *src = (rb.kind ? cand : hist) + ((int64_t)rb.src_row + r0) * d;
+  float *dst = X + ((int64_t)b * kRowAlign + r0) * d;
+  const int n = rows * d, nv = (rb.n_valid - r0) * d;      // nv <= 0: a slice of padding rows
+  if constexpr (VEC) {
+#pragma unroll 4
+    for (int i = threadIdx.x * 4; i < n; i += 1024) {
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+      if (i < nv) v = *(const f32x4 *)(src + i);
+      *(f32x4 *)(dst + i) = v;
+    }
+  } else {
+    for (int i = threadIdx.x; i < n; i += 256) dst[i] = i < nv ? src[i] : 0.f;
   }
 }
 
@@ -61,8 +66,10 @@ void launch_assemble(int dtype, const RowBlock *blocks, const int32_t *list, int
   if (n <= 0) return;
   if (dtype == FLAME_GR_BF16)
     assemble_bf16_kernel<<<dim3(n, 4), 256, 0, s>>>(blocks, list, first, (const bf16_t *)hist, (const bf16_t *)cand, (half_t *)Xh, d);
+  else if (d % 4 == 0 && ((reinterpret_cast<uintptr_t>(hist) | reinterpret_cast<uintptr_t>(cand)) & 15u) == 0)
+    assemble_f32_kernel<true><<<dim3(n, 4), 256, 0, s>>>(blocks, list, first, (const float *)hist, (const float *)cand, X, d);
   else
-    assemble_kernel<float><<<n, 256, 0, s>>>(blocks, list, first, (const float *)hist, (const float *)cand, X, nullptr, d);
+    assemble_f32_kernel<false><<<dim3(n, 4), 256, 0, s>>>(blocks, list, first, (const float *)hist, (const float *)cand, X, d);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -216,11 +223,10 @@ static void ln_gate_dispatch(const void *O, const void *U, const void *g, const 
 #undef LN_CASE
 }
 
-void launch_ln_gate(int dtype, const void *O, const void *U, const void *gamma, const void *beta, void *G,
+void launch_ln_gate(const void *O, const void *U, const void *gamma, const void *beta, void *G,
                     const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first, int d, float eps, hipStream_t s) {
   if (n_blk <= 0) return;
-  if (dtype == FLAME_GR_BF16) ln_gate_dispatch<half_t, bf16_t>(O, U, gamma, beta, G, blocks, blk_list, n_blk, blk_first, d, eps, s);
-  else ln_gate_dispatch<float, float>(O, U, gamma, beta, G, blocks, blk_list, n_blk, blk_first, d, eps, s);
+  ln_gate_dispatch<half_t, bf16_t>(O, U, gamma, beta, G, blocks, blk_list, n_blk, blk_first, d, eps, s);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -1,0 +1,57 @@
+"""The fp32 kernels at the shapes where their tiling, vector loads and padding change: head widths on both sides of a multiple
+of 32, widths and weight pointers that rule out 16-byte loads, row statistics with and without registers, launches large
+enough for the big projection tile.  Against the fp64 oracle on hot inputs, at the bar of the fp32 path."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2509_22681_amd import workloads as W
+from tests.test_gpu_parity import TOL_HOT, score_err
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    "head_10_no_vector_loads": dict(L=[70, 3, 0], M=[9, 33, 2], d=30, H=3),
+    "head_24": dict(L=[65, 31], M=[1, 40], d=48, H=2),
+    "head_48": dict(L=[64, 129], M=[64, 7], d=96, H=2),
+    "head_96": dict(L=[33, 200], M=[65, 3], d=192, H=2),
+    "head_160": dict(L=[40, 70], M=[5, 66], d=160, H=1),
+    "head_256": dict(L=[97], M=[35], d=256, H=1),
+    "wide_512": dict(L=[130], M=[70], d=512, H=8),
+    "wide_640": dict(L=[66], M=[12], d=640, H=10),
+    "wide_520_head_65": dict(L=[40, 33], M=[3, 34], d=520, H=8),
+    "big_projection_tile": dict(L=[130] * 32 + [64], M=[10] * 32 + [0], d=256, H=4),
+}
+
+
+@pytest.mark.parametrize("kind", ["silu", "softmax"])
+@pytest.mark.parametrize("unaligned", [False, True])
+@pytest.mark.parametrize("case", list(CASES))
+def test_f32_shape(case, unaligned, kind):
+    import torch
+    from paper_2509_22681_amd import binding as B
+    c = CASES[case]
+    wl = W.make_custom(c["L"], c["M"], d=c["d"], H=c["H"], n_layers=2, n_buckets=16, max_rel_dist=128, dtype="f32", seed=5,
+                       emb_std=1.0, rab_std=1.0, bias_amp=0.1, affine_random=True, attn_kind=kind, name=case)
+    want = oracle.forward(wl.cfg.to_dict(), wl.weights, wl.history_emb, wl.history_offsets, wl.cand_emb, wl.cand_offsets)
+    dw, hist, cand = B.to_device(wl)
+
+    def shifted(t):     # the same values one float past a 16-byte boundary
+        flat = torch.empty(t.numel() + 1, device=t.device, dtype=t.dtype)[1:]
+        return flat.copy_(t.reshape(-1)).view(t.shape)
+
+    if unaligned:
+        dw = {k: shifted(v) if torch.is_tensor(v) else v for k, v in dw.items()}
+        hist, cand = shifted(hist), shifted(cand)
+    h = B.flame_gr_create(B.config_for(wl))
+    try:
+        out = torch.full((int(wl.cand_offsets[-1]),), float("nan"), device="cuda:0")
+        B.flame_gr_forward(h, dw, hist, wl.history_offsets, cand, wl.cand_offsets, out)
+        torch.cuda.synchronize()
+        g = out.cpu().numpy()
+    finally:
+        B.flame_gr_destroy(h)
+    assert np.isfinite(g).all()
+    worst = score_err(g, want)
+    print(f"{case} unaligned={unaligned} {kind}: {worst:.2e}")
+    assert worst <= TOL_HOT["f32"], worst
