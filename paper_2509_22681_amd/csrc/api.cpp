@@ -307,9 +307,9 @@ void derive_weights(flame_gr *h, const flame_gr_weights *w, hipStream_t s) {
   h->derived_valid = true;
   if (h->cfg.dtype == FLAME_GR_BF16) {
     const int dm = h->sh.d;
-    launch_bf16_to_f16(w->w1, h->W1h, (int64_t)h->sh.n_layers * 4 * dm, dm, true, s);
+    launch_pack_w(w->w1, h->W1h, (int64_t)h->sh.n_layers * 4 * dm, dm, true, s);
     if (k3_fused_supported(dm)) launch_pack_w2(w->w2, h->W2p, dm, h->sh.n_layers, s);
-    else launch_bf16_to_f16(w->w2, h->W2h, (int64_t)h->sh.n_layers * dm, dm, true, s);
+    else launch_pack_w(w->w2, h->W2h, (int64_t)h->sh.n_layers * dm, dm, false, s);
   }
   launch_expand_bias(w->rab, h->bucket_tab, h->bias, h->sh.n_layers * h->sh.H, h->sh.n_buckets, h->sh.D,
                      h->cfg.dtype == FLAME_GR_BF16 ? 0.5f : 1.0f, s);

@@ -93,7 +93,7 @@ __device__ __forceinline__ f16x8 pack8(const float *v) {
 // tile each (two wavefronts per SIMD, so one's MFMAs run under the other's VALU work) and add their partial outputs
 // through LDS at the end, in a fixed order.  The chain is half as many steps and the sums are grouped differently,
 // so the two configurations agree to rounding, not bit for bit.
-template <int DH, bool SOFTMAX, bool KSPLIT>
+template <int DH, bool SOFTMAX, bool KSPLIT, bool NT>
 __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_kernel(PlanePtrs planes, const float *__restrict__ bias_lh,
                                                            const float *__restrict__ tscale_h,
                                                            half_t *__restrict__ O, const AttnItem *__restrict__ items,
@@ -626,7 +626,7 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
     for (int t = 0; t < 32 / RPI; ++t) {
       const int row = t * RPI + rl;
       const f16x8 v = *(const f16x8 *)(pb + row * (DH * 2) + ((c ^ pkey(row)) << 4));
-      if (q_local0 + row < it.n_q) __builtin_nontemporal_store(v, (f16x8 *)(obase + (int64_t)(q_local0 + row) * d));
+      if (q_local0 + row < it.n_q) store_once<NT>(v, (f16x8 *)(obase + (int64_t)(q_local0 + row) * d));
     }
   }
 }
@@ -640,7 +640,7 @@ constexpr int key_split_lds_bytes() { return NSTAGE * (2 * 128 * DH * 2 + 8 * 25
 
 template <int DH, bool SM>
 static hipError_t key_split_setup() {
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_mfma_kernel<DH, SM, true>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_mfma_kernel<DH, SM, true, false>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, key_split_lds_bytes<DH>());
   return attr;
 }
@@ -649,7 +649,7 @@ template <int DH, bool SM>
 static void launch_key_split(int grid, PlanePtrs planes, const float *bias_lh, const float *tscale_h, half_t *O,
                              const AttnItem *items, const Shape &sh, hipStream_t s) {
   (void)key_split_setup<DH, SM>();
-  attn_mfma_kernel<DH, SM, true><<<grid, 512, key_split_lds_bytes<DH>(), s>>>(planes, bias_lh, tscale_h, O, items, sh.H, sh.d, sh.D, sh.ws_rows);
+  attn_mfma_kernel<DH, SM, true, false><<<grid, 512, key_split_lds_bytes<DH>(), s>>>(planes, bias_lh, tscale_h, O, items, sh.H, sh.d, sh.D, sh.ws_rows);
 }
 
 hipError_t attn_latency_setup(const Shape &sh) {
@@ -671,7 +671,9 @@ void launch_attn_bf16(PlanePtrs planes, const float *bias_lh, const float *tscal
     }
     return;
   }
-#define ATTN_CASE(DHV, SM) attn_mfma_kernel<DHV, SM, false><<<grid, 256, 0, s>>>(planes, bias_lh, tscale_h, (half_t *)O, items, sh.H, sh.d, sh.D, sh.ws_rows)
+  const bool nt = (int64_t)n_items * QT * sh.d * 2 > kStreamBytes;
+#define ATTN_LAUNCH(DHV, SM, NTV) attn_mfma_kernel<DHV, SM, false, NTV><<<grid, 256, 0, s>>>(planes, bias_lh, tscale_h, (half_t *)O, items, sh.H, sh.d, sh.D, sh.ws_rows)
+#define ATTN_CASE(DHV, SM) do { if (nt) ATTN_LAUNCH(DHV, SM, true); else ATTN_LAUNCH(DHV, SM, false); } while (0)
   if (sh.softmax) {
     if (sh.dh == 32) ATTN_CASE(32, true);
     else ATTN_CASE(64, true);
@@ -680,6 +682,7 @@ void launch_attn_bf16(PlanePtrs planes, const float *bias_lh, const float *tscal
     else ATTN_CASE(64, false);
   }
 #undef ATTN_CASE
+#undef ATTN_LAUNCH
 }
 
 }  // namespace flame

@@ -73,14 +73,34 @@ __device__ __forceinline__ float max3_f32(float a, float b, float c) {
   return d;
 }
 
-// "k-tile blocked" layout of the fp16 GEMM operands (the activation copy Xh and the converted weight
-// matrices): inside every block of 64 rows the 32-wide k slices follow one another,
+// "k-tile blocked" layout of the fp16 activation copy Xh, the projection's operand: inside every block of 64 rows the 32-wide k slices follow one another,
 // [row / 64][k / 32][row % 64][k % 32], so the 64 rows x 32 k slice a GEMM k-tile needs is 4 KB of
 // contiguous memory and is fetched as whole 128-byte lines.  (Row-major rows of d elements would hand
 // the L1 two 64-byte requests per line, and the number of requests in flight is what bounds it.)
 __device__ __forceinline__ int64_t blocked_index(int64_t row, int k, int K) {
   return (row >> 6) * 64 * K + (int64_t)(k >> 5) * 2048 + (row & 63) * 32 + (k & 31);
 }
+
+// Row order of the MFMA A operand.  Accumulator element e of lane (l32, lhalf) belongs to A-operand
+// row 8*(e/4) + 4*lhalf + e%4.  Feeding tile row sigma32(m) = 16*bit2(m) + 4*(m/8) + m%4 into A-operand
+// row m turns that into tile row 16*lhalf + e: a lane then owns 16 consecutive outputs (features of
+// one token, or tokens of one feature for the feature-major plane) and stores them as two 16-byte
+// words, two lanes covering a contiguous 64 bytes.
+__device__ __forceinline__ int sigma32(int m) { return ((m & 4) << 2) | ((m >> 3) << 2) | (m & 3); }
+
+// Loads and stores of data that is consumed once, past the caches or (NT = false) through them.
+template <bool NT, typename T> __device__ __forceinline__ T load_once(const T *p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool NT, typename T> __device__ __forceinline__ void store_once(T v, T *p) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
+// Layout of the converted projection matrices: MFMA fragments of 32 rows x 16 k, [row / 32][k / 16][lane][8], 1 KB each; lane l holds
+// k 8 (l / 32) + 0..7 of row l & 31, or of row sigma32(l & 31) where the rows play operand A.  A fragment is one contiguous
+// request, from LDS (free of bank conflicts without a swizzle) as well as from L2 straight into registers.
 
 // Number of history keys a query row may look at (the mask of the single-user-multiple-items
 // scoring pass): a history row at index q sees keys 0..q, a candidate row sees all L.

@@ -57,14 +57,9 @@ __device__ __forceinline__ int lds_off(int row, int c) {
 template <int CPR>
 __device__ __forceinline__ int patch_key(int row) { return CPR == 8 ? (row >> 1) & 7 : (row >> 2) & 3; }
 
-// Row order of the MFMA A operand.  Accumulator element e of lane (l32, lhalf) belongs to A-operand
-// row 8*(e/4) + 4*lhalf + e%4.  Feeding tile row sigma32(m) = 16*bit2(m) + 4*(m/8) + m%4 into A-operand
-// row m turns that into tile row 16*lhalf + e: a lane then owns 16 consecutive outputs (features of
-// one token, or tokens of one feature for the feature-major plane) and stores them as two 16-byte
-// words, two lanes covering a contiguous 64 bytes.
-__device__ __forceinline__ int sigma32(int m) { return ((m & 4) << 2) | ((m >> 3) << 2) | (m & 3); }
-
-template <int BN, int EPI>
+// NT: the planes are stored past the caches (kStreamBytes).  (A template argument: of two stores in the branches of an if the compiler makes
+// one, and drops the hint.)
+template <int BN, int EPI, bool NT>
 __global__ __launch_bounds__(256, 2) void gemm_mfma_kernel(
     const half_t *__restrict__ A, const half_t *__restrict__ W, const bf16_t *__restrict__ bias,
     PlanePtrs planes, half_t *__restrict__ Xl, half_t *__restrict__ Xh, int lo_is_zero,
@@ -139,8 +134,10 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_kernel(
   }
   uint32_t alane = (uint32_t)(a_blocked ? rloc * 32 + dch * 8 : rloc * K + dch * 8) * 2u;
   const int a_kstep = (a_blocked ? 64 * BK : BK) * 2;                 // bytes per k tile
-  const char *Wn0 = (const char *)(W + (int64_t)n0 * K);  // n0 % 64 == 0: a block boundary
-  uint32_t blane = (uint32_t)(rloc * 32 + dch * 8) * 2u;
+  // W is packed fragment by fragment (device_common.h): the two fragments of a 32-column block and k tile are 2 KB together.
+  // Instruction q of wavefront w brings fragment w & 1 of column block 2 q + w / 2.
+  const char *Wn0 = (const char *)(W + ((int64_t)(n0 / 32) + (wave >> 1)) * 32 * K + (wave & 1) * 512);  // n0 % 64 == 0
+  uint32_t blane = (uint32_t)lane * 16u;
   // Operand order.  Row-major outputs (U, Q, K planes, X) want each lane to hold 4 consecutive
   // features of one token, which is the transposed accumulator: W rows as the A operand.  The V
   // plane is stored feature-major for the attention kernel (V^T is its A operand) and wants 4
@@ -177,14 +174,15 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_kernel(
         for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
   }
   // fragment byte offsets inside a stage for the two 16-deep steps (32-row blocks are 2048 bytes apart);
-  // the operand that plays A is read in sigma32 row order
+  // the activations are read in sigma32 row order when they play A;
+  // W's fragments are packed in the row order of its role
   int f0[2], g0[2];
   {
-    const int ra = feature_major ? sigma32(l32) : l32, rb = feature_major ? l32 : sigma32(l32);
+    const int ra = feature_major ? sigma32(l32) : l32;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
       f0[ks] = lds_off(wm * 128 + ra, ks * 2 + lhalf);
-      g0[ks] = A_BYTES + lds_off(wn * WN + rb, ks * 2 + lhalf);
+      g0[ks] = A_BYTES + wn * (WN * 64) + ks * 1024 + lane * 16;
     }
   }
 
@@ -209,7 +207,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_kernel(
         __builtin_amdgcn_global_load_lds((gvoid *)(abase[q] + (int64_t)kt_ * a_kstep + alane), (lvoid *)(smem + stage * STAGE + (4 * q + wave) * 1024), 16, 0, 0);
 #pragma unroll
       for (int q = 0; q < B_Q; ++q)
-        __builtin_amdgcn_global_load_lds((gvoid *)(Wn0 + ((size_t)q * 64 * K + (size_t)kt_ * (64 * BK)) * 2 + blane),
+        __builtin_amdgcn_global_load_lds((gvoid *)(Wn0 + ((size_t)q * 64 * K + (size_t)kt_ * (32 * BK)) * 2 + blane),
                                          (lvoid *)(smem + stage * STAGE + A_BYTES + (4 * q + wave) * 1024), 16, 0, 0);
     };
 #define GEMM_MFMA(S, i, j)                                                                              \
@@ -331,8 +329,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_kernel(
         }
         asm volatile("" : "+v"(goff));   // keeps the widening of the offset next to the stores (scalar base + offset form)
 #pragma unroll
-        for (int k = 0; k < NI; ++k)
-          __builtin_nontemporal_store(v[k], (f16x8 *)(gblk + (int64_t)(k * RPI) * d * 2 + goff));
+        for (int k = 0; k < NI; ++k) store_once<NT>(v[k], (f16x8 *)(gblk + (int64_t)(k * RPI) * d * 2 + goff));
       }
     } else {
       // patch[WN features][128 tokens]; lane holds feature 32j + l32, tokens 32i + 16*lhalf + 0..15
@@ -371,8 +368,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_kernel(
           }
           asm volatile("" : "+v"(goff));
 #pragma unroll
-          for (int k = 0; k < NI; ++k)
-            __builtin_nontemporal_store(v[k], (f16x8 *)(gfeat + (int64_t)(4 * (i0 + k)) * ws_rows * 2 + goff));
+          for (int k = 0; k < NI; ++k) store_once<NT>(v[k], (f16x8 *)(gfeat + (int64_t)(4 * (i0 + k)) * ws_rows * 2 + goff));
         }
       }
     }
@@ -409,7 +405,185 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_kernel(
 }
 
 
+// K1 on small tiles: 64 rows x 128 columns per workgroup.  The 64-row block of X sits whole in LDS (its k-tile blocked copy is one
+// contiguous piece, brought by LDS-DMA in one go: the memory latency is paid once and not once per k tile of a short ring), W's
+// fragments come straight from L2 into a register ring eight k tiles deep, and the k loop, unrolled, has no barrier.  Wavefront
+// w owns columns 32 w .. 32 w + 31 of the tile, both 32-row halves.  A tile is two halves of 64 columns, each within one
+// plane.  Every output is the same chain of matrix instructions over the same k order as in the large tile (k starts at the
+// column tile's rotation), so the two agree bit for bit.
+// It serves launches that leave the chip idle at 256-row tiles, where the latency of a lone workgroup is what counts, and narrow
+// models, whose large tile has six k tiles or fewer to hide its start and its epilogue behind; see launch_uvqk_bf16.
+// NK = d / 32.
+template <int NK>
+__global__ __launch_bounds__(256) void gemm_small_kernel(const half_t *__restrict__ A, const half_t *__restrict__ W, const bf16_t *__restrict__ bias,
+                                                         PlanePtrs planes, const int32_t *__restrict__ blk_list, int blk_first, int n_blk, int n_col_tiles,
+                                                         int64_t ws_rows, PlaneSel sel, float alpha) {
+  constexpr int nk = NK, d = NK * BK, rot_cols = d % 128 == 0 ? 128 : 64;
+  extern __shared__ __attribute__((aligned(256))) char lds[];   // [k / 32][64 rows][32 k], swizzled; the output patches afterwards
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, lhalf = lane >> 5;
+  // XCD x takes the row blocks congruent to x mod 8 (see the large tile)
+  int row_blk, col_tile;
+  {
+    constexpr int NXCD = 8;
+    const int wg = blockIdx.x, xcd = wg % NXCD, j = wg / NXCD;
+    const int full = (n_blk / NXCD) * NXCD;
+    const int rt = (j / n_col_tiles) * NXCD + xcd;
+    if (rt < full) {
+      row_blk = rt;
+      col_tile = j % n_col_tiles;
+    } else {
+      const int t = wg - full * n_col_tiles;
+      row_blk = full + t / n_col_tiles;
+      col_tile = t % n_col_tiles;
+    }
+  }
+  const int blk = blk_list ? blk_list[row_blk] : blk_first + row_blk;
+  // X block -> LDS.  Instruction q of a wavefront fills tile rows 16 wave .. + 15 of k tile q (the swizzle of the large tile).
+  typedef __attribute__((address_space(1))) const void gvoid;
+  typedef __attribute__((address_space(3))) void lvoid;
+  {
+    const int rloc = 16 * wave + 4 * (lane >> 4) + ((lane & 15) >> 2);
+    const int dch = (lane & 3) ^ lds_key(rloc);
+    const char *src = (const char *)(A + (int64_t)blk * kRowAlign * d);
+    uint32_t off = (uint32_t)(rloc * 32 + dch * 8) * 2u;
+    asm volatile("" : "+v"(off));
+#pragma unroll
+    for (int q = 0; q < NK; ++q) __builtin_amdgcn_global_load_lds((gvoid *)(src + q * 4096 + off), (lvoid *)(lds + q * 4096 + wave * 1024), 16, 0, 0);
+  }
+  // this wavefront's 32 columns
+  const int cols_per_plane = d / 64;                            // halves of 64 columns per plane
+  const int half = 2 * col_tile + (wave >> 1);                  // index over the selected planes
+  const bool active = half < sel.n * cols_per_plane;            // the last tile may be half a tile
+  const int plane = active ? sel.id[half / cols_per_plane] : sel.id[0];
+  const int n_half = active ? (half % cols_per_plane) * 64 : 0; // first column of the half inside its plane
+  const int n_col = n_half + (wave & 1) * 32;
+  const int n0 = plane * d + n_col;
+  const bool feature_major = plane == 1;
+  const int k_rot = ((plane * d + n_half) / rot_cols) % nk;
+  f32x16 acc[2];
+  {
+    const bf16_t *bp = bias + plane * d + n_col;
+    if (!feature_major) {
+      const bf16x8 b0v = *(const bf16x8 *)(bp + 16 * lhalf), b1v = *(const bf16x8 *)(bp + 16 * lhalf + 8);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][e] = (float)(e < 8 ? b0v[e & 7] : b1v[e & 7]);
+    } else {
+      const float bv = to_f32(bp[l32]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][e] = bv;
+    }
+  }
+  constexpr int PD = NK < 8 ? NK : 8;                           // k tiles of W in flight
+  auto main_loop = [&](auto fm) {
+    constexpr bool FM = decltype(fm)::value;
+    const char *wb = (const char *)(W + (int64_t)(n0 / 32) * 32 * d);
+    uint32_t woff = (uint32_t)lane * 16u;
+    const int aoff[2] = {lds_off(FM ? sigma32(l32) : l32, lhalf), lds_off(FM ? sigma32(l32) : l32, 2 + lhalf)};
+    auto kt_of = [&](int i) { const int k = i + k_rot; return k >= nk ? k - nk : k; };
+    f16x8 fw[PD][2], fa[2][2][2];
+    auto load_w = [&](int i) {
+      asm volatile("" : "+v"(woff));
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) fw[i % PD][ks] = *(const f16x8 *)(wb + (kt_of(i) * 2 + ks) * 1024 + woff);
+    };
+    auto read_a = [&](int i) {
+      const char *t = lds + kt_of(i) * 4096;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int r = 0; r < 2; ++r) fa[i & 1][ks][r] = *(const f16x8 *)(t + aoff[ks] + r * 2048);
+    };
+#pragma unroll
+    for (int p = 0; p < PD; ++p) load_w(p);
+    // X has landed (it was requested ahead of W's fragments)
+    static_assert(2 * PD <= 16, "the wait below counts the fragments requested behind X");
+    if (PD == 8) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    read_a(0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {
+      if (i + 1 < NK) read_a(i + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+          acc[r] = FM ? __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[i & 1][ks][r], fw[i % PD][ks], acc[r], 0, 0, 0)
+                      : __builtin_amdgcn_mfma_f32_32x32x16_f16(fw[i % PD][ks], fa[i & 1][ks][r], acc[r], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (i + PD < NK) load_w(i + PD);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  if (feature_major) main_loop(std::true_type{});
+  else main_loop(std::false_type{});
+  // Epilogue: SiLU, then through an 8 KB patch per half so that whole 128-byte lines leave (see the large tile).
+  __syncthreads();                                              // everybody has read X
+  char *pb = lds + (wave >> 1) * 8192;
+  const float sc = plane == 2 ? alpha * 0.5f : 1.0f;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      f16x8 o;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const float w = silu_fast(acc[i][8 * g + q]);
+        o[q] = to_f16_sat(plane == 2 ? w * sc : w);
+      }
+      const int row = feature_major ? (wave & 1) * 32 + l32 : 32 * i + l32;
+      const int c = feature_major ? 4 * i + 2 * lhalf + g : 4 * (wave & 1) + 2 * lhalf + g;
+      *(f16x8 *)(pb + row * 128 + ((c ^ patch_key<8>(row)) << 4)) = o;
+    }
+  __syncthreads();
+  if (!active) return;
+  half_t *P = (half_t *)(plane == 0 ? planes.u : plane == 1 ? planes.v : plane == 2 ? planes.q : planes.k);
+  const int ht = tid & 127, c = ht & 7;
+#pragma unroll
+  for (int it = 0; it < 4; ++it) {
+    const int r = (ht >> 3) + 16 * it;
+    const f16x8 v = *(const f16x8 *)(pb + r * 128 + ((c ^ patch_key<8>(r)) << 4));
+    half_t *dst = feature_major ? P + (int64_t)(n_half + r) * ws_rows + (int64_t)blk * kRowAlign + c * 8
+                                : P + ((int64_t)blk * kRowAlign + r) * d + n_half + c * 8;
+    *(f16x8 *)dst = v;
+  }
+}
+
 }  // namespace
+
+template <int NK>
+static void launch_small(const void *Xh, const void *W1h, const void *b1, PlanePtrs planes, const int32_t *blk_list, int blk_first, int n_blk, const PlaneSel &sel,
+                         const Shape &sh, hipStream_t s) {
+  const int col_tiles = (sel.n * (sh.d / 64) + 1) / 2;
+  const int lds = 4096 * NK < 16384 ? 16384 : 4096 * NK;       // the X block, at least the two output patches
+  gemm_small_kernel<NK><<<n_blk * col_tiles, 256, lds, s>>>((const half_t *)Xh, (const half_t *)W1h, (const bf16_t *)b1, planes, blk_list, blk_first, n_blk,
+                                                           col_tiles, sh.ws_rows, sel, sh.alpha);
+}
+
+// Up to this many 64-row blocks a launch runs on the small tiles.  The wider the model, the fewer workgroups of the small tile fit a
+// compute unit (its X block is 128 d bytes of LDS) and the more its W traffic, once per 64 rows, weighs against the large
+// tile's, once per 256.  Microseconds per launch, small against large, four planes:
+//   d = 512: 16 blocks 11.2 / 18.5, 48: 16.7 / 19.8, 96: 25.6 / 26.4, 128: 31.6 / 29.3
+//   d = 384: 16: 10.1 / 16.3, 128: 21.5 / 23.4, 384: 48 / 52, 512: 61 / 60
+//   d = 256: 16: 8.6 / 13.6, 256: 21.8 / 23.6, 1024: 62 / 63, 2048: 122 / 116
+//   d = 192: 16: 7.9 / 10.1, 256: 16.9 / 19.7, 1536: 61 / 73, 8192: 348 / 366 (the large tile is 64 columns wide there);  d = 128: 256: 14.6 / 17.3, 4096: 87 / 92
+static int small_tile_blocks(int d) {
+  switch (d) {
+    case 64: case 128: case 192: return 1 << 30;
+    case 256: return 1024;
+    case 384: return 384;
+    case 512: return 96;
+    default: return 0;                                          // no instance
+  }
+}
 
 void launch_uvqk_bf16(const void *Xh, const void *W1h, const void *b1, PlanePtrs planes, const int32_t *blk_list,
                       int n_blk, int blk_first, int plane_mask, const Shape &sh, hipStream_t s) {
@@ -418,17 +592,27 @@ void launch_uvqk_bf16(const void *Xh, const void *W1h, const void *b1, PlanePtrs
   for (int p = 0; p < 4; ++p)
     if (plane_mask & (1 << p)) sel.id[sel.n++] = p;
   const int row_tiles = (n_blk + RB - 1) / RB;
-  if (sh.d % 128 == 0) {
-    const int col_tiles = sel.n * (sh.d / 128);
-    gemm_mfma_kernel<128, 0><<<row_tiles * col_tiles, 256, 0, s>>>((const half_t *)Xh, (const half_t *)W1h, (const bf16_t *)b1,
-                                                                   planes, nullptr, nullptr, 0, blk_list, blk_first, n_blk,
-                                                                   row_tiles, col_tiles, sh.d, sh.d, sh.ws_rows, sel, sh.alpha, true);
-  } else {
-    const int col_tiles = sel.n * (sh.d / 64);
-    gemm_mfma_kernel<64, 0><<<row_tiles * col_tiles, 256, 0, s>>>((const half_t *)Xh, (const half_t *)W1h, (const bf16_t *)b1,
-                                                                  planes, nullptr, nullptr, 0, blk_list, blk_first, n_blk,
-                                                                  row_tiles, col_tiles, sh.d, sh.d, sh.ws_rows, sel, sh.alpha, true);
+  const int bn = sh.d % 128 == 0 ? 128 : 64;
+  const bool nt = (int64_t)n_blk * kRowAlign * sh.d * 2 > kStreamBytes;
+  if (n_blk <= small_tile_blocks(sh.d)) {
+#define K1_SMALL(NK) launch_small<NK>(Xh, W1h, b1, planes, blk_list, blk_first, n_blk, sel, sh, s)
+    switch (sh.d) {
+      case 64: K1_SMALL(2); break;
+      case 128: K1_SMALL(4); break;
+      case 192: K1_SMALL(6); break;
+      case 256: K1_SMALL(8); break;
+      case 384: K1_SMALL(12); break;
+      default: K1_SMALL(16); break;
+    }
+#undef K1_SMALL
+    return;
   }
+  const int col_tiles = sel.n * (sh.d / bn);
+#define K1_CASE(BNV, NTV) gemm_mfma_kernel<BNV, 0, NTV><<<row_tiles * col_tiles, 256, 0, s>>>((const half_t *)Xh, (const half_t *)W1h, (const bf16_t *)b1, planes, nullptr, \
+    nullptr, 0, blk_list, blk_first, n_blk, row_tiles, col_tiles, sh.d, sh.d, sh.ws_rows, sel, sh.alpha, true)
+  if (bn == 128) { if (nt) K1_CASE(128, true); else K1_CASE(128, false); }
+  else { if (nt) K1_CASE(64, true); else K1_CASE(64, false); }
+#undef K1_CASE
 }
 
 void launch_outproj_bf16(const void *G, const void *W2h, const void *b2, void *Xh, void *Xl, bool lo_is_zero, const int32_t *blk_list,
@@ -438,12 +622,12 @@ void launch_outproj_bf16(const void *G, const void *W2h, const void *b2, void *X
   const int row_tiles = (n_blk + RB - 1) / RB;
   if (sh.d % 128 == 0) {
     const int col_tiles = sh.d / 128;
-    gemm_mfma_kernel<128, 1><<<row_tiles * col_tiles, 256, 0, s>>>((const half_t *)G, (const half_t *)W2h, (const bf16_t *)b2, PlanePtrs{}, (half_t *)Xl,
+    gemm_mfma_kernel<128, 1, false><<<row_tiles * col_tiles, 256, 0, s>>>((const half_t *)G, (const half_t *)W2h, (const bf16_t *)b2, PlanePtrs{}, (half_t *)Xl,
                                                                    (half_t *)Xh, lo_is_zero ? 1 : 0, blk_list, blk_first, n_blk, row_tiles, col_tiles,
                                                                    sh.d, sh.d, sh.ws_rows, sel, 1.0f, false);
   } else {
     const int col_tiles = sh.d / 64;
-    gemm_mfma_kernel<64, 1><<<row_tiles * col_tiles, 256, 0, s>>>((const half_t *)G, (const half_t *)W2h, (const bf16_t *)b2, PlanePtrs{}, (half_t *)Xl,
+    gemm_mfma_kernel<64, 1, false><<<row_tiles * col_tiles, 256, 0, s>>>((const half_t *)G, (const half_t *)W2h, (const bf16_t *)b2, PlanePtrs{}, (half_t *)Xl,
                                                                   (half_t *)Xh, lo_is_zero ? 1 : 0, blk_list, blk_first, n_blk, row_tiles, col_tiles,
                                                                   sh.d, sh.d, sh.ws_rows, sel, 1.0f, false);
   }

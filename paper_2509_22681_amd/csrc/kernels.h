@@ -22,9 +22,10 @@ struct Shape {
 // The n blocks are list[0..n) if list is given, else first..first+n.
 void launch_assemble(int dtype, const RowBlock *blocks, const int32_t *list, int n, int first, const void *hist,
                      const void *cand, float *X, void *Xh, int d, hipStream_t s);
-// fp16 copy of a bf16 matrix of `rows` rows of K elements (K % 8 == 0); blocked: written in the k-tile
-// blocked layout of the GEMM operands (rows % 64 == 0, K % 32 == 0), else element for element
-void launch_bf16_to_f16(const void *in, void *out, int64_t rows, int K, bool blocked, hipStream_t s);
+// fp16 copy of a bf16 matrix of `rows` rows of K elements (rows % 32 == 0, K % 64 == 0), packed fragment by fragment
+// (device_common.h); planes: the rows are U | V | Q | K of K rows each, layer after layer (V's rows play operand
+// B in the projection, all others A)
+void launch_pack_w(const void *in, void *out, int64_t rows, int K, bool planes, hipStream_t s);
 // bias[lh][delta] = scale * rab[lh][bucket_tab[delta]] for all layers and heads (scale = 1/2 in the
 // MFMA path, whose attention kernel works on halved logits; 1 in the fp32 path).
 void launch_expand_bias(const float *rab, const int32_t *bucket_tab, float *bias, int n_lh,
@@ -79,7 +80,7 @@ struct PlanePtrs { void *u, *v, *q, *k; };
 
 // ---- bf16-storage path (gemm_mfma.hip, attn_mfma.hip): fp16 MFMA kernels, fp32 accumulation --------
 // Activations (Xh, planes, O, G) and the converted matrices W1h/W2h are fp16; biases stay bf16.
-// Xh, W1h and W2h are k-tile blocked (device_common.h: blocked_index); planes, O and G are row-major.
+// Xh is k-tile blocked (device_common.h: blocked_index), W1h and W2h are packed by fragments (device_common.h); planes, O and G are row-major.
 // U, Q, K planes row-major [row][d]; the V plane is written transposed, Vt[n][row] (row stride ws_rows).
 // plane_mask bit p set = compute plane p (U=1, V=2, Q=4, K=8).
 void launch_uvqk_bf16(const void *Xh, const void *W1h, const void *b1, PlanePtrs planes, const int32_t *blk_list,
@@ -101,6 +102,12 @@ void launch_pack_w2(const void *W2, void *W2p, int d, int n_layers, hipStream_t 
 void launch_k3_fused(const void *O, const void *U, const void *gamma, const void *beta, const void *W2p_layer, const void *b2,
                      void *Xh, void *Xl, bool lo_is_zero, const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first,
                      const Shape &sh, hipStream_t s);
+
+// Planes larger than this are written and read past the caches (nontemporal): a layer's eight arrays of N x d fp16 no longer fit
+// the 256 MB behind the L2s, and what streams through would push the operands that are read many times out of them.  Measured per
+// forward, ordinary against nontemporal: 10 MB per plane (32 x 640 rows, d = 256) 289 against 308 us, 3 MB (one request, d = 512) 1033
+// against 1078 us; 27 MB equal; 100 MB 5.15 against 4.98 ms, 500 MB 65.4 against 63.7 ms.
+constexpr int64_t kStreamBytes = 16 << 20;
 
 constexpr int kAttnQTileBf16 = 128;  // query rows per attention work item, MFMA path
 constexpr int kAttnQTileF32 = 64;    // fp32 path

@@ -143,23 +143,28 @@ void launch_residual_to_f32(const void *Xh, const void *Xl, float *out, int64_t 
 // case) on the scores, fp16's 2^-12 keeps them ten times closer; weights of magnitude >= 2^-14 are
 // represented exactly either way.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void bf16_to_f16_kernel(const bf16_t *__restrict__ in, half_t *__restrict__ out, int64_t n8,
-                                                          int K, bool blocked) {
+// One thread per 16 bytes of the packed matrix, in its order: whole lines are written; the reads, two 16-byte pieces of 32 rows per
+// fragment, come back from L1 for the fragments of the next k.
+__global__ __launch_bounds__(256) void pack_w_kernel(const bf16_t *__restrict__ in, half_t *__restrict__ out, int64_t n8, int K, int d, bool planes) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += (int64_t)gridDim.x * 256) {
-    const bf16x8 v = ((const bf16x8 *)in)[i];
+    const int lane = (int)(i & 63);
+    const int64_t f = i >> 6, nb = f / (K / 16);          // fragment, 32-row block
+    const int ks = (int)(f % (K / 16));
+    const bool plays_a = !(planes && (nb * 32 / d) % 4 == 1);
+    const int64_t row = nb * 32 + (plays_a ? sigma32(lane & 31) : lane & 31);
+    const bf16x8 v = *(const bf16x8 *)(in + row * K + ks * 16 + 8 * (lane >> 5));
     f16x8 o;
 #pragma unroll
     for (int k = 0; k < 8; ++k) o[k] = to_f16_sat((float)v[k]);
-    const int64_t e = i * 8;                              // 8 consecutive k of one row stay together
-    *(f16x8 *)(out + (blocked ? blocked_index(e / K, (int)(e % K), K) : e)) = o;
+    *(f16x8 *)(out + i * 8) = o;
   }
 }
 
-void launch_bf16_to_f16(const void *in, void *out, int64_t rows, int K, bool blocked, hipStream_t s) {
+void launch_pack_w(const void *in, void *out, int64_t rows, int K, bool planes, hipStream_t s) {
   const int64_t n8 = rows * K / 8;   // K % 64 == 0 in the MFMA path
   if (n8 <= 0) return;
   int grid = (int)((n8 + 255) / 256 > 2048 ? 2048 : (n8 + 255) / 256);
-  bf16_to_f16_kernel<<<grid, 256, 0, s>>>((const bf16_t *)in, (half_t *)out, n8, K, blocked);
+  pack_w_kernel<<<grid, 256, 0, s>>>((const bf16_t *)in, (half_t *)out, n8, K, K, planes);
 }
 
 // ---------------------------------------------------------------------------------------------
