@@ -44,13 +44,16 @@ __global__ __launch_bounds__(256) void pack_w2_kernel(const bf16_t *__restrict__
 }
 
 // NWV wavefronts per workgroup, NBW 32-feature blocks per wavefront: d = 32 * NBW * NWV (four wavefronts for
-// d = 128, 256, 512; three for d = 96, 192, 384).  The 64 rows of the block are dealt out RPW per wavefront in
-// phase 1 (with three wavefronts the last one has rows to spare, which it skips).
-// CS workgroups share a row block (blockIdx.y): each repeats phase 1 and takes 1/CS of every wavefront's feature
-// blocks through phases 2 and 3.  CS = 2 is for launches with few row blocks, where a workgroup sits alone on its
-// CU and its run time, not the chip's bandwidth, is what counts; every output element is computed exactly as with
-// CS = 1.
-template <int NWV, int NBW, int CS>
+// d = 128, 256, 512; three for d = 96, 192, 384).  A workgroup takes RH 32-row halves of a 64-row block; its rows are dealt out
+// RPW per wavefront in phase 1 (with three wavefronts the last one has rows to spare, which it skips).
+// CS workgroups share the rows (blockIdx.y): each repeats phase 1 and takes 1/CS of every wavefront's feature
+// blocks through phases 2 and 3.  RH = 2, CS = 1 is for launches that fill the chip.  RH = 1 and CS > 1 are for launches with few
+// row blocks, where a workgroup sits alone on its CU and its run time, not the chip's bandwidth, is what counts: half the
+// rows are one round of loads per wavefront, and everything that does not depend on phase 1 (the first W2 fragments, the
+// residual rows) is requested ahead of it.  Every output element is computed exactly as with RH = 2, CS = 1.
+// NT: O, U and the residual pair bypass the caches (consumed once; data of this size would push W2's fragments and K1's operands
+// out of L2).  Small batches are better off leaving them there for the next kernel (see launch_k3_fused).
+template <int NWV, int NBW, int CS, int RH, bool NT>
 __global__ __launch_bounds__(64 * NWV, 2) void k3_fused_kernel(const half_t *__restrict__ O, const half_t *__restrict__ U,
                                                           const bf16_t *__restrict__ gamma, const bf16_t *__restrict__ beta,
                                                           const half_t *__restrict__ W2p, const bf16_t *__restrict__ b2,
@@ -58,9 +61,11 @@ __global__ __launch_bounds__(64 * NWV, 2) void k3_fused_kernel(const half_t *__r
                                                           const RowBlock *__restrict__ blocks, const int32_t *__restrict__ blk_list,
                                                           int blk_first, float eps) {
   constexpr int d = 32 * NBW * NWV;
+  constexpr int ROWS = 32 * RH;                  // rows of this workgroup
   constexpr int RB4 = 4;                         // rows per batch of phase 1
-  constexpr int RPW = (kRowAlign + NWV * RB4 - 1) / (NWV * RB4) * RB4;   // rows per wavefront in phase 1 (16, or 24 of which 64 exist)
-  constexpr bool EVEN = RPW * NWV == kRowAlign;
+  constexpr int RPW = (ROWS + NWV * RB4 - 1) / (NWV * RB4) * RB4;   // rows per wavefront in phase 1 (with three wavefronts a few too many)
+  constexpr bool EVEN = RPW * NWV == ROWS;
+  constexpr bool EARLY = RH == 1;                // requests that do not wait for phase 1 go out ahead of it
   constexpr int NCHUNK = d / 8;                  // 16-byte chunks per row
   // Swizzle key of the gated rows in LDS.  A row of d fp16 is NCHUNK chunks; the MFMA operand reads take one chunk
   // column of 16 consecutive rows.  With NCHUNK a multiple of 16 the row pitch is a multiple of 256 bytes and the
@@ -68,26 +73,17 @@ __global__ __launch_bounds__(64 * NWV, 2) void k3_fused_kernel(const half_t *__r
   // even rows already sit 128 bytes apart) three bits of row / 2 do, and the XOR stays inside a group of 8 chunks.
   auto gkey = [](int r) { return NCHUNK % 16 == 0 ? r & 15 : (r >> 1) & 7; };
   constexpr int CPL = (NCHUNK + 63) / 64;        // chunks per lane in phase 1
-  extern __shared__ __attribute__((aligned(16))) char smem[];   // sG: 64 rows x d fp16, swizzled
+  extern __shared__ __attribute__((aligned(16))) char smem[];   // sG: ROWS x d fp16, swizzled
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, lhalf = lane >> 5;
-  const int blk = blk_list ? blk_list[blockIdx.x] : blk_first + blockIdx.x;
-  const int n_valid = blocks[blk].n_valid;
-  const int64_t row0 = (int64_t)blk * kRowAlign;
+  const int bx = RH == 2 ? (int)blockIdx.x : (int)blockIdx.x >> 1, half0 = RH == 2 ? 0 : (int)blockIdx.x & 1;
+  const int blk = blk_list ? blk_list[bx] : blk_first + bx;
+  const int n_valid = blocks[blk].n_valid - 32 * half0;
+  const int64_t row0 = (int64_t)blk * kRowAlign + 32 * half0;
 
   // ---- phase 1: G = (LN(O) * gamma + beta) * U -> LDS
-  float g[CPL][8], bt[CPL][8];
-#pragma unroll
-  for (int c = 0; c < CPL; ++c) {
-    const int ch = lane + 64 * c;
-    if (ch < NCHUNK) {
-      const bf16x8 gv = *(const bf16x8 *)(gamma + ch * 8), bv = *(const bf16x8 *)(beta + ch * 8);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) { g[c][k] = (float)gv[k]; bt[c][k] = (float)bv[k]; }
-    }
-  }
   // Rows are taken four at a time, and the loads of the next four are issued before the current
   // four are normalised: with one row in flight per wavefront the kernel would run at the latency,
   // not the bandwidth, of HBM.
@@ -100,17 +96,72 @@ __global__ __launch_bounds__(64 * NWV, 2) void k3_fused_kernel(const half_t *__r
         const int ch = lane + 64 * c;
         if (ch < NCHUNK) {
           const int rr = wave * RPW + batch * RB4 + q;
-          const int64_t off = (row0 + (EVEN || rr < kRowAlign ? rr : kRowAlign - 1)) * d + ch * 8;
-          ov[set][q][c] = __builtin_nontemporal_load((const f16x8 *)(O + off));
-          uv[set][q][c] = __builtin_nontemporal_load((const f16x8 *)(U + off));
+          const int64_t off = (row0 + (EVEN || rr < ROWS ? rr : ROWS - 1)) * d + ch * 8;
+          ov[set][q][c] = load_once<NT>((const f16x8 *)(O + off));
+          uv[set][q][c] = load_once<NT>((const f16x8 *)(U + off));
         }
       }
   };
+  float g[CPL][8], bt[CPL][8];
+  auto load_affine = [&]() {
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
+      const int ch = lane + 64 * c;
+      if (ch < NCHUNK) {
+        const bf16x8 gv = *(const bf16x8 *)(gamma + ch * 8), bv = *(const bf16x8 *)(beta + ch * 8);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) { g[c][k] = (float)gv[k]; bt[c][k] = (float)bv[k]; }
+      }
+    }
+  };
+  if (!EARLY) load_affine();
   issue(0, 0);
+  if (EARLY && RPW / RB4 > 1) issue(1, 1);
+
+  static_assert(NBW % CS == 0, "feature blocks of a wavefront divide among the workgroups of a row block");
+  constexpr int NB2 = NBW / CS;                  // feature blocks per wavefront in this workgroup
+  const int fb0 = wave * NBW + (CS > 1 ? (int)blockIdx.y * NB2 : 0);   // first of them
+  constexpr int NKS = d / 16;
+  // The W2 fragments come from L2, whose latency is several times the 8 MFMAs of a k-step: they are requested
+  // PD - 1 k-steps ahead into a register ring (scheduling barriers keep the compiler from sinking the requests
+  // back to their first use); the activations come from LDS, one step ahead.
+  constexpr int PD = !EARLY || NB2 > 2 ? 4 : NKS % 8 == 0 ? 8 : 4;
+  static_assert(NKS % PD == 0, "k-steps are walked in groups of the ring depth");
+  const half_t *wp = W2p + ((int64_t)fb0 * 64 + lane) * 8;      // + (ks * (d/32) + j) * 512
+  f16x8 fw[PD][NB2], fa[2][RH];
+  auto first_w2 = [&]() {
+#pragma unroll
+    for (int p = 0; p < PD - 1; ++p)
+#pragma unroll
+      for (int j = 0; j < NB2; ++j) fw[p][j] = *(const f16x8 *)(wp + ((int64_t)p * (d / 32) + j) * 512);
+  };
+  constexpr int WF = 32 * NB2;                      // features per wavefront (in this workgroup)
+  constexpr int CPR = WF / 4;                       // 16-byte fp32 chunks per patch row
+  constexpr int RPI = 64 / CPR;                     // patch rows per instruction
+  constexpr int NIT = 32 / RPI;
+  constexpr int XB = NIT < 8 ? NIT : 8;             // residual rows requested ahead
+  const int rl = lane / CPR, cc = lane % CPR;
+  const int n = fb0 * 32 + 4 * cc;                  // this lane's 4 features in the read-out
+  // lo_is_zero: the first layer, whose input rows are embeddings (exact in Xh): Xl is not read, only written
+  f16x4 xh[XB], xl[XB];
+  auto load_x = [&](int i, int t, int it) {
+    const int64_t m = row0 + 32 * i + rl + (int64_t)it * RPI;
+    xh[t] = load_once<NT>((const f16x4 *)(Xh + blocked_index(m, n, d)));
+    xl[t] = f16x4{(half_t)0.f, (half_t)0.f, (half_t)0.f, (half_t)0.f};
+    if (!lo_is_zero) xl[t] = load_once<NT>((const f16x4 *)(Xl + m * d + n));
+  };
+  if (EARLY) {
+    __builtin_amdgcn_sched_barrier(0);
+    first_w2();
+#pragma unroll
+    for (int t = 0; t < XB; ++t) load_x(0, t, t);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (EARLY) load_affine();
 #pragma unroll
   for (int batch = 0; batch < RPW / RB4; ++batch) {
     const int set = batch & 1;
-    if (batch + 1 < RPW / RB4) issue(set ^ 1, batch + 1);
+    if (batch + 1 < RPW / RB4 && !(EARLY && batch == 0)) issue(set ^ 1, batch + 1);
     __builtin_amdgcn_sched_barrier(0);
     // the four rows go through each step together, so that their reduction chains overlap
     float v[RB4][CPL][8], mu[RB4], rstd[RB4];
@@ -144,7 +195,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void k3_fused_kernel(const half_t *__r
 #pragma unroll
     for (int q = 0; q < RB4; ++q) {
       const int r = wave * RPW + batch * RB4 + q;
-      if (!EVEN && r >= kRowAlign) continue;       // a spare row of the last wavefront
+      if (!EVEN && r >= ROWS) continue;            // a spare row of the last wavefront
       const bool pad = r >= n_valid;               // padding rows carry a zero branch so that they stay finite
 #pragma unroll
       for (int c = 0; c < CPL; ++c) {
@@ -162,31 +213,17 @@ __global__ __launch_bounds__(64 * NWV, 2) void k3_fused_kernel(const half_t *__r
   }
   __syncthreads();
 
-  // ---- phase 2: acc[token][feature] over k; features of this wavefront: wave*32*NBW .. +32*NBW-1
-  static_assert(NBW % CS == 0, "feature blocks of a wavefront divide among the workgroups of a row block");
-  constexpr int NB2 = NBW / CS;                  // feature blocks per wavefront in this workgroup
-  const int fb0 = wave * NBW + (CS > 1 ? (int)blockIdx.y * NB2 : 0);   // first of them
-  f32x16 acc[2][NB2];
+  // ---- phase 2: acc[token][feature] over k; features of this wavefront: fb0 * 32 .. + 32 * NB2 - 1
+  f32x16 acc[RH][NB2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < RH; ++i)
 #pragma unroll
     for (int j = 0; j < NB2; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  constexpr int NKS = d / 16;
-  // The W2 fragments come from L2, whose latency is several times the 8 MFMAs of a k-step: they are requested
-  // PD - 1 k-steps ahead into a register ring (scheduling barriers keep the compiler from sinking the requests
-  // back to their first use); the activations come from LDS, one step ahead.
-  constexpr int PD = 4;
-  static_assert(NKS % PD == 0, "k-steps are walked in groups of the ring depth");
-  const half_t *wp = W2p + ((int64_t)fb0 * 64 + lane) * 8;      // + (ks * (d/32) + j) * 512
-  f16x8 fw[PD][NB2], fa[2][2];
+  if (!EARLY) first_w2();
 #pragma unroll
-  for (int p = 0; p < PD - 1; ++p)
-#pragma unroll
-    for (int j = 0; j < NB2; ++j) fw[p][j] = *(const f16x8 *)(wp + ((int64_t)p * (d / 32) + j) * 512);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < RH; ++i) {
     const int r = 32 * i + l32;
     fa[0][i] = *(const f16x8 *)(smem + r * (d * 2) + ((lhalf ^ gkey(r)) << 4));
   }
@@ -201,13 +238,13 @@ __global__ __launch_bounds__(64 * NWV, 2) void k3_fused_kernel(const half_t *__r
 #pragma unroll
       for (int j = 0; j < NB2; ++j) fw[(u + PD - 1) % PD][j] = *(const f16x8 *)(wp + ((int64_t)kw * (d / 32) + j) * 512);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < RH; ++i) {
         const int r = 32 * i + l32;
         fa[nxt][i] = *(const f16x8 *)(smem + r * (d * 2) + (((2 * kn + lhalf) ^ gkey(r)) << 4));
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < RH; ++i)
 #pragma unroll
         for (int j = 0; j < NB2; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fw[u][j], fa[cur][i], acc[i][j], 0, 0, 0);
@@ -221,35 +258,21 @@ __global__ __launch_bounds__(64 * NWV, 2) void k3_fused_kernel(const half_t *__r
   // private slice of the now free LDS (16-byte chunks XOR-swizzled by row) and then walks it row by
   // row: 16 bytes per lane, whole lines of X, 64-byte runs of the blocked fp16 copy.
   __syncthreads();                                  // every wavefront has finished reading G
-  constexpr int WF = 32 * NB2;                      // features per wavefront (in this workgroup)
-  constexpr int CPR = WF / 4;                       // 16-byte fp32 chunks per patch row
-  constexpr int RPI = 64 / CPR;                     // patch rows per instruction
-  constexpr int NIT = 32 / RPI;
   char *pb = smem + wave * (32 * WF * 4);
   // chunk XOR key: 16 consecutive rows of one chunk column use each of the 16 slots of 256 bytes once
   auto pkey = [](int row) { return CPR == 8 ? (row >> 1) & 7 : row & 15; };
-  const int rl = lane / CPR, cc = lane % CPR;
-  const int n = fb0 * 32 + 4 * cc;                  // this lane's 4 features in the read-out
   f32x4 bvf;
   {
     const bf16x4 bv = *(const bf16x4 *)(b2 + n);
 #pragma unroll
     for (int q = 0; q < 4; ++q) bvf[q] = (float)bv[q];
   }
-  constexpr int XB = NIT < 8 ? NIT : 8;             // residual rows requested ahead
-  // lo_is_zero: the first layer, whose input rows are embeddings (exact in Xh): Xl is not read, only written
-  f16x4 xh[XB], xl[XB];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int64_t m0 = row0 + 32 * i + rl;
-    auto load = [&](int t, int it) {
-      const int64_t m = m0 + (int64_t)it * RPI;
-      xh[t] = __builtin_nontemporal_load((const f16x4 *)(Xh + blocked_index(m, n, d)));
-      xl[t] = f16x4{(half_t)0.f, (half_t)0.f, (half_t)0.f, (half_t)0.f};
-      if (!lo_is_zero) xl[t] = __builtin_nontemporal_load((const f16x4 *)(Xl + m * d + n));
-    };
+  for (int i = 0; i < RH; ++i) {
+    if (!EARLY) {
 #pragma unroll
-    for (int t = 0; t < XB; ++t) load(t, t);
+      for (int t = 0; t < XB; ++t) load_x(i, t, t);
+    }
 #pragma unroll
     for (int j = 0; j < NB2; ++j)
 #pragma unroll
@@ -263,7 +286,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void k3_fused_kernel(const half_t *__r
       const int row = it * RPI + rl;
       const f32x4 v = *(const f32x4 *)(pb + row * (WF * 4) + ((cc ^ pkey(row)) << 4));
       const f16x4 h4 = xh[it % XB], l4 = xl[it % XB];
-      if (it + XB < NIT) load(it % XB, it + XB);
+      if (it + XB < NIT) load_x(i, it % XB, it + XB);
       f16x4 oh, ol;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -272,13 +295,16 @@ __global__ __launch_bounds__(64 * NWV, 2) void k3_fused_kernel(const half_t *__r
         ol[q] = to_f16_sat(x - (float)oh[q]);
       }
       const int64_t m = row0 + 32 * i + row;
-      __builtin_nontemporal_store(oh, (f16x4 *)(Xh + blocked_index(m, n, d)));
-      __builtin_nontemporal_store(ol, (f16x4 *)(Xl + m * d + n));
+      store_once<NT>(oh, (f16x4 *)(Xh + blocked_index(m, n, d)));
+      store_once<NT>(ol, (f16x4 *)(Xl + m * d + n));
     }
   }
 }
 
 }  // namespace
+
+// the gated rows, and after them a 32-row fp32 patch of every wavefront's features
+static size_t k3_lds_bytes(int d, int cs, int rh) { const size_t g = (size_t)32 * rh * d * 2, patch = (size_t)32 * (d / cs) * 4; return g > patch ? g : patch; }
 
 bool k3_fused_supported(int d) { return d == 128 || d == 192 || d == 256 || d == 384 || d == 512; }
 
@@ -292,18 +318,25 @@ void launch_k3_fused(const void *O, const void *U, const void *gamma, const void
                      void *Xh, void *Xl, bool lo_is_zero, const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first,
                      const Shape &sh, hipStream_t s) {
   if (n_blk <= 0) return;
-  const size_t lds = (size_t)kRowAlign * sh.d * 2;
-  // few row blocks: two workgroups per block (see the kernel), as long as the launch still fits the chip once over
-  const bool split = n_blk <= 128;
-#define K3_CASE(NWV, NB, CSV) k3_fused_kernel<NWV, NB, CSV><<<dim3(n_blk, CSV), 64 * NWV, lds, s>>>((const half_t *)O, (const half_t *)U, (const bf16_t *)gamma, (const bf16_t *)beta, \
+  // Launches of up to 384 row blocks take half blocks, and cut the features as long as that leaves one workgroup per compute unit
+  // at most: lone workgroups, latency.  Microseconds per launch, whole blocks / half blocks / half blocks with features cut in two
+  // / in four:
+  //   d = 512: 16 blocks 21.6 / 15.8 / 12.0 / 10.1, 64: 22.4 / 17.1 / 14.0 / 13.9, 128: 24.0 / 19.6 / 22.3 / 21.6, 384: 39.8 / 39.0 / 46.3, 512: 45.2 / 49.7
+  //   (44 blocks in a model of 16 layers, whose W2 is in no L2 when a layer starts: 12.9 in two, 14.6 in four)
+  //   d = 256: 16: 16.3 / 11.0 / 9.9, 64: 17.4 / 11.6 / 10.5, 128: 17.9 / 13.0 / 13.4, 384: 23.9 / 23.9, 512: 26.0 / 28.6
+  //   d = 192: 16: 20.1 / 12.4 / 11.5, 64: 20.6 / 12.9 / 12.3, 384: 26.5 / 23.4, 512: 28.0 / 28.4
+  const bool nt = (int64_t)n_blk * kRowAlign * sh.d * 2 > kStreamBytes;
+#define K3_LAUNCH(NWV, NB, CSV, RHV, NTV) k3_fused_kernel<NWV, NB, CSV, RHV, NTV><<<dim3(n_blk * (3 - RHV), CSV), 64 * NWV, k3_lds_bytes(sh.d, CSV, RHV), s>>>((const half_t *)O, (const half_t *)U, (const bf16_t *)gamma, (const bf16_t *)beta, \
     (const half_t *)W2p_layer, (const bf16_t *)b2, (half_t *)Xh, (half_t *)Xl, lo_is_zero ? 1 : 0, blocks, blk_list, blk_first, sh.eps)
-  const bool split4 = n_blk <= 64;
-  if (sh.d == 512) { if (split4) K3_CASE(4, 4, 4); else if (split) K3_CASE(4, 4, 2); else K3_CASE(4, 4, 1); }
-  else if (sh.d == 384) { if (split4) K3_CASE(3, 4, 4); else if (split) K3_CASE(3, 4, 2); else K3_CASE(3, 4, 1); }
-  else if (sh.d == 256) { if (split) K3_CASE(4, 2, 2); else K3_CASE(4, 2, 1); }
-  else if (sh.d == 192) { if (split) K3_CASE(3, 2, 2); else K3_CASE(3, 2, 1); }
-  else K3_CASE(4, 1, 1);
+#define K3_CASE(NWV, NB) do { if (NB == 4 && n_blk <= 32) K3_LAUNCH(NWV, NB, NB, 1, false); else if (n_blk <= 64) K3_LAUNCH(NWV, NB, (NB > 1 ? 2 : 1), 1, false); else if (n_blk <= 384 && !nt) K3_LAUNCH(NWV, NB, 1, 1, false); \
+    else if (nt) K3_LAUNCH(NWV, NB, 1, 2, true); else K3_LAUNCH(NWV, NB, 1, 2, false); } while (0)
+  if (sh.d == 512) K3_CASE(4, 4);
+  else if (sh.d == 384) K3_CASE(3, 4);
+  else if (sh.d == 256) K3_CASE(4, 2);
+  else if (sh.d == 192) K3_CASE(3, 2);
+  else K3_CASE(4, 1);
 #undef K3_CASE
+#undef K3_LAUNCH
 }
 
 }  // namespace flame
