@@ -36,3 +36,28 @@ def test_same_bits_at_every_launch_size(d):
     for idx in ([0], [n - 1], [n], [n + 1], [n + 3], list(range(30, 44)), list(range(n - 100 if n > 120 else 0, n + 4))):
         part = scores(wl.subset(idx))
         assert np.array_equal(part, np.concatenate([whole[co[i]:co[i + 1]] for i in idx])), (d, idx[0], len(idx))
+
+
+@pytest.mark.parametrize("d,H", [(64, 2), (192, 3), (320, 5)])
+def test_hidden_rows_at_any_alignment(d, H):
+    """The gather of the candidates' rows stores 16 bytes at a time where the caller's array allows it."""
+    import torch
+    from paper_2509_22681_amd import binding as B
+    wl = W.make_custom([70, 0, 33], [65, 3, 16], d=d, H=H, n_layers=2, n_buckets=16, max_rel_dist=128, dtype="bf16", seed=5, name=f"hidden{d}")
+    n = int(wl.cand_offsets[-1]) * d
+    h = B.flame_gr_create(B.config_for(wl))
+    try:
+        dw, hist, cand = B.to_device(wl)
+        rows = []
+        for shift in (0, 1, 2, 4):
+            buf = torch.full((n + 8,), float("nan"), device="cuda:0")
+            B.flame_gr_forward_hidden(h, dw, hist, wl.history_offsets, cand, wl.cand_offsets, buf[shift:shift + n].view(-1, d))
+            torch.cuda.synchronize()
+            got = buf.cpu().numpy()
+            assert np.isnan(got[:shift]).all() and np.isnan(got[shift + n:]).all()
+            rows.append(got[shift:shift + n])
+    finally:
+        B.flame_gr_destroy(h)
+    assert np.isfinite(rows[0]).all()
+    for r in rows[1:]:
+        assert np.array_equal(r, rows[0])
