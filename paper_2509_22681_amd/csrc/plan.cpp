@@ -195,6 +195,13 @@ int build_plan(const flame_gr_config &cfg, const int32_t *hoff, const int32_t *c
       row += s.Lp + s.Mp;
       p.total_cands += s.M;
     }
+    const auto tail_longest_first = [](std::vector<AttnItem> &v, int32_t begin) {
+      const auto first = v.begin() + std::max<int64_t>(begin, (int64_t)v.size() - kTailItems);
+      std::stable_sort(first, v.end(), [](const AttnItem &x, const AttnItem &y) { return x.n_kv > y.n_kv; });
+    };
+    tail_longest_first(p.items, G.item_begin);
+    tail_longest_first(p.cand_items, G.citem_begin);
+    tail_longest_first(p.hist_items, G.hitem_begin);
     G.row_end = (int32_t)row;
     G.blk_end = (int32_t)p.blocks.size();
     G.item_end = (int32_t)p.items.size();
