@@ -112,9 +112,9 @@ typedef struct {
                                 values of every layer */
   int32_t latency_mode;      /* 0 = kernels configured for throughput (batches that fill the chip);
                                 1 = the MFMA attention kernel in its latency configuration, for handles that
-                                serve one or a few requests per call: pairs of wavefronts split the keys of a
-                                query tile, which halves the chain of dependent key tiles that bounds a small
-                                batch's run time.  Partial sums are grouped differently: scores agree with
+                                serve one or a few requests per call: four wavefronts split the keys of a
+                                query tile, which cuts the chain of dependent key tiles that bounds a small
+                                batch's run time to a quarter.  Partial sums are grouped differently: scores agree with
                                 mode 0 to rounding (same error bars), not bit for bit.  No effect on fp32 handles */
   int32_t weights_static;    /* 0 = the caller may change the weight values between calls: every call derives its
                                 operand copies (fp16 conversions, packed layouts, the bias table by distance) again;

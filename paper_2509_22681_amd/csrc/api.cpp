@@ -36,6 +36,9 @@ struct StageLayout {  // byte offsets inside one staging buffer (host pinned and
 // What a pass covers: the whole batch, or one stage of the two-stage path (Section 5).
 enum PassMode { PASS_FULL = 0, PASS_HISTORY, PASS_CANDIDATES };
 
+// Query rows per attention work item.
+int attn_q_tile(const flame_gr_config &c) { return c.dtype != FLAME_GR_BF16 ? kAttnQTileF32 : c.latency_mode ? kAttnQTileLatency : kAttnQTileBf16; }
+
 struct ProfEvent { hipEvent_t a, b; int kind; };
 
 // One captured forward: the graph and the plan tables its kernels read (its own copy, so that eager
@@ -427,7 +430,7 @@ int flame_gr_create(const flame_gr_config *cfg_in, flame_gr_t **out) {
   if (!h) { g_create_error = "out of host memory"; return FLAME_GR_HIP_ERROR; }
   h->cfg = cfg;
   h->n_groups = cfg.n_streams > 1 ? cfg.n_streams : 1;
-  h->q_tile = cfg.dtype == FLAME_GR_BF16 ? kAttnQTileBf16 : kAttnQTileF32;
+  h->q_tile = attn_q_tile(cfg);
   h->elt = cfg.dtype == FLAME_GR_BF16 ? 2 : 4;
   h->ws_rows = workspace_rows(cfg);
   h->sh = Shape{cfg.d_model, cfg.n_heads, cfg.d_model / cfg.n_heads, cfg.n_layers, cfg.n_buckets,
@@ -797,7 +800,7 @@ int flame_gr_forward_static(const flame_gr_config *cfg_in, const flame_gr_weight
   if (rc) return rc;
   const bool bf = cfg.dtype == FLAME_GR_BF16;
   h.n_groups = 1;
-  h.q_tile = bf ? kAttnQTileBf16 : kAttnQTileF32;
+  h.q_tile = attn_q_tile(cfg);
   h.elt = bf ? 2 : 4;
   rc = build_plan(cfg, history_offsets, cand_offsets, n_requests, h.q_tile, 1, (int64_t)1 << 40, h.plan, g_create_error);
   if (rc) return rc;
@@ -919,8 +922,7 @@ static int host_plan(const flame_gr_config *cfg_in, const int32_t *history_offse
   int rc = validate_config(cfg, err);
   if (!rc) {
     Plan P;
-    const int q_tile = cfg.dtype == FLAME_GR_BF16 ? kAttnQTileBf16 : kAttnQTileF32;
-    rc = build_plan(cfg, history_offsets, cand_offsets, n_requests, q_tile, cfg.n_streams > 1 ? cfg.n_streams : 1,
+    rc = build_plan(cfg, history_offsets, cand_offsets, n_requests, attn_q_tile(cfg), cfg.n_streams > 1 ? cfg.n_streams : 1,
                     workspace_rows(cfg), P, err, cand_capacity);
     if (!rc) {
       if (tok_off) std::memcpy(tok_off, P.tok_off.data(), P.tok_off.size() * sizeof(int32_t));

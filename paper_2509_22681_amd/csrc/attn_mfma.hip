@@ -49,9 +49,6 @@ namespace flame {
 
 namespace {
 
-constexpr int QT = kAttnQTileBf16;  // query rows per workgroup: four groups of 32 (one 32-row MFMA block each)
-static_assert(QT == 128, "4 groups of 32 query rows");
-constexpr int NSTAGE = 3;           // LDS stages (ring)
 constexpr int KH = 64;              // keys per half tile (one pass of the register-level loop)
 
 // SiLU for small arguments: the polynomial of device_common.h, silu(x) = x/2 + x^2 (a1 + a3 x^2 + a5 x^4).  On the halved
@@ -88,26 +85,33 @@ __device__ __forceinline__ f16x8 pack8(const float *v) {
 //
 // KSPLIT = false is the throughput configuration described at the top: 4 wavefronts, key tiles of 64, three
 // workgroups per CU.  KSPLIT = true is the latency configuration for batches too small to fill the chip, where a
-// workgroup sits alone on its CU and its run time is the chain of key tiles of its longest row: 8 wavefronts, key
-// tiles of 128, and each group of 32 query rows is served by a PAIR of wavefronts that take one 64-key half of every
+// workgroup sits alone on its CU and its run time is the chain of key tiles of its longest row: 64 query rows, 8 wavefronts, key
+// tiles of 256 in two LDS stages, and each group of 32 query rows is served by FOUR wavefronts that take one 64-key quarter of every
 // tile each (two wavefronts per SIMD, so one's MFMAs run under the other's VALU work) and add their partial outputs
-// through LDS at the end, in a fixed order.  The chain is half as many steps and the sums are grouped differently,
-// so the two configurations agree to rounding, not bit for bit.
+// through LDS at the end, in a fixed order.  The chain is a quarter as many steps, and a request of a few thousand rows has enough
+// query tiles for every CU; the sums are grouped differently, so the two configurations agree to rounding, not bit for bit.
+// One request of 2573 + 217, 8 heads: LATENCY_US us per launch (32 with query tiles of 128 and two wavefronts per group on key tiles of 128).
 template <int DH, bool SOFTMAX, bool KSPLIT, bool NT>
 __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_kernel(PlanePtrs planes, const float *__restrict__ bias_lh,
                                                            const float *__restrict__ tscale_h,
                                                            half_t *__restrict__ O, const AttnItem *__restrict__ items,
                                                            int H, int d, int D, int64_t ws_rows) {
   constexpr int NW = KSPLIT ? 8 : 4;   // wavefronts per workgroup
-  constexpr int KT = KSPLIT ? 128 : 64;   // keys per LDS stage
+  constexpr int KP = KSPLIT ? 4 : 1;   // wavefronts per group of 32 query rows
+  constexpr int QG = NW / KP;          // groups
+  constexpr int QT = 32 * QG;          // query rows per workgroup (one 32-row MFMA block per group)
+  static_assert(QT == (KSPLIT ? kAttnQTileLatency : kAttnQTileBf16), "the planner's query tiles");
+  constexpr int NSTAGE = KSPLIT ? 2 : 3;  // LDS stages (ring)
+  constexpr int KT = KH * KP;          // keys per LDS stage
   constexpr int BW = QT + KT;          // bias window per key tile: slot u holds bias[q_first + QT-1 - k0 - u]
   static_assert(BW <= 64 * NW, "one 64-slot window request per wavefront");
   constexpr int KS = DH / 16;          // k-steps of the Q K^T product
   constexpr int DB = DH / 32;          // 32-row blocks of O^T
   constexpr int KCH = DH / 8;          // 16-byte chunks per K row (8 or 4)
   constexpr int KSH = KCH == 8 ? 1 : 2;            // K rows per 256 bytes = 1 << KSH
-  constexpr int VCH = KT / 8;          // 16-byte chunks per V^T row (16 or 8)
-  constexpr int VSH = VCH == 16 ? 0 : 1;           // V^T rows per 256 bytes = 1 << VSH
+  constexpr int VCH = KT / 8;          // 16-byte chunks per V^T row (32 or 8)
+  constexpr int VSH = VCH == 8 ? 1 : 0;            // V^T rows per 256 bytes = 1 << VSH (a row of 32 chunks covers 512)
+  constexpr int VKEY = VCH == 8 ? 7 : 15;          // swizzle key: XORed into the chunk index inside 256 bytes
   constexpr int K_BYTES = KT * DH * 2;             // K tile [KT keys][DH]
   constexpr int V_BYTES = DH * KT * 2;             // V^T tile [DH][KT keys]
   constexpr int W_BYTES = NW * 256;                // bias window: 64 slots per wavefront (BW <= 64 NW of them are used)
@@ -132,9 +136,9 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
   const half_t *Kp = (const half_t *)planes.k + head * DH;
   const float *bias = bias_lh + (int64_t)head * D;
 
-  // this wavefront's 32 query rows and (latency configuration) its half of every key tile
-  const int q_group = KSPLIT ? wave >> 1 : wave;
-  const int k_half = KSPLIT ? wave & 1 : 0;
+  // this wavefront's 32 query rows and (latency configuration) its quarter of every key tile
+  const int q_group = KSPLIT ? wave / KP : wave;
+  const int k_part = KSPLIT ? wave % KP : 0;
   const int q_local0 = q_group * 32;
   const bool wave_active = q_local0 < it.n_q;
   const int my_q_local = q_local0 + l32;
@@ -179,7 +183,7 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
   // scalar offsets for its further instructions.  Bias window: slots 64 w .. 64 w + 63 by wavefront w.
   constexpr int NKI = K_BYTES / 1024, NVI = V_BYTES / 1024;
   static_assert(NKI % NW == 0 && NVI % NW == 0, "every wavefront issues the same number of requests per tile");
-  static_assert((NW * (64 / KCH)) % (KCH << KSH) == 0 && (NW * (64 / VCH)) % (VCH << VSH) == 0, "swizzle keys do not depend on the instruction");
+  static_assert((NW * (64 / KCH)) % (KCH << KSH) == 0 && (NW * (64 / VCH)) % ((VKEY + 1) << VSH) == 0, "swizzle keys do not depend on the instruction");
   constexpr int REQ = NKI / NW + NVI / NW + 1;       // requests per wavefront and tile
   // Addresses are a wave-uniform base (advanced per tile with scalar arithmetic) plus a 32-bit lane offset that
   // never changes: the request instruction takes them as scalar base + vector offset, and a tile costs no
@@ -198,7 +202,7 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
   }
   {
     const int row = wave * (64 / VCH) + lane / VCH;
-    const int c = (lane % VCH) ^ ((row >> VSH) & (VCH - 1));
+    const int c = (lane % VCH) ^ ((row >> VSH) & VKEY);
     oV = (uint32_t)((int64_t)row * ws_rows + c * 8) * 2u;
   }
   auto request_tile = [&](int stage) {
@@ -235,14 +239,15 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
   // (row base | key << 4) ^ (c << 4): one XOR with a constant per fragment.
   const int krow = pi32(l32);
   const int ka0 = (krow * (DH * 2)) | (((((krow >> KSH) & (KCH - 1)) ^ lhalf) << 4));
-  const int va0 = (K_BYTES + l32 * (KT * 2)) | (((((l32 >> VSH) & (VCH - 1)) ^ lhalf) << 4));
+  const int va0 = (K_BYTES + l32 * (KT * 2)) | (((((l32 >> VSH) & VKEY) ^ lhalf) << 4));
 
   // Ring of NSTAGE = 3 stages, requests two tiles ahead.  Past the last tile the requests repeat the last
   // tile (into a free stage), so that "at most REQ requests outstanding" always means "tile t has landed".
+  // (The latency configuration has two stages and requests one tile ahead: a step of four 64-key quarters is longer than the loads.)
   if (n_tiles > 0) {
     request_tile(0);
     if (n_tiles > 1) next_tile();
-    request_tile(1);
+    if (!KSPLIT) request_tile(1);
   }
   // The query fragments are requested behind the first two tiles, not ahead of them: the tiles are what the first
   // step waits for.  (The waits below count requests in order: with at most REQ outstanding, the query loads and
@@ -256,15 +261,23 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
     const char *sb = lds + ST * STAGE;
     // tile t has landed for this wavefront; past the barrier it has landed for all of them, and everybody
     // has left tile t-1, whose stage the next request overwrites
-    if (REQ == 5) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
+    if (KSPLIT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    else if (REQ == 5) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
     else if (REQ == 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
-    if (t + 2 < n_tiles) next_tile();
-    request_tile((ST + 2) % NSTAGE);
+    if constexpr (KSPLIT) {
+      if (t + 1 < n_tiles) {
+        request_tile(ST ^ 1);
+        next_tile();
+      }
+    } else {
+      if (t + 2 < n_tiles) next_tile();
+      request_tile((ST + 2) % NSTAGE);
+    }
     __builtin_amdgcn_sched_barrier(0);   // the requests stay ahead of the tile's arithmetic
 #pragma unroll 1
-    for (int u = KSPLIT ? k_half : 0; u < (KSPLIT ? k_half + 1 : KT / KH); ++u) {
+    for (int u = k_part; u < k_part + 1; ++u) {
     const int k0 = t * KT + u * KH;
     if (wave_active && k0 < wave_vis_max) {
       const char *kb = sb + u * (KH * DH * 2);                 // K rows of this half tile
@@ -491,55 +504,18 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
     }
     }
   };
-  static_assert(NSTAGE == 3, "the tile loop is unrolled over a ring of three stages");
   for (int t = 0; t < n_tiles; t += NSTAGE) {
     tile_step(std::integral_constant<int, 0>{}, t);
     if (t + 1 < n_tiles) tile_step(std::integral_constant<int, 1>{}, t + 1);
-    if (t + 2 < n_tiles) tile_step(std::integral_constant<int, 2>{}, t + 2);
+    if constexpr (NSTAGE == 3)
+      if (t + 2 < n_tiles) tile_step(std::integral_constant<int, 2>{}, t + 2);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the repeated requests of the tail have landed
   __builtin_amdgcn_s_barrier();          // everybody has left the last tile: the stages become output patches
 
-  // ---- latency configuration: the wavefront with the second key half hands its partial output (and its softmax
-  // state) to its partner through LDS, behind the output patches; the partner goes on alone.
-  if constexpr (KSPLIT) {
-    constexpr int PART = DB * 16 * 64 * 4;            // bytes of one wavefront's accumulators
-    char *area = lds + 4 * (32 * DH * 2) + q_group * (PART + 512);
-    if (k_half == 1) {
-#pragma unroll
-      for (int b = 0; b < DB; ++b)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x4 v = {oacc[b][4 * g], oacc[b][4 * g + 1], oacc[b][4 * g + 2], oacc[b][4 * g + 3]};
-          *(f32x4 *)(area + ((b * 4 + g) * 64 + lane) * 16) = v;
-        }
-      if constexpr (SOFTMAX) *(float2 *)(area + PART + lane * 8) = float2{m_run, l_run};
-    }
-    __builtin_amdgcn_s_barrier();
-    if (k_half == 1) return;
-    float s_mine = 1.f, s_other = 1.f;
-    if constexpr (SOFTMAX) {
-      const float2 ml = *(const float2 *)(area + PART + lane * 8);
-      const float m_new = fmaxf(m_run, ml.x);
-      s_mine = __builtin_amdgcn_exp2f(m_run - m_new);
-      s_other = __builtin_amdgcn_exp2f(ml.x - m_new);
-      l_run = l_run * s_mine + ml.y * s_other;
-      m_run = m_new;
-    }
-#pragma unroll
-    for (int b = 0; b < DB; ++b)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 v = *(const f32x4 *)(area + ((b * 4 + g) * 64 + lane) * 16);
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          oacc[b][4 * g + i] = SOFTMAX ? oacc[b][4 * g + i] * s_mine + v[i] * s_other : oacc[b][4 * g + i] + v[i];
-      }
-  }
-
   // ---- candidates: the row itself is one more key, at distance 0.  The wavefront multiplies its 32
-  // candidate rows against themselves and keeps the diagonal.
-  if (it.is_cand && wave_active) {
+  // candidate rows against themselves and keeps the diagonal.  (Latency configuration: the wavefront of the last key quarter.)
+  if (it.is_cand && wave_active && k_part == KP - 1) {
     const float b0 = bias[0];
     const int64_t base_row = it.q_row + q_local0;   // multiple of 32 inside the padded workspace
     f32x16 sacc;
@@ -597,37 +573,84 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
   // through LDS (16-byte chunks XOR-swizzled by row; every wavefront is past the barrier that closes the key
   // loop, nobody reads the tile buffers any more) and stores 16 bytes per lane, a whole head row of
   // 2*DH bytes per group of lanes.
-  if constexpr (SOFTMAX) {
-    const float lt = pair_sum(l_run);
-    const float inv = lt > 0.f ? 1.0f / lt : 0.f;
+  constexpr int CPR = DH / 8;                       // 16-byte chunks per patch row
+  constexpr int RPI = 64 / CPR;                     // patch rows per store instruction
+  char *pb = lds + q_group * (32 * DH * 2);
+  auto pkey = [](int row) { return CPR == 8 ? (row >> 1) & 7 : (row >> 2) & 3; };   // spreads 16 rows over 256 bytes
+  auto to_patch = [&](int b, int g, const f32x4 o) {
+    f16x4 v;
 #pragma unroll
-    for (int b = 0; b < DB; ++b)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) oacc[b][e] *= inv;
-  }
-  {
-    constexpr int CPR = DH / 8;                       // 16-byte chunks per patch row
-    constexpr int RPI = 64 / CPR;                     // patch rows per store instruction
-    char *pb = lds + q_group * (32 * DH * 2);
-    auto pkey = [](int row) { return CPR == 8 ? (row >> 1) & 7 : (row >> 2) & 3; };   // spreads 16 rows over 256 bytes
+    for (int i = 0; i < 4; ++i) v[i] = to_f16_sat(o[i]);
+    const int c = 4 * b + g;
+    *(f16x4 *)(pb + l32 * (DH * 2) + ((c ^ pkey(l32)) << 4) + 8 * lhalf) = v;
+  };
+  const int rl = lane / CPR, c = lane % CPR;
+  half_t *obase = O + (int64_t)it.q_row * d + head * DH + c * 8;
+  auto store_rows = [&](int t) {
+    const int row = t * RPI + rl;
+    const f16x8 v = *(const f16x8 *)(pb + row * (DH * 2) + ((c ^ pkey(row)) << 4));
+    if (q_local0 + row < it.n_q) store_once<NT>(v, (f16x8 *)(obase + (int64_t)(q_local0 + row) * d));
+  };
+  if constexpr (KSPLIT) {
+    // The four wavefronts of a row group leave their partial outputs (and their softmax states) in LDS behind the patches; each
+    // adds up a quarter of the features, in the order (0 + 1) + (2 + 3), and stores a quarter of the rows.
+    constexpr int PART = DB * 16 * 64 * 4;            // bytes of one wavefront's accumulators
+    static_assert(QG * (32 * DH * 2) + NW * (PART + 512) <= NSTAGE * STAGE, "patches and partial outputs fit in the tile buffers");
+    char *area = lds + QG * (32 * DH * 2) + q_group * KP * (PART + 512);
+    char *mine = area + k_part * (PART + 512);
 #pragma unroll
     for (int b = 0; b < DB; ++b)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        f16x4 v;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = to_f16_sat(oacc[b][4 * g + i]);
-        const int c = 4 * b + g;
-        *(f16x4 *)(pb + l32 * (DH * 2) + ((c ^ pkey(l32)) << 4) + 8 * lhalf) = v;
+        const f32x4 v = {oacc[b][4 * g], oacc[b][4 * g + 1], oacc[b][4 * g + 2], oacc[b][4 * g + 3]};
+        *(f32x4 *)(mine + ((b * 4 + g) * 64 + lane) * 16) = v;
       }
-    const int rl = lane / CPR, c = lane % CPR;
-    half_t *obase = O + (int64_t)it.q_row * d + head * DH + c * 8;
+    if constexpr (SOFTMAX) *(float2 *)(mine + PART + lane * 8) = float2{m_run, l_run};
+    __syncthreads();
+    float sc[KP];
+    if constexpr (SOFTMAX) {
+      float2 ml[KP];
 #pragma unroll
-    for (int t = 0; t < 32 / RPI; ++t) {
-      const int row = t * RPI + rl;
-      const f16x8 v = *(const f16x8 *)(pb + row * (DH * 2) + ((c ^ pkey(row)) << 4));
-      if (q_local0 + row < it.n_q) store_once<NT>(v, (f16x8 *)(obase + (int64_t)(q_local0 + row) * d));
+      for (int p = 0; p < KP; ++p) ml[p] = *(const float2 *)(area + p * (PART + 512) + PART + lane * 8);
+      const float m_all = fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x));
+      float l_all = 0.f;
+#pragma unroll
+      for (int p = 0; p < KP; ++p) {
+        sc[p] = __builtin_amdgcn_exp2f(ml[p].x - m_all);
+        l_all += ml[p].y * sc[p];
+      }
+      const float lt = pair_sum(l_all);
+      const float inv = lt > 0.f ? 1.0f / lt : 0.f;
+#pragma unroll
+      for (int p = 0; p < KP; ++p) sc[p] *= inv;
     }
+#pragma unroll
+    for (int b = 0; b < DB; ++b) {
+      f32x4 v[KP];
+#pragma unroll
+      for (int p = 0; p < KP; ++p) {
+        v[p] = *(const f32x4 *)(area + p * (PART + 512) + ((b * 4 + k_part) * 64 + lane) * 16);
+        if constexpr (SOFTMAX) v[p] *= sc[p];
+      }
+      to_patch(b, k_part, (v[0] + v[1]) + (v[2] + v[3]));
+    }
+    __syncthreads();
+    if (k_part < 32 / RPI) store_rows(k_part);
+  } else {
+    if constexpr (SOFTMAX) {
+      const float lt = pair_sum(l_run);
+      const float inv = lt > 0.f ? 1.0f / lt : 0.f;
+#pragma unroll
+      for (int b = 0; b < DB; ++b)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) oacc[b][e] *= inv;
+    }
+#pragma unroll
+    for (int b = 0; b < DB; ++b)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) to_patch(b, g, f32x4{oacc[b][4 * g], oacc[b][4 * g + 1], oacc[b][4 * g + 2], oacc[b][4 * g + 3]});
+#pragma unroll
+    for (int t = 0; t < 32 / RPI; ++t) store_rows(t);
   }
 }
 
@@ -636,7 +659,7 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
 // The latency configuration needs its LDS limit raised once per kernel instance (a function attribute, no
 // allocation); handles in latency mode do it when they are created, outside any stream capture.
 template <int DH>
-constexpr int key_split_lds_bytes() { return NSTAGE * (2 * 128 * DH * 2 + 8 * 256); }
+constexpr int key_split_lds_bytes() { return 2 * (2 * 256 * DH * 2 + 8 * 256); }   // two stages of K, V^T and the bias window
 
 template <int DH, bool SM>
 static hipError_t key_split_setup() {
@@ -671,7 +694,7 @@ void launch_attn_bf16(PlanePtrs planes, const float *bias_lh, const float *tscal
     }
     return;
   }
-  const bool nt = (int64_t)n_items * QT * sh.d * 2 > kStreamBytes;
+  const bool nt = (int64_t)n_items * kAttnQTileBf16 * sh.d * 2 > kStreamBytes;
 #define ATTN_LAUNCH(DHV, SM, NTV) attn_mfma_kernel<DHV, SM, false, NTV><<<grid, 256, 0, s>>>(planes, bias_lh, tscale_h, (half_t *)O, items, sh.H, sh.d, sh.D, sh.ws_rows)
 #define ATTN_CASE(DHV, SM) do { if (nt) ATTN_LAUNCH(DHV, SM, true); else ATTN_LAUNCH(DHV, SM, false); } while (0)
   if (sh.softmax) {

@@ -13,7 +13,7 @@ struct Shape {
   float eps, alpha;
   int64_t ws_rows;  // rows of every workspace matrix (plane stride = ws_rows * d)
   int softmax;      // attention weights: 0 = pointwise SiLU, 1 = softmax with a temperature per layer and head
-  int latency;      // MFMA attention: 0 = throughput configuration, 1 = latency configuration (pairs of wavefronts split the keys)
+  int latency;      // MFMA attention: 0 = throughput configuration, 1 = latency configuration (four wavefronts split the keys of a query tile)
 };
 
 // ---- shared small kernels (misc.hip) --------------------------------------------------------
@@ -110,6 +110,7 @@ void launch_k3_fused(const void *O, const void *U, const void *gamma, const void
 constexpr int64_t kStreamBytes = 16 << 20;
 
 constexpr int kAttnQTileBf16 = 128;  // query rows per attention work item, MFMA path
+constexpr int kAttnQTileLatency = 64;  // the same in the latency configuration
 constexpr int kAttnQTileF32 = 64;    // fp32 path
 
 }  // namespace flame

@@ -165,7 +165,7 @@ int build_plan(const flame_gr_config &cfg, const int32_t *hoff, const int32_t *c
     G.hblk_begin = (int32_t)p.hist_blocks.size();
     for (; si < p.segs.size() && p.segs[si].group == g; ++si) {
       Segment &s = p.segs[si];
-      // The last kSpareRows rows of the workspace stay out of every plan: key tiles of up to 128 rows are loaded
+      // The last kSpareRows rows of the workspace stay out of every plan: key tiles of up to 256 rows are loaded
       // whole, so the tile that starts inside the last segment may reach that far past its end.  (Unsplit
       // batches within the create-time capacities always fit; a split batch repeats histories and may not.)
       if (row + s.Lp + s.Mp > ws_rows - kSpareRows) return fail(FLAME_GR_CAPACITY_EXCEEDED, "padded batch does not fit the workspace sized at create");
