@@ -90,7 +90,7 @@ __device__ __forceinline__ f16x8 pack8(const float *v) {
 // tile each (two wavefronts per SIMD, so one's MFMAs run under the other's VALU work) and add their partial outputs
 // through LDS at the end, in a fixed order.  The chain is a quarter as many steps, and a request of a few thousand rows has enough
 // query tiles for every CU; the sums are grouped differently, so the two configurations agree to rounding, not bit for bit.
-// One request of 2573 + 217, 8 heads: LATENCY_US us per launch (32 with query tiles of 128 and two wavefronts per group on key tiles of 128).
+// One request of 2573 + 217, 8 heads: 22 us per launch (32 with query tiles of 128 and two wavefronts per group on key tiles of 128).
 template <int DH, bool SOFTMAX, bool KSPLIT, bool NT>
 __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_kernel(PlanePtrs planes, const float *__restrict__ bias_lh,
                                                            const float *__restrict__ tscale_h,
