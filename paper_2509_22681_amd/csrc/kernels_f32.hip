@@ -51,7 +51,7 @@ __device__ __forceinline__ float row16_sum(float v) {
 // EPI 1: X[m][n] += C with A = (LayerNorm(O) * gamma + beta) * U, made while the chunk is staged: the statistics of the 64
 //        rows come first (mean, then the centred second moment), and the gated rows never travel through memory.
 // The matrix rate is the bound for large batches (64 cycles per instruction), latency for small ones.  20 480 rows, d = 256:
-// K1 260 -> 106 us (10.7 GFLOP at 101 TFLOP/s; the instruction alone reaches 157), LN, gate and output projection 71 + 11 -> 47 us,
+// K1 260 -> 106 us (10.7 GFLOP at 101 TFLOP/s; the instruction alone reaches 157), LN, gate and output projection 71 + 11 -> 45 us,
 // against plain FMA kernels on 64 x 64 tiles with a LayerNorm pass of its own.
 // ---------------------------------------------------------------------------------------------
 // NI (EPI 1): 16-byte loads per lane and row that the statistics keep in registers, ceil(K / 64) at least; 0: any K, in two reads of the rows.
@@ -144,32 +144,43 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
     }
     __syncthreads();
   }
-  // staging: thread (row = tid / 8 + 32 i, chunk = tid % 8) brings 16 bytes of either operand
+  // staging: thread (row = tid / 8 + 32 i, chunk = tid % 8) brings 16 bytes of either operand.  The loads stay as they come until store():
+  // an operand made in fetch() would wait for its loads ahead of the matrix work that is there to hide them (20 480 rows, d = 256: 59 -> 45 us
+  // per launch, with the residual's requests below; 64 blocks of rows 20 -> 14.4).
+  // VEC loads are unconditional, at a clamped address where the matrix ends, and zeroed in store() (a branch around each costs more).
   const int sr = tid >> 3, sc = tid & 7;
-  f32x4 ra[LPT], rw[LPT];
+  f32x4 ra[LPT], rw[LPT], ru[EPI == 1 ? LPT : 1], rg, rb;
+  float mu[EPI == 1 ? LPT : 1], rstd[EPI == 1 ? LPT : 1];
+  if constexpr (EPI == 1) {
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) { mu[i] = s_mu[sr + 32 * i]; rstd[i] = s_rstd[sr + 32 * i]; }
+  }
+  auto load = [&](const float *p, int k) { return VEC ? *(const f32x4 *)(p + min(k, K - 4)) : load4<false>(p, k, K); };
   auto fetch = [&](int k0) {
     const int k = k0 + 4 * sc;
+    if constexpr (EPI == 1) { rg = load(gamma, k); rb = load(beta, k); }
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
       const int r = sr + 32 * i;
       const int64_t m = row0[T == 1 ? 0 : r >> 6] + (r & 63);
-      ra[i] = load4<VEC>(A + m * K, k, K);
-      if constexpr (EPI == 1) {
-        const f32x4 u = load4<VEC>(U + m * K, k, K), g = load4<VEC>(gamma, k, K), b = load4<VEC>(beta, k, K);
-        const float mu = s_mu[r], rstd = s_rstd[r];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) ra[i][t] = r < n_valid ? ((ra[i][t] - mu) * rstd * g[t] + b[t]) * u[t] : 0.f;
-      }
-      const int n = n0 + r;
-      rw[i] = n < Ncols ? load4<VEC>(W + (int64_t)n * K, k, K) : f32x4{0.f, 0.f, 0.f, 0.f};
+      ra[i] = load(A + m * K, k);
+      if constexpr (EPI == 1) ru[i] = load(U + m * K, k);
+      rw[i] = load(W + (int64_t)min(n0 + r, Ncols - 1) * K, k);     // (columns past the matrix are computed and not stored)
     }
   };
-  auto store = [&](int st) {
+  auto store = [&](int st, int k0) {
+    const bool inside = !VEC || k0 + 4 * sc < K;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
       const int r = sr + 32 * i, off = r * BK + ((sc ^ ((r >> 1) & 7)) << 2);
-      *(f32x4 *)(sA[st] + off) = ra[i];
-      *(f32x4 *)(sW[st] + off) = rw[i];
+      f32x4 v = ra[i];
+      if constexpr (EPI == 1) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] = ((v[t] - mu[i]) * rstd[i] * rg[t] + rb[t]) * ru[i][t];
+      }
+      *(f32x4 *)(sA[st] + off) = inside && (EPI == 0 || r < n_valid) ? v : zero;
+      *(f32x4 *)(sW[st] + off) = inside ? rw[i] : zero;
     }
   };
   f32x16 acc[T][T];
@@ -179,13 +190,22 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
     for (int j = 0; j < T; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  // the residual's 16 values of this lane, requested ahead of the k loop (read one by one between its stores they would cost 16
+  // memory latencies in a row)
+  float xr[16];
+  if constexpr (EPI == 1) {
+    const float *x = out + (row0[0] + wm * 32 + 4 * lhalf) * d + min(n0 + wn * 32 + l32, Ncols - 1);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) xr[e] = x[(int64_t)(8 * (e >> 2) + (e & 3)) * d];
+  }
   fetch(0);
-  store(0);
+  store(0, 0);
   __syncthreads();
   const int nk = (K + BK - 1) / BK;
   for (int kc = 0; kc < nk; ++kc) {
     const int st = kc & 1;
     if (kc + 1 < nk) fetch((kc + 1) * BK);
+    __builtin_amdgcn_sched_barrier(0);     // the requests stay ahead of the matrix work
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       f32x4 fa[T], fw[T];
@@ -200,7 +220,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
 #pragma unroll
         for (int j = 0; j < T; ++j) mfma_f32_k8(fa[i], fw[j], acc[i][j]);
     }
-    if (kc + 1 < nk) store(st ^ 1);       // the other stage: everybody left it at the barrier that opened this chunk
+    __builtin_amdgcn_sched_barrier(0);
+    if (kc + 1 < nk) store(st ^ 1, (kc + 1) * BK);       // the other stage: everybody left it at the barrier that opened this chunk
     __syncthreads();
   }
   // a lane holds one output column and 16 rows: 32 lanes write 128 contiguous bytes of a row
@@ -219,7 +240,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
         const int64_t m = row0[blk] + (rb & 63) + 8 * (e >> 2) + 4 * lhalf + (e & 3);
         const float v = acc[i][j][e] + bn;
         if (EPI == 0) col[m * d] = silu_f32(v);
-        else col[m * d] += v;
+        else col[m * d] = xr[e] + v;
       }
     }
   }
@@ -296,6 +317,8 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
   const int q_index = it.is_cand ? it.L : it.q_pos + q_local;
   const int n_vis = row_valid ? visible_history(it.is_cand, q_index, it.L) : 0;
   const int vis_max = active ? (it.is_cand ? it.L : min(it.q_pos + q0 + 32, it.n_kv)) : 0;
+  // every row of this group sees all keys before vis_min (no row does where the tile ends inside the group)
+  const int vis_min = q0 + 32 > it.n_q ? 0 : it.is_cand ? it.L : it.q_pos + q0 + 1;
   constexpr float kNeg = -1.0e30f;                   // a finite stand-in for -inf
   const float ts = SOFTMAX ? tscale_h[h] : 0.f;
   float m_run = kNeg, l_run = 0.f;                   // softmax: running maximum of my row, and the sum over this lane's keys
@@ -365,14 +388,19 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int c = k0 + 8 * (e >> 2) + 4 * lhalf + (e & 3);
-        p[e] = c < n_vis ? expf(p[e] - m_new) : 0.f;
+        p[e] = expf(p[e] - m_new);
+        asm volatile("" : "+v"(p[e]));     // (keeps the mask below a select: see the other branch)
+        p[e] = c < n_vis ? p[e] : 0.f;
         l_run += p[e];
       }
     } else {
+      // (all weights first, then the mask: written as one conditional expression, the compiler branches around every single weight and
+      // runs sixteen dependent chains one after another: a short launch, 32 x 128 candidates on 512 keys, 33.8 -> 31.0 us)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int c = k0 + 8 * (e >> 2) + 4 * lhalf + (e & 3);
-        p[e] = c < n_vis ? silu_f32(alpha * sacc[e] + bz[e]) : 0.f;
+      for (int e = 0; e < 16; ++e) p[e] = silu_f32(alpha * sacc[e] + bz[e]);
+      if (k0 + 32 > vis_min) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) p[e] = k0 + 8 * (e >> 2) + 4 * lhalf + (e & 3) < n_vis ? p[e] : 0.f;
       }
     }
 #pragma unroll
