@@ -285,8 +285,11 @@ void launch_outproj_f32(const float *O, const float *U, const float *gamma, cons
 // that take every other block of 32 keys and add up at the end (in a fixed order).  Transposed products as in the fp16
 // kernel: S^T = K Q^T puts 16 keys of one query into a lane, in the very slots that O^T += V^T P^T takes as its B operand
 // (instruction e of a block multiplies keys 8 (e / 4) + e % 4 and + 4), so the weights never leave their registers.
-// Operands come straight from global memory: a block of 32 keys is 64 matrix instructions of 64 cycles (head width 64) against 16 KB
-// of K and V, which L1 and L2 deliver many times over, and no barrier ties the wavefronts together.  The matrix rate bounds it.
+// STAGED (heads of exactly 32 or 64): K and V arrive by LDS-DMA in tiles of 64 keys, two stages, the next tile requested while this one is
+// multiplied.  A lane's 16 bytes of a K row from global memory are 32 lines per instruction, 360 requests per block of 32 keys and
+// wavefront, and the compute unit has too few of them in flight to feed the matrix instruction; through LDS a wavefront makes 64 for a tile.
+// 32 x (512 + 128), 4 heads of 64: 106 -> 91 us per launch (43 at the matrix rate), the candidates alone 31 -> 33 us.
+// Other widths read their operands straight from global memory, without a barrier.
 // DB = 32-wide blocks of the head; EXACT: the head is exactly 32 DB wide (vector loads), else elements past it count as zero.
 // A lane's V operand of block b is feature DB * row + b, so that one load brings a lane's features of all blocks.
 // ---------------------------------------------------------------------------------------------
@@ -298,8 +301,17 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
   constexpr int NG = 4 * DB;                         // groups of eight features
   constexpr int DBR = DB < 4 ? DB : 4;               // head blocks that leave per round at the end
   constexpr int PITCH = 32 * DBR + 4;                // floats per row of the output patch of 32 query rows
-  __shared__ __attribute__((aligned(16))) float s_patch[2][32 * PITCH];
-  __shared__ float s_state[2][2][64], s_row[2][2][32];
+  // STAGED: two LDS stages of a tile of 64 keys, K rows and V rows of RB bytes, 16-byte chunks XOR-swizzled by row.  The output patches
+  // and the row states reuse them once the keys are done.
+  constexpr bool STAGED = EXACT && DB <= 2;
+  constexpr int RB = 128 * DB, CH = RB / 16, TILE = 64 * RB, STAGE = 2 * TILE;
+  constexpr int PATCH_BYTES = 2 * 32 * PITCH * 4, TAIL_BYTES = PATCH_BYTES + (2 * 2 * 64 + 2 * 2 * 32) * 4;
+  constexpr int LDS_BYTES = STAGED && 2 * STAGE > TAIL_BYTES ? 2 * STAGE : TAIL_BYTES;
+  __shared__ __attribute__((aligned(256))) char lds[LDS_BYTES];
+  float (*const s_patch)[32 * PITCH] = (float (*)[32 * PITCH])lds;
+  float (*const s_state)[2][64] = (float (*)[2][64])(lds + PATCH_BYTES);
+  float (*const s_row)[2][32] = (float (*)[2][32])(lds + PATCH_BYTES + 2 * 2 * 64 * 4);
+  auto lkey = [](int row) { return CH == 16 ? row & 15 : (row >> 1) & 7; };
   const AttnItem it = items[blockIdx.y];             // heads of an item side by side: the longest items of all heads start first
   const int h = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -345,29 +357,14 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
 #pragma unroll
     for (int g = 0; g < NG; ++g) fk[g] = row4(Kp + ((int64_t)it.kv_row + k0 + l32) * d, g);
   };
-  const int first = split * 32, pitch = 64;
-  if (first < vis_max) load_k(first);
-  for (int k0 = first; k0 < vis_max; k0 += pitch) {
-    // V and the bias of this block are requested ahead of its S, K of the next block ahead of its V^T P
-    float fv[16][DB], bz[16];
+  // One block of 32 keys: S^T, weights, O^T; fv[e][b] = feature DB l32 + b of key 8 (e / 4) + 4 lhalf + e % 4, bz the keys' bias.
+  float fv[16][DB], bz[16];
+  auto load_bias = [&](int k0) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int c = k0 + 8 * (e >> 2) + 4 * lhalf + (e & 3);
-      const float *vr = Vp + ((int64_t)it.kv_row + c) * d + DB * l32;
-      if constexpr (EXACT && DB == 2) { const float2 v = *(const float2 *)vr; fv[e][0] = v.x; fv[e][1] = v.y; }
-      else if constexpr (EXACT && DB == 4) { const f32x4 v = *(const f32x4 *)vr; for (int b = 0; b < DB; ++b) fv[e][b] = v[b]; }
-      else {
-#pragma unroll
-        for (int b = 0; b < DB; ++b) fv[e][b] = EXACT || DB * l32 + b < dh ? vr[b] : 0.f;
-      }
-      bz[e] = bias[max(0, min(D - 1, q_index - c))];
-    }
-    f32x16 sacc;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) sacc[e] = 0.f;
-#pragma unroll
-    for (int g = 0; g < NG; ++g) mfma_f32_k8(fk[g], fq[g], sacc);
-    if (k0 + pitch < vis_max) load_k(k0 + pitch);
+    for (int e = 0; e < 16; ++e) bz[e] = bias[max(0, min(D - 1, q_index - (k0 + 8 * (e >> 2) + 4 * lhalf + (e & 3))))];
+  };
+  float pw[16];
+  auto weigh = [&](int k0, const f32x16 &sacc) {
     float p[16];
     if constexpr (SOFTMAX) {
       float mt = kNeg;
@@ -404,9 +401,92 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
       }
     }
 #pragma unroll
+    for (int e = 0; e < 16; ++e) pw[e] = p[e];
+  };
+  auto add_pv = [&]() {
+#pragma unroll
     for (int e = 0; e < 16; ++e)
 #pragma unroll
-      for (int b = 0; b < DB; ++b) oacc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fv[e][b], p[e], oacc[b], 0, 0, 0);
+      for (int b = 0; b < DB; ++b) oacc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fv[e][b], pw[e], oacc[b], 0, 0, 0);
+  };
+  if constexpr (STAGED) {
+    typedef __attribute__((address_space(1))) const void gvoid;
+    typedef __attribute__((address_space(3))) void lvoid;
+    constexpr int RPI = 1024 / RB, NI = 64 / RPI / 4;    // rows per request, requests per wavefront and operand
+    static_assert(4 * RPI % 16 == 0, "a wavefront's requests of one tile share their swizzle key");
+    const int rq = wave * RPI + lane / CH;               // tile row of this lane in its first request
+    const uint32_t off = (uint32_t)(rq * d + (((lane % CH) ^ lkey(rq)) << 2)) * 4u;
+    auto request = [&](int st, int k0) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int64_t r = (int64_t)(it.kv_row + k0 + 4 * RPI * i) * d;
+        char *dst = lds + st * STAGE + (wave + 4 * i) * 1024;
+        __builtin_amdgcn_global_load_lds((gvoid *)((const char *)(Kp + r) + off), (lvoid *)dst, 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((gvoid *)((const char *)(Vp + r) + off), (lvoid *)(dst + TILE), 16, 0, 0);
+      }
+    };
+    // this lane's K row, and its V bytes of a row whose index has bit 2 clear (the half wavefront adds 4 rows)
+    const int kr = 32 * split + l32;
+    const int ka = kr * RB + ((lhalf ^ lkey(kr)) << 4);
+    const int va = 4 * lhalf * RB + (((DB * l32 / 4) ^ lkey(4 * lhalf)) << 4) + (DB * l32 % 4) * 4;
+    const int n_tiles = (it.n_kv + 63) / 64;             // the same for all wavefronts
+    if (n_tiles > 0) request(0, 0);
+    for (int t = 0; t < n_tiles; ++t) {
+      const int k0 = 64 * t + 32 * split;
+      const bool work = k0 < vis_max;
+      const char *sk = lds + (t & 1) * STAGE, *sv = sk + TILE;
+      // tile t has landed for everybody, and everybody has left tile t - 1, whose stage takes tile t + 1
+      // (the builtin: the compiler knows it and sees that the query rows have landed too)
+      __builtin_amdgcn_s_waitcnt(0x0f70);                // vmcnt(0)
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      if (work) load_bias(k0);
+      if (t + 1 < n_tiles) request((t + 1) & 1, 64 * (t + 1));
+      __builtin_amdgcn_sched_barrier(0);
+      if (!work) continue;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) fk[g] = *(const f32x4 *)(sk + (ka ^ (g << 5)));
+      f32x16 sacc;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sacc[e] = 0.f;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) mfma_f32_k8(fk[g], fq[g], sacc);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int r0 = 8 * (e >> 2) + (e & 3);           // + 32 split: a multiple of the key's period
+        const float *v = (const float *)(sv + (32 * split + r0) * RB + (va ^ (lkey(r0) << 4)));
+        if constexpr (DB == 2) { const float2 w = *(const float2 *)v; fv[e][0] = w.x; fv[e][1] = w.y; }
+        else fv[e][0] = *v;
+      }
+      weigh(k0, sacc);
+      add_pv();
+    }
+    __syncthreads();                                     // everybody has left the last tile
+  } else {
+    const int first = split * 32, pitch = 64;
+    if (first < vis_max) load_k(first);
+    for (int k0 = first; k0 < vis_max; k0 += pitch) {
+      // V and the bias of this block are requested ahead of its S, K of the next block ahead of its V^T P
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const float *vr = Vp + ((int64_t)it.kv_row + k0 + 8 * (e >> 2) + 4 * lhalf + (e & 3)) * d + DB * l32;
+        if constexpr (EXACT && DB == 4) { const f32x4 v = *(const f32x4 *)vr; for (int b = 0; b < DB; ++b) fv[e][b] = v[b]; }
+        else {
+#pragma unroll
+          for (int b = 0; b < DB; ++b) fv[e][b] = EXACT || DB * l32 + b < dh ? vr[b] : 0.f;
+        }
+      }
+      load_bias(k0);
+      f32x16 sacc;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sacc[e] = 0.f;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) mfma_f32_k8(fk[g], fq[g], sacc);
+      if (k0 + pitch < vis_max) load_k(k0 + pitch);
+      weigh(k0, sacc);
+      add_pv();
+    }
   }
   // ---- the two wavefronts of a row group add up, and the rows leave as whole lines: a lane holds scattered features of one
   // query, so the sums pass through a patch of rows in LDS.
