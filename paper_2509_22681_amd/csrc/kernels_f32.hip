@@ -296,7 +296,7 @@ void launch_outproj_f32(const float *O, const float *U, const float *gamma, cons
 template <int DB, bool EXACT, bool SOFTMAX>
 __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__ U_V_Q_K, const float *__restrict__ bias_lh,
                                                        const float *__restrict__ tscale_h,
-                                                       float *__restrict__ O, const AttnItem *__restrict__ items,
+                                                       float *__restrict__ O, const AttnItem *__restrict__ items, int n_items,
                                                        int d, int dh, int D, float alpha, int64_t plane_stride) {
   constexpr int NG = 4 * DB;                         // groups of eight features
   constexpr int DBR = DB < 4 ? DB : 4;               // head blocks that leave per round at the end
@@ -312,7 +312,9 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
   float (*const s_state)[2][64] = (float (*)[2][64])(lds + PATCH_BYTES);
   float (*const s_row)[2][32] = (float (*)[2][32])(lds + PATCH_BYTES + 2 * 2 * 64 * 4);
   auto lkey = [](int row) { return CH == 16 ? row & 15 : (row >> 1) & 7; };
-  const AttnItem it = items[blockIdx.y];             // heads of an item side by side: the longest items of all heads start first
+  const int item = blockIdx.z * gridDim.y + blockIdx.y;   // heads of an item side by side: the longest items of all heads start first
+  if (item >= n_items) return;
+  const AttnItem it = items[item];
   const int h = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l32 = lane & 31, lhalf = lane >> 5;
@@ -578,8 +580,9 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
 void launch_attn_f32(const float *planes, const float *bias_lh, const float *tscale_h, float *O, const AttnItem *items,
                      int n_items, const Shape &sh, hipStream_t s) {
   if (n_items <= 0) return;
-  const dim3 grid(sh.H, n_items);
-#define ATTN_CASE(DBV, EX, SM) attn_f32_kernel<DBV, EX, SM><<<grid, 256, 0, s>>>(planes, bias_lh, tscale_h, O, items, sh.d, sh.dh, sh.D, sh.alpha, sh.ws_rows * sh.d)
+  constexpr int kGridY = 32768;        // a launch takes at most 65 535 workgroups along y
+  const dim3 grid(sh.H, n_items < kGridY ? n_items : kGridY, (n_items + kGridY - 1) / kGridY);
+#define ATTN_CASE(DBV, EX, SM) attn_f32_kernel<DBV, EX, SM><<<grid, 256, 0, s>>>(planes, bias_lh, tscale_h, O, items, n_items, sh.d, sh.dh, sh.D, sh.alpha, sh.ws_rows * sh.d)
 #define ATTN_WIDTH(DBV) do { const bool ex = sh.dh == 32 * DBV; \
     if (sh.softmax) { if (ex) ATTN_CASE(DBV, true, true); else ATTN_CASE(DBV, false, true); } \
     else { if (ex) ATTN_CASE(DBV, true, false); else ATTN_CASE(DBV, false, false); } } while (0)

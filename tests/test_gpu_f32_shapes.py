@@ -55,3 +55,27 @@ def test_f32_shape(case, unaligned, kind):
     worst = score_err(g, want)
     print(f"{case} unaligned={unaligned} {kind}: {worst:.2e}")
     assert worst <= TOL_HOT["f32"], worst
+
+
+def test_f32_more_items_than_one_grid_dimension_holds():
+    """70 000 requests of one history row are more attention items than a launch may have along y; each scores as it does alone."""
+    import torch
+    from paper_2509_22681_amd import binding as B
+    n = 70_000
+    wl = W.make_custom([1] * n, [1] * n, d=32, H=1, n_layers=2, n_buckets=16, max_rel_dist=16, dtype="f32", seed=5, name="many_items")
+
+    def scores(w):
+        h = B.flame_gr_create(B.config_for(w))
+        try:
+            dw, hist, cand = B.to_device(w)
+            out = torch.full((int(w.cand_offsets[-1]),), float("nan"), device="cuda:0")
+            B.flame_gr_forward(h, dw, hist, w.history_offsets, cand, w.cand_offsets, out)
+            torch.cuda.synchronize()
+            return out.cpu().numpy()
+        finally:
+            B.flame_gr_destroy(h)
+
+    whole = scores(wl)
+    assert np.isfinite(whole).all()
+    idx = [0, 32_767, 32_768, 65_535, 65_536, n - 1]
+    assert np.array_equal(scores(wl.subset(idx)), whole[idx])
