@@ -53,8 +53,13 @@ __global__ __launch_bounds__(256) void pack_w2_kernel(const bf16_t *__restrict__
 // residual rows) is requested ahead of it.  Every output element is computed exactly as with RH = 2, CS = 1.
 // NT: O, U and the residual pair bypass the caches (consumed once; data of this size would push W2's fragments and K1's operands
 // out of L2).  Small batches are better off leaving them there for the next kernel (see launch_k3_fused).
+// k3_dense: half blocks with uncut features are for a few hundred row blocks, more than two workgroups per CU.  Three wavefronts per SIMD hold
+// them all at once, where two run a second, nearly empty round; the registers for that come from the residual rows, which are
+// requested behind phase 1 instead of ahead of it, and a shorter W2 ring.  Per launch: 320 row blocks, d = 256: 22.2 -> 18.2 us; 384, d = 192: 23.1 -> 18.4 us
+// (12.8 and 11.6 at the rate of a large copy).
+constexpr bool k3_dense(int cs, int rh, int nbw) { return rh == 1 && cs == 1 && nbw == 2; }
 template <int NWV, int NBW, int CS, int RH, bool NT>
-__global__ __launch_bounds__(64 * NWV, 2) void k3_fused_kernel(const half_t *__restrict__ O, const half_t *__restrict__ U,
+__global__ __launch_bounds__(64 * NWV, k3_dense(CS, RH, NBW) ? 3 : 2) void k3_fused_kernel(const half_t *__restrict__ O, const half_t *__restrict__ U,
                                                           const bf16_t *__restrict__ gamma, const bf16_t *__restrict__ beta,
                                                           const half_t *__restrict__ W2p, const bf16_t *__restrict__ b2,
                                                           half_t *__restrict__ Xh, half_t *__restrict__ Xl, int lo_is_zero,
@@ -66,6 +71,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void k3_fused_kernel(const half_t *__r
   constexpr int RPW = (ROWS + NWV * RB4 - 1) / (NWV * RB4) * RB4;   // rows per wavefront in phase 1 (with three wavefronts a few too many)
   constexpr bool EVEN = RPW * NWV == ROWS;
   constexpr bool EARLY = RH == 1;                // requests that do not wait for phase 1 go out ahead of it
+  constexpr bool DENSE = k3_dense(CS, RH, NBW);  // (but the residual behind it)
   constexpr int NCHUNK = d / 8;                  // 16-byte chunks per row
   // Swizzle key of the gated rows in LDS.  A row of d fp16 is NCHUNK chunks; the MFMA operand reads take one chunk
   // column of 16 consecutive rows.  With NCHUNK a multiple of 16 the row pitch is a multiple of 256 bytes and the
@@ -125,7 +131,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void k3_fused_kernel(const half_t *__r
   // The W2 fragments come from L2, whose latency is several times the 8 MFMAs of a k-step: they are requested
   // PD - 1 k-steps ahead into a register ring (scheduling barriers keep the compiler from sinking the requests
   // back to their first use); the activations come from LDS, one step ahead.
-  constexpr int PD = !EARLY || NB2 > 2 ? 4 : NKS % 8 == 0 ? 8 : 4;
+  constexpr int PD = !EARLY || DENSE || NB2 > 2 ? 4 : NKS % 8 == 0 ? 8 : 4;
   static_assert(NKS % PD == 0, "k-steps are walked in groups of the ring depth");
   const half_t *wp = W2p + ((int64_t)fb0 * 64 + lane) * 8;      // + (ks * (d/32) + j) * 512
   f16x8 fw[PD][NB2], fa[2][RH];
@@ -153,8 +159,10 @@ __global__ __launch_bounds__(64 * NWV, 2) void k3_fused_kernel(const half_t *__r
   if (EARLY) {
     __builtin_amdgcn_sched_barrier(0);
     first_w2();
+    if (!DENSE) {
 #pragma unroll
-    for (int t = 0; t < XB; ++t) load_x(0, t, t);
+      for (int t = 0; t < XB; ++t) load_x(0, t, t);
+    }
     __builtin_amdgcn_sched_barrier(0);
   }
   if (EARLY) load_affine();
@@ -222,6 +230,11 @@ __global__ __launch_bounds__(64 * NWV, 2) void k3_fused_kernel(const half_t *__r
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
   if (!EARLY) first_w2();
+  if (DENSE) {
+#pragma unroll
+    for (int t = 0; t < XB; ++t) load_x(0, t, t);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 #pragma unroll
   for (int i = 0; i < RH; ++i) {
     const int r = 32 * i + l32;
@@ -323,8 +336,8 @@ void launch_k3_fused(const void *O, const void *U, const void *gamma, const void
   // / in four:
   //   d = 512: 16 blocks 21.6 / 15.8 / 12.0 / 10.1, 64: 22.4 / 17.1 / 14.0 / 13.9, 128: 24.0 / 19.6 / 22.3 / 21.6, 384: 39.8 / 39.0 / 46.3, 512: 45.2 / 49.7
   //   (44 blocks in a model of 16 layers, whose W2 is in no L2 when a layer starts: 12.9 in two, 14.6 in four)
-  //   d = 256: 16: 16.3 / 11.0 / 9.9, 64: 17.4 / 11.6 / 10.5, 128: 17.9 / 13.0 / 13.4, 384: 23.9 / 23.9, 512: 26.0 / 28.6
-  //   d = 192: 16: 20.1 / 12.4 / 11.5, 64: 20.6 / 12.9 / 12.3, 384: 26.5 / 23.4, 512: 28.0 / 28.4
+  //   d = 256: 16: 16.3 / 11.0 / 9.9, 64: 17.4 / 11.6 / 10.5, 128: 17.9 / 13.0 / 13.4, 256: - / 15.6, 384: 23.9 / 20.1, 448: 24.1 / 25.9, 512: 25.6 / 26.6
+  //   d = 192: 16: 20.1 / 12.4 / 11.5, 64: 20.6 / 12.9 / 12.3, 256: - / 15.2, 384: 26.5 / 19.8, 512: 27.2 / 26.5
   const bool nt = (int64_t)n_blk * kRowAlign * sh.d * 2 > kStreamBytes;
 #define K3_LAUNCH(NWV, NB, CSV, RHV, NTV) k3_fused_kernel<NWV, NB, CSV, RHV, NTV><<<dim3(n_blk * (3 - RHV), CSV), 64 * NWV, k3_lds_bytes(sh.d, CSV, RHV), s>>>((const half_t *)O, (const half_t *)U, (const bf16_t *)gamma, (const bf16_t *)beta, \
     (const half_t *)W2p_layer, (const bf16_t *)b2, (half_t *)Xh, (half_t *)Xl, lo_is_zero ? 1 : 0, blocks, blk_list, blk_first, sh.eps)
