@@ -36,9 +36,6 @@ struct StageLayout {  // byte offsets inside one staging buffer (host pinned and
 // What a pass covers: the whole batch, or one stage of the two-stage path (Section 5).
 enum PassMode { PASS_FULL = 0, PASS_HISTORY, PASS_CANDIDATES };
 
-// Query rows per attention work item.
-int attn_q_tile(const flame_gr_config &c) { return c.dtype != FLAME_GR_BF16 ? kAttnQTileF32 : c.latency_mode ? kAttnQTileLatency : kAttnQTileBf16; }
-
 struct ProfEvent { hipEvent_t a, b; int kind; };
 
 // One captured forward: the graph and the plan tables its kernels read (its own copy, so that eager
@@ -57,7 +54,6 @@ struct flame_gr {
   Shape sh{};
   int device = 0;
   int n_groups = 1;
-  int q_tile = 0;
   int64_t ws_rows = 0;
   size_t elt = 4;
   std::string err;
@@ -252,7 +248,7 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, const voi
       int n_it = G.item_end - G.item_begin;
       if (mode == PASS_HISTORY) { it = hitems + G.hitem_begin; n_it = G.hitem_end - G.hitem_begin; }
       else if (mode == PASS_CANDIDATES || last) { it = citems + G.citem_begin; n_it = G.citem_end - G.citem_begin; }
-      if (dt == FLAME_GR_BF16) launch_attn_bf16(pp, bias_l, tscale_l, h->O, it, n_it, sh, s);
+      if (dt == FLAME_GR_BF16) launch_attn_bf16(pp, bias_l, tscale_l, h->O, it, n_it, h->plan.q_tile, sh, s);
       else launch_attn_f32((const float *)planes, bias_l, tscale_l, (float *)h->O, it, n_it, sh, s);
     }
     const int32_t *bl = mode == PASS_FULL ? (last ? cl : nullptr) : pass_list;
@@ -430,7 +426,6 @@ int flame_gr_create(const flame_gr_config *cfg_in, flame_gr_t **out) {
   if (!h) { g_create_error = "out of host memory"; return FLAME_GR_HIP_ERROR; }
   h->cfg = cfg;
   h->n_groups = cfg.n_streams > 1 ? cfg.n_streams : 1;
-  h->q_tile = attn_q_tile(cfg);
   h->elt = cfg.dtype == FLAME_GR_BF16 ? 2 : 4;
   h->ws_rows = workspace_rows(cfg);
   h->sh = Shape{cfg.d_model, cfg.n_heads, cfg.d_model / cfg.n_heads, cfg.n_layers, cfg.n_buckets,
@@ -526,7 +521,7 @@ static int forward_common(flame_gr_t *h, const flame_gr_weights *w, const void *
   if (n_requests < 0) return bad("n_requests < 0");
   if (n_requests > 0 && (!history_offsets || !cand_offsets)) return bad("offset arrays are NULL");
   Plan plan;
-  int rc = build_plan(h->cfg, history_offsets, cand_offsets, n_requests, h->q_tile, h->n_groups, h->ws_rows, plan, h->err);
+  int rc = build_plan(h->cfg, history_offsets, cand_offsets, n_requests, h->n_groups, h->ws_rows, plan, h->err);
   if (rc) return rc;
   if (want_hidden && plan.split) { h->err = "hidden rows are not available for split requests"; return FLAME_GR_UNSUPPORTED; }
   const int64_t sumL = n_requests ? history_offsets[n_requests] : 0, sumM = n_requests ? cand_offsets[n_requests] : 0;
@@ -577,7 +572,7 @@ int flame_gr_capture(flame_gr_t *h, int32_t slot, const flame_gr_weights *w, con
   if (n_requests < 0) return bad("n_requests < 0");
   if (n_requests > 0 && (!history_offsets || !cand_offsets)) return bad("offset arrays are NULL");
   Plan plan;
-  int rc = build_plan(h->cfg, history_offsets, cand_offsets, n_requests, h->q_tile, 1, h->ws_rows, plan, h->err);
+  int rc = build_plan(h->cfg, history_offsets, cand_offsets, n_requests, 1, h->ws_rows, plan, h->err);
   if (rc) return rc;
   const int64_t sumL = n_requests ? history_offsets[n_requests] : 0, sumM = n_requests ? cand_offsets[n_requests] : 0;
   if (sumM == 0) return bad("nothing to capture: the batch has no candidates");
@@ -661,7 +656,7 @@ int flame_gr_prefill(flame_gr_t *h, const flame_gr_weights *w, const void *histo
   if (n_requests > 0 && (!history_offsets || !cand_capacity)) return bad("history_offsets or cand_capacity is NULL");
   const std::vector<int32_t> no_cands((size_t)n_requests + 1, 0);
   Plan plan;
-  int rc = build_plan(h->cfg, history_offsets, no_cands.data(), n_requests, h->q_tile, h->n_groups, h->ws_rows, plan,
+  int rc = build_plan(h->cfg, history_offsets, no_cands.data(), n_requests, h->n_groups, h->ws_rows, plan,
                       h->err, cand_capacity);
   if (rc) return rc;
   const int64_t sumL = n_requests ? history_offsets[n_requests] : 0;
@@ -693,7 +688,7 @@ int flame_gr_score(flame_gr_t *h, const flame_gr_weights *w, const void *cand_em
   if (n_requests != (int32_t)h->kv_cap.size()) return bad("n_requests differs from the prefill");
   if (n_requests > 0 && !cand_offsets) return bad("cand_offsets is NULL");
   Plan plan;
-  int rc = build_plan(h->cfg, h->kv_hoff.data(), cand_offsets, n_requests, h->q_tile, h->n_groups, h->ws_rows, plan,
+  int rc = build_plan(h->cfg, h->kv_hoff.data(), cand_offsets, n_requests, h->n_groups, h->ws_rows, plan,
                       h->err, h->kv_cap.data());
   if (rc) return rc;
   const int64_t sumM = n_requests ? cand_offsets[n_requests] : 0;
@@ -800,9 +795,8 @@ int flame_gr_forward_static(const flame_gr_config *cfg_in, const flame_gr_weight
   if (rc) return rc;
   const bool bf = cfg.dtype == FLAME_GR_BF16;
   h.n_groups = 1;
-  h.q_tile = attn_q_tile(cfg);
   h.elt = bf ? 2 : 4;
-  rc = build_plan(cfg, history_offsets, cand_offsets, n_requests, h.q_tile, 1, (int64_t)1 << 40, h.plan, g_create_error);
+  rc = build_plan(cfg, history_offsets, cand_offsets, n_requests, 1, (int64_t)1 << 40, h.plan, g_create_error);
   if (rc) return rc;
   const Plan &P = h.plan;
   const int64_t sumL = n_requests ? history_offsets[n_requests] : 0, sumM = n_requests ? cand_offsets[n_requests] : 0;
@@ -922,7 +916,7 @@ static int host_plan(const flame_gr_config *cfg_in, const int32_t *history_offse
   int rc = validate_config(cfg, err);
   if (!rc) {
     Plan P;
-    rc = build_plan(cfg, history_offsets, cand_offsets, n_requests, attn_q_tile(cfg), cfg.n_streams > 1 ? cfg.n_streams : 1,
+    rc = build_plan(cfg, history_offsets, cand_offsets, n_requests, cfg.n_streams > 1 ? cfg.n_streams : 1,
                     workspace_rows(cfg), P, err, cand_capacity);
     if (!rc) {
       if (tok_off) std::memcpy(tok_off, P.tok_off.data(), P.tok_off.size() * sizeof(int32_t));

@@ -83,25 +83,31 @@ __device__ __forceinline__ f16x8 pack8(const float *v) {
 // with tscale = 2 log2(e) / tau.  The 64 keys of a half tile of one query sit in two lanes (lane and lane ^ 32),
 // which exchange their maxima with one half-swap; their partial sums are only added at the end.
 //
-// KSPLIT = false is the throughput configuration described at the top: 4 wavefronts, key tiles of 64, three
-// workgroups per CU.  KSPLIT = true is the latency configuration for batches too small to fill the chip, where a
-// workgroup sits alone on its CU and its run time is the chain of key tiles of its longest row: 64 query rows, 8 wavefronts, key
-// tiles of 256 in two LDS stages, and each group of 32 query rows is served by FOUR wavefronts that take one 64-key quarter of every
-// tile each (two wavefronts per SIMD, so one's MFMAs run under the other's VALU work) and add their partial outputs
-// through LDS at the end, in a fixed order.  The chain is a quarter as many steps, and a request of a few thousand rows has enough
-// query tiles for every CU; the sums are grouped differently, so the two configurations agree to rounding, not bit for bit.
-// One request of 2573 + 217, 8 heads: 22 us per launch (32 with query tiles of 128 and two wavefronts per group on key tiles of 128).
-template <int DH, bool SOFTMAX, bool KSPLIT, bool NT>
-__global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_kernel(PlanePtrs planes, const float *__restrict__ bias_lh,
+// KP = wavefronts per group of 32 query rows.  KP = 1 is the throughput configuration described at the top: 4 wavefronts, key tiles
+// of 64, three workgroups per CU.  KP > 1 is the latency configuration, for batches too small to fill the chip, where a workgroup
+// sits alone on its CU and its run time is the chain of key tiles of its longest row.  There a row's keys are summed in four
+// partial outputs, 64-key block i going to partial output i % 4, which are added in a fixed order at the end; the sums are
+// grouped differently than with KP = 1, so the two configurations agree to rounding, not bit for bit.  Two shapes with the same bits:
+//   KP = 4: 64 query rows, 8 wavefronts, key tiles of 256 in two LDS stages; each of a group's FOUR wavefronts takes one 64-key quarter
+//     of every tile (two wavefronts per SIMD, so one's MFMAs run under the other's VALU work).  The chain is a quarter as
+//     many steps, and a request of a few thousand rows has enough query tiles for every CU.  One request of 2573 + 217, 8 heads:
+//     22 us per launch (32 with query tiles of 128 and two wavefronts per group on key tiles of 128).
+//   KP = 2: 128 query rows, 8 wavefronts, key tiles of 128 in four LDS stages; each of a group's two wavefronts takes one 64-key half of every
+//     tile, into one of two accumulator sets by the tile's parity.  For latency handles that are given enough rows to
+//     fill the chip all the same: half the K and V traffic per query row (the rule and both sides' times are at kLatencyWideTiles).
+template <int DH, bool SOFTMAX, int KP, bool NT>
+__global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_kernel(PlanePtrs planes, const float *__restrict__ bias_lh,
                                                            const float *__restrict__ tscale_h,
                                                            half_t *__restrict__ O, const AttnItem *__restrict__ items,
                                                            int H, int d, int D, int64_t ws_rows) {
+  constexpr bool KSPLIT = KP > 1;
+  constexpr int NP = KP == 2 ? 2 : 1;  // partial outputs per wavefront
   constexpr int NW = KSPLIT ? 8 : 4;   // wavefronts per workgroup
-  constexpr int KP = KSPLIT ? 4 : 1;   // wavefronts per group of 32 query rows
   constexpr int QG = NW / KP;          // groups
   constexpr int QT = 32 * QG;          // query rows per workgroup (one 32-row MFMA block per group)
-  static_assert(QT == (KSPLIT ? kAttnQTileLatency : kAttnQTileBf16), "the planner's query tiles");
-  constexpr int NSTAGE = KSPLIT ? 2 : 3;  // LDS stages (ring)
+  static_assert(QT == (KP == 4 ? kAttnQTileLatency : KP == 2 ? kAttnQTileLatencyWide : kAttnQTileBf16), "the planner's query tiles");
+  static_assert(KP == 1 || KP * NP == 4, "the latency configuration sums in four partial outputs");
+  constexpr int NSTAGE = KP == 4 ? 2 : KP == 2 ? 4 : 3;  // LDS stages (ring)
   constexpr int KT = KH * KP;          // keys per LDS stage
   constexpr int BW = QT + KT;          // bias window per key tile: slot u holds bias[q_first + QT-1 - k0 - u]
   static_assert(BW <= 64 * NW, "one 64-slot window request per wavefront");
@@ -109,8 +115,8 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
   constexpr int DB = DH / 32;          // 32-row blocks of O^T
   constexpr int KCH = DH / 8;          // 16-byte chunks per K row (8 or 4)
   constexpr int KSH = KCH == 8 ? 1 : 2;            // K rows per 256 bytes = 1 << KSH
-  constexpr int VCH = KT / 8;          // 16-byte chunks per V^T row (32 or 8)
-  constexpr int VSH = VCH == 8 ? 1 : 0;            // V^T rows per 256 bytes = 1 << VSH (a row of 32 chunks covers 512)
+  constexpr int VCH = KT / 8;          // 16-byte chunks per V^T row (32, 16 or 8)
+  constexpr int VSH = VCH == 8 ? 1 : 0;            // V^T rows per 256 bytes = 1 << VSH (a row of 16 chunks is 256 bytes, one of 32 chunks 512)
   constexpr int VKEY = VCH == 8 ? 7 : 15;          // swizzle key: XORed into the chunk index inside 256 bytes
   constexpr int K_BYTES = KT * DH * 2;             // K tile [KT keys][DH]
   constexpr int V_BYTES = DH * KT * 2;             // V^T tile [DH][KT keys]
@@ -136,7 +142,7 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
   const half_t *Kp = (const half_t *)planes.k + head * DH;
   const float *bias = bias_lh + (int64_t)head * D;
 
-  // this wavefront's 32 query rows and (latency configuration) its quarter of every key tile
+  // this wavefront's 32 query rows and (latency configuration) its 64 keys of every key tile
   const int q_group = KSPLIT ? wave / KP : wave;
   const int k_part = KSPLIT ? wave % KP : 0;
   const int q_local0 = q_group * 32;
@@ -155,18 +161,22 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
   const int wave_vis_min = it.is_cand ? it.L : it.q_pos + q_local0 + 1;
   const int wave_vis_max = it.is_cand ? it.L : it.q_pos + q_local0 + 32;
 
-  f32x16 oacc[DB];
+  f32x16 oacc[NP][DB];
 #pragma unroll
-  for (int b = 0; b < DB; ++b)
+  for (int p = 0; p < NP; ++p)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) oacc[b][e] = 0.f;
-  // softmax state of my query row (both lanes of a pair hold the same maximum; each holds the sum over its keys)
+    for (int b = 0; b < DB; ++b)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) oacc[p][b][e] = 0.f;
+  // softmax state of my query row, per partial output (both lanes of a pair hold the same maximum; each holds the sum over its keys)
   // Finite stand-ins for -inf, so that no inf - inf can arise: a masked key's raw logit is kNeg; the running
   // maximum starts below kNeg * tscale for any sensible temperature, so a row whose keys so far were all masked
   // holds weights exp2(0) that the first real maximum scales to zero (every row sees key 0 of tile 0 or itself).
   constexpr float kNeg = -1.0e30f;
   const float ts = SOFTMAX ? tscale_h[head] : 0.f;
-  float m_run = -3.0e38f, l_run = 0.f;
+  float m_run[NP], l_run[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) { m_run[p] = -3.0e38f; l_run[p] = 0.f; }
 
   const int n_tiles = (it.n_kv + KT - 1) / KT;
   const int q_first = it.is_cand ? it.L : it.q_pos;     // position of query row 0 of the workgroup tile
@@ -241,13 +251,14 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
   const int ka0 = (krow * (DH * 2)) | (((((krow >> KSH) & (KCH - 1)) ^ lhalf) << 4));
   const int va0 = (K_BYTES + l32 * (KT * 2)) | (((((l32 >> VSH) & VKEY) ^ lhalf) << 4));
 
-  // Ring of NSTAGE = 3 stages, requests two tiles ahead.  Past the last tile the requests repeat the last
+  // Ring of NSTAGE stages, requests two tiles ahead.  Past the last tile the requests repeat the last
   // tile (into a free stage), so that "at most REQ requests outstanding" always means "tile t has landed".
-  // (The latency configuration has two stages and requests one tile ahead: a step of four 64-key quarters is longer than the loads.)
+  // (KP = 4 has two stages and requests one tile ahead: a step of four 64-key quarters is longer than the loads.)
+  constexpr bool AHEAD1 = NSTAGE == 2;
   if (n_tiles > 0) {
     request_tile(0);
     if (n_tiles > 1) next_tile();
-    if (!KSPLIT) request_tile(1);
+    if (!AHEAD1) request_tile(1);
   }
   // The query fragments are requested behind the first two tiles, not ahead of them: the tiles are what the first
   // step waits for.  (The waits below count requests in order: with at most REQ outstanding, the query loads and
@@ -258,15 +269,16 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
   // every fragment address is a fixed lane offset plus an immediate and costs no instruction.
   auto tile_step = [&](auto stage_c, const int t) {
     constexpr int ST = decltype(stage_c)::value;
+    constexpr int P = NP == 2 ? ST & 1 : 0;          // partial output (the ring is even there: the stage has the tile's parity)
     const char *sb = lds + ST * STAGE;
     // tile t has landed for this wavefront; past the barrier it has landed for all of them, and everybody
     // has left tile t-1, whose stage the next request overwrites
-    if (KSPLIT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (AHEAD1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     else if (REQ == 5) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
     else if (REQ == 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
-    if constexpr (KSPLIT) {
+    if constexpr (AHEAD1) {
       if (t + 1 < n_tiles) {
         request_tile(ST ^ 1);
         next_tile();
@@ -361,17 +373,17 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
           l2[3] = max3_f32(l1[9], sacc[1][14], sacc[1][15]);
           const float l3 = max3_f32(l2[0], l2[1], l2[2]);
           const float mt = max3_f32(l3, l2[3], l2[3]);
-          const float m_new = fmaxf(m_run, pair_max(mt) * ts);
+          const float m_new = fmaxf(m_run[P], pair_max(mt) * ts);
           // the accumulators are rescaled only when some row of the wavefront has a new maximum (rare after the
           // first tiles); the branch is uniform over the wavefront
-          if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0) {
-            const float sc = __builtin_amdgcn_exp2f(m_run - m_new);
-            l_run *= sc;
+          if (__builtin_amdgcn_ballot_w64(m_new != m_run[P]) != 0) {
+            const float sc = __builtin_amdgcn_exp2f(m_run[P] - m_new);
+            l_run[P] *= sc;
 #pragma unroll
             for (int b = 0; b < DB; ++b)
 #pragma unroll
-              for (int e = 0; e < 16; ++e) oacc[b][e] *= sc;
-            m_run = m_new;
+              for (int e = 0; e < 16; ++e) oacc[P][b][e] *= sc;
+            m_run[P] = m_new;
           }
           const float nm = -m_new;
           float psum[4] = {0.f, 0.f, 0.f, 0.f};
@@ -386,7 +398,7 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
             fp[2 * j + 1] = pack8(w + 8);
           }
           const float ps = (psum[0] + psum[1]) + (psum[2] + psum[3]);
-          l_run += ps;
+          l_run[P] += ps;
         } else {
           f16x2 th[2][8];
 #pragma unroll
@@ -497,7 +509,7 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int b = 0; b < DB; ++b)
-            oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fv[s2 & 1][b], fp[s2], oacc[b], 0, 0, 0);
+            oacc[P][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fv[s2 & 1][b], fp[s2], oacc[P][b], 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -507,15 +519,18 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
   for (int t = 0; t < n_tiles; t += NSTAGE) {
     tile_step(std::integral_constant<int, 0>{}, t);
     if (t + 1 < n_tiles) tile_step(std::integral_constant<int, 1>{}, t + 1);
-    if constexpr (NSTAGE == 3)
+    if constexpr (NSTAGE > 2)
       if (t + 2 < n_tiles) tile_step(std::integral_constant<int, 2>{}, t + 2);
+    if constexpr (NSTAGE > 3)
+      if (t + 3 < n_tiles) tile_step(std::integral_constant<int, 3>{}, t + 3);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the repeated requests of the tail have landed
   __builtin_amdgcn_s_barrier();          // everybody has left the last tile: the stages become output patches
 
   // ---- candidates: the row itself is one more key, at distance 0.  The wavefront multiplies its 32
-  // candidate rows against themselves and keeps the diagonal.  (Latency configuration: the wavefront of the last key quarter.)
+  // candidate rows against themselves and keeps the diagonal.  (Latency configuration: in the last partial output.)
   if (it.is_cand && wave_active && k_part == KP - 1) {
+    constexpr int P = NP - 1;
     const float b0 = bias[0];
     const int64_t base_row = it.q_row + q_local0;   // multiple of 32 inside the padded workspace
     f32x16 sacc;
@@ -536,15 +551,15 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
         ys = kv_local == l32 ? sacc[e] * ts : ys;
       }
       const bool mine = ys > kNeg;
-      const float m_new = fmaxf(m_run, pair_max(ys));
-      const float sc = __builtin_amdgcn_exp2f(m_run - m_new);
+      const float m_new = fmaxf(m_run[P], pair_max(ys));
+      const float sc = __builtin_amdgcn_exp2f(m_run[P] - m_new);
       const float pself = mine ? __builtin_amdgcn_exp2f(ys - m_new) : 0.f;
-      m_run = m_new;
-      l_run = l_run * sc + pself;
+      m_run[P] = m_new;
+      l_run[P] = l_run[P] * sc + pself;
 #pragma unroll
       for (int b = 0; b < DB; ++b)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) oacc[b][e] *= sc;
+        for (int e = 0; e < 16; ++e) oacc[P][b][e] *= sc;
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int kv_local = 16 * (e >> 3) + 8 * lhalf + (e & 7);
@@ -563,7 +578,7 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
 #pragma unroll
       for (int b = 0; b < DB; ++b) {
         const f16x8 fv = *(const f16x8 *)(Vt + (int64_t)(32 * b + l32) * ws_rows + base_row + s2 * 16 + lhalf * 8);
-        oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fv, fps[s2], oacc[b], 0, 0, 0);
+        oacc[P][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fv, fps[s2], oacc[P][b], 0, 0, 0);
       }
   }
 
@@ -591,7 +606,29 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
     const f16x8 v = *(const f16x8 *)(pb + row * (DH * 2) + ((c ^ pkey(row)) << 4));
     if (q_local0 + row < it.n_q) store_once<NT>(v, (f16x8 *)(obase + (int64_t)(q_local0 + row) * d));
   };
-  if constexpr (KSPLIT) {
+  // latency configuration: factors of the four partial outputs (softmax: to the common maximum, and divided by the row's sum)
+  auto part_factors = [&](const float2 (&ml)[4], float (&sc)[4]) {
+    const float m_all = fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x));
+    float l_all = 0.f;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      sc[p] = __builtin_amdgcn_exp2f(ml[p].x - m_all);
+      l_all = __builtin_fmaf(ml[p].y, sc[p], l_all);
+    }
+    const float lt = pair_sum(l_all);
+    const float inv = lt > 0.f ? 1.0f / lt : 0.f;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) sc[p] *= inv;
+  };
+  // (multiply-adds written out: left to the compiler, which of two products is rounded first would differ between the kernels)
+  auto add_parts = [&](const f32x4 (&v)[4], const float (&sc)[4]) {
+    if constexpr (!SOFTMAX) return (v[0] + v[1]) + (v[2] + v[3]);
+    f32x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = __builtin_fmaf(v[0][i], sc[0], v[1][i] * sc[1]) + __builtin_fmaf(v[2][i], sc[2], v[3][i] * sc[3]);
+    return o;
+  };
+  if constexpr (KP == 4) {
     // The four wavefronts of a row group leave their partial outputs (and their softmax states) in LDS behind the patches; each
     // adds up a quarter of the features, in the order (0 + 1) + (2 + 3), and stores a quarter of the rows.
     constexpr int PART = DB * 16 * 64 * 4;            // bytes of one wavefront's accumulators
@@ -602,53 +639,100 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
     for (int b = 0; b < DB; ++b)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const f32x4 v = {oacc[b][4 * g], oacc[b][4 * g + 1], oacc[b][4 * g + 2], oacc[b][4 * g + 3]};
+        const f32x4 v = {oacc[0][b][4 * g], oacc[0][b][4 * g + 1], oacc[0][b][4 * g + 2], oacc[0][b][4 * g + 3]};
         *(f32x4 *)(mine + ((b * 4 + g) * 64 + lane) * 16) = v;
       }
-    if constexpr (SOFTMAX) *(float2 *)(mine + PART + lane * 8) = float2{m_run, l_run};
+    if constexpr (SOFTMAX) *(float2 *)(mine + PART + lane * 8) = float2{m_run[0], l_run[0]};
     __syncthreads();
-    float sc[KP];
+    float sc[4];
     if constexpr (SOFTMAX) {
-      float2 ml[KP];
+      float2 ml[4];
 #pragma unroll
-      for (int p = 0; p < KP; ++p) ml[p] = *(const float2 *)(area + p * (PART + 512) + PART + lane * 8);
-      const float m_all = fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x));
-      float l_all = 0.f;
-#pragma unroll
-      for (int p = 0; p < KP; ++p) {
-        sc[p] = __builtin_amdgcn_exp2f(ml[p].x - m_all);
-        l_all += ml[p].y * sc[p];
-      }
-      const float lt = pair_sum(l_all);
-      const float inv = lt > 0.f ? 1.0f / lt : 0.f;
-#pragma unroll
-      for (int p = 0; p < KP; ++p) sc[p] *= inv;
+      for (int p = 0; p < 4; ++p) ml[p] = *(const float2 *)(area + p * (PART + 512) + PART + lane * 8);
+      part_factors(ml, sc);
     }
 #pragma unroll
     for (int b = 0; b < DB; ++b) {
-      f32x4 v[KP];
+      f32x4 v[4];
 #pragma unroll
-      for (int p = 0; p < KP; ++p) {
-        v[p] = *(const f32x4 *)(area + p * (PART + 512) + ((b * 4 + k_part) * 64 + lane) * 16);
-        if constexpr (SOFTMAX) v[p] *= sc[p];
-      }
-      to_patch(b, k_part, (v[0] + v[1]) + (v[2] + v[3]));
+      for (int p = 0; p < 4; ++p) v[p] = *(const f32x4 *)(area + p * (PART + 512) + ((b * 4 + k_part) * 64 + lane) * 16);
+      to_patch(b, k_part, add_parts(v, sc));
     }
     __syncthreads();
     if (k_part < 32 / RPI) store_rows(k_part);
+  } else if constexpr (KP == 2) {
+    // Wavefront k of a group holds partial outputs k and k + 2.  Each leaves the half of the features that its partner adds up (groups
+    // 2, 3 for k = 0, else 0, 1) in LDS, adds up its own half, in the same order as above, and stores half of the rows.
+    constexpr int HALF = NP * DB * 2 * 1024;          // bytes of half the features of a wavefront's two partial outputs
+    static_assert(QG * (32 * DH * 2) + NW * (HALF + NP * 512) <= NSTAGE * STAGE, "patches and partial outputs fit in the tile buffers");
+    char *area = lds + QG * (32 * DH * 2) + q_group * KP * (HALF + NP * 512);
+    char *mine = area + k_part * (HALF + NP * 512);
+    const char *theirs = area + (k_part ^ 1) * (HALF + NP * 512);
+    auto leave = [&](auto k_c) {
+      constexpr int K = decltype(k_c)::value;
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int b = 0; b < DB; ++b)
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const int g = 2 * (K ^ 1) + i;
+            const f32x4 v = {oacc[p][b][4 * g], oacc[p][b][4 * g + 1], oacc[p][b][4 * g + 2], oacc[p][b][4 * g + 3]};
+            *(f32x4 *)(mine + (((p * DB + b) * 2 + i) * 64 + lane) * 16) = v;
+          }
+    };
+    if (k_part == 0) leave(std::integral_constant<int, 0>{});
+    else leave(std::integral_constant<int, 1>{});
+    if constexpr (SOFTMAX) {
+#pragma unroll
+      for (int p = 0; p < NP; ++p) *(float2 *)(mine + HALF + p * 512 + lane * 8) = float2{m_run[p], l_run[p]};
+    }
+    __syncthreads();
+    auto finish = [&](auto k_c) {
+      constexpr int K = decltype(k_c)::value;
+      float sc[4];
+      if constexpr (SOFTMAX) {
+        float2 ml[4];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+          ml[2 * p + K] = float2{m_run[p], l_run[p]};
+          ml[2 * p + (K ^ 1)] = *(const float2 *)(theirs + HALF + p * 512 + lane * 8);
+        }
+        part_factors(ml, sc);
+      }
+#pragma unroll
+      for (int b = 0; b < DB; ++b)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int g = 2 * K + i;
+          f32x4 v[4];
+#pragma unroll
+          for (int p = 0; p < NP; ++p) {
+            v[2 * p + K] = f32x4{oacc[p][b][4 * g], oacc[p][b][4 * g + 1], oacc[p][b][4 * g + 2], oacc[p][b][4 * g + 3]};
+            v[2 * p + (K ^ 1)] = *(const f32x4 *)(theirs + (((p * DB + b) * 2 + i) * 64 + lane) * 16);
+          }
+          to_patch(b, g, add_parts(v, sc));
+        }
+    };
+    if (k_part == 0) finish(std::integral_constant<int, 0>{});
+    else finish(std::integral_constant<int, 1>{});
+    __syncthreads();
+    constexpr int SPW = 32 / RPI / 2;                 // store instructions per wavefront
+#pragma unroll
+    for (int t = 0; t < SPW; ++t) store_rows(k_part * SPW + t);
   } else {
     if constexpr (SOFTMAX) {
-      const float lt = pair_sum(l_run);
+      const float lt = pair_sum(l_run[0]);
       const float inv = lt > 0.f ? 1.0f / lt : 0.f;
 #pragma unroll
       for (int b = 0; b < DB; ++b)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) oacc[b][e] *= inv;
+        for (int e = 0; e < 16; ++e) oacc[0][b][e] *= inv;
     }
 #pragma unroll
     for (int b = 0; b < DB; ++b)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) to_patch(b, g, f32x4{oacc[b][4 * g], oacc[b][4 * g + 1], oacc[b][4 * g + 2], oacc[b][4 * g + 3]});
+      for (int g = 0; g < 4; ++g) to_patch(b, g, f32x4{oacc[0][b][4 * g], oacc[0][b][4 * g + 1], oacc[0][b][4 * g + 2], oacc[0][b][4 * g + 3]});
 #pragma unroll
     for (int t = 0; t < 32 / RPI; ++t) store_rows(t);
   }
@@ -658,44 +742,54 @@ __global__ __launch_bounds__(KSPLIT ? 512 : 256, KSPLIT ? 1 : 3) void attn_mfma_
 
 // The latency configuration needs its LDS limit raised once per kernel instance (a function attribute, no
 // allocation); handles in latency mode do it when they are created, outside any stream capture.
-template <int DH>
-constexpr int key_split_lds_bytes() { return 2 * (2 * 256 * DH * 2 + 8 * 256); }   // two stages of K, V^T and the bias window
+template <int DH, int KP>
+constexpr int key_split_lds_bytes() { return (KP == 4 ? 2 : 4) * (2 * 64 * KP * DH * 2 + 8 * 256); }   // the stages: K, V^T and the bias window each
 
-template <int DH, bool SM>
+template <int DH, bool SM, int KP>
 static hipError_t key_split_setup() {
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_mfma_kernel<DH, SM, true, false>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, key_split_lds_bytes<DH>());
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_mfma_kernel<DH, SM, KP, false>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, key_split_lds_bytes<DH, KP>());
   return attr;
 }
 
 template <int DH, bool SM>
+static hipError_t latency_setup() {
+  const hipError_t e = key_split_setup<DH, SM, 4>();
+  return e != hipSuccess ? e : key_split_setup<DH, SM, 2>();
+}
+
+template <int DH, bool SM, int KP>
 static void launch_key_split(int grid, PlanePtrs planes, const float *bias_lh, const float *tscale_h, half_t *O,
                              const AttnItem *items, const Shape &sh, hipStream_t s) {
-  (void)key_split_setup<DH, SM>();
-  attn_mfma_kernel<DH, SM, true, false><<<grid, 512, key_split_lds_bytes<DH>(), s>>>(planes, bias_lh, tscale_h, O, items, sh.H, sh.d, sh.D, sh.ws_rows);
+  (void)key_split_setup<DH, SM, KP>();
+  attn_mfma_kernel<DH, SM, KP, false><<<grid, 512, key_split_lds_bytes<DH, KP>(), s>>>(planes, bias_lh, tscale_h, O, items, sh.H, sh.d, sh.D, sh.ws_rows);
 }
 
 hipError_t attn_latency_setup(const Shape &sh) {
-  if (sh.softmax) return sh.dh == 32 ? key_split_setup<32, true>() : key_split_setup<64, true>();
-  return sh.dh == 32 ? key_split_setup<32, false>() : key_split_setup<64, false>();
+  if (sh.softmax) return sh.dh == 32 ? latency_setup<32, true>() : latency_setup<64, true>();
+  return sh.dh == 32 ? latency_setup<32, false>() : latency_setup<64, false>();
 }
 
 void launch_attn_bf16(PlanePtrs planes, const float *bias_lh, const float *tscale_h, void *O, const AttnItem *items,
-                      int n_items, const Shape &sh, hipStream_t s) {
+                      int n_items, int q_tile, const Shape &sh, hipStream_t s) {
   if (n_items <= 0) return;
   const int grid = n_items * sh.H;
   if (sh.latency) {
+#define SPLIT_LAUNCH(DHV, SM, KPV) launch_key_split<DHV, SM, KPV>(grid, planes, bias_lh, tscale_h, (half_t *)O, items, sh, s)
+#define SPLIT_CASE(DHV, SM) do { if (q_tile == kAttnQTileLatencyWide) SPLIT_LAUNCH(DHV, SM, 2); else SPLIT_LAUNCH(DHV, SM, 4); } while (0)
     if (sh.softmax) {
-      if (sh.dh == 32) launch_key_split<32, true>(grid, planes, bias_lh, tscale_h, (half_t *)O, items, sh, s);
-      else launch_key_split<64, true>(grid, planes, bias_lh, tscale_h, (half_t *)O, items, sh, s);
+      if (sh.dh == 32) SPLIT_CASE(32, true);
+      else SPLIT_CASE(64, true);
     } else {
-      if (sh.dh == 32) launch_key_split<32, false>(grid, planes, bias_lh, tscale_h, (half_t *)O, items, sh, s);
-      else launch_key_split<64, false>(grid, planes, bias_lh, tscale_h, (half_t *)O, items, sh, s);
+      if (sh.dh == 32) SPLIT_CASE(32, false);
+      else SPLIT_CASE(64, false);
     }
+#undef SPLIT_CASE
+#undef SPLIT_LAUNCH
     return;
   }
   const bool nt = (int64_t)n_items * kAttnQTileBf16 * sh.d * 2 > kStreamBytes;
-#define ATTN_LAUNCH(DHV, SM, NTV) attn_mfma_kernel<DHV, SM, false, NTV><<<grid, 256, 0, s>>>(planes, bias_lh, tscale_h, (half_t *)O, items, sh.H, sh.d, sh.D, sh.ws_rows)
+#define ATTN_LAUNCH(DHV, SM, NTV) attn_mfma_kernel<DHV, SM, 1, NTV><<<grid, 256, 0, s>>>(planes, bias_lh, tscale_h, (half_t *)O, items, sh.H, sh.d, sh.D, sh.ws_rows)
 #define ATTN_CASE(DHV, SM) do { if (nt) ATTN_LAUNCH(DHV, SM, true); else ATTN_LAUNCH(DHV, SM, false); } while (0)
   if (sh.softmax) {
     if (sh.dh == 32) ATTN_CASE(32, true);

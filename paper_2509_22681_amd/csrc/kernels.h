@@ -86,8 +86,9 @@ struct PlanePtrs { void *u, *v, *q, *k; };
 void launch_uvqk_bf16(const void *Xh, const void *W1h, const void *b1, PlanePtrs planes, const int32_t *blk_list,
                       int n_blk, int blk_first, int plane_mask, const Shape &sh, hipStream_t s);
 // tscale_h (softmax only): 2 log2(e) / tau per head (the kernel holds halved logits and uses the base-2 exponential).
+// q_tile: query rows per item of this plan.
 void launch_attn_bf16(PlanePtrs planes, const float *bias_lh, const float *tscale_h, void *O, const AttnItem *items,
-                      int n_items, const Shape &sh, hipStream_t s);
+                      int n_items, int q_tile, const Shape &sh, hipStream_t s);
 // Prepares the latency configuration of the attention kernel for this shape (raises its LDS limit); once per handle.
 hipError_t attn_latency_setup(const Shape &sh);
 // X[row] += G W2h^T + b2 on the residual pair (Xh, Xl); lo_is_zero: Xl is not read (first layer)
@@ -108,9 +109,5 @@ void launch_k3_fused(const void *O, const void *U, const void *gamma, const void
 // forward, ordinary against nontemporal: 10 MB per plane (32 x 640 rows, d = 256) 289 against 308 us, 3 MB (one request, d = 512) 1033
 // against 1078 us; 27 MB equal; 100 MB 5.15 against 4.98 ms, 500 MB 65.4 against 63.7 ms.
 constexpr int64_t kStreamBytes = 16 << 20;
-
-constexpr int kAttnQTileBf16 = 128;  // query rows per attention work item, MFMA path
-constexpr int kAttnQTileLatency = 64;  // the same in the latency configuration
-constexpr int kAttnQTileF32 = 64;    // fp32 path
 
 }  // namespace flame

@@ -73,8 +73,26 @@ int64_t workspace_rows(const flame_gr_config &c) {
   return rows;
 }
 
+// Query rows per attention item.  The two tiles of the latency configuration give the same bits (attn_mfma.hip), so the choice
+// may follow the rows of the pass: those of the history stage, of the candidate stage (reserved layout), or all of them.
+static int32_t attn_q_tile(const flame_gr_config &cfg, const std::vector<Segment> &segs, bool reserved) {
+  if (cfg.dtype != FLAME_GR_BF16) return kAttnQTileF32;
+  if (!cfg.latency_mode) return kAttnQTileBf16;
+  int64_t hist = 0, cand = 0;
+  int32_t longest = 0;
+  for (const Segment &s : segs) {
+    longest = std::max(longest, s.L);
+    hist += (s.L + kAttnQTileLatency - 1) / kAttnQTileLatency;
+    cand += (s.M + kAttnQTileLatency - 1) / kAttnQTileLatency;
+  }
+  const int64_t tiles = reserved && cand > 0 ? cand : hist + cand;
+  const int limit = longest <= kLatencyShortHistory ? kLatencyWideTilesShort
+                    : cfg.attn_kind == FLAME_GR_ATTN_SOFTMAX && cfg.d_model / cfg.n_heads == 32 ? kLatencyWideTilesSoftmax32 : kLatencyWideTiles;
+  return tiles * cfg.n_heads >= limit ? kAttnQTileLatencyWide : kAttnQTileLatency;
+}
+
 int build_plan(const flame_gr_config &cfg, const int32_t *hoff, const int32_t *coff, int32_t B,
-               int32_t q_tile, int32_t n_groups, int64_t ws_rows, Plan &p, std::string &err,
+               int32_t n_groups, int64_t ws_rows, Plan &p, std::string &err,
                const int32_t *cand_capacity) {
   auto fail = [&](int code, const std::string &m) { err = m; return code; };
   if (B < 0) return fail(FLAME_GR_INVALID_ARGUMENT, "n_requests < 0");
@@ -132,6 +150,9 @@ int build_plan(const flame_gr_config &cfg, const int32_t *hoff, const int32_t *c
       if (done < M) p.split = true;
     } while (done < M);
   }
+
+  p.q_tile = attn_q_tile(cfg, p.segs, cand_capacity != nullptr);
+  const int32_t q_tile = p.q_tile;
 
   // 2. stream groups: longest-processing-time first onto the least loaded group
   std::vector<int> order(p.segs.size());

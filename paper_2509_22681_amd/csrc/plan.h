@@ -37,6 +37,12 @@ struct RowBlock {
   int32_t seg;      // owning segment
 };
 
+// Query rows per attention work item.
+constexpr int kAttnQTileBf16 = 128;         // MFMA path, throughput configuration
+constexpr int kAttnQTileLatency = 64;       // latency configuration: four wavefronts per group of 32 rows
+constexpr int kAttnQTileLatencyWide = 128;  // the same for batches that fill the chip: two wavefronts per group, the same bits
+constexpr int kAttnQTileF32 = 64;           // fp32 path
+
 // One attention work item: a tile of query rows of one segment (all heads run it).
 struct AttnItem {
   int32_t q_row;    // workspace row of the first query
@@ -56,6 +62,21 @@ struct AttnItem {
 // 384 tiles 62.0.
 constexpr int kTailItems = 384;
 
+// Latency handles: from this many workgroups of 64 query rows (tiles x heads) on a pass runs on tiles of 128 rows.  With fewer, a workgroup
+// has a compute unit to itself (or shares it little) and the shorter chain of key tiles counts; with more, the chip is full and the K and V
+// traffic does, which a 64-row workgroup makes twice per query row.  Microseconds per launch, tiles of 64 / 128 rows:
+//   heads of 64: one request of 4096 + 2000, 8 heads (768 workgroups) 56.4 / 58.5, of 8192 + 512 (1088) 118.6 / 116.0; requests of 1024 + 256:
+//     8 (1280) 35.7 / 31.3, 16 (2560) 77.5 / 56.7, 32 (5120) 152 / 110
+//   heads of 32: 2573 + 217, 16 heads (720) 27.4 / 27.6, 4096 + 2000 (1536) 79.6 / 71.8; 1024 + 256: 4 (1280) 27.2 / 23.5, 16 (5120) 113 / 82
+//   heads of 32, softmax, whose chain has the exponentials on top: 4096 + 300 (1104) 42.9 / 49.0, 4096 + 2000 (1536) 65.9 / 71.3, 8192 + 512 (2176)
+//     132.1 / 131.1; 1024 + 256: 6 (1920) 31.4 / 27.5
+// Histories of up to 128 keys are one step on either tile, so that 128 rows pay as soon as there is a workgroup for every compute unit: 4 layers,
+// d = 512, 16 x (128 + 64) (384 workgroups) 155 / 144 us per forward, 4 x (128 + 128) (128) 112 / 116.
+constexpr int kLatencyWideTiles = 1280;
+constexpr int kLatencyWideTilesSoftmax32 = 2048;
+constexpr int kLatencyWideTilesShort = 256;
+constexpr int kLatencyShortHistory = 128;
+
 struct Group {
   int32_t row_begin, row_end;          // workspace rows [begin, end) of this stream group (multiples of 64)
   int32_t blk_begin, blk_end;          // RowBlock range
@@ -70,25 +91,26 @@ struct Plan {
   std::vector<int32_t> tok_off;        // logical merged offsets, [B+1]
   std::vector<Segment> segs;           // in workspace order
   std::vector<RowBlock> blocks;        // total_rows / 64 entries
-  std::vector<AttnItem> items;         // per group: cost-descending
+  std::vector<AttnItem> items;         // per group: request by request, the last kTailItems longest first
   std::vector<AttnItem> cand_items;    // candidate tiles only
   std::vector<int32_t> cand_blocks;    // indices of candidate RowBlocks with valid rows, per group contiguous
   std::vector<AttnItem> hist_items;    // history tiles only
   std::vector<int32_t> hist_blocks;    // indices of history RowBlocks, per group contiguous
   std::vector<Group> groups;
+  int32_t q_tile = 0;                  // query rows per attention item
   int32_t total_rows = 0;
   int64_t total_cands = 0;
   bool split = false;                  // some request was split into several segments
 };
 
-// Validation + planning.  q_tile = query rows per attention item.  Returns a flame_gr_status;
+// Validation + planning.  Returns a flame_gr_status;
 // on failure `err` holds the reason.
 int validate_config(const flame_gr_config &cfg, std::string &err);
 // cand_capacity (optional, [B]): rows are reserved for that many candidates per request (>= the actual
 // count), and layout and stream groups depend on the capacities only, not on the actual counts: the plans
 // of a prefill (no candidates yet) and of the score calls that follow it then agree on every row.
 int build_plan(const flame_gr_config &cfg, const int32_t *hoff, const int32_t *coff, int32_t B,
-               int32_t q_tile, int32_t n_groups, int64_t ws_rows, Plan &plan, std::string &err,
+               int32_t n_groups, int64_t ws_rows, Plan &plan, std::string &err,
                const int32_t *cand_capacity = nullptr);
 
 // bucket(delta) for delta in [0, D)
