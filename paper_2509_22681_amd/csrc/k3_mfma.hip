@@ -52,11 +52,11 @@ __global__ __launch_bounds__(256) void pack_w2_kernel(const bf16_t *__restrict__
 // rows are one round of loads per wavefront, and everything that does not depend on phase 1 (the first W2 fragments, the
 // residual rows) is requested ahead of it.  Every output element is computed exactly as with RH = 2, CS = 1.
 // NT: O, U and the residual pair bypass the caches (consumed once; data of this size would push W2's fragments and K1's operands
-// out of L2).  Small batches are better off leaving them there for the next kernel (see launch_k3_fused).
+// out of L2).  Small batches are better off leaving them there for the next kernel (see launch_k3).
 // k3_dense: half blocks with uncut features are for a few hundred row blocks, more than two workgroups per CU.  Three wavefronts per SIMD hold
 // them all at once, where two run a second, nearly empty round; the registers for that come from the residual rows, which are
-// requested behind phase 1 instead of ahead of it, and a shorter W2 ring.  Per launch: 320 row blocks, d = 256: 22.2 -> 18.2 us; 384, d = 192: 23.1 -> 18.4 us
-// (12.8 and 11.6 at the rate of a large copy).
+// requested behind phase 1 instead of ahead of it, and a shorter W2 ring.  384 row blocks, two wavefronts against three: d = 256 24.0 -> 20.1 us, d = 192
+// 25.2 -> 19.8 us per launch.
 constexpr bool k3_dense(int cs, int rh, int nbw) { return rh == 1 && cs == 1 && nbw == 2; }
 template <int NWV, int NBW, int CS, int RH, bool NT>
 __global__ __launch_bounds__(64 * NWV, k3_dense(CS, RH, NBW) ? 3 : 2) void k3_fused_kernel(const half_t *__restrict__ O, const half_t *__restrict__ U,
@@ -327,29 +327,52 @@ void launch_pack_w2(const void *W2, void *W2p, int d, int n_layers, hipStream_t 
   pack_w2_kernel<<<grid, 256, 0, s>>>((const bf16_t *)W2, (half_t *)W2p, d, n_layers);
 }
 
+// Few row blocks: half blocks, with the features cut as long as that leaves one workgroup per compute unit at most (lone workgroups,
+// latency), then half blocks with uncut features.  Microseconds per launch, whole blocks / half blocks / half blocks with features cut
+// in two / in four:
+//   d = 512: 16 blocks 21.1 / 15.8 / 12.0 / 10.1, 64: 22.6 / 17.1 / 13.2 / 13.9, 66: 22.1 / 16.1, 128: 24.1 / 18.6 / 22.3 / 21.6, 256: 28.5 / 26.9
+//   (44 blocks in a model of 16 layers, whose W2 is in no L2 when a layer starts: 12.9 in two, 14.6 in four)
+//   d = 384: 16: 25.4 / - / - / 12.2, 64: 26.1 / - / 14.2, 66: 26.7 / 16.5, 256: 29.8 / 23.9
+//   d = 256: 16: 16.4 / 11.0 / 9.8, 64: 17.2 / 11.6 / 10.9, 66: 17.1 / 11.7, 128: 18.1 / 12.7, 256: 19.2 / 16.2
+//   d = 192: 16: 20.0 / 12.4 / 11.5, 64: 20.5 / 12.9 / 12.0, 66: 20.4 / 13.0, 256: 21.7 / 16.0
+//   d = 128 (one feature block per wavefront, never cut): 16: 13.9 / 9.6, 256: 15.6 / 12.5
+// Past kK3HalfBlocks = 384 row blocks, three workgroups for each of the 256 compute units, a fourth has to wait its turn:
+//   384 / 386 / 448 blocks: d = 128 17.4 / 16.5, 17.5 / 18.3, 17.7 / 18.4;  d = 256 23.5 / 20.1, 23.4 / 23.3, 24.2 / 24.6;
+//   d = 384 36.7 / 35.2, 37.3 / 38.4, 38.2 / 40.2;  d = 512 38.2 / 39.1, 38.3 / 43.6, 40.9 / 46.0
+// (d = 192, whose workgroups have three wavefronts and find room for a fourth, keeps the common limit although half blocks measure ahead beyond
+// it: 448 25.8 / 22.4, 640 32.4 / 28.0, 1024 44.2 / 38.5, 1536 52.8 / 52.5, 2048 68.4 / 69.1.)
+// Whole blocks also where the launch streams (kStreamBytes): from 257 blocks at d = 512 and 342 at d = 384, where the two are
+// level (d = 512: 258 37.6 / 37.0, 342 37.8 / 37.6; d = 384: 342 36.0 / 34.0); at those widths no whole block reads through the caches.
+template <int NWV, int NB>
+static void launch_k3(const half_t *O, const half_t *U, const bf16_t *gamma, const bf16_t *beta, const half_t *W2p, const bf16_t *b2, half_t *Xh, half_t *Xl,
+                      int lo_is_zero, const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first, float eps, hipStream_t s) {
+  constexpr int d = 32 * NB * NWV;
+  const bool nt = (int64_t)n_blk * kRowAlign * d * 2 > kStreamBytes;
+#define K3_LAUNCH(CSV, RHV, NTV) k3_fused_kernel<NWV, NB, CSV, RHV, NTV><<<dim3(n_blk * (3 - RHV), CSV), 64 * NWV, k3_lds_bytes(d, CSV, RHV), s>>>( \
+    O, U, gamma, beta, W2p, b2, Xh, Xl, lo_is_zero, blocks, blk_list, blk_first, eps)
+  if (NB == 4 && n_blk <= kK3CutInFour) K3_LAUNCH(NB, 1, false);
+  else if (n_blk <= kK3CutInTwo) K3_LAUNCH((NB > 1 ? 2 : 1), 1, false);
+  else if (n_blk <= kK3HalfBlocks && !nt) K3_LAUNCH(1, 1, false);
+  else {
+    constexpr bool kWholeOnlyStreams = (int64_t)(kK3HalfBlocks + 1) * kRowAlign * d * 2 > kStreamBytes;
+    if (kWholeOnlyStreams || nt) K3_LAUNCH(1, 2, true);
+    else if constexpr (!kWholeOnlyStreams) K3_LAUNCH(1, 2, false);
+  }
+#undef K3_LAUNCH
+}
+
 void launch_k3_fused(const void *O, const void *U, const void *gamma, const void *beta, const void *W2p_layer, const void *b2,
                      void *Xh, void *Xl, bool lo_is_zero, const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first,
                      const Shape &sh, hipStream_t s) {
   if (n_blk <= 0) return;
-  // Launches of up to 384 row blocks take half blocks, and cut the features as long as that leaves one workgroup per compute unit
-  // at most: lone workgroups, latency.  Microseconds per launch, whole blocks / half blocks / half blocks with features cut in two
-  // / in four:
-  //   d = 512: 16 blocks 21.6 / 15.8 / 12.0 / 10.1, 64: 22.4 / 17.1 / 14.0 / 13.9, 128: 24.0 / 19.6 / 22.3 / 21.6, 384: 39.8 / 39.0 / 46.3, 512: 45.2 / 49.7
-  //   (44 blocks in a model of 16 layers, whose W2 is in no L2 when a layer starts: 12.9 in two, 14.6 in four)
-  //   d = 256: 16: 16.3 / 11.0 / 9.9, 64: 17.4 / 11.6 / 10.5, 128: 17.9 / 13.0 / 13.4, 256: - / 15.6, 384: 23.9 / 20.1, 448: 24.1 / 25.9, 512: 25.6 / 26.6
-  //   d = 192: 16: 20.1 / 12.4 / 11.5, 64: 20.6 / 12.9 / 12.3, 256: - / 15.2, 384: 26.5 / 19.8, 512: 27.2 / 26.5
-  const bool nt = (int64_t)n_blk * kRowAlign * sh.d * 2 > kStreamBytes;
-#define K3_LAUNCH(NWV, NB, CSV, RHV, NTV) k3_fused_kernel<NWV, NB, CSV, RHV, NTV><<<dim3(n_blk * (3 - RHV), CSV), 64 * NWV, k3_lds_bytes(sh.d, CSV, RHV), s>>>((const half_t *)O, (const half_t *)U, (const bf16_t *)gamma, (const bf16_t *)beta, \
-    (const half_t *)W2p_layer, (const bf16_t *)b2, (half_t *)Xh, (half_t *)Xl, lo_is_zero ? 1 : 0, blocks, blk_list, blk_first, sh.eps)
-#define K3_CASE(NWV, NB) do { if (NB == 4 && n_blk <= 32) K3_LAUNCH(NWV, NB, NB, 1, false); else if (n_blk <= 64) K3_LAUNCH(NWV, NB, (NB > 1 ? 2 : 1), 1, false); else if (n_blk <= 384 && !nt) K3_LAUNCH(NWV, NB, 1, 1, false); \
-    else if (nt) K3_LAUNCH(NWV, NB, 1, 2, true); else K3_LAUNCH(NWV, NB, 1, 2, false); } while (0)
+#define K3_CASE(NWV, NB) launch_k3<NWV, NB>((const half_t *)O, (const half_t *)U, (const bf16_t *)gamma, (const bf16_t *)beta, (const half_t *)W2p_layer, \
+    (const bf16_t *)b2, (half_t *)Xh, (half_t *)Xl, lo_is_zero ? 1 : 0, blocks, blk_list, n_blk, blk_first, sh.eps, s)
   if (sh.d == 512) K3_CASE(4, 4);
   else if (sh.d == 384) K3_CASE(3, 4);
   else if (sh.d == 256) K3_CASE(4, 2);
   else if (sh.d == 192) K3_CASE(3, 2);
   else K3_CASE(4, 1);
 #undef K3_CASE
-#undef K3_LAUNCH
 }
 
 }  // namespace flame

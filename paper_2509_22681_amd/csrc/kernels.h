@@ -104,6 +104,10 @@ void launch_k3_fused(const void *O, const void *U, const void *gamma, const void
                      void *Xh, void *Xl, bool lo_is_zero, const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first,
                      const Shape &sh, hipStream_t s);
 
+// Launches of up to this many 64-row blocks run K3 on half blocks: with the features cut in four (d = 384, 512), in two, uncut
+// (both sides of each are at launch_k3).
+constexpr int kK3CutInFour = 32, kK3CutInTwo = 64, kK3HalfBlocks = 384;
+
 // Planes larger than this are written and read past the caches (nontemporal): a layer's eight arrays of N x d fp16 no longer fit
 // the 256 MB behind the L2s, and what streams through would push the operands that are read many times out of them.  Measured per
 // forward, ordinary against nontemporal: 10 MB per plane (32 x 640 rows, d = 256) 289 against 308 us, 3 MB (one request, d = 512) 1033
