@@ -414,7 +414,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_kernel(
 // It serves launches that leave the chip idle at 256-row tiles, where the latency of a lone workgroup is what counts, and narrow
 // models, whose large tile has six k tiles or fewer to hide its start and its epilogue behind; see launch_uvqk_bf16.
 // NK = d / 32.
-template <int NK>
+template <int NK, bool NT>
 __global__ __launch_bounds__(256) void gemm_small_kernel(const half_t *__restrict__ A, const half_t *__restrict__ W, const bf16_t *__restrict__ bias,
                                                          PlanePtrs planes, const int32_t *__restrict__ blk_list, int blk_first, int n_blk, int n_col_tiles,
                                                          int64_t ws_rows, PlaneSel sel, float alpha) {
@@ -553,18 +553,24 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const half_t *__restric
     const f16x8 v = *(const f16x8 *)(pb + r * 128 + ((c ^ patch_key<8>(r)) << 4));
     half_t *dst = feature_major ? P + (int64_t)(n_half + r) * ws_rows + (int64_t)blk * kRowAlign + c * 8
                                 : P + ((int64_t)blk * kRowAlign + r) * d + n_half + c * 8;
-    *(f16x8 *)dst = v;
+    store_once<NT>(v, (f16x8 *)dst);
   }
 }
 
 }  // namespace
 
-template <int NK>
+// The small tile stores past the caches only from this size of a plane on, not from kStreamBytes: it runs the narrow models, whose attention
+// kernel is short and still finds part of such planes in the caches.  From 64 MB on attention is the faster for stores past them.  Microseconds per forward of 4 layers, requests of 64 + 64, through / past the caches:
+//   d = 64: 32 MB 748 / 768, 48 MB 1150 / 1134, 64 MB 1558 / 1461, 128 MB 3103 / 2990
+//   d = 128: 48 MB 794 / 833, 64 MB 1101 / 1084, 128 MB 2189 / 2094;  d = 192: 48 MB 846 / 888, 72 MB 1281 / 1249, 192 MB 3274 / 3203
+// (Attention at d = 64, 64 MB: 105.5 / 95.6 us per launch.)  The wider models leave the small tile long before.
+constexpr int64_t kSmallStreamBytes = 64 << 20;
+template <int NK, bool NT = false>
 static void launch_small(const void *Xh, const void *W1h, const void *b1, PlanePtrs planes, const int32_t *blk_list, int blk_first, int n_blk, const PlaneSel &sel,
                          const Shape &sh, hipStream_t s) {
   const int col_tiles = (sel.n * (sh.d / 64) + 1) / 2;
   const int lds = 4096 * NK < 16384 ? 16384 : 4096 * NK;       // the X block, at least the two output patches
-  gemm_small_kernel<NK><<<n_blk * col_tiles, 256, lds, s>>>((const half_t *)Xh, (const half_t *)W1h, (const bf16_t *)b1, planes, blk_list, blk_first, n_blk,
+  gemm_small_kernel<NK, NT><<<n_blk * col_tiles, 256, lds, s>>>((const half_t *)Xh, (const half_t *)W1h, (const bf16_t *)b1, planes, blk_list, blk_first, n_blk,
                                                            col_tiles, sh.ws_rows, sel, sh.alpha);
 }
 
@@ -574,10 +580,13 @@ static void launch_small(const void *Xh, const void *W1h, const void *b1, PlaneP
 //   d = 512: 16 blocks 11.2 / 18.5, 48: 16.7 / 19.8, 96: 25.6 / 26.4, 128: 31.6 / 29.3
 //   d = 384: 16: 10.1 / 16.3, 128: 21.5 / 23.4, 384: 48 / 52, 512: 61 / 60
 //   d = 256: 16: 8.6 / 13.6, 256: 21.8 / 23.6, 1024: 62 / 63, 2048: 122 / 116
-//   d = 192: 16: 7.9 / 10.1, 256: 16.9 / 19.7, 1536: 61 / 73, 8192: 348 / 366 (the large tile is 64 columns wide there);  d = 128: 256: 14.6 / 17.3, 4096: 87 / 92
+//   d = 192: 16: 7.9 / 10.1, 256: 16.9 / 19.7, 2048: 84 / 91, 8192: 340 / 345 (the large tile is 64 columns wide there)
+//   d = 128: 256: 14.6 / 17.3, 2048: 47 / 50, 8192: 173 / 175, 10240: 229 / 209, 16384: 352 / 343
+//   d = 64: 512: 12.9 / 14.8, 2048: 22.2 / 25.3, 8192: 64 / 81, 16384: 143 / 182
 static int small_tile_blocks(int d) {
   switch (d) {
-    case 64: case 128: case 192: return 1 << 30;
+    case 64: case 192: return 1 << 30;
+    case 128: return 8192;
     case 256: return 1024;
     case 384: return 384;
     case 512: return 96;
@@ -593,13 +602,15 @@ void launch_uvqk_bf16(const void *Xh, const void *W1h, const void *b1, PlanePtrs
     if (plane_mask & (1 << p)) sel.id[sel.n++] = p;
   const int row_tiles = (n_blk + RB - 1) / RB;
   const int bn = sh.d % 128 == 0 ? 128 : 64;
-  const bool nt = (int64_t)n_blk * kRowAlign * sh.d * 2 > kStreamBytes;
+  const int64_t bytes = (int64_t)n_blk * kRowAlign * sh.d * 2;       // of a plane
+  const bool nt = bytes > kStreamBytes;
   if (n_blk <= small_tile_blocks(sh.d)) {
-#define K1_SMALL(NK) launch_small<NK>(Xh, W1h, b1, planes, blk_list, blk_first, n_blk, sel, sh, s)
+    const bool snt = bytes >= kSmallStreamBytes;
+#define K1_SMALL(...) launch_small<__VA_ARGS__>(Xh, W1h, b1, planes, blk_list, blk_first, n_blk, sel, sh, s)
     switch (sh.d) {
-      case 64: K1_SMALL(2); break;
-      case 128: K1_SMALL(4); break;
-      case 192: K1_SMALL(6); break;
+      case 64: if (snt) K1_SMALL(2, true); else K1_SMALL(2); break;
+      case 128: if (snt) K1_SMALL(4, true); else K1_SMALL(4); break;
+      case 192: if (snt) K1_SMALL(6, true); else K1_SMALL(6); break;
       case 256: K1_SMALL(8); break;
       case 384: K1_SMALL(12); break;
       default: K1_SMALL(16); break;
