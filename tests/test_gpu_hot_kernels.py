@@ -12,6 +12,9 @@ The mask is checked through the attention kernels themselves, as integers: with 
 values that are an indicator of (key index mod 64), an output element is (number of visible keys of that row in
 that residue class) x one constant, and the count must equal the row sums of the oracle's mask exactly.
 """
+import re
+from pathlib import Path
+
 import numpy as np
 import pytest
 
@@ -26,10 +29,10 @@ HOT = {
     "d512": dict(L=[3001, 129], M=[333, 65], d=512, H=8, n_layers=2, n_buckets=128, max_rel_dist=4096, seed=11),
     # the long workload's table: 512 buckets, D = 16384, distances reach the log-spaced half (>= 256) and beyond 4096
     "table512": dict(L=[4100], M=[70], d=512, H=8, n_layers=2, n_buckets=512, max_rel_dist=16384, seed=12),
-    # more than 128 row blocks in one launch: the one-workgroup-per-row-block instance of the fused output projection
-    # that the large benchmark batches run (smaller launches split a row block over two or four workgroups)
-    "many_rows": dict(L=[1500, 1700, 1300, 1901, 1600, 300], M=[100, 65, 200, 31, 129, 700], d=512, H=8, n_layers=2,
-                      n_buckets=128, max_rel_dist=2048, seed=13),
+    # the instances of the large batches: K1's large tile and whole row blocks of K3, all three kernels storing past the caches
+    # (test_many_rows_is_past_the_limits holds the sizes against the limits)
+    "many_rows": dict(L=[1500, 300, 1901] + [197 + 89 * i % 400 for i in range(30)], M=[100, 700, 31] + [17 + 53 * i % 120 for i in range(30)], d=512, H=8,
+                      n_layers=2, n_buckets=128, max_rel_dist=2048, seed=13),
 }
 
 
@@ -43,6 +46,19 @@ def oracle_with_stages(wl, weights=None):
     o = oracle.forward(wl.cfg.to_dict(), weights or wl.weights, wl.history_emb, wl.history_offsets, wl.cand_emb,
                        wl.cand_offsets, st)
     return o, st
+
+
+def test_many_rows_is_past_the_limits():
+    """The launches of many_rows are past the size of a plane from which K1, K2 and K3 store past the caches (and K3 takes whole row blocks), and past the
+    small tile of K1: the limits in csrc/kernels.h and csrc/gemm_mfma.hip."""
+    c = HOT["many_rows"]
+    blocks = sum(-(-n // 64) for n in c["L"] + c["M"])
+    items = sum(-(-n // 128) for n in c["L"] + c["M"])
+    csrc = Path(W.__file__).parent / "csrc"
+    m = re.search(r"kStreamBytes = (\d+) << (\d+);", (csrc / "kernels.h").read_text())
+    stream = int(m.group(1)) << int(m.group(2))
+    small = int(re.search(r"case 512: return (\d+);", (csrc / "gemm_mfma.hip").read_text()).group(1))
+    assert blocks * 64 * c["d"] * 2 > stream and items * 128 * c["d"] * 2 > stream and blocks > small, (blocks, items, stream, small)
 
 
 @pytest.fixture(scope="module")
