@@ -760,10 +760,10 @@ int flame_gr_static_scratch_bytes(const flame_gr_config *cfg_in, int64_t padded_
   c.take(bf ? 2 * rows * d * e : rows * d * sizeof(float)); // residual: Xh and Xl (MFMA path) or fp32 X
   c.take(4 * rows * d * e);                                 // U, V, Q, K
   c.take(rows * d * e);                                     // O
-  if (!bf || !k3_fused_supported(cfg.d_model)) c.take(rows * d * e);   // G
+  if (bf && !k3_fused_supported(cfg.d_model)) c.take(rows * d * e);   // G
   if (bf) {
-    c.take(L * 4 * d * d * e);                              // W1 as fp16, k-tile blocked
-    c.take(L * d * d * e);                                  // W2 as fp16 (blocked or fragment-packed)
+    c.take(L * 4 * d * d * e);                              // W1 as fp16, packed by fragments
+    c.take(L * d * d * e);                                  // W2 as fp16, packed by fragments (either layout)
   }
   c.take(L * (size_t)cfg.n_heads * (size_t)cfg.max_rel_dist * sizeof(float));   // bias by distance
   c.take((size_t)cfg.max_rel_dist * sizeof(int32_t));       // bucket table
@@ -836,7 +836,7 @@ int flame_gr_forward_static(const flame_gr_config *cfg_in, const flame_gr_weight
   h.plane_bytes = rows * d * e;
   h.planes = base + c.take(4 * h.plane_bytes);
   h.O = base + c.take(rows * d * e);
-  if (!bf || !k3_fused_supported(cfg.d_model)) h.G = base + c.take(rows * d * e);
+  if (bf && !k3_fused_supported(cfg.d_model)) h.G = base + c.take(rows * d * e);
   if (bf) {
     h.W1h = base + c.take(L * 4 * d * d * e);
     void *w2 = base + c.take(L * d * d * e);

@@ -251,3 +251,14 @@ def test_split_batches_never_reach_the_spare_rows():
     ws = B.flame_gr_host_workspace_rows(cfg)
     _, seg = B.flame_gr_host_plan(cfg, np.array([0, 1, 2, 3, 501], np.int32), np.array([0, 1, 2, 3, 499], np.int32))
     assert max(int(s[4]) + pad(int(s[1])) + pad(int(s[3])) for s in seg) + 256 <= ws
+
+
+@pytest.mark.parametrize("dtype,d,per_row", [("f32", 64, 24 * 64), ("f32", 320, 24 * 320), ("bf16", 128, 14 * 128), ("bf16", 512, 14 * 512),
+                                             ("bf16", 64, 16 * 64), ("bf16", 320, 16 * 320)])
+def test_static_workspace_bytes_per_row(dtype, d, per_row):
+    """The static workspace takes what the header states per padded row (24 d in fp32, 14 d in bf16 where the output projection is fused, 16 d elsewhere)
+    and the plan tables, 120 bytes per 64 rows."""
+    cfg = B.make_config(2, d, d // 32, 16, 64, dtype)
+    rows = 256 * 100
+    bytes_ = B.flame_gr_static_scratch_bytes(cfg, 512 + rows) - B.flame_gr_static_scratch_bytes(cfg, 512)
+    assert bytes_ == rows * per_row + (rows // 64 * 120 + 255) // 256 * 256
