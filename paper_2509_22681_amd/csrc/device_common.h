@@ -130,23 +130,6 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-// Maximum over the 64 lanes, delivered to every lane (same exchange pattern as wave_sum).
-__device__ __forceinline__ float wave_max(float v) {
-  {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-  }
-  {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-  }
-  v = fmaxf(v, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x128, 0xf, 0xf, false)));
-  v = fmaxf(v, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x124, 0xf, 0xf, false)));
-  v = fmaxf(v, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x4e, 0xf, 0xf, false)));
-  v = fmaxf(v, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0xb1, 0xf, 0xf, false)));
-  return v;
-}
-
 // Exchange between the two lanes that share a query column of a 32x32 accumulator block (lane and lane ^ 32):
 // both get the maximum, resp. the sum, of their two values.
 __device__ __forceinline__ float pair_max(float v) {

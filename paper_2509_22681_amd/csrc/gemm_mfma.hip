@@ -121,8 +121,8 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_kernel(
   constexpr int A_Q = BM / 64, B_Q = BN / 64;
   const int rloc = 16 * wave + 4 * (lane >> 4) + ((lane & 15) >> 2);
   const int dch = (lane & 3) ^ lds_key(rloc);
-  // W is k-tile blocked (64 rows x 32 k = 2048 contiguous elements, whole 128-byte lines per request);
-  // A is blocked too when it is the activation copy Xh, row-major when it is G.
+  // A is k-tile blocked (64 rows x 32 k = 2048 contiguous elements, whole 128-byte lines per request) when it is the
+  // activation copy Xh, row-major when it is G.
   // Every request address is a wave-uniform base (64-row block and k tile: scalar arithmetic) plus a fixed 32-bit
   // lane offset in bytes, which is the scalar-base form of the request instruction: no vector address
   // arithmetic per k tile.  (Lane offsets are below 64 rows x K elements.)
@@ -455,9 +455,8 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const half_t *__restric
   // this wavefront's 32 columns
   const int cols_per_plane = d / 64;                            // halves of 64 columns per plane
   const int half = 2 * col_tile + (wave >> 1);                  // index over the selected planes
-  const bool active = half < sel.n * cols_per_plane;            // the last tile may be half a tile
-  const int plane = active ? sel.id[half / cols_per_plane] : sel.id[0];
-  const int n_half = active ? (half % cols_per_plane) * 64 : 0; // first column of the half inside its plane
+  const int plane = sel.id[half / cols_per_plane];
+  const int n_half = (half % cols_per_plane) * 64;              // first column of the half inside its plane
   const int n_col = n_half + (wave & 1) * 32;
   const int n0 = plane * d + n_col;
   const bool feature_major = plane == 1;
@@ -501,7 +500,8 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const half_t *__restric
     };
 #pragma unroll
     for (int p = 0; p < PD; ++p) load_w(p);
-    // X has landed (it was requested ahead of W's fragments)
+    // X has landed (it was requested ahead of W's fragments, and all of those are out: the wait counts them)
+    __builtin_amdgcn_sched_barrier(0);
     static_assert(2 * PD <= 16, "the wait below counts the fragments requested behind X");
     if (PD == 8) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -544,7 +544,6 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const half_t *__restric
       *(f16x8 *)(pb + row * 128 + ((c ^ patch_key<8>(row)) << 4)) = o;
     }
   __syncthreads();
-  if (!active) return;
   half_t *P = (half_t *)(plane == 0 ? planes.u : plane == 1 ? planes.v : plane == 2 ? planes.q : planes.k);
   const int ht = tid & 127, c = ht & 7;
 #pragma unroll
@@ -568,7 +567,7 @@ constexpr int64_t kSmallStreamBytes = 64 << 20;
 template <int NK, bool NT = false>
 static void launch_small(const void *Xh, const void *W1h, const void *b1, PlanePtrs planes, const int32_t *blk_list, int blk_first, int n_blk, const PlaneSel &sel,
                          const Shape &sh, hipStream_t s) {
-  const int col_tiles = (sel.n * (sh.d / 64) + 1) / 2;
+  const int col_tiles = sel.n * (sh.d / 64) / 2;
   const int lds = 4096 * NK < 16384 ? 16384 : 4096 * NK;       // the X block, at least the two output patches
   gemm_small_kernel<NK, NT><<<n_blk * col_tiles, 256, lds, s>>>((const half_t *)Xh, (const half_t *)W1h, (const bf16_t *)b1, planes, blk_list, blk_first, n_blk,
                                                            col_tiles, sh.ws_rows, sel, sh.alpha);
@@ -604,7 +603,7 @@ void launch_uvqk_bf16(const void *Xh, const void *W1h, const void *b1, PlanePtrs
   const int bn = sh.d % 128 == 0 ? 128 : 64;
   const int64_t bytes = (int64_t)n_blk * kRowAlign * sh.d * 2;       // of a plane
   const bool nt = bytes > kStreamBytes;
-  if (n_blk <= small_tile_blocks(sh.d)) {
+  if (n_blk <= small_tile_blocks(sh.d) && sel.n * (sh.d / 64) % 2 == 0) {   // (whole tiles of 128 columns: every pair of planes has them)
     const bool snt = bytes >= kSmallStreamBytes;
 #define K1_SMALL(...) launch_small<__VA_ARGS__>(Xh, W1h, b1, planes, blk_list, blk_first, n_blk, sel, sh, s)
     switch (sh.d) {
