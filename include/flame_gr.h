@@ -114,8 +114,9 @@ typedef struct {
                                 1 = the MFMA attention kernel in its latency configuration, for handles that
                                 serve one or a few requests per call: four wavefronts split the keys of a
                                 query tile, which cuts the chain of dependent key tiles that bounds a small
-                                batch's run time to a quarter.  Partial sums are grouped differently: scores agree with
-                                mode 0 to rounding (same error bars), not bit for bit.  No effect on fp32 handles */
+                                batch's run time to a quarter (two wavefronts and half the chain in calls with enough
+                                rows to fill the chip, with the same bits).  Partial sums are grouped differently: scores
+                                agree with mode 0 to rounding (same error bars), not bit for bit.  No effect on fp32 handles */
   int32_t weights_static;    /* 0 = the caller may change the weight values between calls: every call derives its
                                 operand copies (fp16 conversions, packed layouts, the bias table by distance) again;
                                 1 = the caller promises that the device contents behind the weight pointers do not

@@ -49,7 +49,7 @@ namespace flame {
 
 namespace {
 
-constexpr int KH = 64;              // keys per half tile (one pass of the register-level loop)
+constexpr int KH = 64;              // keys per block (one pass of the register-level loop); an LDS tile has KP of them, one per wavefront of a group
 
 // SiLU for small arguments: the polynomial of device_common.h, silu(x) = x/2 + x^2 (a1 + a3 x^2 + a5 x^4).  On the halved
 // logit s = x/2, with t = s^2:
@@ -80,7 +80,7 @@ __device__ __forceinline__ f16x8 pack8(const float *v) {
 // softmax over its allowed keys of logit / tau (tau per layer and head); the kernel keeps a running maximum and
 // sum per row and rescales its output accumulators when the maximum moves (one pass over the keys).  The logit
 // in the accumulators is halved, so the exponent fed to the base-2 exponential is accumulator * tscale_h[head]
-// with tscale = 2 log2(e) / tau.  The 64 keys of a half tile of one query sit in two lanes (lane and lane ^ 32),
+// with tscale = 2 log2(e) / tau.  The 64 keys of a block of one query sit in two lanes (lane and lane ^ 32),
 // which exchange their maxima with one half-swap; their partial sums are only added at the end.
 //
 // KP = wavefronts per group of 32 query rows.  KP = 1 is the throughput configuration described at the top: 4 wavefronts, key tiles
@@ -292,13 +292,13 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
     for (int u = k_part; u < k_part + 1; ++u) {
     const int k0 = t * KT + u * KH;
     if (wave_active && k0 < wave_vis_max) {
-      const char *kb = sb + u * (KH * DH * 2);                 // K rows of this half tile
+      const char *kb = sb + u * (KH * DH * 2);                 // K rows of this block
       const int vau = va0 ^ (u << 7);                          // V^T: chunks 8 u .. 8 u + 7 of each row
       const bool need_mask = k0 + KH > wave_vis_min;
-      // key 32 j + 16 (e >> 3) + 8 lhalf + (e & 7) of this half tile is visible to my row iff its constant part is below vis_lim
+      // key 32 j + 16 (e >> 3) + 8 lhalf + (e & 7) of this block is visible to my row iff its constant part is below vis_lim
       const int vis_lim = n_vis - k0 - 8 * lhalf;
       {
-        // ---- S^T = K Q^T: blocks [j], j = 32-key half of the half tile.  Fragment reads run one group
+        // ---- S^T = K Q^T: blocks [j], j = 32-key half.  Fragment reads run one group
         // ahead of the MFMAs that use them (and the first V^T group is fetched behind the last K group),
         // so LDS latency hides behind matrix work instead of being paid once per group.
         f32x16 sacc[2];

@@ -2,7 +2,7 @@
 //   K1  [U V Q K] = silu(X W1^T + b1)            (SiLU fused as the GEMM epilogue)
 //   K3b X <- X + G W2^T + b2                     (residual fused as the GEMM epilogue; X is held as the two fp16 words
 //                                                 Xh = fp16(X), k-tile blocked, and Xl = fp16(X - Xh), row-major)
-// Both are C[m][n] = sum_k A[m][k] W[n][k] with A and W row-major, k contiguous.
+// Both are C[m][n] = sum_k A[m][k] W[n][k].
 //
 // Tiling.  A 128x128 tile re-reads 1 byte of operand per 64 flop, which at MFMA speed is twice what
 // the L2 delivers (measured about 19 TB/s), so the block tile is 256 x BN (BN = 128 where d allows):
@@ -17,9 +17,9 @@
 // one barrier (tile kt complete for everybody, tile kt-1 vacated by everybody), requests tile kt+2
 // into the vacated stage - two iterations of flight time - and multiplies tile kt; the fragment reads
 // of the second 16-deep step are issued behind the first MFMAs of the first step, so that they run
-// under matrix work and nothing waits on them early.  LDS rows are 64 bytes; 16-byte chunks are
-// XOR-swizzled over 128-byte lines (each DMA lane fetches the chunk that belongs in its slot), which
-// makes the fragment reads bank-conflict free without padding.
+// under matrix work and nothing waits on them early.  LDS rows of A are 64 bytes; 16-byte chunks are
+// XOR-swizzled over groups of 256 bytes (each DMA lane fetches the chunk that belongs in its slot: lds_off), which
+// makes the fragment reads bank-conflict free without padding; W comes packed by fragments and needs no swizzle.
 //
 // Rows are addressed through 64-row blocks so that the same kernel runs on a contiguous range or on
 // a list of candidate blocks (last-layer pruning).

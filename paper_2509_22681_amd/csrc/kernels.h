@@ -108,10 +108,13 @@ void launch_k3_fused(const void *O, const void *U, const void *gamma, const void
 // (both sides of each are at launch_k3).
 constexpr int kK3CutInFour = 32, kK3CutInTwo = 64, kK3HalfBlocks = 384;
 
-// Planes larger than this are written and read past the caches (nontemporal): a layer's eight arrays of N x d fp16 no longer fit
-// the 256 MB behind the L2s, and what streams through would push the operands that are read many times out of them.  Measured per
-// forward, ordinary against nontemporal: 10 MB per plane (32 x 640 rows, d = 256) 289 against 308 us, 3 MB (one request, d = 512) 1033
-// against 1078 us; 27 MB equal; 100 MB 5.15 against 4.98 ms, 500 MB 65.4 against 63.7 ms.
+// A launch whose rows make a plane (rows x d fp16) larger than this writes and reads what is consumed once past the caches (nontemporal): what streams
+// through would push the operands that are read many times out of them.  The line is where the two measured level, per forward, ordinary
+// against nontemporal: 3 MB per plane (one request, d = 512) 1033 against 1078 us, 10 MB (32 x 640 rows, d = 256) 289 against 308 us; 27 MB equal;
+// 100 MB 5.15 against 4.98 ms, 500 MB 65.4 against 63.7 ms.  (At the line the eight arrays of a layer are 128 MB, half of the cache behind the L2s.)
+// K1's large tile and K3 count the rows of the launch, K2 128 rows per tile.  K1's small tile has a line of its own (kSmallStreamBytes) and none for
+// d >= 256, which it leaves at 32 MB at the latest: d = 256, 32 MB, 4 layers of 512 x (64 + 64) 615 us, with the large tile 625.  The
+// kernels of widths without a fused K3 (ln_gate, output projection) store through the caches at any size.
 constexpr int64_t kStreamBytes = 16 << 20;
 
 }  // namespace flame

@@ -289,7 +289,10 @@ void launch_outproj_f32(const float *O, const float *U, const float *gamma, cons
 // multiplied.  A lane's 16 bytes of a K row from global memory are 32 lines per instruction, 360 requests per block of 32 keys and
 // wavefront, and the compute unit has too few of them in flight to feed the matrix instruction; through LDS a wavefront makes 64 for a tile.
 // 32 x (512 + 128), 4 heads of 64: 106 -> 91 us per launch (43 at the matrix rate), the candidates alone 31 -> 33 us.
-// Other widths read their operands straight from global memory, without a barrier.
+// Other widths read their operands straight from global memory, without a barrier.  Heads of 129 to 256 hold 256 accumulators and the query
+// row's fragments in registers, one wavefront per SIMD, and do not fit: 375 to 397 registers spill (51 to 54 at a width of exactly 256).  They are
+// the slow ones for it, 32 x (256 + 64) on 2 heads 167 us per launch at a width of 160 and 73 at 256, against 32 at 128 (with one
+// wavefront per query row and plain FMAs 4171, 6574 and 3108).
 // DB = 32-wide blocks of the head; EXACT: the head is exactly 32 DB wide (vector loads), else elements past it count as zero.
 // A lane's V operand of block b is feature DB * row + b, so that one load brings a lane's features of all blocks.
 // ---------------------------------------------------------------------------------------------
