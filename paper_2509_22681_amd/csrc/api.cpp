@@ -62,6 +62,7 @@ struct flame_gr {
   void *Xb = nullptr, *Xl = nullptr;                                     // residual stream, MFMA path: fp16(X) (k-tile blocked) and fp16(X - Xb)
   void *planes = nullptr, *O = nullptr, *G = nullptr;
   void *W1h = nullptr, *W2h = nullptr, *W2p = nullptr;                   // fp16 copies of the projection matrices (W2p: fragment-major)
+  void *Ws = nullptr;                                                    // fp32 path: the projection matrices split into bf16 parts (absent: the kernels split them)
   float *bias = nullptr;
   float *tscale = nullptr;                                               // softmax: logit scale per layer and head
   int32_t *bucket_tab = nullptr;
@@ -142,7 +143,7 @@ float half_bits_to_float(uint16_t b) {
 void free_all(flame_gr *h) {
   (void)hipFree(h->X); (void)hipFree(h->Xb); (void)hipFree(h->Xl); (void)hipFree(h->planes); (void)hipFree(h->kv); (void)hipFree(h->O); (void)hipFree(h->G);
   (void)hipFree(h->bias); (void)hipFree(h->tscale); (void)hipFree(h->bucket_tab); (void)hipFree(h->stage_dev);
-  (void)hipFree(h->W1h); (void)hipFree(h->W2h); (void)hipFree(h->W2p);
+  (void)hipFree(h->W1h); (void)hipFree(h->W2h); (void)hipFree(h->W2p); (void)hipFree(h->Ws);
   (void)hipFree(h->cap_planes); (void)hipFree(h->cap_O); (void)hipFree(h->cap_X);
   for (int i = 0; i < kStageSlots; ++i) {
     if (h->stage_host[i]) (void)hipHostFree(h->stage_host[i]);
@@ -218,9 +219,10 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, const voi
       pp.v = h->kv + (size_t)l * 2 * h->plane_bytes;
       pp.k = h->kv + ((size_t)l * 2 + 1) * h->plane_bytes;
     }
-    const char *w1 = (const char *)(dt == FLAME_GR_BF16 ? h->W1h : w.w1) + (size_t)l * 4 * d * d * e;
+    const size_t split_mat = (size_t)split_w_bytes(d, 1) / 5;
+    const char *w1 = h->Ws ? (const char *)h->Ws + (size_t)l * 4 * split_mat : (const char *)(dt == FLAME_GR_BF16 ? h->W1h : w.w1) + (size_t)l * 4 * d * d * e;
     const char *b1 = (const char *)w.b1 + (size_t)l * 4 * d * e;
-    const char *w2 = (const char *)(dt == FLAME_GR_BF16 ? h->W2h : w.w2) + (size_t)l * d * d * e;
+    const char *w2 = h->Ws ? (const char *)h->Ws + ((size_t)sh.n_layers * 4 + l) * split_mat : (const char *)(dt == FLAME_GR_BF16 ? h->W2h : w.w2) + (size_t)l * d * d * e;
     const char *b2 = (const char *)w.b2 + (size_t)l * d * e;
     const char *lg = (const char *)w.ln_g + (size_t)l * d * e;
     const char *lb = (const char *)w.ln_b + (size_t)l * d * e;
@@ -229,17 +231,15 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, const voi
     // In the last layer only candidate rows feed the scores, and history rows never look at
     // candidates: history rows need K and V only, attention and the output projection run on
     // candidate rows only.
-    if (dt == FLAME_GR_BF16) {
+    {
       Timed t(h, KIND_UVQK, s);
-      if (mode == PASS_FULL && last) {
-        launch_uvqk_bf16(h->Xb, w1, b1, pp, nullptr, n_blk, G.blk_begin, 0xA, sh, s);  // V, K: all rows
-        launch_uvqk_bf16(h->Xb, w1, b1, pp, cl, n_cblk, 0, 0x5, sh, s);                // U, Q: candidates
-      } else {
-        launch_uvqk_bf16(h->Xb, w1, b1, pp, pass_list, pass_n, pass_first, mode == PASS_HISTORY && last ? 0xA : 0xF, sh, s);
-      }
-    } else {
-      Timed t(h, KIND_UVQK, s);
-      launch_uvqk_f32(h->X, (const float *)w1, (const float *)b1, (float *)planes, G.blk_begin, n_blk, sh, s);
+      // last layer of a one-pass forward: V and K of all rows, U and Q of the candidates
+      const bool pruned = mode == PASS_FULL && last;
+      const int mask = pruned || (mode == PASS_HISTORY && last) ? 0xA : 0xF;
+      const int32_t *uq = pruned ? cl : nullptr;
+      const int n_uq = pruned ? n_cblk : 0;
+      if (dt == FLAME_GR_BF16) launch_uvqk_bf16(h->Xb, w1, b1, pp, pass_list, pass_n, pass_first, mask, uq, n_uq, sh, s);
+      else launch_uvqk_f32(h->X, w1, h->Ws != nullptr, (const float *)b1, (float *)planes, pass_list, pass_n, pass_first, mask, uq, n_uq, sh, s);
     }
     if (mode == PASS_HISTORY && last) break;  // the history rows of the last layer end at K and V
     {
@@ -266,7 +266,7 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, const voi
       launch_outproj_bf16(h->G, w2, b2, h->Xb, h->Xl, l == 0, bl, nb, bf, sh, s);
     } else {
       Timed t(h, KIND_OUTPROJ, s);
-      launch_outproj_f32((const float *)h->O, (const float *)planes, (const float *)lg, (const float *)lb, (const float *)w2, (const float *)b2, h->X,
+      launch_outproj_f32((const float *)h->O, (const float *)planes, (const float *)lg, (const float *)lb, w2, h->Ws != nullptr, (const float *)b2, h->X,
                          blocks, bl, nb, bf, sh, s);
     }
     if (capture && h->cap_planes) {
@@ -309,6 +309,8 @@ void derive_weights(flame_gr *h, const flame_gr_weights *w, hipStream_t s) {
     launch_pack_w(w->w1, h->W1h, (int64_t)h->sh.n_layers * 4 * dm, dm, true, s);
     if (k3_fused_supported(dm)) launch_pack_w2(w->w2, h->W2p, dm, h->sh.n_layers, s);
     else launch_pack_w(w->w2, h->W2h, (int64_t)h->sh.n_layers * dm, dm, false, s);
+  } else if (h->Ws) {
+    launch_split_w((const float *)w->w1, (const float *)w->w2, h->Ws, h->sh.d, h->sh.n_layers, s);
   }
   launch_expand_bias(w->rab, h->bucket_tab, h->bias, h->sh.n_layers * h->sh.H, h->sh.n_buckets, h->sh.D,
                      h->cfg.dtype == FLAME_GR_BF16 ? 0.5f : 1.0f, s);
@@ -447,7 +449,10 @@ int flame_gr_create(const flame_gr_config *cfg_in, flame_gr_t **out) {
   if (h->sh.latency && cfg.dtype == FLAME_GR_BF16) CR(attn_latency_setup(h->sh));
   const size_t rows = (size_t)h->ws_rows, d = (size_t)cfg.d_model, e = h->elt;
   const bool mfma_path = cfg.dtype == FLAME_GR_BF16;
-  if (!mfma_path) CR(hipMalloc(&h->X, rows * d * sizeof(float)));
+  if (!mfma_path) {
+    CR(hipMalloc(&h->X, rows * d * sizeof(float)));
+    CR(hipMalloc(&h->Ws, (size_t)split_w_bytes(cfg.d_model, cfg.n_layers)));
+  }
   h->plane_bytes = rows * d * e;
   CR(hipMalloc(&h->planes, 4 * h->plane_bytes));
   if (cfg.kv_cache) CR(hipMalloc((void **)&h->kv, (size_t)cfg.n_layers * 2 * h->plane_bytes));
@@ -849,6 +854,7 @@ int flame_gr_forward_static(const flame_gr_config *cfg_in, const flame_gr_weight
   if (!h.sh.softmax) h.tscale = nullptr;
   h.lay = stage_layout(rows / kRowAlign);
   h.stage_dev = (char *)(base + c.take(h.lay.total));
+  if (!bf && c.off + (size_t)split_w_bytes(cfg.d_model, cfg.n_layers) <= kStaticScratchBytes) h.Ws = base + c.off;   // where there is room behind the workspace
   if ((int64_t)c.off != need) { g_create_error = "internal: static workspace layout mismatch"; return FLAME_GR_HIP_ERROR; }
   if (h.sh.latency && bf && attn_latency_setup(h.sh) != hipSuccess) { g_create_error = "attention kernel setup failed"; return FLAME_GR_HIP_ERROR; }
   hipStream_t s = (hipStream_t)stream_v;

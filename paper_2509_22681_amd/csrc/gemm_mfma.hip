@@ -417,7 +417,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_kernel(
 template <int NK, bool NT>
 __global__ __launch_bounds__(256) void gemm_small_kernel(const half_t *__restrict__ A, const half_t *__restrict__ W, const bf16_t *__restrict__ bias,
                                                          PlanePtrs planes, const int32_t *__restrict__ blk_list, int blk_first, int n_blk, int n_col_tiles,
-                                                         int64_t ws_rows, PlaneSel sel, float alpha) {
+                                                         int64_t ws_rows, PlaneSel sel, float alpha, const int32_t *__restrict__ uq_list, int n_uq) {
   constexpr int nk = NK, d = NK * BK, rot_cols = d % 128 == 0 ? 128 : 64;
   extern __shared__ __attribute__((aligned(256))) char lds[];   // [k / 32][64 rows][32 k], swizzled; the output patches afterwards
   const int tid = threadIdx.x, lane = tid & 63;
@@ -425,9 +425,18 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const half_t *__restric
   const int l32 = lane & 31, lhalf = lane >> 5;
   // XCD x takes the row blocks congruent to x mod 8 (see the large tile)
   int row_blk, col_tile;
+  bool second;
   {
     constexpr int NXCD = 8;
-    const int wg = blockIdx.x, xcd = wg % NXCD, j = wg / NXCD;
+    int wg = blockIdx.x;
+    const int n_first = (int)gridDim.x - n_uq * n_col_tiles;
+    second = wg >= n_first;
+    if (second) {                                                // the second part of the launch: U and Q of the blocks in uq_list
+      wg -= n_first;
+      blk_list = uq_list;
+      n_blk = n_uq;
+    }
+    const int xcd = wg % NXCD, j = wg / NXCD;
     const int full = (n_blk / NXCD) * NXCD;
     const int rt = (j / n_col_tiles) * NXCD + xcd;
     if (rt < full) {
@@ -455,7 +464,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const half_t *__restric
   // this wavefront's 32 columns
   const int cols_per_plane = d / 64;                            // halves of 64 columns per plane
   const int half = 2 * col_tile + (wave >> 1);                  // index over the selected planes
-  const int plane = sel.id[half / cols_per_plane];
+  const int plane = second ? 2 * (half / cols_per_plane) : sel.id[half / cols_per_plane];
   const int n_half = (half % cols_per_plane) * 64;              // first column of the half inside its plane
   const int n_col = n_half + (wave & 1) * 32;
   const int n0 = plane * d + n_col;
@@ -566,11 +575,11 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const half_t *__restric
 constexpr int64_t kSmallStreamBytes = 64 << 20;
 template <int NK, bool NT = false>
 static void launch_small(const void *Xh, const void *W1h, const void *b1, PlanePtrs planes, const int32_t *blk_list, int blk_first, int n_blk, const PlaneSel &sel,
-                         const Shape &sh, hipStream_t s) {
+                         const int32_t *uq_list, int n_uq, const Shape &sh, hipStream_t s) {
   const int col_tiles = sel.n * (sh.d / 64) / 2;
   const int lds = 4096 * NK < 16384 ? 16384 : 4096 * NK;       // the X block, at least the two output patches
-  gemm_small_kernel<NK, NT><<<n_blk * col_tiles, 256, lds, s>>>((const half_t *)Xh, (const half_t *)W1h, (const bf16_t *)b1, planes, blk_list, blk_first, n_blk,
-                                                           col_tiles, sh.ws_rows, sel, sh.alpha);
+  gemm_small_kernel<NK, NT><<<(n_blk + n_uq) * col_tiles, 256, lds, s>>>((const half_t *)Xh, (const half_t *)W1h, (const bf16_t *)b1, planes, blk_list, blk_first, n_blk,
+                                                           col_tiles, sh.ws_rows, sel, sh.alpha, uq_list, n_uq);
 }
 
 // Up to this many 64-row blocks a launch runs on the small tiles.  The wider the model, the fewer workgroups of the small tile fit a
@@ -594,7 +603,7 @@ static int small_tile_blocks(int d) {
 }
 
 void launch_uvqk_bf16(const void *Xh, const void *W1h, const void *b1, PlanePtrs planes, const int32_t *blk_list,
-                      int n_blk, int blk_first, int plane_mask, const Shape &sh, hipStream_t s) {
+                      int n_blk, int blk_first, int plane_mask, const int32_t *uq_list, int n_uq, const Shape &sh, hipStream_t s) {
   if (n_blk <= 0 || !(plane_mask & 0xF)) return;
   PlaneSel sel{};
   for (int p = 0; p < 4; ++p)
@@ -605,7 +614,7 @@ void launch_uvqk_bf16(const void *Xh, const void *W1h, const void *b1, PlanePtrs
   const bool nt = bytes > kStreamBytes;
   if (n_blk <= small_tile_blocks(sh.d) && sel.n * (sh.d / 64) % 2 == 0) {   // (whole tiles of 128 columns: every pair of planes has them)
     const bool snt = bytes >= kSmallStreamBytes;
-#define K1_SMALL(...) launch_small<__VA_ARGS__>(Xh, W1h, b1, planes, blk_list, blk_first, n_blk, sel, sh, s)
+#define K1_SMALL(...) launch_small<__VA_ARGS__>(Xh, W1h, b1, planes, blk_list, blk_first, n_blk, sel, uq_list, n_uq, sh, s)
     switch (sh.d) {
       case 64: if (snt) K1_SMALL(2, true); else K1_SMALL(2); break;
       case 128: if (snt) K1_SMALL(4, true); else K1_SMALL(4); break;
@@ -617,6 +626,7 @@ void launch_uvqk_bf16(const void *Xh, const void *W1h, const void *b1, PlanePtrs
 #undef K1_SMALL
     return;
   }
+  if (n_uq > 0) launch_uvqk_bf16(Xh, W1h, b1, planes, uq_list, n_uq, 0, 0x5, nullptr, 0, sh, s);
   const int col_tiles = sel.n * (sh.d / bn);
 #define K1_CASE(BNV, NTV) gemm_mfma_kernel<BNV, 0, NTV><<<row_tiles * col_tiles, 256, 0, s>>>((const half_t *)Xh, (const half_t *)W1h, (const bf16_t *)b1, planes, nullptr, \
     nullptr, 0, blk_list, blk_first, n_blk, row_tiles, col_tiles, sh.d, sh.d, sh.ws_rows, sel, sh.alpha, true)

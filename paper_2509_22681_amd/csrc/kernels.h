@@ -62,16 +62,21 @@ void launch_debug_mask(int L, int M, const int32_t *bucket_tab, int D, uint8_t *
                        hipStream_t s);
 
 // ---- fp32 path (kernels_f32.hip): the fp32 matrix instruction ----------------------------------
-// planes[p][row][n] = silu(X W1^T + b1), p = U,V,Q,K; rows = 64-row blocks [blk_first, blk_first+n_blk)
-void launch_uvqk_f32(const float *X, const float *W1, const float *b1, float *planes, int blk_first,
-                     int n_blk, const Shape &sh, hipStream_t s);
+// The projection matrices of all layers split into bf16 parts for the two products below (kernels_f32.hip), packed by fragments: matrix m of the copy, W1's planes layer after layer
+// and then W2's, starts at m * split_w_bytes(d, 1) / 5.  The products take the packed matrix of the layer (packed), or the matrix itself.
+int64_t split_w_bytes(int d, int n_layers);
+void launch_split_w(const float *W1, const float *W2, void *out, int d, int n_layers, hipStream_t s);
+// planes[p][row][n] = silu(X W1^T + b1), p = U,V,Q,K; rows = the listed 64-row blocks (blk_list == nullptr: [blk_first, blk_first+n_blk));
+// plane_mask: all planes (0xF), U and Q (0x5) or V and K (0xA); uq_list (n_uq blocks, with V and K): their U and Q with it
+void launch_uvqk_f32(const float *X, const void *W1, bool packed, const float *b1, float *planes, const int32_t *blk_list, int n_blk, int blk_first,
+                     int plane_mask, const int32_t *uq_list, int n_uq, const Shape &sh, hipStream_t s);
 // tscale_h (softmax only): per head, the factor from the logit the kernel forms to the exponent it feeds to
 // its exponential: 1 / tau here (natural exponential of the full logit).
 void launch_attn_f32(const float *planes, const float *bias_lh, const float *tscale_h, float *O, const AttnItem *items,
                      int n_items, const Shape &sh, hipStream_t s);
 // X[row] += ((LayerNorm(O[row]) * gamma + beta) * U[row]) W2^T + b2 for the rows of the listed blocks (blk_list == nullptr:
 // contiguous); padding rows of a block get the bias only, so that they stay finite through the layers.
-void launch_outproj_f32(const float *O, const float *U, const float *gamma, const float *beta, const float *W2, const float *b2, float *X,
+void launch_outproj_f32(const float *O, const float *U, const float *gamma, const float *beta, const void *W2, bool packed, const float *b2, float *X,
                         const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first, const Shape &sh, hipStream_t s);
 
 // The four activation planes of a layer (MFMA path), each [ws_rows][d] fp16 (V feature-major [d][ws_rows]).  The
@@ -82,9 +87,10 @@ struct PlanePtrs { void *u, *v, *q, *k; };
 // Activations (Xh, planes, O, G) and the converted matrices W1h/W2h are fp16; biases stay bf16.
 // Xh is k-tile blocked (device_common.h: blocked_index), W1h and W2h are packed by fragments (device_common.h); planes, O and G are row-major.
 // U, Q, K planes row-major [row][d]; the V plane is written transposed, Vt[n][row] (row stride ws_rows).
-// plane_mask bit p set = compute plane p (U=1, V=2, Q=4, K=8).
+// plane_mask bit p set = compute plane p (U=1, V=2, Q=4, K=8); uq_list (n_uq blocks, with the mask of V and K): their U and Q with it, in the same
+// launch where the small tiles run.
 void launch_uvqk_bf16(const void *Xh, const void *W1h, const void *b1, PlanePtrs planes, const int32_t *blk_list,
-                      int n_blk, int blk_first, int plane_mask, const Shape &sh, hipStream_t s);
+                      int n_blk, int blk_first, int plane_mask, const int32_t *uq_list, int n_uq, const Shape &sh, hipStream_t s);
 // tscale_h (softmax only): 2 log2(e) / tau per head (the kernel holds halved logits and uses the base-2 exponential).
 // q_tile: query rows per item of this plan.
 void launch_attn_bf16(PlanePtrs planes, const float *bias_lh, const float *tscale_h, void *O, const AttnItem *items,

@@ -1,10 +1,13 @@
-// fp32 instantiation of the GR block, on the fp32 matrix instruction (32 x 32 x 2: fp32 operands and accumulator, the
-// arithmetic of a chain of FMAs).  It serves the 1e-4 parity case and every shape the fp16 kernels do not cover.
+// fp32 instantiation of the GR block.  It serves the 1e-4 parity case and every shape the fp16 kernels do not cover.  The projections run on the
+// bf16 matrix instruction with operands split into three parts (see gemm_f32_kernel), attention on the fp32 matrix instruction (32 x 32 x 2: fp32
+// operands and accumulator, the arithmetic of a chain of FMAs).
 //
-// Operand layout of that instruction, used throughout: acc[i][j] += sum over two k slots of A[i][k] B[j][k]; lane l
+// Operand layout of the fp32 instruction: acc[i][j] += sum over two k slots of A[i][k] B[j][k]; lane l
 // supplies row l & 31 of either operand for k slot l >> 5.  A lane reads four consecutive floats of its row at offset
 // 4 (l >> 5) of every group of eight, which feeds four instructions (slots {8 g + t, 8 g + 4 + t}) from one 16-byte load.
 // Accumulator element e of a lane is row 8 (e / 4) + 4 (l >> 5) + e % 4 of A, row l & 31 of B.
+#include <type_traits>
+
 #include "device_common.h"
 #include "kernels.h"
 
@@ -31,6 +34,34 @@ __device__ __forceinline__ f32x4 load4(const float *p, int k, int K) {
   return v;
 }
 
+// An fp32 value as the sum of three bf16 values, exactly: each takes the next eight bits (round to nearest, the remainder is exact in fp32), and 8 + 8 + 8
+// bits with signs hold the 24 of the mantissa.
+struct Split3 { bf16x4 p[3]; };
+__device__ __forceinline__ Split3 split3(f32x4 v) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  Split3 s;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    f32x2 x = {v[2 * h], v[2 * h + 1]};
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const bf16x2 b = __builtin_convertvector(x, bf16x2);       // two values per instruction
+      s.p[i][2 * h] = b[0];
+      s.p[i][2 * h + 1] = b[1];
+      if (i < 2) { x[0] -= (float)b[0]; x[1] -= (float)b[1]; }
+    }
+  }
+  return s;
+}
+
+// silu(x) = x / (1 + exp(-x)) with the reciprocal by the hardware's estimate and one Newton step (within an ulp of the quotient, a third of its
+// instructions).  The exponent is capped where 1 + exp(-x) would leave the range: the result there is below 1e-34 either way.
+__device__ __forceinline__ float silu_newton(float x) {
+  const float t = 1.0f + __expf(fminf(-x, 87.0f));
+  const float r = __builtin_amdgcn_rcpf(t);
+  return x * __builtin_fmaf(__builtin_fmaf(-t, r, 1.0f), r, r);
+}
+
 // Sum over the 16 lanes of a row of lanes, delivered to all of them.
 __device__ __forceinline__ float row16_sum(float v) {
   v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x128, 0xf, 0xf, false));  // row_ror:8
@@ -43,38 +74,92 @@ __device__ __forceinline__ float row16_sum(float v) {
 }  // namespace
 
 // ---------------------------------------------------------------------------------------------
-// C[m][n] = sum_k A[m][k] W[n][k] + bias[n] on 64-row blocks.  256 threads = 2 x 2 wavefronts of 32 T x 32 T outputs, so a
-// (64 T)^2 tile per workgroup; k in chunks of 32 through two LDS stages (one barrier per chunk, the next chunk's loads in
-// flight under the current one's matrix work).  LDS rows are 128 bytes, 16-byte chunks XOR-swizzled by row / 2, which the
-// fragment reads take without bank conflicts.
-// EPI 0: planes[n / d][m][n % d] = silu(C) with A = X.
+// The projection matrices as bf16 parts, fragment by fragment: [matrix][row / 32][k / 16][part][lane][8], 1 KB per fragment; lane l holds k 8 (l / 32) + 0..7
+// of row l & 31.  Matrices of d x d, rows and k padded with zeros to multiples of 32: the 4 n_layers planes of W1, then the n_layers matrices of W2.
+// One thread makes 16 bytes of each of the three parts.
+// ---------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void split_w_kernel(const float *__restrict__ W1, const float *__restrict__ W2, char *__restrict__ out, int n1, int n, int d) {
+  const int dp = (d + 31) / 32 * 32, kf = dp / 16;
+  const int64_t per = (int64_t)dp * dp / 8, total = per * n;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
+    const int lane = (int)(i & 63), mat = (int)(i / per);
+    const int f = (int)(i % per >> 6), rb = f / kf, ks = f % kf;
+    const int row = rb * 32 + (lane & 31), k = ks * 16 + 8 * (lane >> 5);
+    const float *src = (mat < n1 ? W1 + (int64_t)mat * d * d : W2 + (int64_t)(mat - n1) * d * d) + (int64_t)row * d;
+    f32x4 v[2];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) v[t >> 2][t & 3] = row < d && k + t < d ? src[k + t] : 0.f;
+    const Split3 s0 = split3(v[0]), s1 = split3(v[1]);
+    char *dst = out + (((int64_t)mat * per >> 6) + f) * 3072 + lane * 16;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      *(bf16x4 *)(dst + p * 1024) = s0.p[p];
+      *(bf16x4 *)(dst + p * 1024 + 8) = s1.p[p];
+    }
+  }
+}
+
+int64_t split_w_bytes(int d, int n_layers) { const int64_t dp = (d + 31) / 32 * 32; return 5 * n_layers * dp * dp * 6; }
+
+void launch_split_w(const float *W1, const float *W2, void *out, int d, int n_layers, hipStream_t s) {
+  const int64_t total = split_w_bytes(d, n_layers) / 48;
+  const int grid = (int)((total + 255) / 256 > 2048 ? 2048 : (total + 255) / 256);
+  split_w_kernel<<<grid, 256, 0, s>>>(W1, W2, (char *)out, 4 * n_layers, 5 * n_layers, d);
+}
+
+// ---------------------------------------------------------------------------------------------
+// C[m][n] = sum_k A[m][k] W[n][k] + bias[n] on 64-row blocks.  256 threads = WM x WN wavefronts of MB x NB blocks of 32 x 32 outputs; k in chunks of 32.
+// Both operands are split into three bf16 values, and six of the nine products run on the bf16 matrix instruction (32 x 32 x 16, fp32
+// accumulators), the small ones first; left out are the three of 2^-26 of the largest and less.  6 x 32 cycles for 16 k against 8 x 64 on the fp32 instruction, and the sums
+// are rounded less often (a product of bf16 values is exact, and 16 k go into an accumulator at a time instead of 2).
+// PACKED: W arrives split (split_w_kernel), by LDS-DMA, a chunk ahead through two stages; else (64 x 64 tiles only: callers without room for the packed copy) it is split here, like A,
+// on the way from registers to LDS.  The split is exact, so the two agree bit for bit.
+// LDS rows of A are 64 bytes per part, 16-byte chunks XOR-swizzled over groups of four rows (key: row bits 2..3), which the fragment reads take
+// without bank conflicts.  Tiles of 64 rows have two stages for A, tiles of 128 one (two workgroups on a compute unit, one's staging under
+// the other's matrix work).
+// EPI 0: planes[p][m][n] = silu(C) with A = X.
 // EPI 1: X[m][n] += C with A = (LayerNorm(O) * gamma + beta) * U, made while the chunk is staged: the statistics of the 64
 //        rows come first (mean, then the centred second moment), and the gated rows never travel through memory.
-// The matrix rate is the bound for large batches (64 cycles per instruction), latency for small ones.  20 480 rows, d = 256:
-// K1 260 -> 106 us (10.7 GFLOP at 101 TFLOP/s; the instruction alone reaches 157), LN, gate and output projection 71 + 11 -> 45 us,
-// against plain FMA kernels on 64 x 64 tiles with a LayerNorm pass of its own.
+// 20 480 rows, d = 256: K1 116 -> 85 us per launch against the fp32 instruction (its work alone is 26 us; a workgroup spends a third of its time on splitting A and on its
+// requests, and two are resident on a compute unit), 45 us where only V and K are needed; the output projection, whose row statistics come first, 45 -> 42.  Error of the scores
+// against 64 bits 0.87 of what it was (24 cases of widths 64 to 256).
 // ---------------------------------------------------------------------------------------------
 // NI (EPI 1): 16-byte loads per lane and row that the statistics keep in registers, ceil(K / 64) at least; 0: any K, in two reads of the rows.
-template <int EPI, int T, bool VEC, int NI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ U, const float *__restrict__ gamma,
+template <int EPI, int WM, int WN, int MB, int NB, bool PACKED, bool VEC, int NI>
+__global__ __launch_bounds__(256, MB * NB == 4 ? 2 : 1) void gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ U, const float *__restrict__ gamma,
                                                        const float *__restrict__ beta, const RowBlock *__restrict__ blocks, float eps,
-                                                       const float *__restrict__ W, const float *__restrict__ bias, float *__restrict__ out,
-                                                       const int32_t *__restrict__ blk_list, int blk_first, int n_blk, int K, int Ncols, int d,
-                                                       int64_t plane_stride) {
-  constexpr int BT = 64 * T, BK = 32, LPT = BT / 32;      // tile side, k chunk, 16-byte loads per thread and operand
-  __shared__ __attribute__((aligned(256))) float sA[2][BT * BK];
-  __shared__ __attribute__((aligned(256))) float sW[2][BT * BK];
+                                                       const void *__restrict__ Wv, const float *__restrict__ bias, float *__restrict__ out,
+                                                       const int32_t *__restrict__ blk_list, int blk_first, int n_blk, int d, int n_planes, int plane0, int plane_step,
+                                                       int64_t plane_stride, int y2, const int32_t *__restrict__ blk_list2, int n_blk2) {
+  static_assert(WM * WN == 4, "four wavefronts");
+  constexpr int BM = 32 * WM * MB, BN = 32 * WN * NB, BK = 32, TB = BM / 64, LPT = BM / 32;   // tile, k chunk, 64-row blocks, 16-byte loads of A per thread
+  constexpr int AST = TB == 1 ? 2 : 1, APART = BM * BK * 2, ASTAGE = 3 * APART, WSTAGE = 3 * BN * BK * 2;
+  __shared__ __attribute__((aligned(256))) char lds[AST * ASTAGE + 2 * WSTAGE];
   __shared__ float s_mu[EPI == 1 ? 64 : 1], s_rstd[EPI == 1 ? 64 : 1];
-  static_assert(EPI == 0 || T == 1, "row statistics are kept for one block of rows");
+  static_assert(EPI == 0 || TB == 1, "row statistics are kept for one block of rows");
+  static_assert(PACKED || (BM == 64 && BN == 64), "raw W: 64 x 64 tiles");
+  char *const ldsw = lds + AST * ASTAGE;
+  const int K = d, dp = (d + 31) / 32 * 32, pb = dp / 32;      // 32-column blocks per plane
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, lhalf = lane >> 5;
-  const int n0 = blockIdx.y * BT;
-  int64_t row0[T];
-  bool present[T];
+  const int wm = wave / WN, wn = wave % WN, l32 = lane & 31, lhalf = lane >> 5;
+  // 32-column block b of the launch, counted over its planes: matrix (plane) and block in it; blocks past the last repeat it and are not stored
+  int cy = blockIdx.y;
+  if (EPI == 0 && cy >= y2) {                              // the second part of the launch: U and Q of its own blocks
+    cy -= y2;
+    plane0 = 0;
+    blk_list = blk_list2;
+    n_blk = n_blk2;
+    if ((int)blockIdx.x * TB >= n_blk) return;
+  }
+  const int nb_all = n_planes * pb, cb0 = cy * (BN / 32);
+  auto plane_of = [&](int b) { return plane0 + min(b, nb_all - 1) / pb * plane_step; };
+  auto block_of = [&](int b) { return min(b, nb_all - 1) % pb; };
+  int64_t row0[TB];
+  bool present[TB];
 #pragma unroll
-  for (int t = 0; t < T; ++t) {
-    const int i = blockIdx.x * T + t;
+  for (int t = 0; t < TB; ++t) {
+    const int i = blockIdx.x * TB + t;
     present[t] = i < n_blk;
     const int ic = present[t] ? i : n_blk - 1;
     row0[t] = (int64_t)(blk_list ? blk_list[ic] : blk_first + ic) * kRowAlign;
@@ -144,103 +229,178 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
     }
     __syncthreads();
   }
-  // staging: thread (row = tid / 8 + 32 i, chunk = tid % 8) brings 16 bytes of either operand.  The loads stay as they come until store():
-  // an operand made in fetch() would wait for its loads ahead of the matrix work that is there to hide them (20 480 rows, d = 256: 59 -> 45 us
-  // per launch, with the residual's requests below; 64 blocks of rows 20 -> 14.4).
-  // VEC loads are unconditional, at a clamped address where the matrix ends, and zeroed in store() (a branch around each costs more).
+  // staging: thread (row = tid / 8 + 32 i, chunk = tid % 8) brings 16 bytes of A.  The loads stay as they come until split():
+  // an operand made in fetch() would wait for its loads ahead of the matrix work that is there to hide them.
+  // VEC loads are unconditional, at a clamped address where the matrix ends, and zeroed in split() (a branch around each costs more).
   const int sr = tid >> 3, sc = tid & 7;
-  f32x4 ra[LPT], rw[LPT], ru[EPI == 1 ? LPT : 1], rg, rb;
+  f32x4 ra[2][LPT], ru[2][EPI == 1 ? LPT : 1], rg[2], rb[2], rw[2][PACKED ? 1 : 2];   // chunks of even and of odd index
   float mu[EPI == 1 ? LPT : 1], rstd[EPI == 1 ? LPT : 1];
   if constexpr (EPI == 1) {
 #pragma unroll
     for (int i = 0; i < LPT; ++i) { mu[i] = s_mu[sr + 32 * i]; rstd[i] = s_rstd[sr + 32 * i]; }
   }
   auto load = [&](const float *p, int k) { return VEC ? *(const f32x4 *)(p + min(k, K - 4)) : load4<false>(p, k, K); };
-  auto fetch = [&](int k0) {
+  auto fetch = [&](auto set_c, int k0) {
+    constexpr int F = decltype(set_c)::value;
     const int k = k0 + 4 * sc;
-    if constexpr (EPI == 1) { rg = load(gamma, k); rb = load(beta, k); }
+    if constexpr (EPI == 1) { rg[F] = load(gamma, k); rb[F] = load(beta, k); }
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
       const int r = sr + 32 * i;
-      const int64_t m = row0[T == 1 ? 0 : r >> 6] + (r & 63);
-      ra[i] = load(A + m * K, k);
-      if constexpr (EPI == 1) ru[i] = load(U + m * K, k);
-      rw[i] = load(W + (int64_t)min(n0 + r, Ncols - 1) * K, k);     // (columns past the matrix are computed and not stored)
+      const int64_t m = row0[TB == 1 ? 0 : r >> 6] + (r & 63);
+      ra[F][i] = load(A + m * K, k);
+      if constexpr (EPI == 1) ru[F][i] = load(U + m * K, k);
+    }
+    if constexpr (!PACKED) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int c = min(block_of(cb0 + i) * 32 + sr, d - 1);      // (columns past the matrix are computed and not stored)
+        rw[F][i] = load((const float *)Wv + ((int64_t)plane_of(cb0 + i) * d + c) * K, k);
+      }
     }
   };
-  auto store = [&](int st, int k0) {
+  Split3 pa[LPT], pw[PACKED ? 1 : 2];
+  auto split = [&](auto set_c, int k0) {
+    constexpr int F = decltype(set_c)::value;
     const bool inside = !VEC || k0 + 4 * sc < K;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
-      const int r = sr + 32 * i, off = r * BK + ((sc ^ ((r >> 1) & 7)) << 2);
-      f32x4 v = ra[i];
+      f32x4 v = ra[F][i];
       if constexpr (EPI == 1) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = ((v[t] - mu[i]) * rstd[i] * rg[t] + rb[t]) * ru[i][t];
+        for (int t = 0; t < 4; ++t) v[t] = ((v[t] - mu[i]) * rstd[i] * rg[F][t] + rb[F][t]) * ru[F][i][t];
       }
-      *(f32x4 *)(sA[st] + off) = inside && (EPI == 0 || r < n_valid) ? v : zero;
-      *(f32x4 *)(sW[st] + off) = inside ? rw[i] : zero;
+      pa[i] = split3(inside && (EPI == 0 || sr + 32 * i < n_valid) ? v : zero);
+    }
+    if constexpr (!PACKED) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) pw[i] = split3(inside ? rw[F][i] : zero);
     }
   };
-  f32x16 acc[T][T];
+  // byte offset of 16-byte chunk c (0..3) of tile row r inside a part of A
+  auto off = [](int r, int c) { return (r >> 2) * 256 + ((((r & 3) << 2) | (c ^ ((r >> 2) & 3))) << 4); };
+  auto store = [&](int ast, int wst) {
 #pragma unroll
-  for (int i = 0; i < T; ++i)
+    for (int i = 0; i < LPT; ++i)
 #pragma unroll
-    for (int j = 0; j < T; ++j)
+      for (int p = 0; p < 3; ++p) *(bf16x4 *)(lds + ast * ASTAGE + p * APART + off(sr + 32 * i, sc >> 1) + (sc & 1) * 8) = pa[i].p[p];
+    if constexpr (!PACKED) {                            // into the fragments' places: k 4 sc .. + 3 of column 32 i + sr
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          *(bf16x4 *)(ldsw + wst * WSTAGE + (i * 6 + (sc >> 2) * 3 + p) * 1024 + (((sc >> 1) & 1) * 32 + sr) * 16 + (sc & 1) * 8) = pw[i].p[p];
+    }
+  };
+  // W of a chunk: six fragments (two of 16 k, three parts) per 32-column block, 6 KB in one piece; fragment q of the tile belongs to wavefront q % 4
+  typedef __attribute__((address_space(1))) const void gvoid;
+  typedef __attribute__((address_space(3))) void lvoid;
+  auto request_w = [&](int kc, int st) {
+    if constexpr (PACKED) {
+#pragma unroll
+      for (int i = 0; i < 6 * (BN / 32) / 4; ++i) {
+        const int q = wave + 4 * i, b = cb0 + q / 6;
+        const char *src = (const char *)Wv + (((int64_t)plane_of(b) * pb + block_of(b)) * (dp / 16) + 2 * kc) * 3072 + (q % 6) * 1024;
+        __builtin_amdgcn_global_load_lds((gvoid *)(src + lane * 16), (lvoid *)(ldsw + st * WSTAGE + q * 1024), 16, 0, 0);
+      }
+    }
+  };
+  // W of the chunk requested last has landed: behind it only the rows of one chunk were fetched
+  auto wait_w = [&]() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(VEC && PACKED ? (EPI == 1 ? 2 * LPT + 2 : LPT) : 0) : "memory"); };
+  f32x16 acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  // the residual's 16 values of this lane, requested ahead of the k loop (read one by one between its stores they would cost 16
-  // memory latencies in a row)
-  float xr[16];
+  typedef std::integral_constant<int, 0> EVEN;
+  typedef std::integral_constant<int, 1> ODD;
+  const int nk = dp / BK;
+  request_w(0, 0);
+  fetch(EVEN{}, 0);
+  if (nk > 1) fetch(ODD{}, BK);
+  // the residual's values of this lane, requested ahead of the k loop (read one by one between its stores they would cost a
+  // memory latency each)
+  float xr[EPI == 1 ? MB : 1][EPI == 1 ? NB : 1][16];
   if constexpr (EPI == 1) {
-    const float *x = out + (row0[0] + wm * 32 + 4 * lhalf) * d + min(n0 + wn * 32 + l32, Ncols - 1);
 #pragma unroll
-    for (int e = 0; e < 16; ++e) xr[e] = x[(int64_t)(8 * (e >> 2) + (e & 3)) * d];
-  }
-  fetch(0);
-  store(0, 0);
-  __syncthreads();
-  const int nk = (K + BK - 1) / BK;
-  for (int kc = 0; kc < nk; ++kc) {
-    const int st = kc & 1;
-    if (kc + 1 < nk) fetch((kc + 1) * BK);
-    __builtin_amdgcn_sched_barrier(0);     // the requests stay ahead of the matrix work
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      f32x4 fa[T], fw[T];
+      for (int j = 0; j < NB; ++j) {
+        const float *x = out + (row0[0] + (wm * MB + i) * 32 + 4 * lhalf) * d + min((cb0 + wn * NB + j) * 32 + l32, d - 1);
 #pragma unroll
-      for (int i = 0; i < T; ++i) {
-        const int r = wm * 32 * T + 32 * i + l32, q = wn * 32 * T + 32 * i + l32;
-        fa[i] = *(const f32x4 *)(sA[st] + r * BK + (((2 * s + lhalf) ^ ((r >> 1) & 7)) << 2));
-        fw[i] = *(const f32x4 *)(sW[st] + q * BK + (((2 * s + lhalf) ^ ((q >> 1) & 7)) << 2));
+        for (int e = 0; e < 16; ++e) xr[i][j][e] = x[(int64_t)(8 * (e >> 2) + (e & 3)) * d];
       }
+  }
+  split(EVEN{}, 0);
+  store(0, 0);
+  wait_w();                                              // W of chunk 0 has landed
+  __syncthreads();
+  // The rows come from far away (past the L2s, several thousand cycles under load): they are fetched two chunks ahead, W (from an L2) one.
+  auto chunk = [&](auto parity_c, const int kc) {
+    constexpr int PAR = decltype(parity_c)::value, ast = AST == 2 ? PAR : 0, wst = PAR;
+    std::integral_constant<int, PAR ^ 1> other;
+    if (kc + 1 < nk) request_w(kc + 1, wst ^ 1);           // everybody left that stage at the barrier that opened this chunk
+    if (kc + 2 < nk) fetch(parity_c, (kc + 2) * BK);
+    __builtin_amdgcn_sched_barrier(0);                     // the requests stay ahead of the matrix work
+    auto multiply = [&](int s) {
+      bf16x8 fa[MB][3], fw[NB][3];
 #pragma unroll
-      for (int i = 0; i < T; ++i)
+      for (int p = 0; p < 3; ++p) {
 #pragma unroll
-        for (int j = 0; j < T; ++j) mfma_f32_k8(fa[i], fw[j], acc[i][j]);
+        for (int i = 0; i < MB; ++i) fa[i][p] = *(const bf16x8 *)(lds + ast * ASTAGE + p * APART + off((wm * MB + i) * 32 + l32, 2 * s + lhalf));
+#pragma unroll
+        for (int j = 0; j < NB; ++j) fw[j][p] = *(const bf16x8 *)(ldsw + wst * WSTAGE + ((wn * NB + j) * 6 + s * 3 + p) * 1024 + lane * 16);
+      }
+      constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PW[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+      for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][PA[q]], fw[j][PW[q]], acc[i][j], 0, 0, 0);
+    };
+    multiply(0);
+    __builtin_amdgcn_sched_barrier(0);
+    // the next chunk is split under the second half of the matrix work
+    multiply(1);
+    split(other, (kc + 1) * BK);                                // (behind the last chunk: of what was fetched for it, and not stored)
+    __builtin_amdgcn_sched_group_barrier(0x100, 3 * (MB + NB), 0);
+#pragma unroll
+    for (int i = 0; i < 6 * MB * NB; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, EPI == 1 ? 8 : 5, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
-    if (kc + 1 < nk) store(st ^ 1, (kc + 1) * BK);       // the other stage: everybody left it at the barrier that opened this chunk
+    if (AST == 1) __syncthreads();                         // everybody has left the stage of A
+    if (kc + 1 < nk) store(AST == 2 ? ast ^ 1 : 0, wst ^ 1);
+    if (kc + 2 < nk) wait_w();
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // W of the next chunk has landed
     __syncthreads();
+  };
+  for (int kc = 0; kc < nk; kc += 2) {
+    chunk(EVEN{}, kc);
+    if (kc + 1 < nk) chunk(ODD{}, kc + 1);
   }
   // a lane holds one output column and 16 rows: 32 lanes write 128 contiguous bytes of a row
 #pragma unroll
-  for (int j = 0; j < T; ++j) {
-    const int n = n0 + wn * 32 * T + 32 * j + l32;
-    if (n >= Ncols) continue;
-    const float bn = bias[n];
-    float *col = EPI == 0 ? out + (int64_t)(n / d) * plane_stride + n % d : out + n;
+  for (int j = 0; j < NB; ++j) {
+    const int b = cb0 + wn * NB + j, plane = plane_of(b), n = block_of(b) * 32 + l32;
+    if (b >= nb_all || n >= d) continue;
+    const float bn = bias[(int64_t)plane * d + n];
+    float *col = out + plane * plane_stride + n;           // (EPI 1: one matrix, its plane is X)
 #pragma unroll
-    for (int i = 0; i < T; ++i) {
-      const int rb = wm * 32 * T + 32 * i, blk = T == 1 ? 0 : rb >> 6;
+    for (int i = 0; i < MB; ++i) {
+      const int r32 = (wm * MB + i) * 32, blk = TB == 1 ? 0 : r32 >> 6;
       if (!present[blk]) continue;
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const int64_t m = row0[blk] + (rb & 63) + 8 * (e >> 2) + 4 * lhalf + (e & 3);
+        const int64_t m = row0[blk] + (r32 & 63) + 8 * (e >> 2) + 4 * lhalf + (e & 3);
         const float v = acc[i][j][e] + bn;
-        if (EPI == 0) col[m * d] = silu_f32(v);
-        else col[m * d] = xr[e] + v;
+        if constexpr (EPI == 0) col[m * d] = silu_newton(v);
+        else col[m * d] = xr[i][j][e] + v;
       }
     }
   }
@@ -249,34 +409,53 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
 // 16-byte loads of the operands: rows of the workspaces start on 16 bytes when d does; weights where the caller put them
 static bool vec4_rows(int d, const void *p) { return d % 4 == 0 && (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-void launch_uvqk_f32(const float *X, const float *W1, const float *b1, float *planes, int blk_first, int n_blk,
-                     const Shape &sh, hipStream_t s) {
+// W, W2: the matrices of the layer, as they are or (packed) as split_w_kernel laid them out
+void launch_uvqk_f32(const float *X, const void *W1, bool packed, const float *b1, float *planes, const int32_t *blk_list, int n_blk, int blk_first, int plane_mask,
+                     const int32_t *uq_list, int n_uq, const Shape &sh, hipStream_t s) {
   if (n_blk <= 0) return;
-  const int N = 4 * sh.d;
-  const bool vec = vec4_rows(sh.d, W1);
-#define UVQK_CASE(TT, VV) gemm_f32_kernel<0, TT, VV, 0><<<dim3((n_blk + TT - 1) / TT, (N + 64 * TT - 1) / (64 * TT)), 256, 0, s>>>( \
-      X, nullptr, nullptr, nullptr, nullptr, 0.f, W1, b1, planes, nullptr, blk_first, n_blk, sh.d, N, sh.d, sh.ws_rows * sh.d)
-  // 128 x 128 tiles halve the operand traffic; a launch needs enough of them for two per compute unit
-  const bool big = (int64_t)((n_blk + 1) / 2) * ((N + 127) / 128) >= 512;
-  if (vec) { if (big) UVQK_CASE(2, true); else UVQK_CASE(1, true); }
-  else UVQK_CASE(1, false);
+  // all planes, or every other one: U and Q, V and K
+  const bool all = plane_mask == 0xF;
+  const int np = all ? 4 : 2, plane0 = plane_mask == 0xA ? 1 : 0, step = all ? 1 : 2, nb = np * ((sh.d + 31) / 32);
+#define UVQK_CASE(WM, WN, MB, NB, PK, VV) do { const int y = (nb + WN * NB - 1) / (WN * NB); \
+    gemm_f32_kernel<0, WM, WN, MB, NB, PK, VV, 0><<<dim3((n_blk + WM * MB / 2 - 1) / (WM * MB / 2), n_uq > 0 ? 2 * y : y), 256, 0, s>>>( \
+      X, nullptr, nullptr, nullptr, nullptr, 0.f, W1, b1, planes, blk_list, blk_first, n_blk, sh.d, np, plane0, step, sh.ws_rows * sh.d, y, uq_list, n_uq); } while (0)
+  const bool vec = sh.d % 4 == 0;
+  if (packed) {
+    // 128 x 128 tiles halve the operand traffic; a launch needs enough of them for two per compute unit
+    const bool big = (int64_t)((n_blk + 1) / 2) * ((nb + 3) / 4) >= 512;
+    if (vec) { if (big) UVQK_CASE(2, 2, 2, 2, true, true); else UVQK_CASE(2, 2, 1, 1, true, true); }
+    else UVQK_CASE(2, 2, 1, 1, true, false);
+  } else {
+    if (vec && vec4_rows(sh.d, W1)) UVQK_CASE(2, 2, 1, 1, false, true);
+    else UVQK_CASE(2, 2, 1, 1, false, false);
+  }
 #undef UVQK_CASE
 }
 
-void launch_outproj_f32(const float *O, const float *U, const float *gamma, const float *beta, const float *W2, const float *b2, float *X,
+void launch_outproj_f32(const float *O, const float *U, const float *gamma, const float *beta, const void *W2, bool packed, const float *b2, float *X,
                         const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first, const Shape &sh, hipStream_t s) {
   if (n_blk <= 0) return;
-  const dim3 grid(n_blk, (sh.d + 63) / 64);
-#define OUT_CASE(VV, NI) gemm_f32_kernel<1, 1, VV, NI><<<grid, 256, 0, s>>>(O, U, gamma, beta, blocks, sh.eps, W2, b2, X, blk_list, blk_first, n_blk, sh.d, sh.d, sh.d, 0)
-  if (vec4_rows(sh.d, W2) && vec4_rows(sh.d, gamma) && vec4_rows(sh.d, beta)) {
-    if (sh.d <= 64) OUT_CASE(true, 1);
-    else if (sh.d <= 128) OUT_CASE(true, 2);
-    else if (sh.d <= 256) OUT_CASE(true, 4);
-    else if (sh.d <= 512) OUT_CASE(true, 8);
-    else OUT_CASE(true, 0);
+  const int nb = (sh.d + 31) / 32;
+#define OUT_CASE(WM, WN, MB, NB, PK, VV, NI) gemm_f32_kernel<1, WM, WN, MB, NB, PK, VV, NI><<<dim3(n_blk, (nb + WN * NB - 1) / (WN * NB)), 256, 0, s>>>( \
+      O, U, gamma, beta, blocks, sh.eps, W2, b2, X, blk_list, blk_first, n_blk, sh.d, 1, 0, 1, 0, 1 << 30, nullptr, 0)
+#define OUT_WIDTHS(PK) do { \
+    if (sh.d <= 64) OUT_CASE(2, 2, 1, 1, PK, true, 1); \
+    else if (sh.d <= 128) OUT_CASE(2, 2, 1, 1, PK, true, 2); \
+    else if (sh.d <= 256) OUT_CASE(2, 2, 1, 1, PK, true, 4); \
+    else if (sh.d <= 512) OUT_CASE(2, 2, 1, 1, PK, true, 8); \
+    else OUT_CASE(2, 2, 1, 1, PK, true, 0); } while (0)
+  const bool vec = vec4_rows(sh.d, gamma) && vec4_rows(sh.d, beta);
+  if (packed) {
+    if (!vec) OUT_CASE(2, 2, 1, 1, true, false, 0);
+    else if (sh.d > 64 && sh.d <= 256 && n_blk >= 128) {
+      if (sh.d <= 128) OUT_CASE(1, 4, 2, 1, true, true, 2);
+      else OUT_CASE(1, 4, 2, 1, true, true, 4);
+    } else OUT_WIDTHS(true);
   } else {
-    OUT_CASE(false, 0);
+    if (vec && vec4_rows(sh.d, W2)) OUT_WIDTHS(false);
+    else OUT_CASE(2, 2, 1, 1, false, false, 0);
   }
+#undef OUT_WIDTHS
 #undef OUT_CASE
 }
 
@@ -399,7 +578,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
       // (all weights first, then the mask: written as one conditional expression, the compiler branches around every single weight and
       // runs sixteen dependent chains one after another: a short launch, 32 x 128 candidates on 512 keys, 33.8 -> 31.0 us)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) p[e] = silu_f32(alpha * sacc[e] + bz[e]);
+      for (int e = 0; e < 16; ++e) p[e] = silu_newton(alpha * sacc[e] + bz[e]);
       if (k0 + 32 > vis_min) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) p[e] = k0 + 8 * (e >> 2) + 4 * lhalf + (e & 3) < n_vis ? p[e] : 0.f;
@@ -528,7 +707,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
         s_mine *= sc;
         s_other *= sc;
       } else {
-        p = silu_f32(logit);
+        p = silu_newton(logit);
       }
     }
     float inv = 1.f;

@@ -79,3 +79,56 @@ def test_f32_more_items_than_one_grid_dimension_holds():
     assert np.isfinite(whole).all()
     idx = [0, 32_767, 32_768, 65_535, 65_536, n - 1]
     assert np.array_equal(scores(wl.subset(idx)), whole[idx])
+
+
+@pytest.mark.parametrize("d,H", [(64, 2), (96, 2), (100, 2), (90, 2), (256, 4)])
+def test_f32_products_do_not_depend_on_the_tile(d, H):
+    """The projection and output products split their operands into three bf16 parts, exactly, and add up in one order: large and small tiles, the packed weights
+    and those that the kernels split themselves (the static workspace, where there is no room for the packed copy) give the same bits."""
+    import ctypes
+    import torch
+    from paper_2509_22681_amd import binding as B
+    need, size = ctypes.c_int64(), 64 << 20
+    split = 5 * 2 * ((d + 31) // 32 * 32) ** 2 * 6
+    L, M = [], []
+    cfg = B.config_for(W.make_custom([1], [1], d=d, H=H, n_layers=2, n_buckets=16, max_rel_dist=1024, dtype="f32", seed=7, name="tiles"))
+    while True:                                    # as many rows as leave no room for the packed weights
+        rows = sum(-(-a // 64) + -(-b // 64) for a, b in zip(L, M)) * 64
+        assert B._lib.flame_gr_static_scratch_bytes(ctypes.byref(cfg), ctypes.c_int64(rows + 128), ctypes.byref(need)) == 0
+        if need.value > size:
+            break
+        L.append([64, 23][len(L) % 2])
+        M.append([17, 64][len(M) % 2])
+    assert B._lib.flame_gr_static_scratch_bytes(ctypes.byref(cfg), ctypes.c_int64(rows), ctypes.byref(need)) == 0
+    assert need.value <= size < need.value + split
+    wl = W.make_custom(L, M, d=d, H=H, n_layers=2, n_buckets=16, max_rel_dist=1024, dtype="f32", seed=7, emb_std=1.0, rab_std=1.0, bias_amp=0.1,
+                       affine_random=True, name="tiles")
+    dw, hist, cand = B.to_device(wl)
+
+    def forward(first, last):
+        ho, co = wl.history_offsets[first:last + 1], wl.cand_offsets[first:last + 1]
+        out = torch.full((int(co[-1] - co[0]),), float("nan"), device="cuda:0")
+        args = (dw, hist[ho[0]:ho[-1]].contiguous(), ho - ho[0], cand[co[0]:co[-1]].contiguous(), co - co[0], out)
+        return args, out
+
+    h = B.flame_gr_create(B.config_for(wl))
+    try:
+        args, whole = forward(0, len(L))
+        B.flame_gr_forward(h, *args)
+        parts = []
+        for r in (0, 1, len(L) - 1):
+            args, out = forward(r, r + 1)
+            B.flame_gr_forward(h, *args)
+            parts.append((r, out))
+    finally:
+        torch.cuda.synchronize()
+        B.flame_gr_destroy(h)
+    args, static = forward(0, len(L))
+    c = B.config_for(wl)
+    c.max_requests = c.max_total_tokens = 0
+    B.flame_gr_forward_static(c, *args)
+    torch.cuda.synchronize()
+    assert torch.isfinite(whole).all()
+    assert torch.equal(whole, static)
+    for r, out in parts:
+        assert torch.equal(out, whole[wl.cand_offsets[r]:wl.cand_offsets[r + 1]]), r
