@@ -22,7 +22,7 @@ namespace {
 
 constexpr uint32_t kMagic = 0x464c4752u;  // "FLGR"
 constexpr int kStageSlots = 2;
-constexpr size_t kStageOneCopyBytes = 64 << 10;   // plan tables up to this size are staged with one copy
+constexpr size_t kStageOneCopyBytes = 64 << 10;   // plan tables up to this size are fetched from pinned memory by the prologue
 constexpr int kMaxGroups = 16;
 constexpr int kMaxGraphs = FLAME_GR_MAX_GRAPHS;
 enum { KIND_ASSEMBLE = 0, KIND_BIAS, KIND_UVQK, KIND_ATTN, KIND_LNGATE, KIND_OUTPROJ, KIND_SCORE, KIND_COUNT };
@@ -184,8 +184,7 @@ struct Timed {
 // layer.  PASS_HISTORY / PASS_CANDIDATES: the history rows (resp. candidate rows) only, every layer
 // on its own set of planes, so that the candidate pass finds K and V of the history rows of layer l
 // where the history pass left them.
-void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, const void *hist, const void *cand,
-               float *scores, hipStream_t s, PassMode mode, float *hidden = nullptr) {
+void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, float *scores, hipStream_t s, PassMode mode, float *hidden = nullptr) {
   const Shape &sh = h->sh;
   const int dt = h->cfg.dtype;
   const int d = sh.d;
@@ -206,7 +205,6 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, const voi
   const int pass_n = mode == PASS_FULL ? n_blk : mode == PASS_HISTORY ? n_hblk : n_cblk;
   const int pass_first = mode == PASS_FULL ? G.blk_begin : 0;
   if (pass_n == 0) return;
-  { Timed t(h, KIND_ASSEMBLE, s); launch_assemble(dt, blocks, pass_list, pass_n, pass_first, hist, cand, h->X, h->Xb, d, s); }
   const int64_t plane = sh.ws_rows * d;
   for (int l = 0; l < sh.n_layers; ++l) {
     const bool capture = mode == PASS_FULL && h->capture_layer == l;
@@ -294,33 +292,44 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, const voi
   }
 }
 
-// What the kernels read in place of the caller's weights: fp16 copies of the projection matrices in
-// the operand layouts of the GEMMs (MFMA path), and the bias table indexed by distance.
 bool same_weight_pointers(const flame_gr_weights &a, const flame_gr_weights &b) {
   return a.w1 == b.w1 && a.w2 == b.w2 && a.rab == b.rab && a.temperature == b.temperature;   // what the copies are made from
 }
 
-void derive_weights(flame_gr *h, const flame_gr_weights *w, hipStream_t s) {
+// The prologue's part of what the kernels read in place of the caller's weights: copies of the projection matrices in
+// the operand layouts of the products, and the bias table indexed by distance.  (The caller owns the weights and may have changed
+// them: made on every pass, unless they are declared static.)
+void add_derived(flame_gr *h, const flame_gr_weights *w, Prologue &p) {
   if (h->cfg.weights_static && h->derived_valid && same_weight_pointers(h->derived_from, *w)) return;
   h->derived_from = *w;
   h->derived_valid = true;
-  if (h->cfg.dtype == FLAME_GR_BF16) {
-    const int dm = h->sh.d;
-    launch_pack_w(w->w1, h->W1h, (int64_t)h->sh.n_layers * 4 * dm, dm, true, s);
-    if (k3_fused_supported(dm)) launch_pack_w2(w->w2, h->W2p, dm, h->sh.n_layers, s);
-    else launch_pack_w(w->w2, h->W2h, (int64_t)h->sh.n_layers * dm, dm, false, s);
-  } else if (h->Ws) {
-    launch_split_w((const float *)w->w1, (const float *)w->w2, h->Ws, h->sh.d, h->sh.n_layers, s);
-  }
-  launch_expand_bias(w->rab, h->bucket_tab, h->bias, h->sh.n_layers * h->sh.H, h->sh.n_buckets, h->sh.D,
-                     h->cfg.dtype == FLAME_GR_BF16 ? 0.5f : 1.0f, s);
+  const bool bf = h->cfg.dtype == FLAME_GR_BF16;
+  p.w1 = w->w1; p.w2 = w->w2; p.rab = w->rab; p.temperature = w->temperature;
+  p.W1h = h->W1h; p.Ws = h->Ws;
+  if (k3_fused_supported(h->sh.d)) p.W2p = h->W2p;
+  else p.W2h = h->W2h;
+  p.bucket_tab = h->bucket_tab; p.bias = h->bias;
+  p.n_layers = h->sh.n_layers; p.H = h->sh.H; p.n_buckets = h->sh.n_buckets; p.D = h->sh.D;
+  p.bias_scale = bf ? 0.5f : 1.0f;
   // softmax: exponent = logit / tau.  The MFMA kernel holds halved logits and uses the base-2 exponential.
-  if (h->sh.softmax)
-    launch_logit_scale(w->temperature, h->tscale, h->sh.n_layers * h->sh.H,
-                       h->cfg.dtype == FLAME_GR_BF16 ? 2.0f * 1.4426950408889634f : 1.0f, s);
+  p.tscale = h->sh.softmax ? h->tscale : nullptr;
+  p.logit_factor = bf ? 2.0f * 1.4426950408889634f : 1.0f;
 }
 
-// Stage h->plan through pinned memory, refresh the derived weights and run `mode` on every stream group.
+// The prologue's assembly of the rows of a pass; block tables at `tables`.
+void add_rows(flame_gr *h, PassMode mode, const char *tables, const void *hist, const void *cand, Prologue &p) {
+  p.dtype = h->cfg.dtype; p.d = h->sh.d;
+  p.blocks = (const RowBlock *)(tables + h->lay.blocks);
+  p.hist = hist; p.cand = cand; p.X = h->X; p.Xh = h->Xb;
+  if (mode == PASS_FULL) {
+    p.n_blk = (int)h->plan.blocks.size();
+  } else {
+    p.list = (const int32_t *)(tables + (mode == PASS_HISTORY ? h->lay.hist_blocks : h->lay.cand_blocks));
+    p.n_blk = (int)(mode == PASS_HISTORY ? h->plan.hist_blocks : h->plan.cand_blocks).size();
+  }
+}
+
+// Stage h->plan through pinned memory, run the prologue and then `mode` on every stream group.
 int enqueue_pass(flame_gr *h, const flame_gr_weights *w, const void *history_emb, const void *cand_emb, float *scores,
                  hipStream_t s0, PassMode mode, float *hidden = nullptr) {
   const Plan &P = h->plan;
@@ -332,7 +341,7 @@ int enqueue_pass(flame_gr *h, const flame_gr_weights *w, const void *history_emb
   // a pass on another stream must not overtake the previous one on this handle
   if (h->has_prev) HIP_TRY(h, hipStreamWaitEvent(s0, h->ev_done, 0));
   // The tables are copied separately, only as far as they are filled and only those the pass reads; on a handle whose
-  // tables are small altogether (one or a few requests) they leave as one copy instead, what lies between them included:
+  // tables are small altogether the prologue fetches them from the pinned buffer instead, what lies between them included:
   // every copy is a few microseconds in front of the first kernel.
   const bool one_copy = h->lay.total <= kStageOneCopyBytes;
   size_t staged_end = 0;
@@ -352,22 +361,28 @@ int enqueue_pass(flame_gr *h, const flame_gr_weights *w, const void *history_emb
     HIP_TRY(h, stage(h->lay.hist_items, P.hist_items.data(), P.hist_items.size() * sizeof(AttnItem)));
     HIP_TRY(h, stage(h->lay.hist_blocks, P.hist_blocks.data(), P.hist_blocks.size() * sizeof(int32_t)));
   }
-  if (one_copy && staged_end > 0) HIP_TRY(h, hipMemcpyAsync(h->stage_dev, sh_, staged_end, hipMemcpyHostToDevice, s0));
+  {
+    Timed t(h, KIND_ASSEMBLE, s0);
+    Prologue p;
+    if (one_copy) {
+      p.tables_src = sh_;
+      p.tables_dst = h->stage_dev;
+      p.n_table_words = (int)((staged_end + 15) / 16 * 4);
+    }
+    add_rows(h, mode, one_copy ? sh_ : h->stage_dev, history_emb, cand_emb, p);
+    add_derived(h, w, p);
+    launch_prologue(p, s0);
+  }
   HIP_TRY(h, hipEventRecord(h->stage_done[slot], s0));
   h->stage_used[slot] = true;
-  {
-    // the caller owns the weights and may have changed them: derive on every pass (unless declared static)
-    Timed t(h, KIND_BIAS, s0);
-    derive_weights(h, w, s0);
-  }
   if (h->n_groups == 1) {
-    run_group(h, *w, P.groups[0], history_emb, cand_emb, scores, s0, mode, hidden);
+    run_group(h, *w, P.groups[0], scores, s0, mode, hidden);
   } else {
     HIP_TRY(h, hipEventRecord(h->ev_fork, s0));
     for (int g = 0; g < h->n_groups; ++g) {
       if (P.groups[g].blk_end == P.groups[g].blk_begin) continue;
       HIP_TRY(h, hipStreamWaitEvent(h->gstream[g], h->ev_fork, 0));
-      run_group(h, *w, P.groups[g], history_emb, cand_emb, scores, h->gstream[g], mode, hidden);
+      run_group(h, *w, P.groups[g], scores, h->gstream[g], mode, hidden);
       HIP_TRY(h, hipEventRecord(h->ev_join[g], h->gstream[g]));
       HIP_TRY(h, hipStreamWaitEvent(s0, h->ev_join[g], 0));
     }
@@ -388,7 +403,7 @@ StageLayout stage_layout(size_t nblk) {
   lay.cand_blocks = lay.cand_items + nblk * sizeof(AttnItem);
   lay.hist_items = lay.cand_blocks + nblk * sizeof(int32_t);
   lay.hist_blocks = lay.hist_items + nblk * sizeof(AttnItem);
-  lay.total = lay.hist_blocks + nblk * sizeof(int32_t);
+  lay.total = (lay.hist_blocks + nblk * sizeof(int32_t) + 15) / 16 * 16;   // (the prologue moves 16 bytes at a time)
   return lay;
 }
 
@@ -486,7 +501,7 @@ int flame_gr_create(const flame_gr_config *cfg_in, flame_gr_t **out) {
   h->lay = stage_layout(rows / kRowAlign);
   CR(hipMalloc(&h->stage_dev, h->lay.total));
   for (int i = 0; i < kStageSlots; ++i) {
-    CR(hipHostMalloc((void **)&h->stage_host[i], h->lay.total, hipHostMallocDefault));
+    CR(hipHostMalloc((void **)&h->stage_host[i], h->lay.total, hipHostMallocCoherent));   // (kernels read it)
     CR(hipEventCreateWithFlags(&h->stage_done[i], hipEventDisableTiming));
   }
   CR(hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming));
@@ -606,7 +621,12 @@ int flame_gr_capture(flame_gr_t *h, int32_t slot, const flame_gr_weights *w, con
   HIP_TRY(h, upload(h->lay.items, P.items.data(), P.items.size() * sizeof(AttnItem)));
   HIP_TRY(h, upload(h->lay.cand_items, P.cand_items.data(), P.cand_items.size() * sizeof(AttnItem)));
   HIP_TRY(h, upload(h->lay.cand_blocks, P.cand_blocks.data(), P.cand_blocks.size() * sizeof(int32_t)));
-  derive_weights(h, w, cs);
+  {
+    Prologue p;
+    p.dtype = h->cfg.dtype; p.d = h->sh.d;
+    add_derived(h, w, p);
+    launch_prologue(p, cs);
+  }
   HIP_TRY(h, hipStreamSynchronize(cs));
   // the layer sequence, recorded instead of run (kernel launches only: no copies, no memsets), reading this slot's tables
   const bool prof = h->profiling;
@@ -616,7 +636,10 @@ int flame_gr_capture(flame_gr_t *h, int32_t slot, const flame_gr_weights *w, con
   hipGraph_t graph = nullptr;
   hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
   if (e == hipSuccess) {
-    run_group(h, *w, P.groups[0], history_emb, cand_emb, scores, cs, PASS_FULL);
+    Prologue p;
+    add_rows(h, PASS_FULL, h->stage_dev, history_emb, cand_emb, p);
+    launch_prologue(p, cs);
+    run_group(h, *w, P.groups[0], scores, cs, PASS_FULL);
     e = hipStreamEndCapture(cs, &graph);
   }
   h->stage_dev = eager_tables;
@@ -864,12 +887,17 @@ int flame_gr_forward_static(const flame_gr_config *cfg_in, const flame_gr_weight
   launch_upload_words(P.cand_items.data(), P.cand_items.size() * sizeof(AttnItem), h.stage_dev + h.lay.cand_items, s);
   launch_upload_words(P.cand_blocks.data(), P.cand_blocks.size() * sizeof(int32_t), h.stage_dev + h.lay.cand_blocks, s);
   launch_bucket_table(cfg.n_buckets, cfg.max_rel_dist, h.bucket_tab, s);
-  derive_weights(&h, w, s);
+  {
+    Prologue p;
+    add_rows(&h, PASS_FULL, h.stage_dev, history_emb, cand_emb, p);
+    add_derived(&h, w, p);
+    launch_prologue(p, s);
+  }
   // The array keeps the last call's contents, laid out for another batch: every row of this batch's blocks is
   // rewritten by the kernels below, and the rows behind them, which whole-tile key loads may read, are cleared.
   if (bf) launch_clear_spare((char *)h.planes + 3 * h.plane_bytes, (char *)h.planes + h.plane_bytes, cfg.d_model, h.ws_rows,
                              P.total_rows, (int)(h.ws_rows - P.total_rows), s);
-  run_group(&h, *w, P.groups[0], history_emb, cand_emb, scores, s, PASS_FULL);
+  run_group(&h, *w, P.groups[0], scores, s, PASS_FULL);
   const hipError_t le = hipGetLastError();
   h.magic = 0;
   if (le != hipSuccess) { g_create_error = std::string("kernel launch: ") + hipGetErrorString(le); return FLAME_GR_HIP_ERROR; }

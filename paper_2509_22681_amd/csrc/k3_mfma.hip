@@ -16,7 +16,7 @@
 //     conflict free (the LDS serves 16 lanes x 16 bytes per clock from 64 banks);
 //   * phase 2: each wavefront owns d/4 output features; the W2 operand comes straight from L2 in a
 //     fragment-major packed layout (one coalesced 1 KB read per MFMA operand, prepared once per forward
-//     by pack_w2_kernel), so LDS holds only the activations and two workgroups fit on a CU;
+//     by the prologue), so LDS holds only the activations and two workgroups fit on a CU;
 //   * phase 3: residual add in fp32 (X = Xh + Xl, exact in fp32) and split into the two fp16 words again, after a
 //     transposition of the accumulators through LDS so that the residual is read and written in whole lines.
 #include "device_common.h"
@@ -25,23 +25,6 @@
 namespace flame {
 
 namespace {
-
-// W2p[ks][cb][lane][0..7] = W2[32*cb + lane%32][16*ks + 8*(lane/32) + 0..7]  (bf16 -> fp16)
-__global__ __launch_bounds__(256) void pack_w2_kernel(const bf16_t *__restrict__ W2, half_t *__restrict__ W2p, int d, int n_layers) {
-  const int64_t per_layer = (int64_t)d * d / 8;            // 16-byte chunks
-  const int64_t total = per_layer * n_layers;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    const int64_t l = i / per_layer, c = i % per_layer;
-    const int lane = (int)(c & 63);
-    const int64_t t = c >> 6;
-    const int cb = (int)(t % (d / 32)), ks = (int)(t / (d / 32));
-    const bf16x8 v = *(const bf16x8 *)(W2 + l * d * d + (int64_t)(32 * cb + (lane & 31)) * d + 16 * ks + 8 * (lane >> 5));
-    f16x8 o;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) o[k] = to_f16_sat((float)v[k]);
-    *(f16x8 *)(W2p + (l * per_layer + c) * 8) = o;
-  }
-}
 
 // NWV wavefronts per workgroup, NBW 32-feature blocks per wavefront: d = 32 * NBW * NWV (four wavefronts for
 // d = 128, 256, 512; three for d = 96, 192, 384).  A workgroup takes RH 32-row halves of a 64-row block; its rows are dealt out
@@ -320,12 +303,6 @@ __global__ __launch_bounds__(64 * NWV, k3_dense(CS, RH, NBW) ? 3 : 2) void k3_fu
 static size_t k3_lds_bytes(int d, int cs, int rh) { const size_t g = (size_t)32 * rh * d * 2, patch = (size_t)32 * (d / cs) * 4; return g > patch ? g : patch; }
 
 bool k3_fused_supported(int d) { return d == 128 || d == 192 || d == 256 || d == 384 || d == 512; }
-
-void launch_pack_w2(const void *W2, void *W2p, int d, int n_layers, hipStream_t s) {
-  const int64_t total = (int64_t)d * d / 8 * n_layers;
-  int grid = (int)((total + 255) / 256 > 2048 ? 2048 : (total + 255) / 256);
-  pack_w2_kernel<<<grid, 256, 0, s>>>((const bf16_t *)W2, (half_t *)W2p, d, n_layers);
-}
 
 // Few row blocks: half blocks, with the features cut as long as that leaves one workgroup per compute unit at most (lone workgroups,
 // latency), then half blocks with uncut features.  Microseconds per launch, whole blocks / half blocks / half blocks with features cut

@@ -17,19 +17,33 @@ struct Shape {
 };
 
 // ---- shared small kernels (misc.hip) --------------------------------------------------------
-// rows of blocks <- embeddings: fp32 X in the fp32 path, the k-tile blocked fp16 word Xh in the MFMA path (whose residual is
-// the pair Xh = fp16(X), Xl = fp16(X - Xh); embeddings are exact in Xh and Xl is not written); padding rows zeroed.
-// The n blocks are list[0..n) if list is given, else first..first+n.
-void launch_assemble(int dtype, const RowBlock *blocks, const int32_t *list, int n, int first, const void *hist,
-                     const void *cand, float *X, void *Xh, int d, hipStream_t s);
-// fp16 copy of a bf16 matrix of `rows` rows of K elements (rows % 32 == 0, K % 64 == 0), packed fragment by fragment
-// (device_common.h); planes: the rows are U | V | Q | K of K rows each, layer after layer (V's rows play operand
-// B in the projection, all others A)
-void launch_pack_w(const void *in, void *out, int64_t rows, int K, bool planes, hipStream_t s);
-// bias[lh][delta] = scale * rab[lh][bucket_tab[delta]] for all layers and heads (scale = 1/2 in the
-// MFMA path, whose attention kernel works on halved logits; 1 in the fp32 path).
-void launch_expand_bias(const float *rab, const int32_t *bucket_tab, float *bias, int n_lh,
-                        int n_buckets, int D, float scale, hipStream_t s);
+// Prologue of a pass (one launch; misc.hip): any of its parts may be absent.
+struct Prologue {
+  // plan tables, host (pinned) -> device; n_table_words % 4 == 0, both on 16 bytes
+  const void *tables_src = nullptr;
+  void *tables_dst = nullptr;
+  int n_table_words = 0;
+  // rows of blocks <- embeddings: fp32 X in the fp32 path, the k-tile blocked fp16 word Xh in the MFMA path (whose residual is
+  // the pair Xh = fp16(X), Xl = fp16(X - Xh); embeddings are exact in Xh and Xl is not written); padding rows zeroed.
+  // The n_blk blocks are list[0..n_blk) if list is given, else first..first+n_blk (blocks and list: pinned host or device memory).
+  int dtype = 0, d = 0, n_blk = 0, first = 0;
+  const RowBlock *blocks = nullptr;
+  const int32_t *list = nullptr;
+  const void *hist = nullptr, *cand = nullptr;
+  float *X = nullptr;
+  void *Xh = nullptr;
+  // what is derived from the weights (w1 == nullptr: nothing): the projection matrices packed by fragments as fp16 (W1h, and W2p for the fused K3, else W2h), or
+  // (fp32 path, if Ws) split into bf16 parts; bias[lh][distance] = bias_scale * rab[lh][bucket_tab[distance]] for all layers and heads (scale = 1/2 in the MFMA path, whose
+  // attention kernel works on halved logits; 1 in the fp32 path); tscale[i] = logit_factor / temperature[i] (softmax)
+  const void *w1 = nullptr, *w2 = nullptr;
+  void *W1h = nullptr, *W2h = nullptr, *W2p = nullptr, *Ws = nullptr;
+  const float *rab = nullptr, *temperature = nullptr;
+  const int32_t *bucket_tab = nullptr;
+  float *bias = nullptr, *tscale = nullptr;
+  int n_layers = 0, H = 0, n_buckets = 0, D = 0;
+  float bias_scale = 1.f, logit_factor = 1.f;
+};
+void launch_prologue(const Prologue &p, hipStream_t s);
 // G = (LayerNorm(O) * gamma + beta) * U, one row at a time (MFMA path, for widths whose output projection is not fused with it);
 // padding rows of a block get G = 0 so that they stay finite through the layers.
 void launch_ln_gate(const void *O, const void *U, const void *gamma, const void *beta,
@@ -38,8 +52,6 @@ void launch_ln_gate(const void *O, const void *U, const void *gamma, const void 
 // scores[src_row + i] = <X[row], w_s> + b_s for the valid rows of every candidate block (MFMA path: X = Xh + Xl).
 void launch_scores(int dtype, const float *X, const void *Xh, const void *Xl, const void *w_s, float b_s, const RowBlock *blocks,
                    const int32_t *cand_blocks, int n_cblk, float *scores, int d, hipStream_t s);
-// out[i] = factor / temperature[i] (the per-layer, per-head logit scale of the softmax attention).
-void launch_logit_scale(const float *temperature, float *out, int n, float factor, hipStream_t s);
 // hidden[(src_row + i) * d ..] = X[row] for the valid rows of every candidate block (fp32).
 // (Xh given: the residual is the pair Xh, Xl of the MFMA path; else fp32 X)
 void launch_gather_hidden(const float *X, const void *Xh, const void *Xl, const RowBlock *blocks, const int32_t *cand_blocks, int n_cblk,
@@ -65,7 +77,6 @@ void launch_debug_mask(int L, int M, const int32_t *bucket_tab, int D, uint8_t *
 // The projection matrices of all layers split into bf16 parts for the two products below (kernels_f32.hip), packed by fragments: matrix m of the copy, W1's planes layer after layer
 // and then W2's, starts at m * split_w_bytes(d, 1) / 5.  The products take the packed matrix of the layer (packed), or the matrix itself.
 int64_t split_w_bytes(int d, int n_layers);
-void launch_split_w(const float *W1, const float *W2, void *out, int d, int n_layers, hipStream_t s);
 // planes[p][row][n] = silu(X W1^T + b1), p = U,V,Q,K; rows = the listed 64-row blocks (blk_list == nullptr: [blk_first, blk_first+n_blk));
 // plane_mask: all planes (0xF), U and Q (0x5) or V and K (0xA); uq_list (n_uq blocks, with V and K): their U and Q with it
 void launch_uvqk_f32(const float *X, const void *W1, bool packed, const float *b1, float *planes, const int32_t *blk_list, int n_blk, int blk_first,
@@ -102,9 +113,8 @@ void launch_outproj_bf16(const void *G, const void *W2h, const void *b2, void *X
                          const int32_t *blk_list, int n_blk, int blk_first, const Shape &sh, hipStream_t s);
 
 // K3 fused (k3_mfma.hip): LayerNorm * U gate + output projection + residual in one kernel, for
-// d in {128, 192, 256, 384, 512}; W2p is the fragment-major packed fp16 copy of W2 written by launch_pack_w2.
+// d in {128, 192, 256, 384, 512}; W2p is the fragment-major packed fp16 copy of W2 written by the prologue.
 bool k3_fused_supported(int d);
-void launch_pack_w2(const void *W2, void *W2p, int d, int n_layers, hipStream_t s);
 // (residual pair Xh, Xl as above; lo_is_zero: Xl is not read)
 void launch_k3_fused(const void *O, const void *U, const void *gamma, const void *beta, const void *W2p_layer, const void *b2,
                      void *Xh, void *Xl, bool lo_is_zero, const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first,

@@ -34,26 +34,6 @@ __device__ __forceinline__ f32x4 load4(const float *p, int k, int K) {
   return v;
 }
 
-// An fp32 value as the sum of three bf16 values, exactly: each takes the next eight bits (round to nearest, the remainder is exact in fp32), and 8 + 8 + 8
-// bits with signs hold the 24 of the mantissa.
-struct Split3 { bf16x4 p[3]; };
-__device__ __forceinline__ Split3 split3(f32x4 v) {
-  typedef float f32x2 __attribute__((ext_vector_type(2)));
-  Split3 s;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    f32x2 x = {v[2 * h], v[2 * h + 1]};
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const bf16x2 b = __builtin_convertvector(x, bf16x2);       // two values per instruction
-      s.p[i][2 * h] = b[0];
-      s.p[i][2 * h + 1] = b[1];
-      if (i < 2) { x[0] -= (float)b[0]; x[1] -= (float)b[1]; }
-    }
-  }
-  return s;
-}
-
 // silu(x) = x / (1 + exp(-x)) with the reciprocal by the hardware's estimate and one Newton step (within an ulp of the quotient, a third of its
 // instructions).  The exponent is capped where 1 + exp(-x) would leave the range: the result there is below 1e-34 either way.
 __device__ __forceinline__ float silu_newton(float x) {
@@ -74,45 +54,11 @@ __device__ __forceinline__ float row16_sum(float v) {
 }  // namespace
 
 // ---------------------------------------------------------------------------------------------
-// The projection matrices as bf16 parts, fragment by fragment: [matrix][row / 32][k / 16][part][lane][8], 1 KB per fragment; lane l holds k 8 (l / 32) + 0..7
-// of row l & 31.  Matrices of d x d, rows and k padded with zeros to multiples of 32: the 4 n_layers planes of W1, then the n_layers matrices of W2.
-// One thread makes 16 bytes of each of the three parts.
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void split_w_kernel(const float *__restrict__ W1, const float *__restrict__ W2, char *__restrict__ out, int n1, int n, int d) {
-  const int dp = (d + 31) / 32 * 32, kf = dp / 16;
-  const int64_t per = (int64_t)dp * dp / 8, total = per * n;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    const int lane = (int)(i & 63), mat = (int)(i / per);
-    const int f = (int)(i % per >> 6), rb = f / kf, ks = f % kf;
-    const int row = rb * 32 + (lane & 31), k = ks * 16 + 8 * (lane >> 5);
-    const float *src = (mat < n1 ? W1 + (int64_t)mat * d * d : W2 + (int64_t)(mat - n1) * d * d) + (int64_t)row * d;
-    f32x4 v[2];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) v[t >> 2][t & 3] = row < d && k + t < d ? src[k + t] : 0.f;
-    const Split3 s0 = split3(v[0]), s1 = split3(v[1]);
-    char *dst = out + (((int64_t)mat * per >> 6) + f) * 3072 + lane * 16;
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      *(bf16x4 *)(dst + p * 1024) = s0.p[p];
-      *(bf16x4 *)(dst + p * 1024 + 8) = s1.p[p];
-    }
-  }
-}
-
-int64_t split_w_bytes(int d, int n_layers) { const int64_t dp = (d + 31) / 32 * 32; return 5 * n_layers * dp * dp * 6; }
-
-void launch_split_w(const float *W1, const float *W2, void *out, int d, int n_layers, hipStream_t s) {
-  const int64_t total = split_w_bytes(d, n_layers) / 48;
-  const int grid = (int)((total + 255) / 256 > 2048 ? 2048 : (total + 255) / 256);
-  split_w_kernel<<<grid, 256, 0, s>>>(W1, W2, (char *)out, 4 * n_layers, 5 * n_layers, d);
-}
-
-// ---------------------------------------------------------------------------------------------
 // C[m][n] = sum_k A[m][k] W[n][k] + bias[n] on 64-row blocks.  256 threads = WM x WN wavefronts of MB x NB blocks of 32 x 32 outputs; k in chunks of 32.
 // Both operands are split into three bf16 values, and six of the nine products run on the bf16 matrix instruction (32 x 32 x 16, fp32
 // accumulators), the small ones first; left out are the three of 2^-26 of the largest and less.  6 x 32 cycles for 16 k against 8 x 64 on the fp32 instruction, and the sums
 // are rounded less often (a product of bf16 values is exact, and 16 k go into an accumulator at a time instead of 2).
-// PACKED: W arrives split (split_w_kernel), by LDS-DMA, a chunk ahead through two stages; else (64 x 64 tiles only: callers without room for the packed copy) it is split here, like A,
+// PACKED: W arrives split and packed by fragments (split_w in misc.hip), by LDS-DMA, a chunk ahead through two stages; else (64 x 64 tiles only: callers without room for the packed copy) it is split here, like A,
 // on the way from registers to LDS.  The split is exact, so the two agree bit for bit.
 // LDS rows of A are 64 bytes per part, 16-byte chunks XOR-swizzled over groups of four rows (key: row bits 2..3), which the fragment reads take
 // without bank conflicts.  Tiles of 64 rows have two stages for A, tiles of 128 one (two workgroups on a compute unit, one's staging under
@@ -409,7 +355,7 @@ __global__ __launch_bounds__(256, MB * NB == 4 ? 2 : 1) void gemm_f32_kernel(con
 // 16-byte loads of the operands: rows of the workspaces start on 16 bytes when d does; weights where the caller put them
 static bool vec4_rows(int d, const void *p) { return d % 4 == 0 && (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// W, W2: the matrices of the layer, as they are or (packed) as split_w_kernel laid them out
+// W, W2: the matrices of the layer, as they are or (packed) split and packed by fragments
 void launch_uvqk_f32(const float *X, const void *W1, bool packed, const float *b1, float *planes, const int32_t *blk_list, int n_blk, int blk_first, int plane_mask,
                      const int32_t *uq_list, int n_uq, const Shape &sh, hipStream_t s) {
   if (n_blk <= 0) return;

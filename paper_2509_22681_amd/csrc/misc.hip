@@ -1,30 +1,37 @@
 // Small bandwidth-bound kernels of the GR forward: input assembly, bias-table expansion,
 // LayerNorm * U gating, score head, and the debug evaluation of the mask predicate.
+#include <algorithm>
+
 #include "device_common.h"
 #include "kernels.h"
 
 namespace flame {
 
 // ---------------------------------------------------------------------------------------------
+// Prologue of a pass: what its kernels read that is neither an embedding nor a weight as the caller holds it.  Independent pieces, in one launch, since each alone is a
+// few microseconds of launch for next to no work:
+//   * plan tables of a small plan, from pinned host memory to the device (larger ones are copied ahead of the launch);
+//   * assembly of the token rows;
+//   * the projection matrices in the operand layouts of the products;
+//   * the bias table by distance, and the logit scales of softmax attention.
+// A workgroup does one of them, by its index.
+// Before, each was a launch or a copy of its own: 32 x (512 + 128), d = 256, bf16 252 -> 231 us per forward, in fp32 671 -> 656; one request of 64 + 16 in fp32 52 -> 46 us.
+// ---------------------------------------------------------------------------------------------
+
 // Assembly: the token matrix of a request is its history rows followed by its candidate rows
-// (Section 2.1: candidates are appended after the behaviour sequence).  One workgroup per 64-row
-// block of the padded workspace; rows past n_valid are zero so that they stay finite downstream.
+// (Section 2.1: candidates are appended after the behaviour sequence).  A workgroup takes a quarter of a 64-row
+// block of the padded workspace, so that a small batch spreads over many compute units; rows past n_valid are zero so that they stay finite downstream.
 // fp32 path: X is row-major fp32.  MFMA path: the residual is held as two fp16 words, Xh = fp16(X) (k-tile blocked, the
 // projection's operand) and Xl = fp16(X - Xh); embeddings are exact in Xh, so assembly writes Xh only and the first layer
 // treats Xl as zero.
-// ---------------------------------------------------------------------------------------------
-// VEC: 16 bytes per lane (d % 4 == 0, embeddings on 16-byte boundaries).  Each 64-row block is cut into gridDim.y row slices.
-template <bool VEC>
-__global__ __launch_bounds__(256) void assemble_f32_kernel(const RowBlock *__restrict__ blocks, const int32_t *__restrict__ list, int blk_begin,
-                                                           const float *__restrict__ hist, const float *__restrict__ cand,
-                                                           float *__restrict__ X, int d) {
-  const int b = list ? list[blockIdx.x] : blk_begin + blockIdx.x;
-  const RowBlock rb = blocks[b];
-  const int rows = kRowAlign / gridDim.y, r0 = blockIdx.y * rows;
+constexpr int kSlices = 4;
+__device__ __forceinline__ void assemble_f32(const RowBlock rb, int b, int slice, const float *hist, const float *cand, float *X, int d, bool vec) {
+  constexpr int rows = kRowAlign / kSlices;
+  const int r0 = slice * rows;
   const float *src = (rb.kind ? cand : hist) + ((int64_t)rb.src_row + r0) * d;
   float *dst = X + ((int64_t)b * kRowAlign + r0) * d;
   const int n = rows * d, nv = (rb.n_valid - r0) * d;      // nv <= 0: a slice of padding rows
-  if constexpr (VEC) {
+  if (vec) {                                               // 16 bytes per lane
 #pragma unroll 4
     for (int i = threadIdx.x * 4; i < n; i += 1024) {
       f32x4 v = {0.f, 0.f, 0.f, 0.f};
@@ -36,16 +43,11 @@ __global__ __launch_bounds__(256) void assemble_f32_kernel(const RowBlock *__res
   }
 }
 
-// bf16 inputs: 16 bytes per lane, each 64-row block cut into gridDim.y row slices so that a small batch
-// still spreads over many compute units and no lane walks a long chain of dependent loads.
-__global__ __launch_bounds__(256) void assemble_bf16_kernel(const RowBlock *__restrict__ blocks, const int32_t *__restrict__ list,
-                                                            int blk_begin, const bf16_t *__restrict__ hist,
-                                                            const bf16_t *__restrict__ cand, half_t *__restrict__ Xh, int d) {
-  const int b = list ? list[blockIdx.x] : blk_begin + blockIdx.x;
-  const RowBlock rb = blocks[b];
+__device__ __forceinline__ void assemble_bf16(const RowBlock rb, int b, int slice, const bf16_t *hist, const bf16_t *cand, half_t *Xh, int d) {
   const bf16_t *src = rb.kind ? cand : hist;
   const int cpr = d / 8;                                   // 16-byte chunks per row
-  const int rows = kRowAlign / gridDim.y, r0 = blockIdx.y * rows;
+  constexpr int rows = kRowAlign / kSlices;
+  const int r0 = slice * rows;
   const int64_t row_base = (int64_t)b * kRowAlign;
 #pragma unroll 4
   for (int i = threadIdx.x; i < rows * cpr; i += 256) {
@@ -61,41 +63,109 @@ __global__ __launch_bounds__(256) void assemble_bf16_kernel(const RowBlock *__re
   }
 }
 
-void launch_assemble(int dtype, const RowBlock *blocks, const int32_t *list, int n, int first, const void *hist,
-                     const void *cand, float *X, void *Xh, int d, hipStream_t s) {
-  if (n <= 0) return;
-  if (dtype == FLAME_GR_BF16)
-    assemble_bf16_kernel<<<dim3(n, 4), 256, 0, s>>>(blocks, list, first, (const bf16_t *)hist, (const bf16_t *)cand, (half_t *)Xh, d);
-  else if (d % 4 == 0 && ((reinterpret_cast<uintptr_t>(hist) | reinterpret_cast<uintptr_t>(cand)) & 15u) == 0)
-    assemble_f32_kernel<true><<<dim3(n, 4), 256, 0, s>>>(blocks, list, first, (const float *)hist, (const float *)cand, X, d);
-  else
-    assemble_f32_kernel<false><<<dim3(n, 4), 256, 0, s>>>(blocks, list, first, (const float *)hist, (const float *)cand, X, d);
+// bf16 -> fp16 copies of the projection matrices.  The MFMA path works on fp16 operands: with eight
+// to sixteen layers the 2^-9 rounding of bf16 intermediates alone puts about 1e-2 rms (5e-2 worst
+// case) on the scores, fp16's 2^-12 keeps them ten times closer; weights of magnitude >= 2^-14 are
+// represented exactly either way.
+__device__ __forceinline__ f16x8 to_f16x8(const bf16x8 v) {
+  f16x8 o;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) o[k] = to_f16_sat((float)v[k]);
+  return o;
 }
 
-// ---------------------------------------------------------------------------------------------
-// bias[lh][delta] = rab[lh][bucket(delta)]: the attention kernels index the bias by distance.
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void expand_bias_kernel(const float *__restrict__ rab, const int32_t *__restrict__ tab,
-                                                          float *__restrict__ bias, int nb, int D, float scale) {
-  const int lh = blockIdx.y;
-  for (int t = blockIdx.x * 256 + threadIdx.x; t < D; t += gridDim.x * 256)
-    bias[(int64_t)lh * D + t] = rab[(int64_t)lh * nb + tab[t]] * scale;
+// Chunk i (16 bytes) of a matrix packed fragment by fragment (device_common.h): whole lines are written; the reads, two 16-byte pieces of 32 rows per
+// fragment, come back from L1 for the fragments of the next k.  planes: the rows are U | V | Q | K of K rows each, layer after layer (V's rows play operand
+// B in the projection, all others A).
+__device__ __forceinline__ void pack_w(const bf16_t *in, half_t *out, int64_t i, int K, bool planes) {
+  const int lane = (int)(i & 63);
+  const int64_t f = i >> 6, nb = f / (K / 16);          // fragment, 32-row block
+  const int ks = (int)(f % (K / 16));
+  const bool plays_a = !(planes && (nb * 32 / K) % 4 == 1);
+  const int64_t row = nb * 32 + (plays_a ? sigma32(lane & 31) : lane & 31);
+  *(f16x8 *)(out + i * 8) = to_f16x8(*(const bf16x8 *)(in + row * K + ks * 16 + 8 * (lane >> 5)));
 }
 
-void launch_expand_bias(const float *rab, const int32_t *bucket_tab, float *bias, int n_lh, int n_buckets,
-                        int D, float scale, hipStream_t s) {
-  dim3 grid((D + 255) / 256 > 64 ? 64 : (D + 255) / 256, n_lh);
-  expand_bias_kernel<<<grid, 256, 0, s>>>(rab, bucket_tab, bias, n_buckets, D, scale);
+// Chunk i of the fused K3's copy: W2p[layer][ks][cb][lane][0..7] = W2[32*cb + lane%32][16*ks + 8*(lane/32) + 0..7]
+__device__ __forceinline__ void pack_w2(const bf16_t *W2, half_t *W2p, int64_t i, int d) {
+  const int64_t per_layer = (int64_t)d * d / 8, l = i / per_layer, c = i % per_layer, t = c >> 6;
+  const int lane = (int)(c & 63), cb = (int)(t % (d / 32)), ks = (int)(t / (d / 32));
+  *(f16x8 *)(W2p + i * 8) = to_f16x8(*(const bf16x8 *)(W2 + l * d * d + (int64_t)(32 * cb + (lane & 31)) * d + 16 * ks + 8 * (lane >> 5)));
 }
 
-__global__ __launch_bounds__(256) void logit_scale_kernel(const float *__restrict__ temperature, float *__restrict__ out, int n,
-                                                          float factor) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) out[i] = factor / temperature[i];
+// fp32 path: the projection matrices as bf16 parts, fragment by fragment, [matrix][row / 32][k / 16][part][lane][8], 1 KB per fragment; lane l holds k 8 (l / 32) + 0..7
+// of row l & 31.  Matrices of d x d, rows and k padded with zeros to multiples of 32: the n1 planes of W1, then W2's matrices.  Item i: 16 bytes of each of the three parts.
+__device__ __forceinline__ void split_w(const float *W1, const float *W2, char *out, int64_t i, int n1, int d) {
+  const int dp = (d + 31) / 32 * 32, kf = dp / 16;
+  const int64_t per = (int64_t)dp * dp / 8;
+  const int lane = (int)(i & 63), mat = (int)(i / per);
+  const int f = (int)(i % per >> 6), rb = f / kf, ks = f % kf;
+  const int row = rb * 32 + (lane & 31), k = ks * 16 + 8 * (lane >> 5);
+  const float *src = (mat < n1 ? W1 + (int64_t)mat * d * d : W2 + (int64_t)(mat - n1) * d * d) + (int64_t)row * d;
+  f32x4 v[2];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) v[t >> 2][t & 3] = row < d && k + t < d ? src[k + t] : 0.f;
+  const Split3 s0 = split3(v[0]), s1 = split3(v[1]);
+  char *dst = out + (((int64_t)mat * per >> 6) + f) * 3072 + lane * 16;
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    *(bf16x4 *)(dst + p * 1024) = s0.p[p];
+    *(bf16x4 *)(dst + p * 1024 + 8) = s1.p[p];
+  }
 }
 
-void launch_logit_scale(const float *temperature, float *out, int n, float factor, hipStream_t s) {
-  if (n > 0) logit_scale_kernel<<<(n + 255) / 256, 256, 0, s>>>(temperature, out, n, factor);
+int64_t split_w_bytes(int d, int n_layers) { const int64_t dp = (d + 31) / 32 * 32; return 5 * n_layers * dp * dp * 6; }
+
+__global__ __launch_bounds__(256) void prologue_kernel(const Prologue p, int wg_tables, int wg_rows, int wg_w, int64_t n_w1, int64_t n_w, bool vec) {
+  int wg = blockIdx.x;
+  if (wg < wg_tables) {
+    const int i = wg * 256 + threadIdx.x;
+    if (i < p.n_table_words / 4) ((uint4 *)p.tables_dst)[i] = ((const uint4 *)p.tables_src)[i];
+    return;
+  }
+  wg -= wg_tables;
+  if (wg < wg_rows) {
+    const int t = wg / kSlices, slice = wg % kSlices;
+    const int b = p.list ? p.list[t] : p.first + t;
+    const RowBlock rb = p.blocks[b];
+    if (p.dtype == FLAME_GR_BF16) assemble_bf16(rb, b, slice, (const bf16_t *)p.hist, (const bf16_t *)p.cand, (half_t *)p.Xh, p.d);
+    else assemble_f32(rb, b, slice, (const float *)p.hist, (const float *)p.cand, p.X, p.d, vec);
+    return;
+  }
+  wg -= wg_rows;
+  if (wg < wg_w) {
+    for (int64_t i = (int64_t)wg * 256 + threadIdx.x; i < n_w; i += (int64_t)wg_w * 256) {
+      if (p.dtype != FLAME_GR_BF16) split_w((const float *)p.w1, (const float *)p.w2, (char *)p.Ws, i, 4 * p.n_layers, p.d);
+      else if (i < n_w1) pack_w((const bf16_t *)p.w1, (half_t *)p.W1h, i, p.d, true);
+      else if (p.W2p) pack_w2((const bf16_t *)p.w2, (half_t *)p.W2p, i - n_w1, p.d);
+      else pack_w((const bf16_t *)p.w2, (half_t *)p.W2h, i - n_w1, p.d, false);
+    }
+    return;
+  }
+  wg -= wg_w;
+  // bias[lh][distance] = rab[lh][bucket(distance)]: the attention kernels index the bias by distance (D is a power of two)
+  const int step = ((int)gridDim.x - wg_tables - wg_rows - wg_w) * 256, n_lh = p.n_layers * p.H, shift = 31 - __builtin_clz(p.D);
+  for (int64_t i = wg * 256 + threadIdx.x; i < (int64_t)n_lh * p.D; i += step)
+    p.bias[i] = p.rab[(i >> shift) * p.n_buckets + p.bucket_tab[i & (p.D - 1)]] * p.bias_scale;
+  if (p.tscale)
+    for (int i = wg * 256 + threadIdx.x; i < n_lh; i += step) p.tscale[i] = p.logit_factor / p.temperature[i];
+}
+
+void launch_prologue(const Prologue &p, hipStream_t s) {
+  auto workgroups = [](int64_t items, int64_t most) { return (int)std::min((items + 255) / 256, most); };
+  const int wg_tables = p.tables_src ? workgroups(p.n_table_words / 4, 1 << 20) : 0, wg_rows = p.n_blk * kSlices;
+  int64_t n_w1 = 0, n_w = 0;
+  int wg_bias = 0;
+  if (p.w1) {
+    const int64_t dd8 = (int64_t)p.d * p.d / 8;                       // (MFMA path: d % 64 == 0)
+    if (p.dtype == FLAME_GR_BF16) { n_w1 = 4 * p.n_layers * dd8; n_w = 5 * p.n_layers * dd8; }
+    else if (p.Ws) n_w = split_w_bytes(p.d, p.n_layers) / 48;
+    wg_bias = std::max(1, workgroups((int64_t)p.n_layers * p.H * p.D, 2048));
+  }
+  const int wg_w = workgroups(n_w, 2048), grid = wg_tables + wg_rows + wg_w + wg_bias;
+  if (grid == 0) return;
+  const bool vec = p.d % 4 == 0 && ((reinterpret_cast<uintptr_t>(p.hist) | reinterpret_cast<uintptr_t>(p.cand)) & 15u) == 0;
+  prologue_kernel<<<grid, 256, 0, s>>>(p, wg_tables, wg_rows, wg_w, n_w1, n_w, vec);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -153,36 +223,6 @@ void launch_residual_to_f32(const void *Xh, const void *Xl, float *out, int64_t 
   if (n <= 0) return;
   const int grid = (int)((n + 255) / 256 > 4096 ? 4096 : (n + 255) / 256);
   residual_to_f32_kernel<<<grid, 256, 0, s>>>((const half_t *)Xh, (const half_t *)Xl, out, row_begin * d, n, d);
-}
-
-// ---------------------------------------------------------------------------------------------
-// bf16 -> fp16 copy of the projection matrices.  The MFMA path works on fp16 operands: with eight
-// to sixteen layers the 2^-9 rounding of bf16 intermediates alone puts about 1e-2 rms (5e-2 worst
-// case) on the scores, fp16's 2^-12 keeps them ten times closer; weights of magnitude >= 2^-14 are
-// represented exactly either way.
-// ---------------------------------------------------------------------------------------------
-// One thread per 16 bytes of the packed matrix, in its order: whole lines are written; the reads, two 16-byte pieces of 32 rows per
-// fragment, come back from L1 for the fragments of the next k.
-__global__ __launch_bounds__(256) void pack_w_kernel(const bf16_t *__restrict__ in, half_t *__restrict__ out, int64_t n8, int K, int d, bool planes) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += (int64_t)gridDim.x * 256) {
-    const int lane = (int)(i & 63);
-    const int64_t f = i >> 6, nb = f / (K / 16);          // fragment, 32-row block
-    const int ks = (int)(f % (K / 16));
-    const bool plays_a = !(planes && (nb * 32 / d) % 4 == 1);
-    const int64_t row = nb * 32 + (plays_a ? sigma32(lane & 31) : lane & 31);
-    const bf16x8 v = *(const bf16x8 *)(in + row * K + ks * 16 + 8 * (lane >> 5));
-    f16x8 o;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) o[k] = to_f16_sat((float)v[k]);
-    *(f16x8 *)(out + i * 8) = o;
-  }
-}
-
-void launch_pack_w(const void *in, void *out, int64_t rows, int K, bool planes, hipStream_t s) {
-  const int64_t n8 = rows * K / 8;   // K % 64 == 0 in the MFMA path
-  if (n8 <= 0) return;
-  int grid = (int)((n8 + 255) / 256 > 2048 ? 2048 : (n8 + 255) / 256);
-  pack_w_kernel<<<grid, 256, 0, s>>>((const bf16_t *)in, (half_t *)out, n8, K, K, planes);
 }
 
 // ---------------------------------------------------------------------------------------------
