@@ -206,17 +206,24 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, float *sc
   const int pass_first = mode == PASS_FULL ? G.blk_begin : 0;
   if (pass_n == 0) return;
   const int64_t plane = sh.ws_rows * d;
-  for (int l = 0; l < sh.n_layers; ++l) {
-    const bool capture = mode == PASS_FULL && h->capture_layer == l;
-    const bool last = (l == sh.n_layers - 1) && !capture;
-    // one-pass: the four planes of the handle, reused by every layer; two-stage: U and Q there, V and K in the
-    // layer's own pair of planes, where the candidate pass finds the history rows that the history pass left
-    char *planes = (char *)h->planes;
-    PlanePtrs pp{planes, planes + h->plane_bytes, planes + 2 * h->plane_bytes, planes + 3 * h->plane_bytes};
+  // K3 of a layer and K1 of the next as one kernel (not where a layer's planes are to be looked at)
+  const bool fused = dt == FLAME_GR_BF16 && h->capture_layer < 0 && layer_fused(d, pass_n);
+  // one-pass: the four planes of the handle, reused by every layer; two-stage: U and Q there, V and K in the
+  // layer's own pair of planes, where the candidate pass finds the history rows that the history pass left
+  auto planes_of = [&](int l) {
+    char *p = (char *)h->planes;
+    PlanePtrs pp{p, p + h->plane_bytes, p + 2 * h->plane_bytes, p + 3 * h->plane_bytes};
     if (mode != PASS_FULL) {
       pp.v = h->kv + (size_t)l * 2 * h->plane_bytes;
       pp.k = h->kv + ((size_t)l * 2 + 1) * h->plane_bytes;
     }
+    return pp;
+  };
+  for (int l = 0; l < sh.n_layers; ++l) {
+    const bool capture = mode == PASS_FULL && h->capture_layer == l;
+    const bool last = (l == sh.n_layers - 1) && !capture;
+    char *planes = (char *)h->planes;
+    const PlanePtrs pp = planes_of(l);
     const size_t split_mat = (size_t)split_w_bytes(d, 1) / 5;
     const char *w1 = h->Ws ? (const char *)h->Ws + (size_t)l * 4 * split_mat : (const char *)(dt == FLAME_GR_BF16 ? h->W1h : w.w1) + (size_t)l * 4 * d * d * e;
     const char *b1 = (const char *)w.b1 + (size_t)l * 4 * d * e;
@@ -229,7 +236,7 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, float *sc
     // In the last layer only candidate rows feed the scores, and history rows never look at
     // candidates: history rows need K and V only, attention and the output projection run on
     // candidate rows only.
-    {
+    if (l == 0 || !fused) {
       Timed t(h, KIND_UVQK, s);
       // last layer of a one-pass forward: V and K of all rows, U and Q of the candidates
       const bool pruned = mode == PASS_FULL && last;
@@ -252,7 +259,12 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, float *sc
     const int32_t *bl = mode == PASS_FULL ? (last ? cl : nullptr) : pass_list;
     const int nb = mode == PASS_FULL ? (last ? n_cblk : n_blk) : pass_n;
     const int bf = mode == PASS_FULL && !last ? G.blk_begin : 0;
-    if (dt == FLAME_GR_BF16 && k3_fused_supported(d)) {
+    if (fused && l + 1 < sh.n_layers) {
+      Timed t(h, KIND_OUTPROJ, s);
+      const bool next_last = l + 2 == sh.n_layers;         // its history rows need V and K only
+      launch_layer(h->O, planes, lg, lb, (const char *)h->W2p + (size_t)l * d * d * e, b2, h->Xb, h->Xl, l == 0, blocks, bl, nb, bf,
+                   w1 + (size_t)4 * d * d * e, b1 + (size_t)4 * d * e, planes_of(l + 1), !next_last || mode == PASS_CANDIDATES, true, sh, s);
+    } else if (dt == FLAME_GR_BF16 && k3_fused_supported(d)) {
       Timed t(h, KIND_OUTPROJ, s);
       launch_k3_fused(h->O, planes, lg, lb, (const char *)h->W2p + (size_t)l * d * d * e, b2, h->Xb, h->Xl, l == 0, blocks, bl, nb, bf, sh, s);
     } else if (dt == FLAME_GR_BF16) {
@@ -462,6 +474,7 @@ int flame_gr_create(const flame_gr_config *cfg_in, flame_gr_t **out) {
   } while (0)
   CR(hipGetDevice(&h->device));
   if (h->sh.latency && cfg.dtype == FLAME_GR_BF16) CR(attn_latency_setup(h->sh));
+  if (cfg.dtype == FLAME_GR_BF16) CR(layer_setup(cfg.d_model));
   const size_t rows = (size_t)h->ws_rows, d = (size_t)cfg.d_model, e = h->elt;
   const bool mfma_path = cfg.dtype == FLAME_GR_BF16;
   if (!mfma_path) {
@@ -879,6 +892,7 @@ int flame_gr_forward_static(const flame_gr_config *cfg_in, const flame_gr_weight
   h.stage_dev = (char *)(base + c.take(h.lay.total));
   if (!bf && c.off + (size_t)split_w_bytes(cfg.d_model, cfg.n_layers) <= kStaticScratchBytes) h.Ws = base + c.off;   // where there is room behind the workspace
   if ((int64_t)c.off != need) { g_create_error = "internal: static workspace layout mismatch"; return FLAME_GR_HIP_ERROR; }
+  if (bf && layer_setup(cfg.d_model) != hipSuccess) { g_create_error = "kernel setup failed"; return FLAME_GR_HIP_ERROR; }
   if (h.sh.latency && bf && attn_latency_setup(h.sh) != hipSuccess) { g_create_error = "attention kernel setup failed"; return FLAME_GR_HIP_ERROR; }
   hipStream_t s = (hipStream_t)stream_v;
   // plan tables as kernel arguments, bucket table computed on the device: no copies, no memsets, no events
