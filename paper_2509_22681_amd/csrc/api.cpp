@@ -253,7 +253,7 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, float *sc
       int n_it = G.item_end - G.item_begin;
       if (mode == PASS_HISTORY) { it = hitems + G.hitem_begin; n_it = G.hitem_end - G.hitem_begin; }
       else if (mode == PASS_CANDIDATES || last) { it = citems + G.citem_begin; n_it = G.citem_end - G.citem_begin; }
-      if (dt == FLAME_GR_BF16) launch_attn_bf16(pp, bias_l, tscale_l, h->O, it, n_it, h->plan.q_tile, sh, s);
+      if (dt == FLAME_GR_BF16) launch_attn_bf16(pp, bias_l, tscale_l, h->O, it, n_it, h->plan.q_tile, h->plan.longest, sh, s);
       else launch_attn_f32((const float *)planes, bias_l, tscale_l, (float *)h->O, it, n_it, sh, s);
     }
     const int32_t *bl = mode == PASS_FULL ? (last ? cl : nullptr) : pass_list;
@@ -473,7 +473,7 @@ int flame_gr_create(const flame_gr_config *cfg_in, flame_gr_t **out) {
     if (e_ != hipSuccess) return fail(std::string(#expr) + ": " + hipGetErrorString(e_), FLAME_GR_HIP_ERROR); \
   } while (0)
   CR(hipGetDevice(&h->device));
-  if (h->sh.latency && cfg.dtype == FLAME_GR_BF16) CR(attn_latency_setup(h->sh));
+  if (cfg.dtype == FLAME_GR_BF16) CR(attn_setup(h->sh));
   if (cfg.dtype == FLAME_GR_BF16) CR(layer_setup(cfg.d_model));
   const size_t rows = (size_t)h->ws_rows, d = (size_t)cfg.d_model, e = h->elt;
   const bool mfma_path = cfg.dtype == FLAME_GR_BF16;
@@ -893,7 +893,7 @@ int flame_gr_forward_static(const flame_gr_config *cfg_in, const flame_gr_weight
   if (!bf && c.off + (size_t)split_w_bytes(cfg.d_model, cfg.n_layers) <= kStaticScratchBytes) h.Ws = base + c.off;   // where there is room behind the workspace
   if ((int64_t)c.off != need) { g_create_error = "internal: static workspace layout mismatch"; return FLAME_GR_HIP_ERROR; }
   if (bf && layer_setup(cfg.d_model) != hipSuccess) { g_create_error = "kernel setup failed"; return FLAME_GR_HIP_ERROR; }
-  if (h.sh.latency && bf && attn_latency_setup(h.sh) != hipSuccess) { g_create_error = "attention kernel setup failed"; return FLAME_GR_HIP_ERROR; }
+  if (bf && attn_setup(h.sh) != hipSuccess) { g_create_error = "attention kernel setup failed"; return FLAME_GR_HIP_ERROR; }
   hipStream_t s = (hipStream_t)stream_v;
   // plan tables as kernel arguments, bucket table computed on the device: no copies, no memsets, no events
   launch_upload_words(P.blocks.data(), P.blocks.size() * sizeof(RowBlock), h.stage_dev + h.lay.blocks, s);

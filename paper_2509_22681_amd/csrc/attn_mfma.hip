@@ -95,12 +95,19 @@ __device__ __forceinline__ f16x8 pack8(const float *v) {
 //   KP = 2: 128 query rows, 8 wavefronts, key tiles of 128 in four LDS stages; each of a group's two wavefronts takes one 64-key half of every
 //     tile, into one of two accumulator sets by the tile's parity.  For latency handles that are given enough rows to
 //     fill the chip all the same: half the K and V traffic per query row (the rule and both sides' times are at kLatencyWideTiles).
-template <int DH, bool SOFTMAX, int KP, bool NT>
+// SEQ: the throughput configuration in launches that leave most of the chip idle, where a wavefront alone runs through all keys of its 32 rows
+// at 1750 cycles per 64 of them (760 for the weights, 370 each for the two products, the rest bias and requests).  The key tiles of KP = 4, but the four wavefronts of a
+// group only make the weights, each of its 64 keys, and leave them in LDS (over the tile's K, which everybody has read; behind the stages with heads of 32);
+// one wavefront per feature block then adds V^T P^T up over the tile in the order of the keys.  That is the one-wavefront order, block by block of 64 keys on the same SiLU route, so the
+// bits are the same.  An item of 128 rows is two workgroups of 64.  One request of 1024 + 256, 8 heads, 16 layers: 17.5 -> 12 us per launch, forward 642 -> 556 us.
+// (Pointwise weights only: a running maximum would have to pass from wavefront to wavefront.)
+template <int DH, bool SOFTMAX, int KP, bool NT, bool SEQ = false>
 __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_kernel(PlanePtrs planes, const float *__restrict__ bias_lh,
                                                            const float *__restrict__ tscale_h,
                                                            half_t *__restrict__ O, const AttnItem *__restrict__ items,
                                                            int H, int d, int D, int64_t ws_rows) {
   constexpr bool KSPLIT = KP > 1;
+  static_assert(!SEQ || (KP == 4 && !SOFTMAX), "the key-ordered split is the KP = 4 one, pointwise");
   constexpr int NP = KP == 2 ? 2 : 1;  // partial outputs per wavefront
   constexpr int NW = KSPLIT ? 8 : 4;   // wavefronts per workgroup
   constexpr int QG = NW / KP;          // groups
@@ -122,6 +129,7 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
   constexpr int V_BYTES = DH * KT * 2;             // V^T tile [DH][KT keys]
   constexpr int W_BYTES = NW * 256;                // bias window: 64 slots per wavefront (BW <= 64 NW of them are used)
   constexpr int STAGE = K_BYTES + V_BYTES + W_BYTES;
+  constexpr bool P_OVER_K = SEQ && K_BYTES >= NW * 4096;   // where the weights of a tile go: over its K, or behind the stages
   static_assert(K_BYTES % 1024 == 0 && V_BYTES % 1024 == 0 && STAGE % 256 == 0, "stage parts start on 256-byte boundaries");
   static_assert(QT * DH * 2 <= NSTAGE * STAGE, "output patches fit in the tile buffers");
   // the stages; the output patches of the wavefronts reuse them once the key loop is over.  The latency
@@ -131,7 +139,17 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
   char *const lds = KSPLIT ? lds_dynamic : lds_static;
 
   const int head = blockIdx.x % H;
-  const AttnItem it = items[blockIdx.x / H];
+  AttnItem it = items[blockIdx.x / H >> (SEQ ? 1 : 0)];
+  if constexpr (SEQ) {                 // an item of 128 rows is two workgroups, the one with more keys first
+    const int off = (blockIdx.x / H & 1) ? 0 : QT;
+    if (off >= it.n_q) return;
+    it.q_row += off;
+    it.n_q = min(QT, it.n_q - off);
+    if (!it.is_cand) {
+      it.q_pos += off;
+      it.n_kv = it.q_pos + it.n_q;
+    }
+  }
   const int tid = threadIdx.x, lane = tid & 63;
   // wavefront index as a scalar: every branch on it is then a uniform (scalar) branch
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -158,14 +176,17 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
     n_vis = visible_history(it.is_cand, q_index, it.L);
     q_row_clamped = row;
   }
+  // SEQ: which wavefront of a group adds up which feature block (one per SIMD; -1: none)
+  const int sum_b = SEQ && k_part - 2 * q_group >= 0 && k_part - 2 * q_group < DB ? k_part - 2 * q_group : -1;
   const int wave_vis_min = it.is_cand ? it.L : it.q_pos + q_local0 + 1;
   const int wave_vis_max = it.is_cand ? it.L : it.q_pos + q_local0 + 32;
 
-  f32x16 oacc[NP][DB];
+  constexpr int ODB = SEQ ? 1 : DB;    // feature blocks that a wavefront adds up
+  f32x16 oacc[NP][ODB];
 #pragma unroll
   for (int p = 0; p < NP; ++p)
 #pragma unroll
-    for (int b = 0; b < DB; ++b)
+    for (int b = 0; b < ODB; ++b)
 #pragma unroll
       for (int e = 0; e < 16; ++e) oacc[p][b][e] = 0.f;
   // softmax state of my query row, per partial output (both lanes of a pair hold the same maximum; each holds the sum over its keys)
@@ -291,7 +312,9 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
 #pragma unroll 1
     for (int u = k_part; u < k_part + 1; ++u) {
     const int k0 = t * KT + u * KH;
-    if (wave_active && k0 < wave_vis_max) {
+    const bool seen = wave_active && k0 < wave_vis_max;
+    if (P_OVER_K && !seen) __builtin_amdgcn_s_barrier();     // (the one behind S^T)
+    if (seen) {
       const char *kb = sb + u * (KH * DH * 2);                 // K rows of this block
       const int vau = va0 ^ (u << 7);                          // V^T: chunks 8 u .. 8 u + 7 of each row
       const bool need_mask = k0 + KH > wave_vis_min;
@@ -334,7 +357,7 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
 #pragma unroll
             for (int j = 0; j < 2; ++j)
               fk[(s + 1) & 1][j] = *(const f16x8 *)(kb + j * (32 * DH * 2) + (ka0 ^ ((s + 1) << 5)));
-          } else {
+          } else if (!SEQ) {
 #pragma unroll
             for (int b = 0; b < DB; ++b) fv[0][b] = *(const f16x8 *)(sb + b * (32 * KT * 2) + vau);
           }
@@ -342,6 +365,10 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
 #pragma unroll
           for (int j = 0; j < 2; ++j)
             sacc[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fk[s & 1][j], fq[s], sacc[j], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (P_OVER_K) {
+          __builtin_amdgcn_s_barrier();                      // everybody has read K: its place takes the weights
           __builtin_amdgcn_sched_barrier(0);
         }
         // ---- P^T = silu(S^T) (the bias is already in the accumulators), or the softmax numerators
@@ -498,7 +525,12 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
             fp[2 * j + 1] = pack8(p + 8);
           }
         }
+        if constexpr (SEQ) {
+#pragma unroll
+          for (int s2 = 0; s2 < 4; ++s2) *(f16x8 *)(lds + (P_OVER_K ? ST : NSTAGE) * STAGE + (q_group * KP + u) * 4096 + s2 * 1024 + lane * 16) = fp[s2];
+        }
         // ---- O^T += V^T P^T; V^T fragments read one group ahead
+        if constexpr (!SEQ)
 #pragma unroll
         for (int s2 = 0; s2 < 4; ++s2) {
           if (s2 + 1 < 4) {
@@ -515,6 +547,38 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
       }
     }
     }
+    if constexpr (SEQ) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();                          // the weights of the tile are complete
+      __builtin_amdgcn_sched_barrier(0);
+      if (sum_b >= 0 && wave_active) {
+        // The tile's keys in order, 16 a product, the visible 64-key blocks of them: as one wavefront alone adds them up.
+        const char *pp = lds + (P_OVER_K ? ST : NSTAGE) * STAGE + q_group * (KP * 4096) + lane * 16;
+        const char *vp = sb + sum_b * (32 * KT * 2);
+        f16x8 pw[4], vw[4];
+        auto fetch = [&](int i) {
+          pw[i & 3] = *(const f16x8 *)(pp + i * 1024);
+          vw[i & 3] = *(const f16x8 *)(vp + (va0 ^ (i << 5)));
+        };
+        const int n_blk = min(KP, (wave_vis_max - t * KT + KH - 1) / KH);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) fetch(i);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < KP; ++b) {
+          if (b < n_blk) {
+#pragma unroll
+            for (int s2 = 0; s2 < 4; ++s2) {
+              const int i = 4 * b + s2;
+              if (i + 3 < 4 * KP) fetch(i + 3);
+              __builtin_amdgcn_sched_barrier(0);
+              oacc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vw[i & 3], pw[i & 3], oacc[0][0], 0, 0, 0);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
+        }
+      }
+    }
   };
   for (int t = 0; t < n_tiles; t += NSTAGE) {
     tile_step(std::integral_constant<int, 0>{}, t);
@@ -529,7 +593,7 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
 
   // ---- candidates: the row itself is one more key, at distance 0.  The wavefront multiplies its 32
   // candidate rows against themselves and keeps the diagonal.  (Latency configuration: in the last partial output.)
-  if (it.is_cand && wave_active && k_part == KP - 1) {
+  if (it.is_cand && wave_active && (SEQ ? sum_b >= 0 : k_part == KP - 1)) {
     constexpr int P = NP - 1;
     const float b0 = bias[0];
     const int64_t base_row = it.q_row + q_local0;   // multiple of 32 inside the padded workspace
@@ -576,8 +640,8 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
 #pragma unroll
     for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
-      for (int b = 0; b < DB; ++b) {
-        const f16x8 fv = *(const f16x8 *)(Vt + (int64_t)(32 * b + l32) * ws_rows + base_row + s2 * 16 + lhalf * 8);
+      for (int b = 0; b < ODB; ++b) {
+        const f16x8 fv = *(const f16x8 *)(Vt + (int64_t)(32 * (SEQ ? sum_b : b) + l32) * ws_rows + base_row + s2 * 16 + lhalf * 8);
         oacc[P][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fv, fps[s2], oacc[P][b], 0, 0, 0);
       }
   }
@@ -628,7 +692,14 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
     for (int i = 0; i < 4; ++i) o[i] = __builtin_fmaf(v[0][i], sc[0], v[1][i] * sc[1]) + __builtin_fmaf(v[2][i], sc[2], v[3][i] * sc[3]);
     return o;
   };
-  if constexpr (KP == 4) {
+  if constexpr (SEQ) {
+    if (sum_b >= 0) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) to_patch(sum_b, g, f32x4{oacc[0][0][4 * g], oacc[0][0][4 * g + 1], oacc[0][0][4 * g + 2], oacc[0][0][4 * g + 3]});
+    }
+    __syncthreads();
+    if (k_part < 32 / RPI) store_rows(k_part);
+  } else if constexpr (KP == 4) {
     // The four wavefronts of a row group leave their partial outputs (and their softmax states) in LDS behind the patches; each
     // adds up a quarter of the features, in the order (0 + 1) + (2 + 3), and stores a quarter of the rows.
     constexpr int PART = DB * 16 * 64 * 4;            // bytes of one wavefront's accumulators
@@ -740,15 +811,17 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
 
 }  // namespace
 
-// The latency configuration needs its LDS limit raised once per kernel instance (a function attribute, no
-// allocation); handles in latency mode do it when they are created, outside any stream capture.
-template <int DH, int KP>
-constexpr int key_split_lds_bytes() { return (KP == 4 ? 2 : 4) * (2 * 64 * KP * DH * 2 + 8 * 256); }   // the stages: K, V^T and the bias window each
+// The configurations that split the keys need their LDS limit raised once per kernel instance (a function attribute, no
+// allocation); handles do it when they are created, outside any stream capture.
+template <int DH, int KP, bool SEQ = false>
+constexpr int key_split_lds_bytes() {   // the stages: K, V^T and the bias window each; the weights of a tile where they do not fit over its K
+  return (KP == 4 ? 2 : 4) * (2 * 64 * KP * DH * 2 + 8 * 256) + (SEQ && 64 * KP * DH * 2 < 8 * 4096 ? 8 * 4096 : 0);
+}
 
-template <int DH, bool SM, int KP>
+template <int DH, bool SM, int KP, bool SEQ = false>
 static hipError_t key_split_setup() {
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_mfma_kernel<DH, SM, KP, false>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, key_split_lds_bytes<DH, KP>());
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_mfma_kernel<DH, SM, KP, false, SEQ>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, key_split_lds_bytes<DH, KP, SEQ>());
   return attr;
 }
 
@@ -765,13 +838,23 @@ static void launch_key_split(int grid, PlanePtrs planes, const float *bias_lh, c
   attn_mfma_kernel<DH, SM, KP, false><<<grid, 512, key_split_lds_bytes<DH, KP>(), s>>>(planes, bias_lh, tscale_h, O, items, sh.H, sh.d, sh.D, sh.ws_rows);
 }
 
-hipError_t attn_latency_setup(const Shape &sh) {
+hipError_t attn_setup(const Shape &sh) {
+  if (!sh.latency) return sh.softmax ? hipSuccess : sh.dh == 32 ? key_split_setup<32, false, 4, true>() : key_split_setup<64, false, 4, true>();
   if (sh.softmax) return sh.dh == 32 ? latency_setup<32, true>() : latency_setup<64, true>();
   return sh.dh == 32 ? latency_setup<32, false>() : latency_setup<64, false>();
 }
 
+// Workgroups of 128 rows (tiles x heads) up to which a launch takes the key-ordered split, by the longest history of the pass: its 64-row workgroups sit alone on
+// a compute unit, so they pay while the chain of key tiles is what counts.  Forwards of four layers, one wavefront per group / split (us):
+//   1024 + 256, 8 heads: 80 workgroups 152 / 132, 160: 170 / 151, 240: 186 / 181; 2 heads: 20: 125 / 105, 160: 151 / 133, 240: 158 / 152; 1024 + 1024: 128: 157 / 138, 192: 155 / 155
+//   2048 + 256, 8 heads: 144: 229 / 188, 288: 268 / 257, 432: 307 / 326; 2 heads: 36: 182 / 137, 252: 209 / 184, 396: 220 / 239; 8192 + 512, 2 heads: 136: 520 / 330
+//   512 + 128, 8 heads: 40: 119 / 109, 120: 135 / 125, 200: 161 / 163; 2 heads: 130: 119 / 115, 190: 127 / 133
+//   320 + 128, 2 heads: 24: 91 / 88, 128: 107 / 109; 128 + 64: 40: 82 / 84, 160: 98 / 119 (a history of one or two 256-key tiles has no chain to shorten)
+constexpr int kAttnSeqHistory = 384, kAttnSeqWorkgroups = 128;
+constexpr int attn_seq_workgroups(int longest) { return longest < kAttnSeqHistory ? 0 : longest < 1024 ? kAttnSeqWorkgroups : longest < 2048 ? 160 : 224; }
+
 void launch_attn_bf16(PlanePtrs planes, const float *bias_lh, const float *tscale_h, void *O, const AttnItem *items,
-                      int n_items, int q_tile, const Shape &sh, hipStream_t s) {
+                      int n_items, int q_tile, int longest, const Shape &sh, hipStream_t s) {
   if (n_items <= 0) return;
   const int grid = n_items * sh.H;
   if (sh.latency) {
@@ -786,6 +869,13 @@ void launch_attn_bf16(PlanePtrs planes, const float *bias_lh, const float *tscal
     }
 #undef SPLIT_CASE
 #undef SPLIT_LAUNCH
+    return;
+  }
+  if (!sh.softmax && grid <= attn_seq_workgroups(longest)) {
+#define SEQ_LAUNCH(DHV) attn_mfma_kernel<DHV, false, 4, false, true><<<2 * grid, 512, key_split_lds_bytes<DHV, 4, true>(), s>>>(planes, bias_lh, tscale_h, (half_t *)O, items, sh.H, sh.d, sh.D, sh.ws_rows)
+    if (sh.dh == 32) SEQ_LAUNCH(32);
+    else SEQ_LAUNCH(64);
+#undef SEQ_LAUNCH
     return;
   }
   const bool nt = (int64_t)n_items * kAttnQTileBf16 * sh.d * 2 > kStreamBytes;

@@ -152,6 +152,7 @@ int build_plan(const flame_gr_config &cfg, const int32_t *hoff, const int32_t *c
   }
 
   p.q_tile = attn_q_tile(cfg, p.segs, cand_capacity != nullptr);
+  for (const Segment &s : p.segs) p.longest = std::max(p.longest, s.L);
   const int32_t q_tile = p.q_tile;
 
   // 2. stream groups: longest-processing-time first onto the least loaded group

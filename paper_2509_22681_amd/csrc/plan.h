@@ -98,6 +98,7 @@ struct Plan {
   std::vector<int32_t> hist_blocks;    // indices of history RowBlocks, per group contiguous
   std::vector<Group> groups;
   int32_t q_tile = 0;                  // query rows per attention item
+  int32_t longest = 0;                 // longest history
   int32_t total_rows = 0;
   int64_t total_cands = 0;
   bool split = false;                  // some request was split into several segments
