@@ -250,10 +250,10 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, float *sc
     {
       Timed t(h, KIND_ATTN, s);
       const AttnItem *it = items + G.item_begin;
-      int n_it = G.item_end - G.item_begin;
-      if (mode == PASS_HISTORY) { it = hitems + G.hitem_begin; n_it = G.hitem_end - G.hitem_begin; }
-      else if (mode == PASS_CANDIDATES || last) { it = citems + G.citem_begin; n_it = G.citem_end - G.citem_begin; }
-      if (dt == FLAME_GR_BF16) launch_attn_bf16(pp, bias_l, tscale_l, h->O, it, n_it, h->plan.q_tile, h->plan.longest, sh, s);
+      int n_it = G.item_end - G.item_begin, n_cand = G.citem_end - G.citem_begin;
+      if (mode == PASS_HISTORY) { it = hitems + G.hitem_begin; n_it = G.hitem_end - G.hitem_begin; n_cand = 0; }
+      else if (mode == PASS_CANDIDATES || last) { it = citems + G.citem_begin; n_it = n_cand; }
+      if (dt == FLAME_GR_BF16) launch_attn_bf16(pp, bias_l, tscale_l, h->O, it, n_it, n_cand, h->plan.q_tile, h->plan.longest, sh, s);
       else launch_attn_f32((const float *)planes, bias_l, tscale_l, (float *)h->O, it, n_it, sh, s);
     }
     const int32_t *bl = mode == PASS_FULL ? (last ? cl : nullptr) : pass_list;

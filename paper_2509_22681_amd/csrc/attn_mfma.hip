@@ -844,17 +844,23 @@ hipError_t attn_setup(const Shape &sh) {
   return sh.dh == 32 ? latency_setup<32, false>() : latency_setup<64, false>();
 }
 
-// Workgroups of 128 rows (tiles x heads) up to which a launch takes the key-ordered split, by the longest history of the pass: its 64-row workgroups sit alone on
-// a compute unit, so they pay while the chain of key tiles is what counts.  Forwards of four layers, one wavefront per group / split (us):
+// Workgroups of 128 rows (tiles x heads) up to which a launch takes the key-ordered split, by the longest history of the pass.  Its workgroups have 64 rows and a
+// compute unit each, so up to 128 are one round of them; beyond, it pays only where most tiles are history tiles, whose chains of keys are half as long on average, and the longest
+// chain is what the other kernel takes.  Forwards of four layers, one wavefront per group / split (us):
 //   1024 + 256, 8 heads: 80 workgroups 152 / 132, 160: 170 / 151, 240: 186 / 181; 2 heads: 20: 125 / 105, 160: 151 / 133, 240: 158 / 152; 1024 + 1024: 128: 157 / 138, 192: 155 / 155
 //   2048 + 256, 8 heads: 144: 229 / 188, 288: 268 / 257, 432: 307 / 326; 2 heads: 36: 182 / 137, 252: 209 / 184, 396: 220 / 239; 8192 + 512, 2 heads: 136: 520 / 330
 //   512 + 128, 8 heads: 40: 119 / 109, 120: 135 / 125, 200: 161 / 163; 2 heads: 130: 119 / 115, 190: 127 / 133
 //   320 + 128, 2 heads: 24: 91 / 88, 128: 107 / 109; 128 + 64: 40: 82 / 84, 160: 98 / 119 (a history of one or two 256-key tiles has no chain to shorten)
+// Candidate tiles alone (one layer), 4 heads: 512 + 128: 64: 48 / 46, 128: 53 / 53, 160: 59 / 65; 2048 + 128: 64: 87 / 79, 128: 140 / 136, 160: 152 / 169.
 constexpr int kAttnSeqHistory = 384, kAttnSeqWorkgroups = 128;
-constexpr int attn_seq_workgroups(int longest) { return longest < kAttnSeqHistory ? 0 : longest < 1024 ? kAttnSeqWorkgroups : longest < 2048 ? 160 : 224; }
+static bool attn_seq(int grid, int n_items, int n_cand, int longest) {
+  if (longest < kAttnSeqHistory) return false;
+  const int limit = longest < 1024 || 2 * n_cand > n_items ? kAttnSeqWorkgroups : longest < 2048 ? 160 : 224;
+  return grid <= limit;
+}
 
 void launch_attn_bf16(PlanePtrs planes, const float *bias_lh, const float *tscale_h, void *O, const AttnItem *items,
-                      int n_items, int q_tile, int longest, const Shape &sh, hipStream_t s) {
+                      int n_items, int n_cand, int q_tile, int longest, const Shape &sh, hipStream_t s) {
   if (n_items <= 0) return;
   const int grid = n_items * sh.H;
   if (sh.latency) {
@@ -871,7 +877,7 @@ void launch_attn_bf16(PlanePtrs planes, const float *bias_lh, const float *tscal
 #undef SPLIT_LAUNCH
     return;
   }
-  if (!sh.softmax && grid <= attn_seq_workgroups(longest)) {
+  if (!sh.softmax && attn_seq(grid, n_items, n_cand, longest)) {
 #define SEQ_LAUNCH(DHV) attn_mfma_kernel<DHV, false, 4, false, true><<<2 * grid, 512, key_split_lds_bytes<DHV, 4, true>(), s>>>(planes, bias_lh, tscale_h, (half_t *)O, items, sh.H, sh.d, sh.D, sh.ws_rows)
     if (sh.dh == 32) SEQ_LAUNCH(32);
     else SEQ_LAUNCH(64);

@@ -103,9 +103,9 @@ struct PlanePtrs { void *u, *v, *q, *k; };
 void launch_uvqk_bf16(const void *Xh, const void *W1h, const void *b1, PlanePtrs planes, const int32_t *blk_list,
                       int n_blk, int blk_first, int plane_mask, const int32_t *uq_list, int n_uq, const Shape &sh, hipStream_t s);
 // tscale_h (softmax only): 2 log2(e) / tau per head (the kernel holds halved logits and uses the base-2 exponential).
-// q_tile, longest: query rows per item and the longest history of this plan.
+// n_cand: candidate tiles among the items; q_tile, longest: query rows per item and the longest history of this plan.
 void launch_attn_bf16(PlanePtrs planes, const float *bias_lh, const float *tscale_h, void *O, const AttnItem *items,
-                      int n_items, int q_tile, int longest, const Shape &sh, hipStream_t s);
+                      int n_items, int n_cand, int q_tile, int longest, const Shape &sh, hipStream_t s);
 // Prepares the configurations of the attention kernel that split the keys, for this shape (raises their LDS limit); once per handle.
 hipError_t attn_setup(const Shape &sh);
 // X[row] += G W2h^T + b2 on the residual pair (Xh, Xl); lo_is_zero: Xl is not read (first layer)
