@@ -99,7 +99,7 @@ __device__ __forceinline__ f16x8 pack8(const float *v) {
 // at 1750 cycles per 64 of them (760 for the weights, 370 each for the two products, the rest bias and requests).  The key tiles of KP = 4, but the four wavefronts of a
 // group only make the weights, each of its 64 keys, and leave them in LDS (over the tile's K, which everybody has read; behind the stages with heads of 32);
 // one wavefront per feature block then adds V^T P^T up over the tile in the order of the keys.  That is the one-wavefront order, block by block of 64 keys on the same SiLU route, so the
-// bits are the same.  An item of 128 rows is two workgroups of 64.  One request of 1024 + 256, 8 heads, 16 layers: 17.5 -> 12 us per launch, forward 642 -> 556 us.
+// bits are the same.  An item of 128 rows is two workgroups of 64.  One request of 1024 + 256, 8 heads, 16 layers: 17.5 -> 13 us per launch, forward 642 -> 556 us.
 // (Pointwise weights only: a running maximum would have to pass from wavefront to wavefront.)
 template <int DH, bool SOFTMAX, int KP, bool NT, bool SEQ = false>
 __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_kernel(PlanePtrs planes, const float *__restrict__ bias_lh,
