@@ -70,11 +70,12 @@ __device__ __forceinline__ float row16_sum(float v) {
 // requests, and two are resident on a compute unit), 45 us where only V and K are needed; the output projection, whose row statistics come first, 45 -> 42.  Error of the scores
 // against 64 bits 0.87 of what it was (24 cases of widths 64 to 256).
 // ---------------------------------------------------------------------------------------------
+// (A, U, gamma, beta and W carry no __restrict__: loads that the compiler knows to be unchanging may pass any fence, and the counted waits for W need the requests in order.)
 // NI (EPI 1): 16-byte loads per lane and row that the statistics keep in registers, ceil(K / 64) at least; 0: any K, in two reads of the rows.
 template <int EPI, int WM, int WN, int MB, int NB, bool PACKED, bool VEC, int NI>
-__global__ __launch_bounds__(256, MB * NB == 4 ? 2 : 1) void gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ U, const float *__restrict__ gamma,
-                                                       const float *__restrict__ beta, const RowBlock *__restrict__ blocks, float eps,
-                                                       const void *__restrict__ Wv, const float *__restrict__ bias, float *__restrict__ out,
+__global__ __launch_bounds__(256, MB * NB == 4 ? 2 : 1) void gemm_f32_kernel(const float *A, const float *U, const float *gamma,
+                                                       const float *beta, const RowBlock *__restrict__ blocks, float eps,
+                                                       const void *Wv, const float *__restrict__ bias, float *__restrict__ out,
                                                        const int32_t *__restrict__ blk_list, int blk_first, int n_blk, int d, int n_planes, int plane0, int plane_step,
                                                        int64_t plane_stride, int y2, const int32_t *__restrict__ blk_list2, int n_blk2) {
   static_assert(WM * WN == 4, "four wavefronts");
@@ -252,7 +253,9 @@ __global__ __launch_bounds__(256, MB * NB == 4 ? 2 : 1) void gemm_f32_kernel(con
       }
     }
   };
-  // W of the chunk requested last has landed: behind it only the rows of one chunk were fetched
+  // W of the chunk requested last has landed: behind it at least the rows of one chunk were fetched (VEC: always, past the last chunk that chunk's again,
+  // so that the count holds; else the loads are as many as the matrix has, and the wait is for all).  pin() keeps requests in the order in which they are counted.
+  auto pin = [&]() { asm volatile("" ::: "memory"); __builtin_amdgcn_sched_barrier(0); };
   auto wait_w = [&]() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(VEC && PACKED ? (EPI == 1 ? 2 * LPT + 2 : LPT) : 0) : "memory"); };
   f32x16 acc[MB][NB];
 #pragma unroll
@@ -265,8 +268,10 @@ __global__ __launch_bounds__(256, MB * NB == 4 ? 2 : 1) void gemm_f32_kernel(con
   typedef std::integral_constant<int, 1> ODD;
   const int nk = dp / BK;
   request_w(0, 0);
+  pin();
   fetch(EVEN{}, 0);
-  if (nk > 1) fetch(ODD{}, BK);
+  if (VEC || nk > 1) fetch(ODD{}, min(1, nk - 1) * BK);
+  pin();
   // the residual's values of this lane, requested ahead of the k loop (read one by one between its stores they would cost a
   // memory latency each)
   float xr[EPI == 1 ? MB : 1][EPI == 1 ? NB : 1][16];
@@ -289,8 +294,9 @@ __global__ __launch_bounds__(256, MB * NB == 4 ? 2 : 1) void gemm_f32_kernel(con
     constexpr int PAR = decltype(parity_c)::value, ast = AST == 2 ? PAR : 0, wst = PAR;
     std::integral_constant<int, PAR ^ 1> other;
     if (kc + 1 < nk) request_w(kc + 1, wst ^ 1);           // everybody left that stage at the barrier that opened this chunk
-    if (kc + 2 < nk) fetch(parity_c, (kc + 2) * BK);
-    __builtin_amdgcn_sched_barrier(0);                     // the requests stay ahead of the matrix work
+    pin();
+    if (VEC || kc + 2 < nk) fetch(parity_c, min(kc + 2, nk - 1) * BK);
+    pin();                                                 // the requests stay ahead of the matrix work
     auto multiply = [&](int s) {
       bf16x8 fa[MB][3], fw[NB][3];
 #pragma unroll
@@ -322,8 +328,7 @@ __global__ __launch_bounds__(256, MB * NB == 4 ? 2 : 1) void gemm_f32_kernel(con
     __builtin_amdgcn_sched_barrier(0);
     if (AST == 1) __syncthreads();                         // everybody has left the stage of A
     if (kc + 1 < nk) store(AST == 2 ? ast ^ 1 : 0, wst ^ 1);
-    if (kc + 2 < nk) wait_w();
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // W of the next chunk has landed
+    wait_w();                                              // W of the next chunk has landed
     __syncthreads();
   };
   for (int kc = 0; kc < nk; kc += 2) {

@@ -11,6 +11,9 @@ from tests.test_gpu_parity import TOL_HOT, score_err
 pytestmark = pytest.mark.gpu
 
 CASES = {
+    "one_chunk_16": dict(L=[70, 3, 0], M=[9, 33, 2], d=16, H=1),        # a single chunk of 32 k: W is waited for with no second chunk behind it
+    "one_chunk_20": dict(L=[70, 3, 0], M=[9, 33, 2], d=20, H=2),
+    "one_chunk_32": dict(L=[70, 3, 0], M=[9, 33, 2], d=32, H=2),
     "head_10_no_vector_loads": dict(L=[70, 3, 0], M=[9, 33, 2], d=30, H=3),
     "head_24": dict(L=[65, 31], M=[1, 40], d=48, H=2),
     "head_48": dict(L=[64, 129], M=[64, 7], d=96, H=2),
