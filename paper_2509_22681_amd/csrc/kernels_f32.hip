@@ -35,11 +35,13 @@ __device__ __forceinline__ f32x4 load4(const float *p, int k, int K) {
 }
 
 // silu(x) = x / (1 + exp(-x)) with the reciprocal by the hardware's estimate and one Newton step (within an ulp of the quotient, a third of its
-// instructions).  The exponent is capped where 1 + exp(-x) would leave the range: the result there is below 1e-34 either way.
+// instructions).  Where exp(-x) overflows (x below about -88.7) the estimate is 0 and its error no number: held to the most that an estimate is off by, it adds nothing
+// and the result is -0, as the quotient's.  (Between there and -87.3 the estimate is subnormal and may be flushed: 0 in place of 1e-36.)  -inf gives NaN, as the quotient.
 __device__ __forceinline__ float silu_newton(float x) {
-  const float t = 1.0f + __expf(fminf(-x, 87.0f));
+  const float t = 1.0f + __expf(-x);
   const float r = __builtin_amdgcn_rcpf(t);
-  return x * __builtin_fmaf(__builtin_fmaf(-t, r, 1.0f), r, r);
+  const float e = fmaxf(__builtin_fmaf(-t, r, 1.0f), -1e-6f);
+  return x * __builtin_fmaf(e, r, r);
 }
 
 // Sum over the 16 lanes of a row of lanes, delivered to all of them.

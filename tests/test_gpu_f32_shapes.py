@@ -135,3 +135,43 @@ def test_f32_products_do_not_depend_on_the_tile(d, H):
     assert torch.equal(whole, static)
     for r, out in parts:
         assert torch.equal(out, whole[wl.cand_offsets[r]:wl.cand_offsets[r + 1]]), r
+
+
+def planes_of_layer(wl, keys=("U", "V", "Q", "K", "O")):
+    """The planes of a one-layer fp32 model by capture, rows in merged token order."""
+    import torch
+    from paper_2509_22681_amd import binding as B
+    dw, hist, cand = B.to_device(wl)
+    h = B.flame_gr_create(B.config_for(wl))
+    try:
+        B.flame_gr_debug_capture(h, 0)
+        out = torch.empty((int(wl.cand_offsets[-1]),), device="cuda:0")
+        B.flame_gr_forward(h, dw, hist, wl.history_offsets, cand, wl.cand_offsets, out)
+        torch.cuda.synchronize()
+        n = int(wl.history_offsets[-1] + wl.cand_offsets[-1])
+        return {k: B.flame_gr_debug_stage(h, "UVQKO".index(k), n, wl.cfg.d_model) for k in keys}
+    finally:
+        B.flame_gr_destroy(h)
+
+
+@pytest.mark.parametrize("d,H", [(64, 2), (48, 1)])       # heads that are staged through LDS, and that are not
+def test_f32_silu_over_the_whole_range(d, H):
+    """silu as the quotient x / (1 + exp(-x)) has it over the range of fp32: 0 far below zero, whatever the magnitude, in projections and attention weights."""
+    wl = W.make_custom([70, 3], [5, 33], d=d, H=H, n_layers=1, n_buckets=16, max_rel_dist=128, dtype="f32", seed=5, emb_std=1.0, name="ends")
+    x = np.array([0.0, 1e-30, -1e-30, 1.0, -1.0, -20.0, -50.0, -86.0, -87.2, -87.5, -88.5, -88.8, -90.0, -150.0, -1e4, -1e30, -3.4e38, 20.0, 86.0, 90.0, 1e4, 1e30, 3.4e38],
+                 np.float32)
+    wl.weights["w1"][:] = 0.0
+    wl.weights["b1"][0, :d] = np.resize(np.concatenate([x, np.array([-np.inf, np.nan, np.inf], np.float32)]), d)       # U = silu(b1)
+    got = planes_of_layer(wl, ("U",))["U"]
+    assert (got == got[0])[:, ~np.isnan(got[0])].all()
+    x64 = x.astype(np.float64)
+    want = x64 * np.exp(-np.logaddexp(0.0, -x64))
+    # exp of an argument of up to 87 in fp32: the argument's rounding (87 ulps of 2^-24 and the scaling to base 2) and a few ulps; below -87, where 1e-36 may be flushed, absolute
+    err = np.abs(got[0, :len(x)] - want)
+    assert (err <= np.maximum(2e-5 * np.abs(want), 1.5e-36)).all(), list(zip(x, got[0], want))
+    assert np.isnan(got[0, len(x):len(x) + 2]).all() and got[0, len(x) + 2] == np.inf
+    # attention weights: logits of -1e36 weigh nothing (and their values add nothing), the self term's likewise
+    wl = W.make_custom([70, 3], [5, 33], d=d, H=H, n_layers=1, n_buckets=16, max_rel_dist=128, dtype="f32", seed=5, emb_std=1.0, name="ends")
+    wl.weights["rab"][:] = -1e36
+    got = planes_of_layer(wl, ("V", "O"))
+    assert np.abs(got["V"]).max() > 0.1 and np.abs(got["O"]).max() < 1e-30
