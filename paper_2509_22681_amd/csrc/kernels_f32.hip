@@ -255,8 +255,8 @@ __global__ __launch_bounds__(256, MB * NB == 4 ? 2 : 1) void gemm_f32_kernel(con
       }
     }
   };
-  // W of the chunk requested last has landed: behind it at least the rows of one chunk were fetched (VEC: always, past the last chunk that chunk's again,
-  // so that the count holds; else the loads are as many as the matrix has, and the wait is for all).  pin() keeps requests in the order in which they are counted.
+  // W of the chunk requested last has landed: behind it at least the rows of one chunk were fetched (without 16-byte loads they are as many as the matrix has, and the
+  // wait is for all).  pin() keeps requests in the order in which they are counted.
   auto pin = [&]() { asm volatile("" ::: "memory"); __builtin_amdgcn_sched_barrier(0); };
   auto wait_w = [&]() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(VEC && PACKED ? (EPI == 1 ? 2 * LPT + 2 : LPT) : 0) : "memory"); };
   f32x16 acc[MB][NB];
@@ -272,7 +272,7 @@ __global__ __launch_bounds__(256, MB * NB == 4 ? 2 : 1) void gemm_f32_kernel(con
   request_w(0, 0);
   pin();
   fetch(EVEN{}, 0);
-  if (VEC || nk > 1) fetch(ODD{}, min(1, nk - 1) * BK);
+  if (nk > 1) fetch(ODD{}, BK);
   pin();
   // the residual's values of this lane, requested ahead of the k loop (read one by one between its stores they would cost a
   // memory latency each)
@@ -292,12 +292,13 @@ __global__ __launch_bounds__(256, MB * NB == 4 ? 2 : 1) void gemm_f32_kernel(con
   wait_w();                                              // W of chunk 0 has landed
   __syncthreads();
   // The rows come from far away (past the L2s, several thousand cycles under load): they are fetched two chunks ahead, W (from an L2) one.
-  auto chunk = [&](auto parity_c, const int kc) {
+  auto chunk = [&](auto parity_c, auto ahead_c, const int kc) {
+    constexpr bool AHEAD = decltype(ahead_c)::value;     // there is a chunk after the next
     constexpr int PAR = decltype(parity_c)::value, ast = AST == 2 ? PAR : 0, wst = PAR;
     std::integral_constant<int, PAR ^ 1> other;
-    if (kc + 1 < nk) request_w(kc + 1, wst ^ 1);           // everybody left that stage at the barrier that opened this chunk
+    if (AHEAD || kc + 1 < nk) request_w(kc + 1, wst ^ 1);           // everybody left that stage at the barrier that opened this chunk
     pin();
-    if (VEC || kc + 2 < nk) fetch(parity_c, min(kc + 2, nk - 1) * BK);
+    if constexpr (AHEAD) fetch(parity_c, (kc + 2) * BK);
     pin();                                                 // the requests stay ahead of the matrix work
     auto multiply = [&](int s) {
       bf16x8 fa[MB][3], fw[NB][3];
@@ -329,13 +330,28 @@ __global__ __launch_bounds__(256, MB * NB == 4 ? 2 : 1) void gemm_f32_kernel(con
     }
     __builtin_amdgcn_sched_barrier(0);
     if (AST == 1) __syncthreads();                         // everybody has left the stage of A
-    if (kc + 1 < nk) store(AST == 2 ? ast ^ 1 : 0, wst ^ 1);
-    wait_w();                                              // W of the next chunk has landed
+    if (AHEAD || kc + 1 < nk) store(AST == 2 ? ast ^ 1 : 0, wst ^ 1);
+    // W of the next chunk has landed
+    if constexpr (AHEAD) wait_w();
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
   };
-  for (int kc = 0; kc < nk; kc += 2) {
-    chunk(EVEN{}, kc);
-    if (kc + 1 < nk) chunk(ODD{}, kc + 1);
+  // The last two chunks, which fetch no rows and wait for all, are code of their own: what is waited for never depends on a branch.  (As a branch in the loop: base_f32 676 us per
+  // forward, with the last chunk's rows fetched over again so that the count holds 690, so 654.)
+  typedef std::true_type AHEAD;
+  typedef std::false_type TAIL;
+  int kc = 0;
+  for (; kc + 3 < nk; kc += 2) {
+    chunk(EVEN{}, AHEAD{}, kc);
+    chunk(ODD{}, AHEAD{}, kc + 1);
+  }
+  if (kc + 2 < nk) {
+    chunk(EVEN{}, AHEAD{}, kc);
+    chunk(ODD{}, TAIL{}, kc + 1);
+    chunk(EVEN{}, TAIL{}, kc + 2);
+  } else {
+    chunk(EVEN{}, TAIL{}, kc);
+    if (kc + 1 < nk) chunk(ODD{}, TAIL{}, kc + 1);
   }
   // a lane holds one output column and 16 rows: 32 lanes write 128 contiguous bytes of a row
 #pragma unroll
