@@ -117,18 +117,24 @@ template <bool NT, typename T> __device__ __forceinline__ void store_once(T v, T
 // k 8 (l / 32) + 0..7 of row l & 31, or of row sigma32(l & 31) where the rows play operand A.  A fragment is one contiguous
 // request, from LDS (free of bank conflicts without a swizzle) as well as from L2 straight into registers.
 
-// An fp32 value as the sum of three bf16 values, exactly: each takes the next eight bits (round to nearest, the remainder is exact in fp32), and 8 + 8 + 8
-// bits with signs hold the 24 of the mantissa.
+// An fp32 value as the sum of three bf16 values: each takes the next eight bits (round to nearest, the remainder is exact in fp32), and 8 + 8 + 8
+// bits with signs hold the 24 of the mantissa.  Exact for all finite values but those below 2^-110, whose lower parts fall under the range of normal numbers and may be flushed
+// (off by less than 2^-125).
+// The first two parts end at bf16's largest value, so that what rounds past it leaves a finite remainder, and an infinity (or a NaN) comes out in the last part:
+// in the products it then meets the other operand's first part alone, which has that operand's sign.
 struct Split3 { bf16x4 p[3]; };
 __device__ __forceinline__ Split3 split3(f32x4 v) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));
+  constexpr float kBf16Max = 0x1.fep127f;
   Split3 s;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     f32x2 x = {v[2 * h], v[2 * h + 1]};
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-      const bf16x2 b = __builtin_convertvector(x, bf16x2);       // two values per instruction
+      f32x2 c = x;
+      if (i < 2) c = f32x2{__builtin_amdgcn_fmed3f(x[0], -kBf16Max, kBf16Max), __builtin_amdgcn_fmed3f(x[1], -kBf16Max, kBf16Max)};
+      const bf16x2 b = __builtin_convertvector(c, bf16x2);       // two values per instruction
       s.p[i][2 * h] = b[0];
       s.p[i][2 * h + 1] = b[1];
       if (i < 2) { x[0] -= (float)b[0]; x[1] -= (float)b[1]; }

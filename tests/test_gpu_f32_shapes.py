@@ -175,3 +175,35 @@ def test_f32_silu_over_the_whole_range(d, H):
     wl.weights["rab"][:] = -1e36
     got = planes_of_layer(wl, ("V", "O"))
     assert np.abs(got["V"]).max() > 0.1 and np.abs(got["O"]).max() < 1e-30
+
+
+@pytest.mark.parametrize("d,H", [(32, 1), (90, 2), (256, 4)])
+def test_f32_products_at_the_ends_of_the_range(d, H):
+    """Operands that round past bf16's largest value, and infinities: the finite and infinite products that fp32 arithmetic has."""
+    big, tiny = np.finfo(np.float32).max, np.float32(2.0 ** -122)
+    M = 9
+    wl = W.make_custom([70], [M], d=d, H=H, n_layers=1, n_buckets=16, max_rel_dist=128, dtype="f32", seed=5, emb_std=1.0, name="range")
+    w1 = wl.weights["w1"][0]
+    # meets the large embeddings.  (One bf16 part each: the lower parts of anything else below 2^-110 are under the range of normal numbers and lost, up to 2^-125, which
+    # a factor of 2^128 would show as 8.)
+    w1[:, 1] = tiny * np.resize(np.array([1.0, -1.0, 0.25, -0.5, 3.0, 1.25], np.float32), 4 * d)
+    x = wl.cand_emb
+    x[:, 1] = [big, -big, 3.4e38, 3.396e38, 3.39e38, -3.3953e38, np.inf, -np.inf, 1.0]
+    wl.history_emb[:, 1] = 1.0
+    x[:, 2] = tiny * np.resize(np.array([1.0, -0.75], np.float32), M)                                     # meets the large weights
+    wl.history_emb[:, 2] = tiny
+    w1[:, 2] = 0.0
+    w1[:9, 2] = [big, -big, 3.4e38, 3.396e38, 3.39e38, -3.3953e38, np.inf, -np.inf, 1.0]
+    w1[d:d + 6, 2] = big
+    got = planes_of_layer(wl, ("U", "V", "Q", "K"))
+    rows = np.concatenate([wl.history_emb, wl.cand_emb]).astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        z = (rows[:, None, :] * w1.astype(np.float64)[None]).sum(-1)
+        want = z * np.exp(-np.logaddexp(0.0, -z))                 # NaN at -inf, as -inf / (1 + inf)
+    assert np.isfinite(want).sum() > 0.9 * want.size * 70 / 79 and np.isinf(want).any() and np.isnan(want).any()
+    for p, name in enumerate("UVQK"):
+        g, t = got[name].astype(np.float64), want[:, p * d:(p + 1) * d]
+        assert np.array_equal(np.isnan(g), np.isnan(t)), name
+        assert np.array_equal(np.isposinf(g), np.isposinf(t)), name
+        ok = np.isfinite(t)
+        assert (np.abs(g[ok] - t[ok]) <= 2e-5 * (1.0 + np.abs(t[ok]))).all(), name    # sums of up to 256 terms of size 1 (256 x 2^-24) and two terms of up to 200
