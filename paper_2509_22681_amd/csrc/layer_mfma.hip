@@ -40,9 +40,9 @@ constexpr int kPatchBytes = 4 * 8192;          // step 4: 64 rows x 64 columns p
 template <int NK>
 constexpr int layer_lds_bytes() { return (64 * 32 * NK * 2 > kPatchBytes ? 64 * 32 * NK * 2 : kPatchBytes) + 64 * 32 * NK * 2; }
 
-// NK = d / 32
+// NK = d / 32.  (U is the plane that planes.u overwrites, each workgroup its own rows, which it has read in step 1: no __restrict__.)
 template <int NK>
-__global__ __launch_bounds__(512, 4) void layer_kernel(const half_t *__restrict__ O, const half_t *__restrict__ U, const bf16_t *__restrict__ gamma, const bf16_t *__restrict__ beta,
+__global__ __launch_bounds__(512, 4) void layer_kernel(const half_t *__restrict__ O, const half_t *U, const bf16_t *__restrict__ gamma, const bf16_t *__restrict__ beta,
                                                        const half_t *__restrict__ W2p, const bf16_t *__restrict__ b2, half_t *__restrict__ Xh, half_t *__restrict__ Xl, int lo_is_zero,
                                                        const RowBlock *__restrict__ blocks, const int32_t *__restrict__ blk_list, int blk_first, float eps,
                                                        const half_t *__restrict__ W1, const bf16_t *__restrict__ b1, PlanePtrs planes, int all_hist, int all_cand, int64_t ws_rows,
