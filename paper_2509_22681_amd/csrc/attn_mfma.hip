@@ -811,8 +811,8 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
 
 }  // namespace
 
-// The configurations that split the keys need their LDS limit raised once per kernel instance (a function attribute, no
-// allocation); handles do it when they are created, outside any stream capture.
+// The configurations that split the keys need their LDS limit raised once per kernel instance and device (a function attribute, no
+// allocation): attn_setup, ahead of any launch.
 template <int DH, int KP, bool SEQ = false>
 constexpr int key_split_lds_bytes() {   // the stages: K, V^T and the bias window each; the weights of a tile where they do not fit over its K
   return (KP == 4 ? 2 : 4) * (2 * 64 * KP * DH * 2 + 8 * 256) + (SEQ && 64 * KP * DH * 2 < 8 * 4096 ? 8 * 4096 : 0);
@@ -820,9 +820,8 @@ constexpr int key_split_lds_bytes() {   // the stages: K, V^T and the bias windo
 
 template <int DH, bool SM, int KP, bool SEQ = false>
 static hipError_t key_split_setup() {
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_mfma_kernel<DH, SM, KP, false, SEQ>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, key_split_lds_bytes<DH, KP, SEQ>());
-  return attr;
+  static std::atomic<uint64_t> done{0};
+  return raise_lds_limit(reinterpret_cast<const void *>(&attn_mfma_kernel<DH, SM, KP, false, SEQ>), key_split_lds_bytes<DH, KP, SEQ>(), done);
 }
 
 template <int DH, bool SM>
@@ -834,7 +833,6 @@ static hipError_t latency_setup() {
 template <int DH, bool SM, int KP>
 static void launch_key_split(int grid, PlanePtrs planes, const float *bias_lh, const float *tscale_h, half_t *O,
                              const AttnItem *items, const Shape &sh, hipStream_t s) {
-  (void)key_split_setup<DH, SM, KP>();
   attn_mfma_kernel<DH, SM, KP, false><<<grid, 512, key_split_lds_bytes<DH, KP>(), s>>>(planes, bias_lh, tscale_h, O, items, sh.H, sh.d, sh.D, sh.ws_rows);
 }
 

@@ -1,6 +1,8 @@
 // Launch interface between the host API and the gfx950 kernels.  All pointers are device
 // pointers unless stated; every launcher only enqueues work on `s`.
 #pragma once
+#include <atomic>
+
 #include <hip/hip_runtime.h>
 
 #include "plan.h"
@@ -106,7 +108,10 @@ void launch_uvqk_bf16(const void *Xh, const void *W1h, const void *b1, PlanePtrs
 // n_cand: candidate tiles among the items; q_tile, longest: query rows per item and the longest history of this plan.
 void launch_attn_bf16(PlanePtrs planes, const float *bias_lh, const float *tscale_h, void *O, const AttnItem *items,
                       int n_items, int n_cand, int q_tile, int longest, const Shape &sh, hipStream_t s);
-// Prepares the configurations of the attention kernel that split the keys, for this shape (raises their LDS limit); once per handle.
+// Raises the dynamic LDS limit of a kernel on the current device.  The limit is a property of the kernel on one device, so `done`, the kernel's own, holds a bit per
+// device; a failure is not kept.  Safe from several threads.
+hipError_t raise_lds_limit(const void *kernel, int bytes, std::atomic<uint64_t> &done);
+// Prepares the configurations of the attention kernel that split the keys, for this shape (raises their LDS limit); once per handle, on its device.
 hipError_t attn_setup(const Shape &sh);
 // X[row] += G W2h^T + b2 on the residual pair (Xh, Xl); lo_is_zero: Xl is not read (first layer)
 void launch_outproj_bf16(const void *G, const void *W2h, const void *b2, void *Xh, void *Xl, bool lo_is_zero,

@@ -342,8 +342,8 @@ bool layer_fused(int d, int n_blk) {
 
 template <int NK>
 static hipError_t layer_limit() {
-  static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&layer_kernel<NK>), hipFuncAttributeMaxDynamicSharedMemorySize, layer_lds_bytes<NK>());
-  return e;
+  static std::atomic<uint64_t> done{0};
+  return raise_lds_limit(reinterpret_cast<const void *>(&layer_kernel<NK>), layer_lds_bytes<NK>(), done);
 }
 
 hipError_t layer_setup(int d) { return d == 128 ? layer_limit<4>() : d == 192 ? layer_limit<6>() : d == 256 ? layer_limit<8>() : hipSuccess; }

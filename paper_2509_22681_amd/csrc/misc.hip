@@ -7,6 +7,16 @@
 
 namespace flame {
 
+hipError_t raise_lds_limit(const void *kernel, int bytes, std::atomic<uint64_t> &done) {
+  int dev = -1;
+  if (const hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
+  const uint64_t bit = dev >= 0 && dev < 64 ? (uint64_t)1 << dev : 0;
+  if (done.load() & bit) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess) done.fetch_or(bit);
+  return e;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Prologue of a pass: what its kernels read that is neither an embedding nor a weight as the caller holds it.  Independent pieces, in one launch, since each alone is a
 // few microseconds of launch for next to no work:
