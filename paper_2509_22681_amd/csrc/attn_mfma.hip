@@ -850,10 +850,11 @@ hipError_t attn_setup(const Shape &sh) {
 //   512 + 128, 8 heads: 40: 119 / 109, 120: 135 / 125, 200: 161 / 163; 2 heads: 130: 119 / 115, 190: 127 / 133
 //   320 + 128, 2 heads: 24: 91 / 88, 128: 107 / 109; 128 + 64: 40: 82 / 84, 160: 98 / 119 (a history of one or two 256-key tiles has no chain to shorten)
 // Candidate tiles alone (one layer), 4 heads: 512 + 128: 64: 48 / 46, 128: 53 / 53, 160: 59 / 65; 2048 + 128: 64: 87 / 79, 128: 140 / 136, 160: 152 / 169.
-constexpr int kAttnSeqHistory = 384, kAttnSeqWorkgroups = 128;
-static bool attn_seq(int grid, int n_items, int n_cand, int longest) {
+constexpr int kAttnSeqHistory = 384, kAttnSeqWorkgroups = 128;                            // from this history on; up to this many workgroups, and where history tiles prevail
+constexpr int kAttnSeqLongHistory = 1024, kAttnSeqLongWorkgroups = 160, kAttnSeqLongerHistory = 2048, kAttnSeqLongerWorkgroups = 224;   // up to these
+bool attn_key_ordered(int grid, int n_items, int n_cand, int longest) {
   if (longest < kAttnSeqHistory) return false;
-  const int limit = longest < 1024 || 2 * n_cand > n_items ? kAttnSeqWorkgroups : longest < 2048 ? 160 : 224;
+  const int limit = longest < kAttnSeqLongHistory || 2 * n_cand > n_items ? kAttnSeqWorkgroups : longest < kAttnSeqLongerHistory ? kAttnSeqLongWorkgroups : kAttnSeqLongerWorkgroups;
   return grid <= limit;
 }
 
@@ -875,7 +876,7 @@ void launch_attn_bf16(PlanePtrs planes, const float *bias_lh, const float *tscal
 #undef SPLIT_LAUNCH
     return;
   }
-  if (!sh.softmax && attn_seq(grid, n_items, n_cand, longest)) {
+  if (!sh.softmax && attn_key_ordered(grid, n_items, n_cand, longest)) {
 #define SEQ_LAUNCH(DHV) attn_mfma_kernel<DHV, false, 4, false, true><<<2 * grid, 512, key_split_lds_bytes<DHV, 4, true>(), s>>>(planes, bias_lh, tscale_h, (half_t *)O, items, sh.H, sh.d, sh.D, sh.ws_rows)
     if (sh.dh == 32) SEQ_LAUNCH(32);
     else SEQ_LAUNCH(64);

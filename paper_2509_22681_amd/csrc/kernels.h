@@ -108,6 +108,8 @@ void launch_uvqk_bf16(const void *Xh, const void *W1h, const void *b1, PlanePtrs
 // n_cand: candidate tiles among the items; q_tile, longest: query rows per item and the longest history of this plan.
 void launch_attn_bf16(PlanePtrs planes, const float *bias_lh, const float *tscale_h, void *O, const AttnItem *items,
                       int n_items, int n_cand, int q_tile, int longest, const Shape &sh, hipStream_t s);
+// Whether a pointwise launch of a throughput handle (grid = items x heads) takes the key-ordered split.
+bool attn_key_ordered(int grid, int n_items, int n_cand, int longest);
 // Raises the dynamic LDS limit of a kernel on the current device.  The limit is a property of the kernel on one device, so `done`, the kernel's own, holds a bit per
 // device; a failure is not kept.  Safe from several threads.
 hipError_t raise_lds_limit(const void *kernel, int bytes, std::atomic<uint64_t> &done);

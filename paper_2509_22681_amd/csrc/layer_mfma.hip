@@ -335,8 +335,9 @@ __global__ __launch_bounds__(512, 4) void layer_kernel(const half_t *__restrict_
 //   d = 192   64 blocks        (2: 87 -> 91, 32: 96 -> 97, 64: 111 -> 106, 256: 162 -> 140, 512: 263 -> 230),
 //   d = 256  160 blocks        (2: 81 -> 102, 64: 114 -> 126, 128: 141 -> 142, 192: 163 -> 151, 512: 323 -> 291).
 // Below, a block's d / 64 turns of columns one after another are longer than K1's small tiles side by side on a chip that is mostly idle.
+constexpr int kLayerFrom192 = 64, kLayerFrom256 = 160;
 bool layer_fused(int d, int n_blk) {
-  const int from = d == 128 ? 1 : d == 192 ? 64 : 160;
+  const int from = d == 128 ? 1 : d == 192 ? kLayerFrom192 : kLayerFrom256;
   return (d == 128 || d == 192 || d == 256) && n_blk >= from && (int64_t)n_blk * kRowAlign * d * 2 <= kStreamBytes;
 }
 

@@ -1,18 +1,21 @@
 """The kernel that makes a layer's output projection and the next layer's projections in one launch, against the two kernels that run
 where a handle's planes are to be looked at: the same instructions in the same order, so the same bits, in each pass that can take it,
-on both sides of the sizes at which it begins and ends; and against the fp64 oracle at the hot bar."""
+on both sides of the sizes at which it begins and ends (which of them ran is read from the launches that a profiled handle counts); and against the fp64 oracle at the hot bar."""
 import numpy as np
 import pytest
 
 import oracle
 from paper_2509_22681_amd import workloads as W
 from tests.test_gpu_parity import TOL_HOT, score_err
+from tests.test_routes import LAYER_BLOCKS
 
 pytestmark = pytest.mark.gpu
 
-# (width, heads, 64-row blocks of the batch)
-SIZES = [(128, 2, 2), (128, 4, 66), (128, 2, 1024), (128, 2, 1026), (192, 3, 62), (192, 3, 64), (192, 6, 132), (192, 3, 682), (192, 3, 684),
-         (256, 4, 158), (256, 4, 160), (256, 8, 310), (256, 4, 512), (256, 4, 514)]
+# (width, heads, 64-row blocks of the batch): sizes between, and both sides of where the rule begins and ends (an even number of blocks)
+SIZES = [(128, 2, 2), (128, 4, 66), (192, 6, 132), (256, 8, 310)]
+for width, heads in ((128, 2), (192, 3), (256, 4)):
+    first, last = LAYER_BLOCKS[width]
+    SIZES += [(width, heads, n) for n in (first - 2, first, last // 2 * 2, last // 2 * 2 + 2) if n > 2]
 
 
 def batch(blocks):
@@ -32,7 +35,7 @@ def test_one_launch_per_layer_gives_the_same_bits(d, H, blocks, kind):
     dw, hist, cand = B.to_device(wl)
     n = int(wl.cand_offsets[-1])
 
-    def scores(two_stage, captured, n_streams=0):
+    def scores(two_stage, captured, n_streams=0, launches=None):
         h = B.flame_gr_create(B.config_for(wl, n_streams=n_streams, kv_cache=int(two_stage)))
         try:
             if captured:
@@ -42,15 +45,22 @@ def test_one_launch_per_layer_gives_the_same_bits(d, H, blocks, kind):
                 B.flame_gr_prefill(h, dw, hist, wl.history_offsets, np.asarray(M, np.int32))
                 B.flame_gr_score(h, dw, cand, wl.cand_offsets, out)
             else:
+                if launches is not None:
+                    B.flame_gr_debug_profile(h, True)
                 B.flame_gr_forward(h, dw, hist, wl.history_offsets, cand, wl.cand_offsets, out)
+                if launches is not None:
+                    launches.update({k: n for k, (_, n) in B.flame_gr_debug_profile_read(h).items()})
             torch.cuda.synchronize()
             return out.cpu().numpy()
         finally:
             B.flame_gr_destroy(h)
 
-    want = scores(False, True)
+    two, one = {}, {}
+    want = scores(False, True, launches=two)
     assert np.isfinite(want).all()
-    assert np.array_equal(scores(False, False), want)
+    assert np.array_equal(scores(False, False, launches=one), want)
+    first, last = LAYER_BLOCKS[d]
+    assert two["uvqk"] == 3 and one["uvqk"] == (1 if first <= blocks <= last else 3)
     assert np.array_equal(scores(False, False, n_streams=2), want)
     assert np.array_equal(scores(True, False), want) and np.array_equal(scores(True, True), want)
     if blocks <= 160:

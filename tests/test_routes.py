@@ -1,12 +1,63 @@
 """Properties of the launch code that need no GPU to check."""
+import ctypes
 import re
 import subprocess
 import sys
 from pathlib import Path
 
+import pytest
+
 from paper_2509_22681_amd import build as build_mod
 
 CSRC = Path(build_mod.CSRC)
+
+
+def constants(source, pattern):
+    return {k: int(v) for k, v in re.findall(pattern + r" = (\d+)(?=[,;])", (CSRC / source).read_text())}
+
+
+# Limits of the rules below, as the sources have them: of the key-ordered attention, and the 64-row blocks from and up to which the layer kernel runs
+KEY_ORDERED = constants("attn_mfma.hip", r"\bkAttnSeq(\w+)")
+LAYER_BLOCKS = {d: (first, (16 << 20) // (64 * 2 * d)) for d, first in {128: 1, **{int(k): v for k, v in constants("layer_mfma.hip", r"\bkLayerFrom(\d+)").items()}}.items()}
+
+
+def library():
+    """The library's own rules (internal symbols: the launches call them)."""
+    from paper_2509_22681_amd import binding
+    return binding._lib
+
+
+def key_ordered(grid, n_items, n_cand, longest):
+    f = library()._ZN5flame16attn_key_orderedEiiii
+    f.restype = ctypes.c_bool
+    return f(grid, n_items, n_cand, longest)
+
+
+def layer_fused(d, blocks):
+    f = library()._ZN5flame11layer_fusedEii
+    f.restype = ctypes.c_bool
+    return f(d, blocks)
+
+
+def test_layer_kernel_runs_between_its_limits():
+    assert set(LAYER_BLOCKS) == {128, 192, 256}
+    for d, (first, last) in LAYER_BLOCKS.items():
+        assert [layer_fused(d, n) for n in (first - 1, first, last, last + 1)] == [False, True, True, False]
+    for d in (64, 96, 320, 384, 512, 1024):
+        assert not any(layer_fused(d, n) for n in (1, 64, 160, 256, 512, 1024))
+
+
+# (shortest and longest history of the row, limit where history tiles prevail)
+@pytest.mark.parametrize("lo,hi,limit", [("History", "LongHistory", "Workgroups"), ("LongHistory", "LongerHistory", "LongWorkgroups"), ("LongerHistory", None, "LongerWorkgroups")])
+def test_key_ordered_attention_runs_up_to_its_limits(lo, hi, limit):
+    k = KEY_ORDERED
+    assert len(k) == 6
+    n = k[limit]
+    for longest in (k[lo], k[hi] - 1 if hi else 1 << 20):
+        assert key_ordered(n, n, n // 2, longest) and not key_ordered(n + 1, n + 1, (n + 1) // 2, longest)
+        m = k["Workgroups"]                      # candidate tiles prevail
+        assert key_ordered(m, m, m // 2 + 1, longest) and not key_ordered(m + 1, m + 1, m // 2 + 2, longest)
+    assert not key_ordered(1, 1, 0, k["History"] - 1)
 
 
 def test_the_plane_that_the_layer_kernel_overwrites_is_not_restrict():
