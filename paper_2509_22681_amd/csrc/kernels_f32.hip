@@ -416,7 +416,10 @@ void launch_outproj_f32(const float *O, const float *U, const float *gamma, cons
   const bool vec = vec4_rows(sh.d, gamma) && vec4_rows(sh.d, beta);
   if (packed) {
     if (!vec) OUT_CASE(2, 2, 1, 1, true, false, 0);
-    else if (sh.d > 64 && sh.d <= 256 && n_blk >= 128) {
+    // 64 x 128 tiles where they have no empty columns and there are as many as two rounds of the chip at two per compute unit.  Forwards of five layers with 64 x 64 tiles / with
+    // these (us), 64-row blocks: d = 256: 128: 326 / 329, 192: 451 / 450, 256: 560 / 535, 512: 1063 / 1006; d = 128: 256: 240 / 242, 320: 331 / 333, 512: 435 / 421;
+    // with empty columns, d = 192: 128: 254 / 261, 512: 714 / 722; d = 160: 512: 585 / 594.
+    else if (nb % 4 == 0 && sh.d <= 256 && (int64_t)n_blk * nb >= 2048) {
       if (sh.d <= 128) OUT_CASE(1, 4, 2, 1, true, true, 2);
       else OUT_CASE(1, 4, 2, 1, true, true, 4);
     } else OUT_WIDTHS(true);

@@ -24,6 +24,9 @@ CASES = {
     "wide_640": dict(L=[66], M=[12], d=640, H=10),
     "wide_520_head_65": dict(L=[40, 33], M=[3, 34], d=520, H=8),
     "big_projection_tile": dict(L=[130] * 32 + [64], M=[10] * 32 + [0], d=256, H=4),
+    "wide_output_tile_256": dict(L=[1, 33] * 64, M=[2, 64] * 64, d=256, H=4),            # 256 row blocks: the first of the 64 x 128 tiles
+    "narrow_output_tile_256": dict(L=[1, 33] * 63 + [5], M=[2, 64] * 63 + [0], d=256, H=4),
+    "wide_output_tile_124": dict(L=[1, 33] * 128, M=[2, 64] * 128, d=124, H=2),         # 512, the last columns of a tile empty
 }
 
 
