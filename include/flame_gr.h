@@ -34,7 +34,10 @@
  *     pointer is INVALID_ARGUMENT.
  *
  * Arithmetic of the two element types
- *   - FLAME_GR_F32: fp32 operands, fp32 accumulation (fp32 matrix instructions).
+ *   - FLAME_GR_F32: fp32 operands, fp32 accumulation.  Attention runs on the fp32 matrix instructions; in the projections
+ *     each operand is the sum of three bf16 values and six of the nine products are added up in fp32 (the other three
+ *     come to 2^-24 of the product at most), with infinities and NaN as in fp32 arithmetic (an infinite operand that
+ *     meets one of magnitude 2^8 and more may give NaN) and operands below 2^-110 off by up to 2^-125.
  *   - FLAME_GR_BF16 names the STORAGE type at this boundary: embeddings, W1, b1, ln_g, ln_b, W2, b2 and w_s
  *     arrive as bf16.  Inside, the matrix instructions run on IEEE binary16 (fp16) operands with fp32
  *     accumulation: embeddings and projection matrices are converted bf16 -> fp16 once, and the
@@ -354,7 +357,10 @@ int flame_gr_debug_profile(flame_gr_t *h, int32_t enable);
 /* Summed milliseconds and launch counts, by kernel kind, of all forwards since profiling was
  * enabled or last read: HOST arrays of 7 entries in the order assemble, bias expansion, UVQK
  * projection, attention, LayerNorm-gate, output projection, score head.  Waits for the last forward
- * to finish, then resets the sums. */
+ * to finish, then resets the sums.  A launch that does several of these counts once: the assembly of the
+ * rows, the bias expansion and the operand copies of the weights are one launch, under assemble (bias
+ * expansion is always 0); where a launch does the output projection of a layer and the UVQK projection of
+ * the next (narrow models in the middle of the range of batch sizes), it is under output projection. */
 int flame_gr_debug_profile_read(flame_gr_t *h, float *ms_by_kind, int32_t *launches_by_kind);
 
 #ifdef __cplusplus

@@ -31,6 +31,8 @@ FLAME_GR_F32, FLAME_GR_BF16 = 0, 1
 FLAME_GR_ATTN_SILU, FLAME_GR_ATTN_SOFTMAX = 0, 1
 STATUS = {0: "OK", -1: "INVALID_ARGUMENT", -2: "CAPACITY_EXCEEDED", -3: "HIP_ERROR", -4: "BAD_HANDLE",
           -5: "UNSUPPORTED"}
+# what is timed apart; "assemble" holds the bias expansion and the weights' operand copies ("bias" is always 0), and "outproj" the next layer's
+# projections where one launch does both
 KERNEL_KINDS = ("assemble", "bias", "uvqk", "attn", "ln_gate", "outproj", "score")
 
 

@@ -552,7 +552,8 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
       __builtin_amdgcn_s_barrier();                          // the weights of the tile are complete
       __builtin_amdgcn_sched_barrier(0);
       if (sum_b >= 0 && wave_active) {
-        // The tile's keys in order, 16 a product, the visible 64-key blocks of them: as one wavefront alone adds them up.
+        // The tile's keys in order, 16 a product, the visible 64-key blocks of them: as one wavefront alone adds them up.  (As built, the reads three products ahead are
+        // waited for at each block's branch.)
         const char *pp = lds + (P_OVER_K ? ST : NSTAGE) * STAGE + q_group * (KP * 4096) + lane * 16;
         const char *vp = sb + sum_b * (32 * KT * 2);
         f16x8 pw[4], vw[4];

@@ -33,13 +33,8 @@ template <> __device__ __forceinline__ float from_f32<float>(float v) { return v
 template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float v) { return (bf16_t)v; }  // round to nearest even
 template <> __device__ __forceinline__ half_t from_f32<half_t>(float v) { return to_f16_sat(v); }
 
-// silu(x) = x / (1 + exp(-x)).  exp2 of a large positive argument gives +inf and the quotient 0,
-// of a large negative one gives 0 and the quotient x: both limits are the right ones.
-__device__ __forceinline__ float silu_f32(float x) {
-  return x / (1.0f + __expf(-x));
-}
-
-// Faster variant: hardware exp2 and reciprocal (about 1 ulp each), same limits.
+// silu(x) = x / (1 + exp(-x)) by the hardware's exp2 and reciprocal (about 1 ulp each).  exp2 of a large positive argument gives +inf and the
+// result 0, of a large negative one gives 0 and the result x: both limits are the right ones.
 __device__ __forceinline__ float silu_fast(float x) {
   float e = __builtin_amdgcn_exp2f(x * -1.4426950408889634f);
   return x * __builtin_amdgcn_rcpf(1.0f + e);

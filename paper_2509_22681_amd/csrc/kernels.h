@@ -27,8 +27,8 @@ struct Prologue {
   int n_table_words = 0;
   // rows of blocks <- embeddings: fp32 X in the fp32 path, the k-tile blocked fp16 word Xh in the MFMA path (whose residual is
   // the pair Xh = fp16(X), Xl = fp16(X - Xh); embeddings are exact in Xh and Xl is not written); padding rows zeroed.
-  // The n_blk blocks are list[0..n_blk) if list is given, else first..first+n_blk (blocks and list: pinned host or device memory).
-  int dtype = 0, d = 0, n_blk = 0, first = 0;
+  // The n_blk blocks are list[0..n_blk) if list is given, else the first n_blk (blocks and list: pinned host or device memory).
+  int dtype = 0, d = 0, n_blk = 0;
   const RowBlock *blocks = nullptr;
   const int32_t *list = nullptr;
   const void *hist = nullptr, *cand = nullptr;
@@ -75,7 +75,7 @@ void launch_clear_spare(void *K, void *Vt, int d, int64_t ws_rows, int64_t row0,
 void launch_debug_mask(int L, int M, const int32_t *bucket_tab, int D, uint8_t *mask, int32_t *bucket,
                        hipStream_t s);
 
-// ---- fp32 path (kernels_f32.hip): the fp32 matrix instruction ----------------------------------
+// ---- fp32 path (kernels_f32.hip): projections on split bf16 operands, attention on the fp32 matrix instruction ----------------------------------
 // The projection matrices of all layers split into bf16 parts for the two products below (kernels_f32.hip), packed by fragments: matrix m of the copy, W1's planes layer after layer
 // and then W2's, starts at m * split_w_bytes(d, 1) / 5.  The products take the packed matrix of the layer (packed), or the matrix itself.
 int64_t split_w_bytes(int d, int n_layers);

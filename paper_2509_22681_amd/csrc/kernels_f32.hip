@@ -58,10 +58,11 @@ __device__ __forceinline__ float row16_sum(float v) {
 // ---------------------------------------------------------------------------------------------
 // C[m][n] = sum_k A[m][k] W[n][k] + bias[n] on 64-row blocks.  256 threads = WM x WN wavefronts of MB x NB blocks of 32 x 32 outputs; k in chunks of 32.
 // Both operands are split into three bf16 values, and six of the nine products run on the bf16 matrix instruction (32 x 32 x 16, fp32
-// accumulators), the small ones first; left out are the three of 2^-26 of the largest and less.  6 x 32 cycles for 16 k against 8 x 64 on the fp32 instruction, and the sums
+// accumulators), the small ones first; left out are three, of up to 2^-25 of the product each (a part is up to 2^-8 of the one before it) and 2^-24 together.  6 x 32 cycles for 16 k against 8 x 64 on the fp32 instruction, and the sums
 // are rounded less often (a product of bf16 values is exact, and 16 k go into an accumulator at a time instead of 2).
 // PACKED: W arrives split and packed by fragments (split_w in misc.hip), by LDS-DMA, a chunk ahead through two stages; else (64 x 64 tiles only: callers without room for the packed copy) it is split here, like A,
-// on the way from registers to LDS.  The split is exact, so the two agree bit for bit.
+// on the way from registers to LDS.  The split is the same, so the two agree bit for bit.  (Forwards that fill the static workspace so, against 128 x 128 tiles on the fp32
+// instruction: d = 128, 4 layers 354 -> 327 us, d = 256, 4 layers 470 -> 379, d = 512, 2 layers 364 -> 273.)
 // LDS rows of A are 64 bytes per part, 16-byte chunks XOR-swizzled over groups of four rows (key: row bits 2..3), which the fragment reads take
 // without bank conflicts.  Tiles of 64 rows have two stages for A, tiles of 128 one (two workgroups on a compute unit, one's staging under
 // the other's matrix work).
@@ -291,7 +292,8 @@ __global__ __launch_bounds__(256, MB * NB == 4 ? 2 : 1) void gemm_f32_kernel(con
   store(0, 0);
   wait_w();                                              // W of chunk 0 has landed
   __syncthreads();
-  // The rows come from far away (past the L2s, several thousand cycles under load): they are fetched two chunks ahead, W (from an L2) one.
+  // The rows come from far away (past the L2s, several thousand cycles under load): they are fetched two chunks ahead, W (from an L2) one.  As built, the look-ahead of the rows is lost:
+  // a __syncthreads with LDS-DMA pending waits for all loads, and with EPI 1 such a wait stands ahead of a chunk's first LDS read.
   auto chunk = [&](auto parity_c, auto ahead_c, const int kc) {
     constexpr bool AHEAD = decltype(ahead_c)::value;     // there is a chunk after the next
     constexpr int PAR = decltype(parity_c)::value, ast = AST == 2 ? PAR : 0, wst = PAR;
@@ -319,7 +321,7 @@ __global__ __launch_bounds__(256, MB * NB == 4 ? 2 : 1) void gemm_f32_kernel(con
     };
     multiply(0);
     __builtin_amdgcn_sched_barrier(0);
-    // the next chunk is split under the second half of the matrix work
+    // the next chunk is split under the second half of the matrix work (where its parts are stored unconditionally; else the compiler moves the split to the store)
     multiply(1);
     split(other, (kc + 1) * BK);                                // (behind the last chunk: of what was fetched for it, and not stored)
     __builtin_amdgcn_sched_group_barrier(0x100, 3 * (MB + NB), 0);

@@ -4,7 +4,7 @@
 //
 // What it is for: launches of a few hundred row blocks, which are chains of short kernels.  Each of the two is 16 to 19 us there, of which about 5 are what any launch
 // costs and several more its first memory latency, the tail of its last workgroups and (K1) reading the rows back that K3 has just written; the matrix work of both together is 3 us.
-// Measured, K3 + K1 of a layer -> one launch: d = 256, 384 blocks 36 -> 34 us (and a launch less), d = 192, 320 blocks 35 -> 27; the forward 226 -> 217 and 1311 -> 1125 us.
+// Measured, K3 + K1 of a layer -> one launch: d = 256, 320 blocks 36 -> 36 to 37 us and a launch less, d = 192, 320 blocks 35 -> 28 to 29; the forward 226 -> 217 and 1311 -> 1125 us.
 // Bound by its steps' latencies: of 39 thousand cycles per workgroup 7 go to step 1, 4 to step 2, 5 to step 3, 19 to step 4 (8 of them its products) and the rest to barriers.
 //
 // Eight wavefronts, two workgroups on a compute unit:
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(512, 4) void layer_kernel(const half_t *__restrict_
       __builtin_amdgcn_sched_barrier(0);
     }
     half += 4;
-    start(half);                                       // the next columns' first fragments, under the epilogue
+    start(half);                                       // the next columns' first fragments (as built, under the epilogue for V; for U, Q and K the compiler moves them behind its barrier)
     __builtin_amdgcn_sched_barrier(0);
     const float sc = alpha * 0.5f;
 #pragma unroll

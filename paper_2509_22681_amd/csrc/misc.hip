@@ -136,7 +136,7 @@ __global__ __launch_bounds__(256) void prologue_kernel(const Prologue p, int wg_
   wg -= wg_tables;
   if (wg < wg_rows) {
     const int t = wg / kSlices, slice = wg % kSlices;
-    const int b = p.list ? p.list[t] : p.first + t;
+    const int b = p.list ? p.list[t] : t;
     const RowBlock rb = p.blocks[b];
     if (p.dtype == FLAME_GR_BF16) assemble_bf16(rb, b, slice, (const bf16_t *)p.hist, (const bf16_t *)p.cand, (half_t *)p.Xh, p.d);
     else assemble_f32(rb, b, slice, (const float *)p.hist, (const float *)p.cand, p.X, p.d, vec);
