@@ -69,9 +69,9 @@ __device__ __forceinline__ float row16_sum(float v) {
 // EPI 0: planes[p][m][n] = silu(C) with A = X.
 // EPI 1: X[m][n] += C with A = (LayerNorm(O) * gamma + beta) * U, made while the chunk is staged: the statistics of the 64
 //        rows come first (mean, then the centred second moment), and the gated rows never travel through memory.
-// 20 480 rows, d = 256: K1 116 -> 85 us per launch against the fp32 instruction (its work alone is 26 us; a workgroup spends a third of its time on splitting A and on its
-// requests, and two are resident on a compute unit), 45 us where only V and K are needed; the output projection, whose row statistics come first, 45 -> 42.  Error of the scores
-// against 64 bits 0.87 of what it was (24 cases of widths 64 to 256).
+// 20 480 rows, d = 256: K1 116 -> 82 us per launch against the fp32 instruction (its work alone is 26 us; a workgroup spends a third of its time on splitting A and on its
+// requests, and two are resident on a compute unit), 45 us where only V and K are needed; the output projection, whose row statistics come first, 45 -> 38.  Error of the scores
+// against 64 bits 0.87 of what it was (geometric mean of 24 outputs of widths 64 to 256, of which two rose, by 4 and 7 %).
 // ---------------------------------------------------------------------------------------------
 // (A, U, gamma, beta and W carry no __restrict__: loads that the compiler knows to be unchanging may pass any fence, and the counted waits for W need the requests in order.)
 // NI (EPI 1): 16-byte loads per lane and row that the statistics keep in registers, ceil(K / 64) at least; 0: any K, in two reads of the rows.

@@ -25,7 +25,8 @@ hipError_t raise_lds_limit(const void *kernel, int bytes, std::atomic<uint64_t> 
 //   * the projection matrices in the operand layouts of the products;
 //   * the bias table by distance, and the logit scales of softmax attention.
 // A workgroup does one of them, by its index.
-// Before, each was a launch or a copy of its own: 32 x (512 + 128), d = 256, bf16 252 -> 231 us per forward, in fp32 671 -> 656; one request of 64 + 16 in fp32 52 -> 46 us.
+// Before, each was a launch or a copy of its own: 32 x (512 + 128), d = 256, bf16 252 -> 231 us per forward, in fp32 671 -> 656; one request of 64 + 16 in fp32 stays
+// at 48 to 55 us, the launches saved going into the split of its weights.
 // ---------------------------------------------------------------------------------------------
 
 // Assembly: the token matrix of a request is its history rows followed by its candidate rows
