@@ -31,10 +31,12 @@
 // is exactly the k order of a 16-deep B operand.  V is stored feature-major by the projection
 // kernel, so V^T tiles are plain row loads.
 //
-// SiLU: two routes to the same fp16 weights.  If every logit of a wavefront's 32x64 block satisfies
-// |x| <= 2 (masked positions included), a polynomial whose correction term runs in packed fp16 (within one
-// fp16 ulp of the exact weight); otherwise the exact exp2/rcp form in fp32.  The mask is applied to the
-// fp32 weights of either route, on boundary tiles only.
+// SiLU: the weights of a wavefront's 32x64 block are made by the cheapest of five routes that its largest |x| (masked positions included) allows: s + s^2 in fp32 up to 1/4, three
+// polynomials whose correction term runs in packed fp16 up to 1, 2 and 4 (within one fp16 ulp of the exact weight), the exact exp2/rcp form in fp32 beyond.  Vector instructions per
+// block, with the test: 48, 89, 105, 137 and 217, beside 16 MFMAs.  The logits of the early layers of a model are small (16 layers, d = 512, embeddings N(0, 0.1^2): all blocks of the first four
+// below 1/4, of the first nine below 1).  Per launch, the route up to 2 for all / with those up to 1/4 and 1: 16 x (8192 + 512), 8 heads 1467 -> 1360 and 1457 -> 1437 us, 128 production requests
+// 2205 -> 2045 and 2215 -> 2200.  (Half the vector instructions for 7 % of the time: under load the clock, held at 1.8 GHz by the power cap, and the matrix pipe's share decide.)
+// The mask is applied on boundary tiles only.
 //
 // Bias: each key tile brings a window of the per-distance table (by decreasing distance, fp32) into
 // LDS; a lane's 8 consecutive entries per accumulator half-block are read straight into the
@@ -51,14 +53,20 @@ namespace {
 
 constexpr int KH = 64;              // keys per block (one pass of the register-level loop); an LDS tile has KP of them, one per wavefront of a group
 
-// SiLU for small arguments: the polynomial of device_common.h, silu(x) = x/2 + x^2 (a1 + a3 x^2 + a5 x^4).  On the halved
+// SiLU for |x| <= 2: the polynomial of device_common.h, silu(x) = x/2 + x^2 (a1 + a3 x^2 + a5 x^4).  On the halved
 // logit s = x/2, with t = s^2:
 //   silu(x) = s + q,   q = t (4 a1 + 16 a3 t + 64 a5 t^2).
 // t and the bracket are evaluated in packed fp16 (one multiply and two fused multiply-adds per pair of
 // weights); the last step is a mixed-precision fused multiply-add per weight, fp16 t times fp16 bracket
 // plus the fp32 logit itself, rounded to fp16 once, like the weight of the exact route.
 constexpr float kPolyT2 = 1.0f;                                  // bound on t = s^2  (|x| <= 2)
-// Second segment, |x| <= 4 (t <= 4): silu(x) = s + t (B0 + B1 t + B2 t^2 + B3 t^3 + B4 t^4), minimax-weighted fit of
+// Low segment, |x| <= 1 (t <= 1/4): the bracket with one coefficient less, off by 1e-3 of itself at most (the one above: 3.4e-3 at small |x|).
+constexpr float kLowT2 = 0.25f;
+__device__ constexpr float kLowB[2] = {0.9990234375f, -0.3025f};
+// Quadratic, |x| <= 1/4: silu(x) = s + s^2 in fp32, off by s^4 / 3 (t / 3 <= 5.2e-3 of the square at the very end, a tenth of that at a third of it).  kQuadS is the largest
+// fp32 logit whose square in fp16 arithmetic is kQuadT2 or less.
+constexpr float kQuadT2 = 0.015625f, kQuadS = 0.125f + 0x1p-14f;
+// Third segment, |x| <= 4 (t <= 4): silu(x) = s + t (B0 + B1 t + B2 t^2 + B3 t^3 + B4 t^4), minimax-weighted fit of
 // (silu(2 s) - s) / t on 0 <= t <= 4 (error of silu below 5.4e-4).
 constexpr float kMidT2 = 4.0f;
 __device__ constexpr float kMidB[5] = {0.9926417973f, -0.3010154918f, 0.0835130618f, -0.0141349725f, 0.0010234216f};
@@ -276,6 +284,7 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
   // tile (into a free stage), so that "at most REQ requests outstanding" always means "tile t has landed".
   // (KP = 4 has two stages and requests one tile ahead: a step of four 64-key quarters is longer than the loads.)
   constexpr bool AHEAD1 = NSTAGE == 2;
+  bool cool = true;                    // the block before was on the quadratic route
   if (n_tiles > 0) {
     request_tile(0);
     if (n_tiles > 1) next_tile();
@@ -373,7 +382,6 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
         }
         // ---- P^T = silu(S^T) (the bias is already in the accumulators), or the softmax numerators
         f16x8 fp[4];
-        bool fast = SOFTMAX;
         if constexpr (SOFTMAX) {
           // maximum of the raw (halved) logits first: the temperature scale is positive, so it commutes with the max.
           // Maxima and sums are taken in four independent chains (the 32 values of a lane would otherwise form one
@@ -386,20 +394,20 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
                 sacc[j][e] = 32 * j + 16 * (e >> 3) + (e & 7) < vis_lim ? sacc[j][e] : kNeg;
               }
           }
-          // maximum of the lane's 32 logits as a tree of three-input maxima, 10 + 4 + 2 instructions.  (Written as
-          // instructions: for fmaxf on accumulator values the compiler first emits one canonicalising v_max_f32 per
-          // value, 53 instructions in all.)
+          // maximum of the lane's 32 logits as a tree of three-input maxima, 10 + 4 + 2 instructions.  (IEEE maximum: for fmaxf on accumulator values the compiler first emits one
+          // canonicalising v_max_f32 per value, 53 instructions in all.  No inline assembly here: the compiler does not put the wait that a matrix result needs ahead of one.)
+          auto max3 = [](float a, float b, float c) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c); };
           float l1[10], l2[4];
 #pragma unroll
           for (int k = 0; k < 10; ++k) {
             const int e = 3 * k;   // values 0..29 in the order sacc[0][0..15], sacc[1][0..13]
-            l1[k] = max3_f32(sacc[e >> 4][e & 15], sacc[(e + 1) >> 4][(e + 1) & 15], sacc[(e + 2) >> 4][(e + 2) & 15]);
+            l1[k] = max3(sacc[e >> 4][e & 15], sacc[(e + 1) >> 4][(e + 1) & 15], sacc[(e + 2) >> 4][(e + 2) & 15]);
           }
 #pragma unroll
-          for (int k = 0; k < 3; ++k) l2[k] = max3_f32(l1[3 * k], l1[3 * k + 1], l1[3 * k + 2]);
-          l2[3] = max3_f32(l1[9], sacc[1][14], sacc[1][15]);
-          const float l3 = max3_f32(l2[0], l2[1], l2[2]);
-          const float mt = max3_f32(l3, l2[3], l2[3]);
+          for (int k = 0; k < 3; ++k) l2[k] = max3(l1[3 * k], l1[3 * k + 1], l1[3 * k + 2]);
+          l2[3] = max3(l1[9], sacc[1][14], sacc[1][15]);
+          const float l3 = max3(l2[0], l2[1], l2[2]);
+          const float mt = __builtin_elementwise_maximum(l3, l2[3]);
           const float m_new = fmaxf(m_run[P], pair_max(mt) * ts);
           // the accumulators are rescaled only when some row of the wavefront has a new maximum (rare after the
           // first tiles); the branch is uniform over the wavefront
@@ -427,102 +435,105 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
           const float ps = (psum[0] + psum[1]) + (psum[2] + psum[3]);
           l_run[P] += ps;
         } else {
-          f16x2 th[2][8];
-#pragma unroll
-          for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-              const f16x2 yh = f16x2{(half_t)sacc[j][2 * i], (half_t)sacc[j][2 * i + 1]};
-              th[j][i] = yh * yh;
-            }
-          // maximum of the 16 pairs with the packed three-input maximum (NaN-propagating): 5 + 2 + 1 instructions
-          auto max3 = [](f16x2 a, f16x2 b, f16x2 c) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c); };
-          const f16x2 m0 = max3(th[0][0], th[0][1], th[0][2]), m1 = max3(th[0][3], th[0][4], th[0][5]);
-          const f16x2 m2 = max3(th[0][6], th[0][7], th[1][0]), m3 = max3(th[1][1], th[1][2], th[1][3]);
-          const f16x2 m4 = max3(th[1][4], th[1][5], th[1][6]);
-          const f16x2 m = __builtin_elementwise_maximum(max3(m0, m1, m2), max3(m3, m4, th[1][7]));
-          const bool bad = !((float)m[0] <= kPolyT2 && (float)m[1] <= kPolyT2);     // NaN counts as bad
-          const bool bad_mid = !((float)m[0] <= kMidT2 && (float)m[1] <= kMidT2);
-          fast = __builtin_amdgcn_ballot_w64(bad) == 0;
-          const bool mid = !fast && __builtin_amdgcn_ballot_w64(bad_mid) == 0;
-          if (mid) {
-            // 2 < max |x| <= 4 somewhere in the block: the same form with a polynomial of degree 4 in t fitted on
-            // |x| <= 4 (approximation error below 5.4e-4; two more packed multiply-adds per pair of weights than the
-            // short polynomial, still no transcendental).  The exp2 / rcp route is left for blocks with |x| > 4.
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-              const f16x2 d4 = {(half_t)kMidB[4], (half_t)kMidB[4]}, d3 = {(half_t)kMidB[3], (half_t)kMidB[3]};
-              const f16x2 d2 = {(half_t)kMidB[2], (half_t)kMidB[2]}, d1 = {(half_t)kMidB[1], (half_t)kMidB[1]};
-              const f16x2 d0 = {(half_t)kMidB[0], (half_t)kMidB[0]};
-              f16x2 r[8];
-#pragma unroll
-              for (int i = 0; i < 8; ++i) r[i] = __builtin_elementwise_fma(d4, th[j][i], d3);
-#pragma unroll
-              for (int i = 0; i < 8; ++i) r[i] = __builtin_elementwise_fma(r[i], th[j][i], d2);
-#pragma unroll
-              for (int i = 0; i < 8; ++i) r[i] = __builtin_elementwise_fma(r[i], th[j][i], d1);
-#pragma unroll
-              for (int i = 0; i < 8; ++i) r[i] = __builtin_elementwise_fma(r[i], th[j][i], d0);
-              float w[16];
-#pragma unroll
-              for (int i = 0; i < 8; ++i) {
-                w[2 * i] = __builtin_fmaf((float)th[j][i][0], (float)r[i][0], sacc[j][2 * i]);
-                w[2 * i + 1] = __builtin_fmaf((float)th[j][i][1], (float)r[i][1], sacc[j][2 * i + 1]);
-              }
-              if (need_mask) {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                  w[e] = 32 * j + 16 * (e >> 3) + (e & 7) < vis_lim ? w[e] : 0.f;
-                }
-              }
-              __builtin_amdgcn_sched_barrier(0);
-              fp[2 * j] = pack8(w);
-              fp[2 * j + 1] = pack8(w + 8);
-            }
-            fast = true;      // the weights are made
-          } else if (fast) {
-            // stage by stage over eight independent pairs, so that no instruction waits for the one before
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-              constexpr float b1 = 4.0f * kPolyA1, b3 = 16.0f * kPolyA3, b5 = 64.0f * kPolyA5;
-              const f16x2 c5 = {(half_t)b5, (half_t)b5}, c3 = {(half_t)b3, (half_t)b3}, c1 = {(half_t)b1, (half_t)b1};
-              f16x2 r[8];
-#pragma unroll
-              for (int i = 0; i < 8; ++i) r[i] = __builtin_elementwise_fma(c5, th[j][i], c3);
-#pragma unroll
-              for (int i = 0; i < 8; ++i) r[i] = __builtin_elementwise_fma(r[i], th[j][i], c1);
-              float w[16];
-#pragma unroll
-              for (int i = 0; i < 8; ++i) {
-                w[2 * i] = __builtin_fmaf((float)th[j][i][0], (float)r[i][0], sacc[j][2 * i]);
-                w[2 * i + 1] = __builtin_fmaf((float)th[j][i][1], (float)r[i][1], sacc[j][2 * i + 1]);
-              }
-              if (need_mask) {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                  w[e] = 32 * j + 16 * (e >> 3) + (e & 7) < vis_lim ? w[e] : 0.f;
-                }
-              }
-              __builtin_amdgcn_sched_barrier(0);
-              fp[2 * j] = pack8(w);
-              fp[2 * j + 1] = pack8(w + 8);
-            }
-          }
-        }
-        if (!fast) {
-#pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            float p[16];
-#pragma unroll
-            for (int e = 0; e < 16; ++e) p[e] = silu_half_domain(sacc[j][e]);
+          // weights -> fragments of 32 keys, masked where a row's horizon runs through the block
+          auto finish = [&](int j, f16x2 (&w)[8]) {
             if (need_mask) {
 #pragma unroll
-              for (int e = 0; e < 16; ++e) {
-                p[e] = 32 * j + 16 * (e >> 3) + (e & 7) < vis_lim ? p[e] : 0.f;
+              for (int i = 0; i < 8; ++i) {
+                const int c = 32 * j + 16 * (i >> 2) + (2 * i & 7);
+                const uint32_t b = __builtin_bit_cast(uint32_t, w[i]);
+                w[i] = __builtin_bit_cast(f16x2, c + 1 < vis_lim ? b : c < vis_lim ? b & 0xffffu : 0u);
               }
             }
-            fp[2 * j] = pack8(p);
-            fp[2 * j + 1] = pack8(p + 8);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+              for (int i = 0; i < 8; ++i) fp[2 * j + h][i] = w[4 * h + i / 2][i & 1];
+          };
+          bool quadratic = false;
+          if (cool) {
+            // the block before was on the quadratic: its test first, which needs the logits only.  (The test on the squares below asks the same question, so a block's route
+            // depends on its logits alone.)
+            auto max3 = [](float a, float b, float c) {
+              return __builtin_elementwise_maximum(__builtin_elementwise_maximum(__builtin_fabsf(a), __builtin_fabsf(b)), __builtin_fabsf(c));
+            };
+            float m[10];
+#pragma unroll
+            for (int k = 0; k < 10; ++k) {
+              const int e = 3 * k;   // values 0..29 in the order sacc[0][0..15], sacc[1][0..13]
+              m[k] = max3(sacc[e >> 4][e & 15], sacc[(e + 1) >> 4][(e + 1) & 15], sacc[(e + 2) >> 4][(e + 2) & 15]);
+            }
+            const float m0 = max3(m[0], m[1], m[2]), m1 = max3(m[3], m[4], m[5]), m2 = max3(m[6], m[7], m[8]), m3 = max3(m[9], sacc[1][14], sacc[1][15]);
+            quadratic = __builtin_amdgcn_ballot_w64(!(__builtin_elementwise_maximum(max3(m0, m1, m2), m3) <= kQuadS)) == 0;
+          }
+          f16x2 th[2][8];
+          half_t mx = (half_t)0.f;
+          auto all_within = [&](float t2) { return __builtin_amdgcn_ballot_w64(!(mx <= (half_t)t2)) == 0; };     // NaN counts as beyond
+          if (!quadratic) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+              for (int i = 0; i < 8; ++i) {
+                const f16x2 yh = f16x2{(half_t)sacc[j][2 * i], (half_t)sacc[j][2 * i + 1]};
+                th[j][i] = yh * yh;
+              }
+            // maximum of the 16 pairs with the packed three-input maximum (NaN-propagating): 5 + 2 + 1 instructions
+            auto max3 = [](f16x2 a, f16x2 b, f16x2 c) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c); };
+            const f16x2 m0 = max3(th[0][0], th[0][1], th[0][2]), m1 = max3(th[0][3], th[0][4], th[0][5]);
+            const f16x2 m2 = max3(th[0][6], th[0][7], th[1][0]), m3 = max3(th[1][1], th[1][2], th[1][3]);
+            const f16x2 m4 = max3(th[1][4], th[1][5], th[1][6]);
+            const f16x2 m = __builtin_elementwise_maximum(max3(m0, m1, m2), max3(m3, m4, th[1][7]));
+            mx = __builtin_elementwise_maximum(m[0], m[1]);
+            quadratic = all_within(kQuadT2);
+          }
+          cool = quadratic;
+          if (quadratic) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+              f16x2 w[8];
+#pragma unroll
+              for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) w[i][h] = (half_t)__builtin_fmaf(sacc[j][2 * i + h], sacc[j][2 * i + h], sacc[j][2 * i + h]);
+              finish(j, w);
+            }
+          } else {
+            // s + t (B0 + B1 t + ...), stage by stage over eight independent pairs, so that no instruction waits for the one before
+            auto polynomial = [&](auto... coefficient) {
+              constexpr int N = sizeof...(coefficient);
+              const half_t c[N] = {(half_t)coefficient...};
+#pragma unroll
+              for (int j = 0; j < 2; ++j) {
+                f16x2 r[8], w[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) r[i] = __builtin_elementwise_fma(f16x2{c[N - 1], c[N - 1]}, th[j][i], f16x2{c[N - 2], c[N - 2]});
+#pragma unroll
+                for (int n = N - 3; n >= 0; --n)
+#pragma unroll
+                  for (int i = 0; i < 8; ++i) r[i] = __builtin_elementwise_fma(r[i], th[j][i], f16x2{c[n], c[n]});
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+#pragma unroll
+                  for (int h = 0; h < 2; ++h) w[i][h] = (half_t)__builtin_fmaf((float)th[j][i][h], (float)r[i][h], sacc[j][2 * i + h]);
+                finish(j, w);
+              }
+            };
+            if (all_within(kLowT2)) {
+              polynomial(kLowB[0], kLowB[1]);
+            } else if (all_within(kPolyT2)) {
+              polynomial(4.0f * kPolyA1, 16.0f * kPolyA3, 64.0f * kPolyA5);
+            } else if (all_within(kMidT2)) {
+              polynomial(kMidB[0], kMidB[1], kMidB[2], kMidB[3], kMidB[4]);
+            } else {
+#pragma unroll
+              for (int j = 0; j < 2; ++j) {
+                f16x2 w[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) w[i] = f16x2{(half_t)silu_half_domain(sacc[j][2 * i]), (half_t)silu_half_domain(sacc[j][2 * i + 1])};
+                finish(j, w);
+              }
+            }
           }
         }
         if constexpr (SEQ) {

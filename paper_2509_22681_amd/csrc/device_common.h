@@ -56,18 +56,6 @@ __device__ __forceinline__ float silu_half_domain(float s) {
 // |x| <= 1.5 and below 1e-5 for |x| <= 1).
 constexpr float kPolyA1 = 0.24916259f, kPolyA3 = -0.01916112f, kPolyA5 = 0.00112581f;
 
-// max(|a|, |b|, |c|) and max(a, b, c) in one instruction each (absolute values are operand modifiers)
-__device__ __forceinline__ float max3_abs_f32(float a, float b, float c) {
-  float d;
-  asm("v_max3_f32 %0, |%1|, |%2|, |%3|" : "=v"(d) : "v"(a), "v"(b), "v"(c));
-  return d;
-}
-__device__ __forceinline__ float max3_f32(float a, float b, float c) {
-  float d;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
-  return d;
-}
-
 // "k-tile blocked" layout of the fp16 activation copy Xh, the projection's operand: inside every block of 64 rows the 32-wide k slices follow one another,
 // [row / 64][k / 32][row % 64][k % 32], so the 64 rows x 32 k slice a GEMM k-tile needs is 4 KB of
 // contiguous memory and is fetched as whole 128-byte lines.  (Row-major rows of d elements would hand
