@@ -96,10 +96,11 @@ __device__ __forceinline__ f16x8 pack8(const float *v) {
 // sits alone on its CU and its run time is the chain of key tiles of its longest row.  There a row's keys are summed in four
 // partial outputs, 64-key block i going to partial output i % 4, which are added in a fixed order at the end; the sums are
 // grouped differently than with KP = 1, so the two configurations agree to rounding, not bit for bit.  Two shapes with the same bits:
-//   KP = 4: 64 query rows, 8 wavefronts, key tiles of 256 in two LDS stages; each of a group's FOUR wavefronts takes one 64-key quarter
+//   KP = 4: 64 query rows, 8 wavefronts and 4 feeders, key tiles of 256 in two LDS stages; each of a group's FOUR wavefronts takes one 64-key quarter
 //     of every tile (two wavefronts per SIMD, so one's MFMAs run under the other's VALU work).  The chain is a quarter as
 //     many steps, and a request of a few thousand rows has enough query tiles for every CU.  One request of 2573 + 217, 8 heads:
-//     22 us per launch (32 with query tiles of 128 and two wavefronts per group on key tiles of 128).
+//     22 us per launch (32 with query tiles of 128 and two wavefronts per group on key tiles of 128), 20 with the feeders: four wavefronts that do nothing but make the tiles'
+//     66 requests of 1 KB, 1000 cycles of the compute unit's address path per tile, which the others else wait out ahead of their arithmetic.
 //   KP = 2: 128 query rows, 8 wavefronts, key tiles of 128 in four LDS stages; each of a group's two wavefronts takes one 64-key half of every
 //     tile, into one of two accumulator sets by the tile's parity.  For latency handles that are given enough rows to
 //     fill the chip all the same: half the K and V traffic per query row (the rule and both sides' times are at kLatencyWideTiles).
@@ -107,17 +108,18 @@ __device__ __forceinline__ f16x8 pack8(const float *v) {
 // at 1750 cycles per 64 of them (760 for the weights, 370 each for the two products, the rest bias and requests).  The key tiles of KP = 4, but the four wavefronts of a
 // group only make the weights, each of its 64 keys, and leave them in LDS (over the tile's K, which everybody has read; behind the stages with heads of 32);
 // one wavefront per feature block then adds V^T P^T up over the tile in the order of the keys.  That is the one-wavefront order, block by block of 64 keys on the same SiLU route, so the
-// bits are the same.  An item of 128 rows is two workgroups of 64.  One request of 1024 + 256, 8 heads, 16 layers: 17.5 -> 13 us per launch, forward 642 -> 556 us.
+// bits are the same.  An item of 128 rows is two workgroups of 64.  One request of 1024 + 256, 8 heads, 16 layers: 17.5 -> 13 us per launch, forward 642 -> 556 us; with the feeders 12.8 -> 11.7 us.
 // (Pointwise weights only: a running maximum would have to pass from wavefront to wavefront.)
 template <int DH, bool SOFTMAX, int KP, bool NT, bool SEQ = false>
-__global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_kernel(PlanePtrs planes, const float *__restrict__ bias_lh,
+__global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_kernel(PlanePtrs planes, const float *__restrict__ bias_lh,
                                                            const float *__restrict__ tscale_h,
                                                            half_t *__restrict__ O, const AttnItem *__restrict__ items,
                                                            int H, int d, int D, int64_t ws_rows) {
   constexpr bool KSPLIT = KP > 1;
   static_assert(!SEQ || (KP == 4 && !SOFTMAX), "the key-ordered split is the KP = 4 one, pointwise");
   constexpr int NP = KP == 2 ? 2 : 1;  // partial outputs per wavefront
-  constexpr int NW = KSPLIT ? 8 : 4;   // wavefronts per workgroup
+  constexpr int NW = KSPLIT ? 8 : 4;   // wavefronts per workgroup that compute
+  constexpr bool FEEDERS = KP == 4;    // four more that make the requests
   constexpr int QG = NW / KP;          // groups
   constexpr int QT = 32 * QG;          // query rows per workgroup (one 32-row MFMA block per group)
   static_assert(QT == (KP == 4 ? kAttnQTileLatency : KP == 2 ? kAttnQTileLatencyWide : kAttnQTileBf16), "the planner's query tiles");
@@ -231,18 +233,19 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
   // vector address arithmetic.  (Lane offsets stay below 2^32: at most 64 rows of d, resp. DH rows of ws_rows.)
   const char *bK = (const char *)(Kp + (int64_t)it.kv_row * d);
   const char *bV = (const char *)(Vt + it.kv_row);
+  const int rw = wave % NW;              // the share of the requests (a feeder has two: of wavefronts rw and rw + 4)
   uint32_t oK, oV;
   // (candidate tiles shift the window by one slot: all their rows read it at the same slots, which then start on a
   // 16-byte boundary and leave as four-float reads)
-  const int dW0 = q_first + (QT - 1) + (it.is_cand ? 1 : 0) - (wave * 64 + lane);   // distance held by window slot 64 w + lane in tile 0
+  const int dW0 = q_first + (QT - 1) + (it.is_cand ? 1 : 0) - (rw * 64 + lane);   // distance held by window slot 64 w + lane in tile 0
   int sW = 0;                                                 // keys the next tile to request lies behind tile 0 (scalar)
   {
-    const int row = wave * (64 / KCH) + lane / KCH;
+    const int row = rw * (64 / KCH) + lane / KCH;
     const int c = (lane % KCH) ^ ((row >> KSH) & (KCH - 1));
     oK = (uint32_t)(row * d + c * 8) * 2u;
   }
   {
-    const int row = wave * (64 / VCH) + lane / VCH;
+    const int row = rw * (64 / VCH) + lane / VCH;
     const int c = (lane % VCH) ^ ((row >> VSH) & VKEY);
     oV = (uint32_t)((int64_t)row * ws_rows + c * 8) * 2u;
   }
@@ -253,21 +256,65 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
     asm volatile("" : "+v"(oK), "+v"(oV));
 #pragma unroll
     for (int i = 0; i < NKI / NW; ++i)
-      __builtin_amdgcn_global_load_lds((gvoid *)(bK + (int64_t)(i * NW * (64 / KCH)) * d * 2 + oK), (lvoid *)(sb + (wave + NW * i) * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((gvoid *)(bK + (int64_t)(i * NW * (64 / KCH)) * d * 2 + oK), (lvoid *)(sb + (rw + NW * i) * 1024), 16, 0, 0);
 #pragma unroll
     for (int i = 0; i < NVI / NW; ++i)
-      __builtin_amdgcn_global_load_lds((gvoid *)(bV + (int64_t)(i * NW * (64 / VCH)) * ws_rows * 2 + oV), (lvoid *)(sb + K_BYTES + (wave + NW * i) * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((gvoid *)(bV + (int64_t)(i * NW * (64 / VCH)) * ws_rows * 2 + oV), (lvoid *)(sb + K_BYTES + (rw + NW * i) * 1024), 16, 0, 0);
     // every wavefront issues one window request, so that all of them have the same number of requests in
     // flight per tile (slots past the window are filled too and never read)
     uint32_t oW = (uint32_t)max(0, min(D - 1, dW0 - sW)) * 4u;
     asm volatile("" : "+v"(oW));
-    __builtin_amdgcn_global_load_lds((gvoid *)((const char *)bias + oW), (lvoid *)(sb + K_BYTES + V_BYTES + wave * 256), 4, 0, 0);
+    __builtin_amdgcn_global_load_lds((gvoid *)((const char *)bias + oW), (lvoid *)(sb + K_BYTES + V_BYTES + rw * 256), 4, 0, 0);
   };
   auto next_tile = [&]() {
     bK += (int64_t)KT * d * 2;
     bV += KT * 2;
     sW += KT;
   };
+
+  if constexpr (FEEDERS) {
+    // A feeder requests the tiles, two shares of them, one tile ahead of the others and in step with them: they meet at the same barriers.
+    if (wave >= NW) {
+      static_assert(NSTAGE == 2 && NW == 8, "two stages, eight shares");
+      const int row2 = (rw + 4) * (64 / VCH) + lane / VCH, k2 = (rw + 4) * (64 / KCH) + lane / KCH;
+      uint32_t oK2 = (uint32_t)(k2 * d + ((lane % KCH) ^ ((k2 >> KSH) & (KCH - 1))) * 8) * 2u;
+      uint32_t oV2 = (uint32_t)((int64_t)row2 * ws_rows + ((lane % VCH) ^ ((row2 >> VSH) & VKEY)) * 8) * 2u;
+      auto request_second = [&](int stage) {
+        char *sb = lds + stage * STAGE;
+        asm volatile("" : "+v"(oK2), "+v"(oV2));
+#pragma unroll
+        for (int i = 0; i < NKI / NW; ++i)
+          __builtin_amdgcn_global_load_lds((gvoid *)(bK + (int64_t)(i * NW * (64 / KCH)) * d * 2 + oK2), (lvoid *)(sb + (rw + 4 + NW * i) * 1024), 16, 0, 0);
+#pragma unroll
+        for (int i = 0; i < NVI / NW; ++i)
+          __builtin_amdgcn_global_load_lds((gvoid *)(bV + (int64_t)(i * NW * (64 / VCH)) * ws_rows * 2 + oV2), (lvoid *)(sb + K_BYTES + (rw + 4 + NW * i) * 1024), 16, 0, 0);
+        uint32_t oW = (uint32_t)max(0, min(D - 1, dW0 - 256 - sW)) * 4u;
+        asm volatile("" : "+v"(oW));
+        __builtin_amdgcn_global_load_lds((gvoid *)((const char *)bias + oW), (lvoid *)(sb + K_BYTES + V_BYTES + (rw + 4) * 256), 4, 0, 0);
+      };
+      for (int t = 0; t < n_tiles; ++t) {
+        if (t == 0) {
+          request_tile(0);
+          request_second(0);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();                      // tile t has landed, and everybody has left tile t - 1
+        if (t + 1 < n_tiles) {
+          next_tile();
+          request_tile((t + 1) & 1);
+          request_second((t + 1) & 1);
+        }
+        if constexpr (SEQ) {
+          if (P_OVER_K) __builtin_amdgcn_s_barrier();      // (the one behind S^T)
+          __builtin_amdgcn_s_barrier();                    // (the weights of the tile are complete)
+        }
+      }
+      __builtin_amdgcn_s_barrier();                        // the keys are done
+#pragma unroll
+      for (int i = 0; i < (SEQ ? 1 : 2); ++i) __builtin_amdgcn_s_barrier();   // (those of the end)
+      return;
+    }
+  }
 
   // Window slot of (my row, key 0 of the tile) is QT-1 - m + 8*lhalf with m the row's index in the
   // workgroup tile; keys further right sit at increasing slots.  Candidate rows all sit at the same distance
@@ -284,13 +331,12 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
 
   // Ring of NSTAGE stages, requests two tiles ahead.  Past the last tile the requests repeat the last
   // tile (into a free stage), so that "at most REQ requests outstanding" always means "tile t has landed".
-  // (KP = 4 has two stages and requests one tile ahead: a step of four 64-key quarters is longer than the loads.)
-  constexpr bool AHEAD1 = NSTAGE == 2;
+  // (KP = 4 has two stages, and its feeders request one tile ahead: a step of four 64-key quarters is longer than the loads.)
   bool cool = true;                    // the block before was on the quadratic route
-  if (n_tiles > 0) {
+  if (!FEEDERS && n_tiles > 0) {
     request_tile(0);
     if (n_tiles > 1) next_tile();
-    if (!AHEAD1) request_tile(1);
+    request_tile(1);
   }
   // The query fragments are requested behind the first two tiles, not ahead of them: the tiles are what the first
   // step waits for.  (The waits below count requests in order: with at most REQ outstanding, the query loads and
@@ -305,17 +351,12 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
     const char *sb = lds + ST * STAGE;
     // tile t has landed for this wavefront; past the barrier it has landed for all of them, and everybody
     // has left tile t-1, whose stage the next request overwrites
-    if (AHEAD1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (FEEDERS) asm volatile("" ::: "memory");
     else if (REQ == 5) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
     else if (REQ == 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
-    if constexpr (AHEAD1) {
-      if (t + 1 < n_tiles) {
-        request_tile(ST ^ 1);
-        next_tile();
-      }
-    } else {
+    if constexpr (!FEEDERS) {
       if (t + 2 < n_tiles) next_tile();
       request_tile((ST + 2) % NSTAGE);
     }
@@ -454,7 +495,7 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
 #pragma unroll
               for (int i = 0; i < 8; ++i) fp[2 * j + h][i] = w[4 * h + i / 2][i & 1];
           };
-          bool quadratic = false;
+          bool quadratic = false, low = false, poly = false;
           if (cool) {
             // the block before was on the quadratic: its test first, which needs the logits only.  (The test on the squares below asks the same question, so a block's route
             // depends on its logits alone.)
@@ -488,7 +529,9 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
             const f16x2 m4 = max3(th[1][4], th[1][5], th[1][6]);
             const f16x2 m = __builtin_elementwise_maximum(max3(m0, m1, m2), max3(m3, m4, th[1][7]));
             mx = __builtin_elementwise_maximum(m[0], m[1]);
-            quadratic = all_within(kQuadT2);
+            poly = all_within(kPolyT2);
+            low = poly && all_within(kLowT2);
+            quadratic = low && all_within(kQuadT2);
           }
           cool = quadratic;
           if (quadratic) {
@@ -522,9 +565,9 @@ __global__ __launch_bounds__(KP > 1 ? 512 : 256, KP > 1 ? 1 : 3) void attn_mfma_
                 finish(j, w);
               }
             };
-            if (all_within(kLowT2)) {
+            if (low) {
               polynomial(kLowB[0], kLowB[1]);
-            } else if (all_within(kPolyT2)) {
+            } else if (poly) {
               polynomial(4.0f * kPolyA1, 16.0f * kPolyA3, 64.0f * kPolyA5);
             } else if (all_within(kMidT2)) {
               polynomial(kMidB[0], kMidB[1], kMidB[2], kMidB[3], kMidB[4]);
@@ -848,7 +891,7 @@ static hipError_t latency_setup() {
 template <int DH, bool SM, int KP>
 static void launch_key_split(int grid, PlanePtrs planes, const float *bias_lh, const float *tscale_h, half_t *O,
                              const AttnItem *items, const Shape &sh, hipStream_t s) {
-  attn_mfma_kernel<DH, SM, KP, false><<<grid, 512, key_split_lds_bytes<DH, KP>(), s>>>(planes, bias_lh, tscale_h, O, items, sh.H, sh.d, sh.D, sh.ws_rows);
+  attn_mfma_kernel<DH, SM, KP, false><<<grid, KP == 4 ? 768 : 512, key_split_lds_bytes<DH, KP>(), s>>>(planes, bias_lh, tscale_h, O, items, sh.H, sh.d, sh.D, sh.ws_rows);
 }
 
 hipError_t attn_setup(const Shape &sh) {
@@ -892,7 +935,7 @@ void launch_attn_bf16(PlanePtrs planes, const float *bias_lh, const float *tscal
     return;
   }
   if (!sh.softmax && attn_key_ordered(grid, n_items, n_cand, longest)) {
-#define SEQ_LAUNCH(DHV) attn_mfma_kernel<DHV, false, 4, false, true><<<2 * grid, 512, key_split_lds_bytes<DHV, 4, true>(), s>>>(planes, bias_lh, tscale_h, (half_t *)O, items, sh.H, sh.d, sh.D, sh.ws_rows)
+#define SEQ_LAUNCH(DHV) attn_mfma_kernel<DHV, false, 4, false, true><<<2 * grid, 768, key_split_lds_bytes<DHV, 4, true>(), s>>>(planes, bias_lh, tscale_h, (half_t *)O, items, sh.H, sh.d, sh.D, sh.ws_rows)
     if (sh.dh == 32) SEQ_LAUNCH(32);
     else SEQ_LAUNCH(64);
 #undef SEQ_LAUNCH
