@@ -10,14 +10,14 @@
 // rescaling.
 //
 // Work decomposition: one workgroup = (query tile of 128 rows, head); 4 wavefronts of 32 query rows
-// (one 32-row MFMA block each: about 160 registers per lane and 51 KB of LDS per workgroup, so three
+// (one 32-row MFMA block each: about 150 registers per lane and 38 KB of LDS per workgroup, so three
 // workgroups = three wavefronts per SIMD fit a CU; the kernel is bound by MFMA + VALU issue, and a third
 // wavefront per SIMD fills part of the issue slots that two leave empty: measured 1.46x from one to two,
 // 1.04x from two to three, the latter net of twice the K/V tile traffic of 256-row query tiles).  Keys
-// are walked in tiles of 64.  A tile (K rows, V^T rows and the window of the bias table it needs) is
-// brought into a ring of three LDS stages by LDS-DMA loads (global_load_lds: no staging registers, no
-// LDS store instructions), requested two tiles ahead right after the barrier that opens the current
-// tile.  LDS rows are unpadded (a DMA instruction fills 1 KB of consecutive LDS) and 16-byte chunks are
+// are walked in tiles of 64.  A tile (K rows and V^T rows) is brought into one of two LDS stages by LDS-DMA loads
+// (global_load_lds: no staging registers, no LDS store instructions), requested one tile ahead right after the
+// barrier that opens the current tile (three tiles' time of a wavefront alone, as three share a SIMD: a third
+// stage with requests two tiles ahead is no faster).  LDS rows are unpadded (a DMA instruction fills 1 KB of consecutive LDS) and 16-byte chunks are
 // XOR-swizzled so that 16 consecutive lanes of a fragment read fall into 16 different slots of the 256
 // bytes the LDS serves per clock.
 //
@@ -38,10 +38,13 @@
 // 2205 -> 2045 and 2215 -> 2200.  (Half the vector instructions for 7 % of the time: under load the clock, held at 1.8 GHz by the power cap, and the matrix pipe's share decide.)
 // The mask is applied on boundary tiles only.
 //
-// Bias: each key tile brings a window of the per-distance table (by decreasing distance, fp32) into
-// LDS; a lane's 8 consecutive entries per accumulator half-block are read straight into the
-// accumulator registers, so the bias add costs LDS bandwidth but no VALU instruction (on this
-// chip VALU and MFMA work of one SIMD largely serialise, so every VALU instruction saved counts).
+// Bias: a lane's eight consecutive entries (by decreasing distance, fp32) per accumulator half-block are read from LDS
+// straight into the accumulator registers, so the bias add costs LDS bandwidth but no VALU instruction (on this
+// chip VALU and MFMA work of one SIMD largely serialise, so every VALU instruction saved counts).  The rows of a
+// wavefront start at all offsets; a ring of 256 entries in four copies, one entry apart from each other, makes every
+// lane's reads aligned 16-byte ones (beside a window per stage read by dwords, forwards: 16 x (8192 + 512), 8 heads, 2 layers
+// 2310 -> 2283 us, 40 x (2500 + 300), 4 layers 2894 -> 2875, softmax 3047 -> 2978; softmax with heads of 32 3571 -> 3590: that
+// instance keeps the window and three stages).  A tile adds 64 entries.
 #include <type_traits>
 
 #include "device_common.h"
@@ -124,7 +127,8 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
   constexpr int QT = 32 * QG;          // query rows per workgroup (one 32-row MFMA block per group)
   static_assert(QT == (KP == 4 ? kAttnQTileLatency : KP == 2 ? kAttnQTileLatencyWide : kAttnQTileBf16), "the planner's query tiles");
   static_assert(KP == 1 || KP * NP == 4, "the latency configuration sums in four partial outputs");
-  constexpr int NSTAGE = KP == 4 ? 2 : KP == 2 ? 4 : 3;  // LDS stages (ring)
+  constexpr bool BRING = KP == 1 && (DH == 64 || !SOFTMAX);   // bias: a ring over all tiles in four copies, beside the stages, instead of a window in each
+  constexpr int NSTAGE = KP == 2 ? 4 : KP == 4 || BRING ? 2 : 3;  // LDS stages (ring)
   constexpr int KT = KH * KP;          // keys per LDS stage
   constexpr int BW = QT + KT;          // bias window per key tile: slot u holds bias[q_first + QT-1 - k0 - u]
   static_assert(BW <= 64 * NW, "one 64-slot window request per wavefront");
@@ -137,7 +141,8 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
   constexpr int VKEY = VCH == 8 ? 7 : 15;          // swizzle key: XORed into the chunk index inside 256 bytes
   constexpr int K_BYTES = KT * DH * 2;             // K tile [KT keys][DH]
   constexpr int V_BYTES = DH * KT * 2;             // V^T tile [DH][KT keys]
-  constexpr int W_BYTES = NW * 256;                // bias window: 64 slots per wavefront (BW <= 64 NW of them are used)
+  constexpr int BCOPY = (256 + 64) * 4 + 64;       // bytes of a copy: 256 slots, the first 64 again behind them, and a quarter of the banks to the next copy
+  constexpr int W_BYTES = BRING ? 0 : NW * 256;    // bias window: 64 slots per wavefront (BW <= 64 NW of them are used)
   constexpr int STAGE = K_BYTES + V_BYTES + W_BYTES;
   constexpr bool P_OVER_K = SEQ && K_BYTES >= NW * 4096;   // where the weights of a tile go: over its K, or behind the stages
   static_assert(K_BYTES % 1024 == 0 && V_BYTES % 1024 == 0 && STAGE % 256 == 0, "stage parts start on 256-byte boundaries");
@@ -145,7 +150,7 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
   // the stages; the output patches of the wavefronts reuse them once the key loop is over.  The latency
   // configuration needs more than the 64 KB a static array may have and takes its stages from dynamic LDS.
   extern __shared__ __attribute__((aligned(256))) char lds_dynamic[];
-  __shared__ __attribute__((aligned(256))) char lds_static[KSPLIT ? 256 : NSTAGE * STAGE];
+  __shared__ __attribute__((aligned(256))) char lds_static[KSPLIT ? 256 : NSTAGE * STAGE + (BRING ? 4 * BCOPY : 0)];
   char *const lds = KSPLIT ? lds_dynamic : lds_static;
 
   const int head = blockIdx.x % H;
@@ -237,7 +242,7 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
   uint32_t oK, oV;
   // (candidate tiles shift the window by one slot: all their rows read it at the same slots, which then start on a
   // 16-byte boundary and leave as four-float reads)
-  const int dW0 = q_first + (QT - 1) + (it.is_cand ? 1 : 0) - (rw * 64 + lane);   // distance held by window slot 64 w + lane in tile 0
+  const int dW0 = q_first + (QT - 1) + (!BRING && it.is_cand ? 1 : 0) - (BRING ? rw + lane : rw * 64 + lane);   // distance held by window slot 64 w + lane in tile 0 (ring: slot lane of copy w)
   int sW = 0;                                                 // keys the next tile to request lies behind tile 0 (scalar)
   {
     const int row = rw * (64 / KCH) + lane / KCH;
@@ -260,11 +265,20 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
 #pragma unroll
     for (int i = 0; i < NVI / NW; ++i)
       __builtin_amdgcn_global_load_lds((gvoid *)(bV + (int64_t)(i * NW * (64 / VCH)) * ws_rows * 2 + oV), (lvoid *)(sb + K_BYTES + (rw + NW * i) * 1024), 16, 0, 0);
+    if constexpr (BRING) return;
     // every wavefront issues one window request, so that all of them have the same number of requests in
     // flight per tile (slots past the window are filled too and never read)
     uint32_t oW = (uint32_t)max(0, min(D - 1, dW0 - sW)) * 4u;
     asm volatile("" : "+v"(oW));
     __builtin_amdgcn_global_load_lds((gvoid *)((const char *)bias + oW), (lvoid *)(sb + K_BYTES + V_BYTES + rw * 256), 4, 0, 0);
+  };
+  // Bias ring: slots 64 b .. 64 b + 63 of the absolute index p, copy w by wavefront w; physical slot p % 256, the first 64 of them twice.
+  auto request_bias = [&](int b) {
+    uint32_t oW = (uint32_t)max(0, min(D - 1, dW0 - 64 * b)) * 4u;
+    asm volatile("" : "+v"(oW));
+    char *dst = lds + NSTAGE * STAGE + rw * BCOPY + (b & 3) * 256;
+    __builtin_amdgcn_global_load_lds((gvoid *)((const char *)bias + oW), (lvoid *)dst, 4, 0, 0);
+    if ((b & 3) == 0) __builtin_amdgcn_global_load_lds((gvoid *)((const char *)bias + oW), (lvoid *)(dst + 1024), 4, 0, 0);
   };
   auto next_tile = [&]() {
     bK += (int64_t)KT * d * 2;
@@ -319,7 +333,9 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
   // Window slot of (my row, key 0 of the tile) is QT-1 - m + 8*lhalf with m the row's index in the
   // workgroup tile; keys further right sit at increasing slots.  Candidate rows all sit at the same distance
   // from a key (m = 0), and their window is shifted by one slot: QT + 8*lhalf, a 16-byte boundary.
-  const int bias_idx = it.is_cand ? QT + 8 * lhalf : (QT - 1) - my_q_local + 8 * lhalf;
+  // Ring: value p of the index is p & ~3 of copy p & 3, so that a lane's four consecutive values are one aligned 16-byte read whatever its row.
+  const int bias_idx = BRING ? (QT - 1) - (it.is_cand ? 0 : my_q_local) + 8 * lhalf : it.is_cand ? QT + 8 * lhalf : (QT - 1) - my_q_local + 8 * lhalf;
+  const int ring_copy = NSTAGE * STAGE + (bias_idx & 3) * BCOPY, ring_at = (bias_idx & ~3) * 4;
   // fragment byte offsets inside a stage.  K (A operand of S^T): MFMA row m takes key pi32(m); per 32-key
   // block j the row advances by 32 (key bits 0..4 unchanged, so the swizzle key is the same).  V^T (A
   // operand of O^T): row = feature 32 b + l32, chunk = key / 8.
@@ -331,9 +347,13 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
 
   // Ring of NSTAGE stages, requests two tiles ahead.  Past the last tile the requests repeat the last
   // tile (into a free stage), so that "at most REQ requests outstanding" always means "tile t has landed".
-  // (KP = 4 has two stages, and its feeders request one tile ahead: a step of four 64-key quarters is longer than the loads.)
+  // (Two stages: one tile ahead, and no repetition.)
   bool cool = true;                    // the block before was on the quadratic route
-  if (!FEEDERS && n_tiles > 0) {
+  if (BRING && n_tiles > 0) {
+    request_tile(0);
+#pragma unroll
+    for (int b = 0; b < 3; ++b) request_bias(b);
+  } else if (!FEEDERS && n_tiles > 0) {
     request_tile(0);
     if (n_tiles > 1) next_tile();
     request_tile(1);
@@ -352,11 +372,18 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
     // tile t has landed for this wavefront; past the barrier it has landed for all of them, and everybody
     // has left tile t-1, whose stage the next request overwrites
     if (FEEDERS) asm volatile("" ::: "memory");
+    else if (BRING) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     else if (REQ == 5) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
     else if (REQ == 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
-    if constexpr (!FEEDERS) {
+    if constexpr (BRING) {
+      if (t + 1 < n_tiles) {
+        next_tile();
+        request_tile(ST ^ 1);
+        request_bias(t + 3);
+      }
+    } else if constexpr (!FEEDERS) {
       if (t + 2 < n_tiles) next_tile();
       request_tile((ST + 2) % NSTAGE);
     }
@@ -381,10 +408,10 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
           // one address register, the 32 reads use immediate offsets (the empty asm keeps the compiler
           // from folding constant parts of the address into every read as a separate add)
           typedef const __attribute__((address_space(3))) float *lds_cfloat;
-          lds_cfloat bp = (lds_cfloat)(sb + K_BYTES + V_BYTES) + (bias_idx + u * KH);
+          typedef const __attribute__((address_space(3))) f32x4 *lds_cf4;
+          lds_cfloat bp = BRING ? (lds_cfloat)(lds + ring_copy + ((ring_at + 4 * k0) & 1023)) : (lds_cfloat)(sb + K_BYTES + V_BYTES) + (bias_idx + u * KH);
           asm volatile("" : "+v"(bp));
-          if (it.is_cand) {
-            typedef const __attribute__((address_space(3))) f32x4 *lds_cf4;
+          if (BRING || it.is_cand) {
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
