@@ -27,7 +27,7 @@ namespace flame {
 namespace {
 
 // NWV wavefronts per workgroup, NBW 32-feature blocks per wavefront: d = 32 * NBW * NWV (four wavefronts for
-// d = 128, 256, 512; three for d = 96, 192, 384).  A workgroup takes RH 32-row halves of a 64-row block; its rows are dealt out
+// d = 128, 256, 512; three for d = 96, 192, 384; twice as many for d = 384 and 512 where a workgroup has a compute unit to itself).  A workgroup takes RH 32-row halves of a 64-row block; its rows are dealt out
 // RPW per wavefront in phase 1 (with three wavefronts the last one has rows to spare, which it skips).
 // CS workgroups share the rows (blockIdx.y): each repeats phase 1 and takes 1/CS of every wavefront's feature
 // blocks through phases 2 and 3.  RH = 2, CS = 1 is for launches that fill the chip.  RH = 1 and CS > 1 are for launches with few
@@ -40,9 +40,9 @@ namespace {
 // them all at once, where two run a second, nearly empty round; the registers for that come from the residual rows, which are
 // requested behind phase 1 instead of ahead of it, and a shorter W2 ring.  384 row blocks, two wavefronts against three: d = 256 24.0 -> 20.1 us, d = 192
 // 25.2 -> 19.8 us per launch.
-constexpr bool k3_dense(int cs, int rh, int nbw) { return rh == 1 && cs == 1 && nbw == 2; }
+constexpr bool k3_dense(int nwv, int cs, int rh, int nbw) { return nwv < 6 && rh == 1 && cs == 1 && nbw == 2; }
 template <int NWV, int NBW, int CS, int RH, bool NT>
-__global__ __launch_bounds__(64 * NWV, k3_dense(CS, RH, NBW) ? 3 : 2) void k3_fused_kernel(const half_t *__restrict__ O, const half_t *__restrict__ U,
+__global__ __launch_bounds__(64 * NWV, k3_dense(NWV, CS, RH, NBW) ? 3 : 2) void k3_fused_kernel(const half_t *__restrict__ O, const half_t *__restrict__ U,
                                                           const bf16_t *__restrict__ gamma, const bf16_t *__restrict__ beta,
                                                           const half_t *__restrict__ W2p, const bf16_t *__restrict__ b2,
                                                           half_t *__restrict__ Xh, half_t *__restrict__ Xl, int lo_is_zero,
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(64 * NWV, k3_dense(CS, RH, NBW) ? 3 : 2) void k3_fu
   constexpr int RPW = (ROWS + NWV * RB4 - 1) / (NWV * RB4) * RB4;   // rows per wavefront in phase 1 (with three wavefronts a few too many)
   constexpr bool EVEN = RPW * NWV == ROWS;
   constexpr bool EARLY = RH == 1;                // requests that do not wait for phase 1 go out ahead of it
-  constexpr bool DENSE = k3_dense(CS, RH, NBW);  // (but the residual behind it)
+  constexpr bool DENSE = k3_dense(NWV, CS, RH, NBW);  // (but the residual behind it)
   constexpr int NCHUNK = d / 8;                  // 16-byte chunks per row
   // Swizzle key of the gated rows in LDS.  A row of d fp16 is NCHUNK chunks; the MFMA operand reads take one chunk
   // column of 16 consecutive rows.  With NCHUNK a multiple of 16 the row pitch is a multiple of 256 bytes and the
@@ -306,13 +306,16 @@ bool k3_fused_supported(int d) { return d == 128 || d == 192 || d == 256 || d ==
 
 // Few row blocks: half blocks, with the features cut as long as that leaves one workgroup per compute unit at most (lone workgroups,
 // latency), then half blocks with uncut features.  Microseconds per launch, whole blocks / half blocks / half blocks with features cut
-// in two / in four:
+// in two / in four, all with three or four wavefronts:
 //   d = 512: 16 blocks 21.1 / 15.8 / 12.0 / 10.1, 64: 22.6 / 17.1 / 13.2 / 13.9, 66: 22.1 / 16.1, 128: 24.1 / 18.6 / 22.3 / 21.6, 256: 28.5 / 26.9
-//   (44 blocks in a model of 16 layers, whose W2 is in no L2 when a layer starts: 12.9 in two, 14.6 in four)
 //   d = 384: 16: 25.4 / - / - / 12.2, 64: 26.1 / - / 14.2, 66: 26.7 / 16.5, 256: 29.8 / 23.9
 //   d = 256: 16: 16.4 / 11.0 / 9.8, 64: 17.2 / 11.6 / 10.9, 66: 17.1 / 11.7, 128: 18.1 / 12.7, 256: 19.2 / 16.2
 //   d = 192: 16: 20.0 / 12.4 / 11.5, 64: 20.5 / 12.9 / 12.0, 66: 20.4 / 13.0, 256: 21.7 / 16.0
 //   d = 128 (one feature block per wavefront, never cut): 16: 13.9 / 9.6, 256: 15.6 / 12.5
+// d = 384 and 512: a workgroup alone on its compute unit leaves each SIMD one wavefront; with six or eight of them half as wide the rows' phase is half as long and two
+// wavefronts share a SIMD.  Forwards of 8 layers, three or four wavefronts (by the rule above) / twice as many, features cut in two / uncut (us):
+//   d = 512: 22 blocks 242.6 / 242.6 / 263.9, 25: 256.9 / 251.4 / 275.8, 36: 326 / 315 / 335, 60: 449 / 438 / 456, 70: 382 / 394 / 365, 110: 446 / 462 / 432, 150: 574 / 600 / 584
+//   d = 384: 10: 204 / 196 / 214, 40: 320 / 302 / 320, 64: 405 / 385 / 405, 70: 339 / 355 / 320, 110: 383 / 406 / 367, 150: 450 / 498 / 472
 // Past kK3HalfBlocks = 384 row blocks, three workgroups for each of the 256 compute units, a fourth has to wait its turn:
 //   384 / 386 / 448 blocks: d = 128 17.4 / 16.5, 17.5 / 18.3, 17.7 / 18.4;  d = 256 23.5 / 20.1, 23.4 / 23.3, 24.2 / 24.6;
 //   d = 384 36.7 / 35.2, 37.3 / 38.4, 38.2 / 40.2;  d = 512 38.2 / 39.1, 38.3 / 43.6, 40.9 / 46.0
@@ -327,8 +330,21 @@ static void launch_k3(const half_t *O, const half_t *U, const bf16_t *gamma, con
   const bool nt = (int64_t)n_blk * kRowAlign * d * 2 > kStreamBytes;
 #define K3_LAUNCH(CSV, RHV, NTV) k3_fused_kernel<NWV, NB, CSV, RHV, NTV><<<dim3(n_blk * (3 - RHV), CSV), 64 * NWV, k3_lds_bytes(d, CSV, RHV), s>>>( \
     O, U, gamma, beta, W2p, b2, Xh, Xl, lo_is_zero, blocks, blk_list, blk_first, eps)
-  if (NB == 4 && n_blk <= kK3CutInFour) K3_LAUNCH(NB, 1, false);
-  else if (n_blk <= kK3CutInTwo) K3_LAUNCH((NB > 1 ? 2 : 1), 1, false);
+  if constexpr (NB == 4) {
+#define K3_WIDE(CSV) k3_fused_kernel<2 * NWV, 2, CSV, 1, false><<<dim3(2 * n_blk, CSV), 128 * NWV, k3_lds_bytes(d, CSV, 1), s>>>( \
+    O, U, gamma, beta, W2p, b2, Xh, Xl, lo_is_zero, blocks, blk_list, blk_first, eps)
+    if (d == 512 && n_blk <= kK3CutInFour) {
+      if constexpr (d == 512) K3_LAUNCH(4, 1, false);
+      return;
+    }
+    if (n_blk <= kK3OneEach) {
+      if (n_blk <= kK3CutInTwo) K3_WIDE(2);
+      else K3_WIDE(1);
+      return;
+    }
+#undef K3_WIDE
+  }
+  if (NB < 4 && n_blk <= kK3CutInTwo) K3_LAUNCH((NB == 2 ? 2 : 1), 1, false);
   else if (n_blk <= kK3HalfBlocks && !nt) K3_LAUNCH(1, 1, false);
   else {
     constexpr bool kWholeOnlyStreams = (int64_t)(kK3HalfBlocks + 1) * kRowAlign * d * 2 > kStreamBytes;

@@ -137,9 +137,9 @@ void launch_layer(const void *O, const void *U, const void *gamma, const void *b
                   const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first, const void *W1h_next, const void *b1_next, PlanePtrs planes, bool all_hist, bool all_cand,
                   const Shape &sh, hipStream_t s);
 
-// Launches of up to this many 64-row blocks run K3 on half blocks: with the features cut in four (d = 384, 512), in two, uncut
-// (both sides of each are at launch_k3).
-constexpr int kK3CutInFour = 32, kK3CutInTwo = 64, kK3HalfBlocks = 384;
+// Launches of up to this many 64-row blocks run K3 on half blocks: with the features cut in four (d = 512), in two, uncut with a compute unit for each
+// (d = 384, 512), uncut (both sides of each are at launch_k3).
+constexpr int kK3CutInFour = 22, kK3CutInTwo = 64, kK3OneEach = 128, kK3HalfBlocks = 384;
 
 // A launch whose rows make a plane (rows x d fp16) larger than this writes and reads what is consumed once past the caches (nontemporal): what streams
 // through would push the operands that are read many times out of them.  The line is where the two measured level, per forward, ordinary
