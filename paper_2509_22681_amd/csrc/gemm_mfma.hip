@@ -392,17 +392,17 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_kernel(
 }
 
 
-// K1 on small tiles: 64 rows x 128 columns per workgroup.  The 64-row block of X sits whole in LDS (its k-tile blocked copy is one
+// K1 on small tiles: 64 rows x 128 columns (CW = 4) or 256 (CW = 8) per workgroup.  The 64-row block of X sits whole in LDS (its k-tile blocked copy is one
 // contiguous piece, brought by LDS-DMA in one go: the memory latency is paid once and not once per k tile of a short ring), W's
-// fragments come straight from L2 into a register ring eight k tiles deep, and the k loop, unrolled, has no barrier.  Wavefront
-// w owns columns 32 w .. 32 w + 31 of the tile, both 32-row halves.  A tile is two halves of 64 columns, each within one
+// fragments come straight from L2 into a register ring eight (CW = 8: four) k tiles deep, and the k loop, unrolled, has no barrier.  Wavefront
+// w of CW owns columns 32 w .. 32 w + 31 of the tile, both 32-row halves.  A tile is halves of 64 columns, each within one
 // plane.  Every output is the same chain of matrix instructions over the same k order as in the large tile (k starts at the
 // column tile's rotation), so the two agree bit for bit.
 // It serves launches that leave the chip idle at 256-row tiles, where the latency of a lone workgroup is what counts, and narrow
 // models, whose large tile has six k tiles or fewer to hide its start and its epilogue behind; see launch_uvqk_bf16.
 // NK = d / 32.
-template <int NK, bool NT>
-__global__ __launch_bounds__(256) void gemm_small_kernel(const half_t *__restrict__ A, const half_t *__restrict__ W, const bf16_t *__restrict__ bias,
+template <int NK, bool NT, int CW>
+__global__ __launch_bounds__(64 * CW, CW == 8 ? 4 : 1) void gemm_small_kernel(const half_t *__restrict__ A, const half_t *__restrict__ W, const bf16_t *__restrict__ bias,
                                                          PlanePtrs planes, const int32_t *__restrict__ blk_list, int blk_first, int n_blk, int n_col_tiles,
                                                          int64_t ws_rows, PlaneSel sel, float alpha, const int32_t *__restrict__ uq_list, int n_uq) {
   constexpr int nk = NK, d = NK * BK, rot_cols = d % 128 == 0 ? 128 : 64;
@@ -440,17 +440,20 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const half_t *__restric
   typedef __attribute__((address_space(1))) const void gvoid;
   typedef __attribute__((address_space(3))) void lvoid;
   {
-    const int rloc = 16 * wave + 4 * (lane >> 4) + ((lane & 15) >> 2);
+    const int rloc = 16 * (wave & 3) + 4 * (lane >> 4) + ((lane & 15) >> 2);
     const int dch = (lane & 3) ^ lds_key(rloc);
     const char *src = (const char *)(A + (int64_t)blk * kRowAlign * d);
     uint32_t off = (uint32_t)(rloc * 32 + dch * 8) * 2u;
     asm volatile("" : "+v"(off));
 #pragma unroll
-    for (int q = 0; q < NK; ++q) __builtin_amdgcn_global_load_lds((gvoid *)(src + q * 4096 + off), (lvoid *)(lds + q * 4096 + wave * 1024), 16, 0, 0);
+    for (int i = 0; i < 4 * NK / CW; ++i) {
+      const int q = CW / 4 * i + (wave >> 2);
+      __builtin_amdgcn_global_load_lds((gvoid *)(src + q * 4096 + off), (lvoid *)(lds + q * 4096 + (wave & 3) * 1024), 16, 0, 0);
+    }
   }
   // this wavefront's 32 columns
   const int cols_per_plane = d / 64;                            // halves of 64 columns per plane
-  const int half = 2 * col_tile + (wave >> 1);                  // index over the selected planes
+  const int half = CW / 2 * col_tile + (wave >> 1);             // index over the selected planes
   const int plane = second ? 2 * (half / cols_per_plane) : sel.id[half / cols_per_plane];
   const int n_half = (half % cols_per_plane) * 64;              // first column of the half inside its plane
   const int n_col = n_half + (wave & 1) * 32;
@@ -474,7 +477,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const half_t *__restric
         for (int e = 0; e < 16; ++e) acc[i][e] = bv;
     }
   }
-  constexpr int PD = NK < 8 ? NK : 8;                           // k tiles of W in flight
+  constexpr int PD = NK < 8 ? NK : CW == 8 ? 4 : 8;             // k tiles of W in flight
   auto main_loop = [&](auto fm) {
     constexpr bool FM = decltype(fm)::value;
     const char *wb = (const char *)(W + (int64_t)(n0 / 32) * 32 * d);
@@ -498,8 +501,9 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const half_t *__restric
     for (int p = 0; p < PD; ++p) load_w(p);
     // X has landed (it was requested ahead of W's fragments, and all of those are out: the wait counts them)
     __builtin_amdgcn_sched_barrier(0);
-    static_assert(2 * PD <= 16, "the wait below counts the fragments requested behind X");
+    static_assert((PD == 8 || CW == 4 || PD == 4) && NK * 4 % CW == 0, "the waits below count the fragments requested behind X");
     if (PD == 8) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+    else if (CW == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     read_a(0);
@@ -560,12 +564,12 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const half_t *__restric
 //   d = 128: 48 MB 794 / 833, 64 MB 1101 / 1084, 128 MB 2189 / 2094;  d = 192: 48 MB 846 / 888, 72 MB 1281 / 1249, 192 MB 3274 / 3203
 // (Attention at d = 64, 64 MB: 105.5 / 95.6 us per launch.)  The wider models leave the small tile long before.
 constexpr int64_t kSmallStreamBytes = 64 << 20;
-template <int NK, bool NT = false>
+template <int NK, bool NT = false, int CW = 4>
 static void launch_small(const void *Xh, const void *W1h, const void *b1, PlanePtrs planes, const int32_t *blk_list, int blk_first, int n_blk, const PlaneSel &sel,
                          const int32_t *uq_list, int n_uq, const Shape &sh, hipStream_t s) {
-  const int col_tiles = sel.n * (sh.d / 64) / 2;
-  const int lds = 4096 * NK < 16384 ? 16384 : 4096 * NK;       // the X block, at least the two output patches
-  gemm_small_kernel<NK, NT><<<(n_blk + n_uq) * col_tiles, 256, lds, s>>>((const half_t *)Xh, (const half_t *)W1h, (const bf16_t *)b1, planes, blk_list, blk_first, n_blk,
+  const int col_tiles = sel.n * (sh.d / 64) / (CW / 2);
+  const int lds = 4096 * (NK < CW ? CW : NK);                  // the X block, at least the output patches
+  gemm_small_kernel<NK, NT, CW><<<(n_blk + n_uq) * col_tiles, 64 * CW, lds, s>>>((const half_t *)Xh, (const half_t *)W1h, (const bf16_t *)b1, planes, blk_list, blk_first, n_blk,
                                                            col_tiles, sh.ws_rows, sel, sh.alpha, uq_list, n_uq);
 }
 
@@ -578,13 +582,19 @@ static void launch_small(const void *Xh, const void *W1h, const void *b1, PlaneP
 //   d = 192: 16: 7.9 / 10.1, 256: 16.9 / 19.7, 2048: 84 / 91, 8192: 340 / 345 (the large tile is 64 columns wide there)
 //   d = 128: 256: 14.6 / 17.3, 2048: 47 / 50, 8192: 173 / 175, 10240: 229 / 209, 16384: 352 / 343
 //   d = 64: 512: 12.9 / 14.8, 2048: 22.2 / 25.3, 8192: 64 / 81, 16384: 143 / 182
+// d = 384 and 512 from these blocks on with eight wavefronts, 64 rows x 256 columns, which halve the traffic of X, once per column tile, where there are enough tiles all the same.
+// Forwards of 8 layers (us), 128 columns wide (or the large tile, from 97 and 385 blocks on) / 256:
+//   d = 512: 16: 212 / 217, 18: 236 / 230, 45: 349 / 350, 63: 463 / 452, 90: 385 / 367, 150: 575 / 534, 250: 738 / 727, 400: 1088 / 1065, 500: 1283 / 1301, 1000: 2481 / 2585
+//   d = 384: 100: 330 / 351, 180: 485 / 493, 210: 526 / 524, 300: 724 / 721, 450: 926 / 901, 800: 1542 / 1529, 1000: 1772 / 1836
+// (Stores past the caches: d = 512, 300 blocks 904, 400: 1091; d = 384, 800: 1567.)
+constexpr int kWideFrom512 = 17, kWideFrom384 = 210;
 static int small_tile_blocks(int d) {
   switch (d) {
     case 64: case 192: return 1 << 30;
     case 128: return 8192;
     case 256: return 1024;
-    case 384: return 384;
-    case 512: return 96;
+    case 384: return 800;
+    case 512: return 400;
     default: return 0;                                          // no instance
   }
 }
@@ -607,8 +617,8 @@ void launch_uvqk_bf16(const void *Xh, const void *W1h, const void *b1, PlanePtrs
       case 128: if (snt) K1_SMALL(4, true); else K1_SMALL(4); break;
       case 192: if (snt) K1_SMALL(6, true); else K1_SMALL(6); break;
       case 256: K1_SMALL(8); break;
-      case 384: K1_SMALL(12); break;
-      default: K1_SMALL(16); break;
+      case 384: if (n_blk >= kWideFrom384 && sel.n % 2 == 0) K1_SMALL(12, false, 8); else K1_SMALL(12); break;
+      default: if (n_blk >= kWideFrom512) K1_SMALL(16, false, 8); else K1_SMALL(16); break;
     }
 #undef K1_SMALL
     return;
