@@ -587,7 +587,9 @@ static void launch_small(const void *Xh, const void *W1h, const void *b1, PlaneP
 //   d = 512: 16: 212 / 217, 18: 236 / 230, 45: 349 / 350, 63: 463 / 452, 90: 385 / 367, 150: 575 / 534, 250: 738 / 727, 400: 1088 / 1065, 500: 1283 / 1301, 1000: 2481 / 2585
 //   d = 384: 100: 330 / 351, 180: 485 / 493, 210: 526 / 524, 300: 724 / 721, 450: 926 / 901, 800: 1542 / 1529, 1000: 1772 / 1836
 // (Stores past the caches: d = 512, 300 blocks 904, 400: 1091; d = 384, 800: 1567.)
-constexpr int kWideFrom512 = 17, kWideFrom384 = 210;
+// Between, d = 512: up to 32 blocks the wide tiles are one for each compute unit, and up to 47 a second one for less than half of them (45 blocks: 13.9 / 14.8 us per launch).
+constexpr int kWideFrom512 = 17, kWideOneEach512 = 32, kWideAgainFrom512 = 48, kWideFrom384 = 210;
+static bool wide_512(int n_blk) { return n_blk >= kWideFrom512 && (n_blk <= kWideOneEach512 || n_blk >= kWideAgainFrom512); }
 static int small_tile_blocks(int d) {
   switch (d) {
     case 64: case 192: return 1 << 30;
@@ -618,7 +620,7 @@ void launch_uvqk_bf16(const void *Xh, const void *W1h, const void *b1, PlanePtrs
       case 192: if (snt) K1_SMALL(6, true); else K1_SMALL(6); break;
       case 256: K1_SMALL(8); break;
       case 384: if (n_blk >= kWideFrom384 && sel.n % 2 == 0) K1_SMALL(12, false, 8); else K1_SMALL(12); break;
-      default: if (n_blk >= kWideFrom512) K1_SMALL(16, false, 8); else K1_SMALL(16); break;
+      default: if (wide_512(n_blk)) K1_SMALL(16, false, 8); else K1_SMALL(16); break;
     }
 #undef K1_SMALL
     return;

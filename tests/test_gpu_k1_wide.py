@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("d", [384, 512])
 def test_same_bits_where_the_tile_becomes_wide(d, monkeypatch):
     text = (sizes.CSRC / "gemm_mfma.hip").read_text()
-    first = int(re.search(rf"kWideFrom{d} = (\d+)", text).group(1))
-    # the last even number of blocks before, and (the last layer's launches over the candidates' blocks alone) twice that
-    monkeypatch.setattr(sizes, "limits", lambda _: [(first - 1) // 2 * 2, (first - 1) // 2 * 4])
+    names = ["kWideFrom384"] if d == 384 else ["kWideFrom512", "kWideOneEach512", "kWideAgainFrom512"]
+    limits = [int(re.search(rf"{n} = (\d+)", text).group(1)) for n in names]
+    # the last even number of blocks before each, and (the last layer's launches over the candidates' blocks alone) twice that
+    monkeypatch.setattr(sizes, "limits", lambda _: [k * ((n - 1) // 2 * 2) for n in limits for k in (1, 2)])
     sizes.test_same_bits_at_every_launch_size(d)
