@@ -4,7 +4,7 @@
 // Both products run on the fp32 matrix instruction (32 x 32 x 2, fp32 operands and accumulator, the same
 // arithmetic as a chain of FMAs) whenever d is a multiple of 32 and the operands are 16-byte aligned: a
 // wavefront owns a 32 x 32 output tile and feeds the instruction straight from global memory, one 16-byte
-// load per operand and lane for four instructions, no LDS staging.  Other shapes take fp32 FMA kernels with
+// load per operand and lane for four instructions, no LDS staging (passes of many rows: head_kernel, one launch, rows in LDS).  Other shapes take fp32 FMA kernels with
 // LDS tiling (64 x 64 output tile, 64-deep k chunks, 256 threads each owning a 4 x 4 patch).
 #include <hip/hip_runtime.h>
 
@@ -337,6 +337,142 @@ __global__ __launch_bounds__(256) void expert_mfma_kernel(const float *__restric
   if (seg == 0 && r < rows) probs[r * T + t] = sigmoid_f32(s + c[t]);
 }
 
+// Fusion and task head of 32 rows in one workgroup, for passes with enough rows to give every compute unit one (kHeadRows): a wavefront per gate block and 32 features, then per
+// 32 expert units.  The rows of all blocks sit in LDS (by LDS-DMA, 16-byte chunks XOR-swizzled by row), since with every wavefront reading its operand rows from memory the two
+// kernels above are bound by the lines that the L1 serves; the fused rows take their place for the head.  Weights come from L2 through a ring of two groups of four steps, whose
+// four loads use up whole lines.  Sums, products and their order are those of the two kernels.  8192 rows, d = 192, 2 blocks, 2 tasks of 256 units: 68 -> 46 us (26 at the
+// fp32 matrix rate).
+__global__ __launch_bounds__(1024) void head_kernel(HiddenPtrs H, int n_blocks, const float *__restrict__ wg, const float *__restrict__ cg, float *__restrict__ F, int64_t rows, int d,
+                                                    const float *__restrict__ a_w, const float *__restrict__ a_b, const float *__restrict__ v, const float *__restrict__ c,
+                                                    float *__restrict__ probs, int E, int T) {
+  extern __shared__ __attribute__((aligned(256))) char lds[];
+  typedef __attribute__((address_space(1))) const void gvoid;
+  typedef __attribute__((address_space(3))) void lvoid;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  const int64_t row0 = (int64_t)blockIdx.x * 32;
+  const int K = n_blocks * d, strips = d >> 5, gate = wave / strips, f = (wave % strips) * 32 + l32;
+  const int pitch = d * 4, block = 32 * pitch;                    // bytes of a row, of the 32 rows of a block
+  auto at = [&](int r, int chunk) { return r * pitch + (((chunk & ~15) | ((chunk ^ r) & 15)) << 4); };
+  {
+    const int cpr = d >> 2, per = d >> 3;                         // chunks of a row, requests (1 KB) of a block
+    for (int q = wave; q < n_blocks * per; q += nw) {
+      const int b = q / per, i = q - b * per, at_chunk = 64 * i + lane, r = at_chunk / cpr, pc = at_chunk - r * cpr;
+      const float *src = H.h[b] + min(row0 + r, rows - 1) * d + 4 * ((pc & ~15) | ((pc ^ r) & 15));
+      __builtin_amdgcn_global_load_lds((gvoid *)src, (lvoid *)(lds + b * block + i * 1024), 16, 0, 0);
+    }
+  }
+  // acc[row][column] over `len` values of the rows at `base` (whole blocks of d each) and of this lane's weight row
+  auto product = [&](const float *wrow, int base, int len, auto ready) {
+    const float *wp = wrow + 4 * lh;
+    float4 w[2][4];
+    auto fetch = [&](float4 (&g)[4], int k) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p) g[p] = *(const float4 *)(wp + k + 8 * p);
+    };
+    fetch(w[0], 0);
+    ready();
+    f32x16 acc = {};
+    int blk = base, kin = 0;                                      // block in LDS and position in it
+    auto group = [&](float4 (&g)[4], float4 (&next)[4], int k) {
+      fetch(next, min(k + 32, len - 32));
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const float4 a = *(const float4 *)(lds + blk + at(l32, (kin >> 2) + 2 * p + lh));
+        mfma_step(a, g[p], acc);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      kin += 32;
+      if (kin == d) { kin = 0; blk += block; }
+    };
+    for (int k = 0; k < len; k += 64) {
+      group(w[0], w[1], k);
+      group(w[1], w[0], k + 32);
+    }
+    return acc;
+  };
+  const f32x16 acc = product(wg + ((int64_t)gate * d + f) * K, 0, K, []() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();                                 // the rows are there for everybody
+  });
+  float s[16], hb[16];
+  const float bias = cg[gate * d + f];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int r = 8 * (e >> 2) + 4 * lh + (e & 3);
+    hb[e] = *(const float *)(lds + gate * block + at(r, f >> 2) + (f & 3) * 4);
+    s[e] = sigmoid_f32(acc[e] + bias);
+  }
+  __syncthreads();                                                // everybody has read the rows: the fused ones take the first block's place
+  for (int b = 0; b < n_blocks; ++b) {
+    if (gate == b) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int r = 8 * (e >> 2) + 4 * lh + (e & 3);
+        float *x = (float *)(lds + at(r, f >> 2) + (f & 3) * 4);
+        const float sum = fmaf(s[e], hb[e], b > 0 ? *x : 0.f);
+        *x = sum;
+        if (b == n_blocks - 1 && row0 + r < rows) F[(row0 + r) * d + f] = sum;
+      }
+    }
+    __syncthreads();
+  }
+  // the head: strip u of 32 units, of task u / (E / 32); up to two a wavefront
+  const int us = E >> 5, nu = T * us;
+  float (*red)[4][32][32 + 1] = (float (*)[4][32][32 + 1])(lds + block);
+  float part[2][16], vl[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int u = wave + nw * i;
+    if (u < nu) {
+      const int unit = u * 32 + l32;                              // over all tasks
+      const f32x16 ex = product(a_w + (int64_t)unit * d, 0, d, []() {});
+      const float ab = a_b[unit];
+      vl[i] = v[unit];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) part[i][e] = fmaxf(ex[e] + ab, 0.f);
+    }
+  }
+  for (int j = 0; j < us / 4; ++j) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int u = wave + nw * i, t = u / us, k = u - t * us;
+      if (u < nu && k >> 2 == j) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          float *x = &red[t][k & 3][8 * (e >> 2) + 4 * lh + (e & 3)][l32];
+          *x = fmaf(part[i][e], vl[i], j > 0 ? *x : 0.f);
+        }
+      }
+    }
+    __syncthreads();
+  }
+  // as in expert_mfma_kernel, 256 threads a task
+  const int t = threadIdx.x >> 8, rr = (threadIdx.x & 255) >> 3, seg = threadIdx.x & 7;
+  if (t < T) {
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sum += red[t][w][rr][seg * 4 + q];
+    sum += __shfl_xor(sum, 1);
+    sum += __shfl_xor(sum, 2);
+    sum += __shfl_xor(sum, 4);
+    if (seg == 0 && row0 + rr < rows) probs[(row0 + rr) * T + t] = sigmoid_f32(sum + c[t]);
+  }
+}
+
+// The one-launch head's wavefronts, or 0 where the model does not fit it (wavefronts, LDS, whole strips) or the rows are too few.
+// Up to 4096 rows the two kernels have a compute unit for each of their workgroups, which are shorter: 4096 rows 40 us against 44, 16 384 130 against 88; d = 256, E = 128, one task:
+// 4096: 44 / 50, 8192: 75 / 53; d = 128, 4 blocks: 8192: 80 / 58.
+constexpr int kHeadRows = 4097;
+inline int head_waves(int n_blocks, int d, int E, int T, int64_t rows) {
+  const int nw = n_blocks * (d / 32);
+  const bool fits = d % 64 == 0 && nw <= 16 && n_blocks * d <= 512 && E % 128 == 0 && T * (E / 32) <= 2 * nw && T * 4 <= nw && 128 * d + T * 4 * 32 * 33 * 4 <= 65536;
+  return fits && rows >= kHeadRows ? nw : 0;
+}
+
 inline bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
 thread_local const char *g_head_error = "";
@@ -366,6 +502,14 @@ int flame_climber_head(const flame_climber_head_config *cfg, const flame_climber
   hipStream_t s = (hipStream_t)stream;
   bool mfma = cfg->d_model % (8 * PD) == 0 && aligned16(w->wg) && aligned16(w->a_w) && aligned16(fused);
   for (int b = 0; b < cfg->n_blocks; ++b) mfma = mfma && aligned16(hidden[b]);
+  if (const int nw = mfma ? head_waves(cfg->n_blocks, cfg->d_model, cfg->expert_width, cfg->n_tasks, n_rows) : 0) {
+    const size_t rows_lds = (size_t)128 * cfg->n_blocks * cfg->d_model, head_lds = (size_t)128 * cfg->d_model + (size_t)cfg->n_tasks * 4 * 32 * 33 * 4;
+    head_kernel<<<(unsigned)((n_rows + 31) / 32), 64 * nw, rows_lds > head_lds ? rows_lds : head_lds, s>>>(H, cfg->n_blocks, w->wg, w->cg, fused, n_rows, cfg->d_model, w->a_w, w->a_b, w->v,
+                                                                                                          w->c, probs, cfg->expert_width, cfg->n_tasks);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) { g_head_error = hipGetErrorString(e); return FLAME_GR_HIP_ERROR; }
+    return FLAME_GR_OK;
+  }
   if (mfma) {
     const unsigned tiles32 = (unsigned)((n_rows + 31) / 32);
     fuse_mfma_kernel<<<dim3(tiles32, (cfg->d_model + 127) / 128), 256, 0, s>>>(H, cfg->n_blocks, w->wg, w->cg, fused, n_rows, cfg->d_model);
