@@ -219,6 +219,7 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, float *sc
     }
     return pp;
   };
+  bool scored = false;
   for (int l = 0; l < sh.n_layers; ++l) {
     const bool capture = mode == PASS_FULL && h->capture_layer == l;
     const bool last = (l == sh.n_layers - 1) && !capture;
@@ -276,8 +277,10 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, float *sc
       launch_outproj_bf16(h->G, w2, b2, h->Xb, h->Xl, l == 0, bl, nb, bf, sh, s);
     } else {
       Timed t(h, KIND_OUTPROJ, s);
+      // (the last layer of a narrow model: the scores at once)
+      scored = last && !hidden && outproj_scores_f32((const float *)lg, (const float *)lb, w2, h->Ws != nullptr, sh);
       launch_outproj_f32((const float *)h->O, (const float *)planes, (const float *)lg, (const float *)lb, w2, h->Ws != nullptr, (const float *)b2, h->X,
-                         blocks, bl, nb, bf, sh, s);
+                         blocks, bl, nb, bf, (const float *)w.w_s, w.b_s, scored ? scores : nullptr, sh, s);
     }
     if (capture && h->cap_planes) {
       const size_t r0 = (size_t)G.row_begin * d, nr = (size_t)(G.row_end - G.row_begin) * d;
@@ -296,7 +299,7 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, float *sc
       else (void)hipMemcpyAsync(h->cap_X + r0, h->X + r0, nr * sizeof(float), hipMemcpyDeviceToDevice, s);
     }
   }
-  if (mode == PASS_HISTORY) return;
+  if (mode == PASS_HISTORY || scored) return;
   {
     Timed t(h, KIND_SCORE, s);
     if (hidden) launch_gather_hidden(h->X, h->Xb, h->Xl, blocks, cl, n_cblk, hidden, d, s);

@@ -89,8 +89,10 @@ void launch_attn_f32(const float *planes, const float *bias_lh, const float *tsc
                      int n_items, const Shape &sh, hipStream_t s);
 // X[row] += ((LayerNorm(O[row]) * gamma + beta) * U[row]) W2^T + b2 for the rows of the listed blocks (blk_list == nullptr:
 // contiguous); padding rows of a block get the bias only, so that they stay finite through the layers.
+// scores (where outproj_scores_f32 allows it): the rows' scores instead of the rows.
+bool outproj_scores_f32(const float *gamma, const float *beta, const void *W2, bool packed, const Shape &sh);
 void launch_outproj_f32(const float *O, const float *U, const float *gamma, const float *beta, const void *W2, bool packed, const float *b2, float *X,
-                        const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first, const Shape &sh, hipStream_t s);
+                        const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first, const float *w_s, float b_s, float *scores, const Shape &sh, hipStream_t s);
 
 // The four activation planes of a layer (MFMA path), each [ws_rows][d] fp16 (V feature-major [d][ws_rows]).  The
 // one-pass forward keeps them in one allocation; the two-stage path points v and k at the layer's cache.

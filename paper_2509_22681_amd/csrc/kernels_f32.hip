@@ -75,12 +75,13 @@ __device__ __forceinline__ float row16_sum(float v) {
 // ---------------------------------------------------------------------------------------------
 // (A, U, gamma, beta and W carry no __restrict__: loads that the compiler knows to be unchanging may pass any fence, and the counted waits for W need the requests in order.)
 // NI (EPI 1): 16-byte loads per lane and row that the statistics keep in registers, ceil(K / 64) at least; 0: any K, in two reads of the rows.
-template <int EPI, int WM, int WN, int MB, int NB, bool PACKED, bool VEC, int NI>
+template <int EPI, int WM, int WN, int MB, int NB, bool PACKED, bool VEC, int NI, bool SCORE = false>
 __global__ __launch_bounds__(256, MB * NB == 4 ? 2 : 1) void gemm_f32_kernel(const float *A, const float *U, const float *gamma,
                                                        const float *beta, const RowBlock *__restrict__ blocks, float eps,
                                                        const void *Wv, const float *__restrict__ bias, float *__restrict__ out,
                                                        const int32_t *__restrict__ blk_list, int blk_first, int n_blk, int d, int n_planes, int plane0, int plane_step,
-                                                       int64_t plane_stride, int y2, const int32_t *__restrict__ blk_list2, int n_blk2) {
+                                                       int64_t plane_stride, int y2, const int32_t *__restrict__ blk_list2, int n_blk2,
+                                                       const float *__restrict__ w_s = nullptr, float b_s = 0.f, float *__restrict__ scores = nullptr) {
   static_assert(WM * WN == 4, "four wavefronts");
   constexpr int BM = 32 * WM * MB, BN = 32 * WN * NB, BK = 32, TB = BM / 64, LPT = BM / 32;   // tile, k chunk, 64-row blocks, 16-byte loads of A per thread
   constexpr int AST = TB == 1 ? 2 : 1, APART = BM * BK * 2, ASTAGE = 3 * APART, WSTAGE = 3 * BN * BK * 2;
@@ -355,6 +356,36 @@ __global__ __launch_bounds__(256, MB * NB == 4 ? 2 : 1) void gemm_f32_kernel(con
     chunk(EVEN{}, TAIL{}, kc);
     if (kc + 1 < nk) chunk(ODD{}, TAIL{}, kc + 1);
   }
+  if constexpr (SCORE) {
+    // The last layer of a model of up to 64 features: the workgroup has its candidates' whole rows, which only the score head reads.  Sums in the order of score_kernel: columns n
+    // and n + 32 first (the two wavefronts of the rows, through the free stage of A), then the 32 lanes.
+    static_assert(EPI == 1 && WM == 2 && WN == 2 && MB == 1 && NB == 1, "a row block of 64 features");
+    const int n = wn * 32 + l32;
+    const bool inside = n < d;
+    const float w = inside ? w_s[n] : 0.f, bn = inside ? bias[n] : 0.f;
+    float p[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) p[e] = inside ? __builtin_fmaf(xr[0][0][e] + (acc[0][0][e] + bn), w, 0.f) : 0.f;
+    __syncthreads();
+    float *part = (float *)lds + (wm * 16 * 64 + lane);
+    if (wn == 1) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) part[e * 64] = p[e];
+    }
+    __syncthreads();
+    if (wn == 0) {
+      const int src = blocks[row0[0] / kRowAlign].src_row;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        float v = p[e] + part[e * 64];
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = row16_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+        const int row = wm * 32 + 8 * (e >> 2) + 4 * lhalf + (e & 3);
+        if (l32 == 0 && row < n_valid) scores[src + row] = v + b_s;
+      }
+    }
+    return;
+  }
   // a lane holds one output column and 16 rows: 32 lanes write 128 contiguous bytes of a row
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
@@ -403,10 +434,22 @@ void launch_uvqk_f32(const float *X, const void *W1, bool packed, const float *b
 #undef UVQK_CASE
 }
 
+bool outproj_scores_f32(const float *gamma, const float *beta, const void *W2, bool packed, const Shape &sh) {
+  return sh.d <= 64 && vec4_rows(sh.d, gamma) && vec4_rows(sh.d, beta) && (packed || vec4_rows(sh.d, W2));
+}
+
 void launch_outproj_f32(const float *O, const float *U, const float *gamma, const float *beta, const void *W2, bool packed, const float *b2, float *X,
-                        const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first, const Shape &sh, hipStream_t s) {
+                        const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first, const float *w_s, float b_s, float *scores, const Shape &sh, hipStream_t s) {
   if (n_blk <= 0) return;
   const int nb = (sh.d + 31) / 32;
+  if (scores) {
+#define OUT_SCORE(PK) gemm_f32_kernel<1, 2, 2, 1, 1, PK, true, 1, true><<<dim3(n_blk, 1), 256, 0, s>>>( \
+      O, U, gamma, beta, blocks, sh.eps, W2, b2, X, blk_list, blk_first, n_blk, sh.d, 1, 0, 1, 0, 1 << 30, nullptr, 0, w_s, b_s, scores)
+    if (packed) OUT_SCORE(true);
+    else OUT_SCORE(false);
+#undef OUT_SCORE
+    return;
+  }
 #define OUT_CASE(WM, WN, MB, NB, PK, VV, NI) gemm_f32_kernel<1, WM, WN, MB, NB, PK, VV, NI><<<dim3(n_blk, (nb + WN * NB - 1) / (WN * NB)), 256, 0, s>>>( \
       O, U, gamma, beta, blocks, sh.eps, W2, b2, X, blk_list, blk_first, n_blk, sh.d, 1, 0, 1, 0, 1 << 30, nullptr, 0)
 #define OUT_WIDTHS(PK) do { \
