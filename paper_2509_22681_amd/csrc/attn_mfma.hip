@@ -103,7 +103,8 @@ __device__ __forceinline__ f16x8 pack8(const float *v) {
 //     of every tile (two wavefronts per SIMD, so one's MFMAs run under the other's VALU work).  The chain is a quarter as
 //     many steps, and a request of a few thousand rows has enough query tiles for every CU.  One request of 2573 + 217, 8 heads:
 //     22 us per launch (32 with query tiles of 128 and two wavefronts per group on key tiles of 128), 20 with the feeders: four wavefronts that do nothing but make the tiles'
-//     66 requests of 1 KB, 1000 cycles of the compute unit's address path per tile, which the others else wait out ahead of their arithmetic.
+//     64 requests of 1 KB, 1000 cycles of the compute unit's address path per tile, which the others else wait out ahead of their arithmetic; 19 with the bias window in four
+//     copies as above (20 requests of 256 bytes).
 //   KP = 2: 128 query rows, 8 wavefronts, key tiles of 128 in four LDS stages; each of a group's two wavefronts takes one 64-key half of every
 //     tile, into one of two accumulator sets by the tile's parity.  For latency handles that are given enough rows to
 //     fill the chip all the same: half the K and V traffic per query row (the rule and both sides' times are at kLatencyWideTiles).
@@ -142,10 +143,12 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
   constexpr int K_BYTES = KT * DH * 2;             // K tile [KT keys][DH]
   constexpr int V_BYTES = DH * KT * 2;             // V^T tile [DH][KT keys]
   constexpr int BCOPY = (256 + 64) * 4 + 64;       // bytes of a copy: 256 slots, the first 64 again behind them, and a quarter of the banks to the next copy
-  constexpr int W_BYTES = BRING ? 0 : NW * 256;    // bias window: 64 slots per wavefront (BW <= 64 NW of them are used)
+  constexpr int WCOPY = BW * 4 + 64;               // FEEDERS: the window in four copies too, BW slots and a quarter of the banks each
+  constexpr int W_BYTES = BRING ? 0 : FEEDERS ? 4 * WCOPY : NW * 256;    // bias window: 64 slots per wavefront (BW <= 64 NW of them are used)
   constexpr int STAGE = K_BYTES + V_BYTES + W_BYTES;
   constexpr bool P_OVER_K = SEQ && K_BYTES >= NW * 4096;   // where the weights of a tile go: over its K, or behind the stages
   static_assert(K_BYTES % 1024 == 0 && V_BYTES % 1024 == 0 && STAGE % 256 == 0, "stage parts start on 256-byte boundaries");
+  static_assert(!FEEDERS || (W_BYTES == 4 * 1344 && BW % 64 == 0), "key_split_lds_bytes");
   static_assert(QT * DH * 2 <= NSTAGE * STAGE, "output patches fit in the tile buffers");
   // the stages; the output patches of the wavefronts reuse them once the key loop is over.  The latency
   // configuration needs more than the 64 KB a static array may have and takes its stages from dynamic LDS.
@@ -242,7 +245,8 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
   uint32_t oK, oV;
   // (candidate tiles shift the window by one slot: all their rows read it at the same slots, which then start on a
   // 16-byte boundary and leave as four-float reads)
-  const int dW0 = q_first + (QT - 1) + (!BRING && it.is_cand ? 1 : 0) - (BRING ? rw + lane : rw * 64 + lane);   // distance held by window slot 64 w + lane in tile 0 (ring: slot lane of copy w)
+  constexpr bool BCOPIES = BRING || FEEDERS;
+  const int dW0 = q_first + (QT - 1) + (!BCOPIES && it.is_cand ? 1 : 0) - (BCOPIES ? rw + lane : rw * 64 + lane);   // distance held by window slot 64 w + lane in tile 0 (copies: slot lane of copy w)
   int sW = 0;                                                 // keys the next tile to request lies behind tile 0 (scalar)
   {
     const int row = rw * (64 / KCH) + lane / KCH;
@@ -265,7 +269,7 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
 #pragma unroll
     for (int i = 0; i < NVI / NW; ++i)
       __builtin_amdgcn_global_load_lds((gvoid *)(bV + (int64_t)(i * NW * (64 / VCH)) * ws_rows * 2 + oV), (lvoid *)(sb + K_BYTES + (rw + NW * i) * 1024), 16, 0, 0);
-    if constexpr (BRING) return;
+    if constexpr (BCOPIES) return;
     // every wavefront issues one window request, so that all of them have the same number of requests in
     // flight per tile (slots past the window are filled too and never read)
     uint32_t oW = (uint32_t)max(0, min(D - 1, dW0 - sW)) * 4u;
@@ -302,9 +306,12 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
 #pragma unroll
         for (int i = 0; i < NVI / NW; ++i)
           __builtin_amdgcn_global_load_lds((gvoid *)(bV + (int64_t)(i * NW * (64 / VCH)) * ws_rows * 2 + oV2), (lvoid *)(sb + K_BYTES + (rw + 4 + NW * i) * 1024), 16, 0, 0);
-        uint32_t oW = (uint32_t)max(0, min(D - 1, dW0 - 256 - sW)) * 4u;
-        asm volatile("" : "+v"(oW));
-        __builtin_amdgcn_global_load_lds((gvoid *)((const char *)bias + oW), (lvoid *)(sb + K_BYTES + V_BYTES + (rw + 4) * 256), 4, 0, 0);
+#pragma unroll
+        for (int j = 0; j < BW / 64; ++j) {                // copy rw of the window
+          uint32_t oW = (uint32_t)max(0, min(D - 1, dW0 - 64 * j - sW)) * 4u;
+          asm volatile("" : "+v"(oW));
+          __builtin_amdgcn_global_load_lds((gvoid *)((const char *)bias + oW), (lvoid *)(sb + K_BYTES + V_BYTES + rw * WCOPY + j * 256), 4, 0, 0);
+        }
       };
       for (int t = 0; t < n_tiles; ++t) {
         if (t == 0) {
@@ -334,8 +341,8 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
   // workgroup tile; keys further right sit at increasing slots.  Candidate rows all sit at the same distance
   // from a key (m = 0), and their window is shifted by one slot: QT + 8*lhalf, a 16-byte boundary.
   // Ring: value p of the index is p & ~3 of copy p & 3, so that a lane's four consecutive values are one aligned 16-byte read whatever its row.
-  const int bias_idx = BRING ? (QT - 1) - (it.is_cand ? 0 : my_q_local) + 8 * lhalf : it.is_cand ? QT + 8 * lhalf : (QT - 1) - my_q_local + 8 * lhalf;
-  const int ring_copy = NSTAGE * STAGE + (bias_idx & 3) * BCOPY, ring_at = (bias_idx & ~3) * 4;
+  const int bias_idx = BCOPIES ? (QT - 1) - (it.is_cand ? 0 : my_q_local) + 8 * lhalf : it.is_cand ? QT + 8 * lhalf : (QT - 1) - my_q_local + 8 * lhalf;
+  const int ring_copy = BRING ? NSTAGE * STAGE + (bias_idx & 3) * BCOPY : K_BYTES + V_BYTES + (bias_idx & 3) * WCOPY, ring_at = (bias_idx & ~3) * 4;
   // fragment byte offsets inside a stage.  K (A operand of S^T): MFMA row m takes key pi32(m); per 32-key
   // block j the row advances by 32 (key bits 0..4 unchanged, so the swizzle key is the same).  V^T (A
   // operand of O^T): row = feature 32 b + l32, chunk = key / 8.
@@ -409,9 +416,9 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
           // from folding constant parts of the address into every read as a separate add)
           typedef const __attribute__((address_space(3))) float *lds_cfloat;
           typedef const __attribute__((address_space(3))) f32x4 *lds_cf4;
-          lds_cfloat bp = BRING ? (lds_cfloat)(lds + ring_copy + ((ring_at + 4 * k0) & 1023)) : (lds_cfloat)(sb + K_BYTES + V_BYTES) + (bias_idx + u * KH);
+          lds_cfloat bp = BRING ? (lds_cfloat)(lds + ring_copy + ((ring_at + 4 * k0) & 1023)) : FEEDERS ? (lds_cfloat)(sb + ring_copy + ring_at + 4 * KH * u) : (lds_cfloat)(sb + K_BYTES + V_BYTES) + (bias_idx + u * KH);
           asm volatile("" : "+v"(bp));
-          if (BRING || it.is_cand) {
+          if (BCOPIES || it.is_cand) {
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -900,7 +907,7 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
 // allocation): attn_setup, ahead of any launch.
 template <int DH, int KP, bool SEQ = false>
 constexpr int key_split_lds_bytes() {   // the stages: K, V^T and the bias window each; the weights of a tile where they do not fit over its K
-  return (KP == 4 ? 2 : 4) * (2 * 64 * KP * DH * 2 + 8 * 256) + (SEQ && 64 * KP * DH * 2 < 8 * 4096 ? 8 * 4096 : 0);
+  return (KP == 4 ? 2 : 4) * (2 * 64 * KP * DH * 2 + (KP == 4 ? 4 * 1344 : 8 * 256)) + (SEQ && 64 * KP * DH * 2 < 8 * 4096 ? 8 * 4096 : 0);
 }
 
 template <int DH, bool SM, int KP, bool SEQ = false>
