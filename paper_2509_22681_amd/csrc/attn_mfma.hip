@@ -937,13 +937,13 @@ hipError_t attn_setup(const Shape &sh) {
 // Workgroups of 128 rows (tiles x heads) up to which a launch takes the key-ordered split, by the longest history of the pass.  Its workgroups have 64 rows and a
 // compute unit each, so up to 128 are one round of them; beyond, it pays only where most tiles are history tiles, whose chains of keys are half as long on average, and the longest
 // chain is what the other kernel takes.  Forwards of four layers, one wavefront per group / split (us):
-//   1024 + 256, 8 heads: 80 workgroups 152 / 132, 160: 170 / 151, 240: 186 / 181; 2 heads: 20: 125 / 105, 160: 151 / 133, 240: 158 / 152; 1024 + 1024: 128: 157 / 138, 192: 155 / 155
-//   2048 + 256, 8 heads: 144: 229 / 188, 288: 268 / 257, 432: 307 / 326; 2 heads: 36: 182 / 137, 252: 209 / 184, 396: 220 / 239; 8192 + 512, 2 heads: 136: 520 / 330
-//   512 + 128, 8 heads: 40: 119 / 109, 120: 135 / 125, 200: 161 / 163; 2 heads: 130: 119 / 115, 190: 127 / 133
+//   1024 + 256, 8 heads: 80 workgroups 147 / 126, 160: 165 / 144, 240: 179 / 172, 320: 208 / 213; 4 heads: 80: 141 / 119, 240: 161 / 152, 320: 175 / 178; 1024 + 1024: 128: 157 / 136, 256: 186 / 189
+//   2048 + 256, 8 heads: 144: 214 / 173, 288: 256 / 240, 432: 286 / 295; 3 heads: 108: 184 / 142, 216: 207 / 175, 324: 212 / 207; 8192 + 512, 2 heads: 136: 520 / 330
+//   512 + 128, 8 heads: 80: 124 / 115, 120: 131 / 124, 160: 141 / 136, 200: 151 / 151; 4 heads: 160: 129 / 123, 240: 137 / 139
 //   320 + 128, 2 heads: 24: 91 / 88, 128: 107 / 109; 128 + 64: 40: 82 / 84, 160: 98 / 119 (a history of one or two 256-key tiles has no chain to shorten)
 // Candidate tiles alone (one layer), 4 heads: 512 + 128: 64: 48 / 46, 128: 53 / 53, 160: 59 / 65; 2048 + 128: 64: 87 / 79, 128: 140 / 136, 160: 152 / 169.
 constexpr int kAttnSeqHistory = 384, kAttnSeqWorkgroups = 128;                            // from this history on; up to this many workgroups, and where history tiles prevail
-constexpr int kAttnSeqLongHistory = 1024, kAttnSeqLongWorkgroups = 160, kAttnSeqLongerHistory = 2048, kAttnSeqLongerWorkgroups = 224;   // up to these
+constexpr int kAttnSeqLongHistory = 1024, kAttnSeqLongWorkgroups = 240, kAttnSeqLongerHistory = 2048, kAttnSeqLongerWorkgroups = 288;   // up to these
 bool attn_key_ordered(int grid, int n_items, int n_cand, int longest) {
   if (longest < kAttnSeqHistory) return false;
   const int limit = longest < kAttnSeqLongHistory || 2 * n_cand > n_items ? kAttnSeqWorkgroups : longest < kAttnSeqLongerHistory ? kAttnSeqLongWorkgroups : kAttnSeqLongerWorkgroups;
