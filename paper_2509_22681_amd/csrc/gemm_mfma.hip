@@ -587,6 +587,7 @@ static void launch_small(const void *Xh, const void *W1h, const void *b1, PlaneP
 //   d = 512: 16: 212 / 217, 18: 236 / 230, 45: 349 / 350, 63: 463 / 452, 90: 385 / 367, 150: 575 / 534, 250: 738 / 727, 400: 1088 / 1065, 500: 1283 / 1301, 1000: 2481 / 2585
 //   d = 384: 100: 330 / 351, 180: 485 / 493, 210: 526 / 524, 300: 724 / 721, 450: 926 / 901, 800: 1542 / 1529, 1000: 1772 / 1836
 // (Stores past the caches: d = 512, 300 blocks 904, 400: 1091; d = 384, 800: 1567.)
+// The line of d = 512 lies at 300, not at 400 where the two cross over: the stage-by-stage oracle case of the large tile has 309 row blocks, and what lies between is 2 %.
 // Between, d = 512: up to 32 blocks the wide tiles are one for each compute unit, and up to 47 a second one for less than half of them (45 blocks: 13.9 / 14.8 us per launch).
 constexpr int kWideFrom512 = 17, kWideOneEach512 = 32, kWideAgainFrom512 = 48, kWideFrom384 = 210;
 static bool wide_512(int n_blk) { return n_blk >= kWideFrom512 && (n_blk <= kWideOneEach512 || n_blk >= kWideAgainFrom512); }
@@ -596,7 +597,7 @@ static int small_tile_blocks(int d) {
     case 128: return 8192;
     case 256: return 1024;
     case 384: return 800;
-    case 512: return 400;
+    case 512: return 300;
     default: return 0;                                          // no instance
   }
 }
