@@ -352,9 +352,8 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
   const int ka0 = (krow * (DH * 2)) | (((((krow >> KSH) & (KCH - 1)) ^ lhalf) << 4));
   const int va0 = (K_BYTES + l32 * (KT * 2)) | (((((l32 >> VSH) & VKEY) ^ lhalf) << 4));
 
-  // Ring of NSTAGE stages, requests two tiles ahead.  Past the last tile the requests repeat the last
-  // tile (into a free stage), so that "at most REQ requests outstanding" always means "tile t has landed".
-  // (Two stages: one tile ahead, and no repetition.)
+  // Two stages: requests one tile ahead, all of them landed at the barrier that opens a tile.  Three or four: two tiles ahead, and past the last tile
+  // the requests repeat it (into a free stage), so that "at most REQ requests outstanding" always means "tile t has landed".
   bool cool = true;                    // the block before was on the quadratic route
   if (BRING && n_tiles > 0) {
     request_tile(0);
@@ -365,8 +364,8 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
     if (n_tiles > 1) next_tile();
     request_tile(1);
   }
-  // The query fragments are requested behind the first two tiles, not ahead of them: the tiles are what the first
-  // step waits for.  (The waits below count requests in order: with at most REQ outstanding, the query loads and
+  // The query fragments are requested behind the first tiles, not ahead of them: the tiles are what the first
+  // step waits for.  (Where the waits below count requests, they do so in order: with at most REQ outstanding, the query loads and
   // every tile before the newest have landed.)
 #pragma unroll
   for (int s = 0; s < KS; ++s) fq[s] = *(const f16x8 *)(Qp + q_row_clamped * d + s * 16 + lhalf * 8);
