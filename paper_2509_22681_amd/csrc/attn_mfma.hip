@@ -31,11 +31,10 @@
 // is exactly the k order of a 16-deep B operand.  V is stored feature-major by the projection
 // kernel, so V^T tiles are plain row loads.
 //
-// SiLU: the weights of a wavefront's 32x64 block are made by the cheapest of five routes that its largest |x| (masked positions included) allows: s + s^2 in fp32 up to 1/4, three
-// polynomials whose correction term runs in packed fp16 up to 1, 2 and 4 (within one fp16 ulp of the exact weight), the exact exp2/rcp form in fp32 beyond.  Vector instructions per
-// block, with the test: 48, 89, 105, 137 and 217, beside 16 MFMAs.  The logits of the early layers of a model are small (16 layers, d = 512, embeddings N(0, 0.1^2): all blocks of the first four
-// below 1/4, of the first nine below 1).  Per launch, the route up to 2 for all / with those up to 1/4 and 1: 16 x (8192 + 512), 8 heads 1467 -> 1360 and 1457 -> 1437 us, 128 production requests
-// 2205 -> 2045 and 2215 -> 2200.  (Half the vector instructions for 7 % of the time: under load the clock, held at 1.8 GHz by the power cap, and the matrix pipe's share decide.)
+// SiLU: the weights of a wavefront's 32x64 block are made by the cheapest of three routes that its largest |x| (masked positions included) allows: polynomials whose correction term runs
+// in packed fp16 up to 2 and 4, the exact exp2/rcp form in fp32 beyond.  Vector instructions per block, with the test: 105, 137 and 217, beside 16 MFMAs.  Error of a weight, largest and
+// root mean square over the range (the fp16 rounding of the weight included): 1.4e-3 and 2.4e-4 up to 2, 4.8e-3 and 8.2e-4 up to 4.
+// (A form s + s^2 for |x| <= 1/4 and a bracket of two coefficients up to 1 save half and a seventh of the instructions, but are further off where their ranges end.)
 // The mask is applied on boundary tiles only.
 //
 // Bias: a lane's eight consecutive entries (by decreasing distance, fp32) per accumulator half-block are read from LDS
@@ -63,13 +62,7 @@ constexpr int KH = 64;              // keys per block (one pass of the register-
 // weights); the last step is a mixed-precision fused multiply-add per weight, fp16 t times fp16 bracket
 // plus the fp32 logit itself, rounded to fp16 once, like the weight of the exact route.
 constexpr float kPolyT2 = 1.0f;                                  // bound on t = s^2  (|x| <= 2)
-// Low segment, |x| <= 1 (t <= 1/4): the bracket with one coefficient less, off by 1e-3 of itself at most (the one above: 3.4e-3 at small |x|).
-constexpr float kLowT2 = 0.25f;
-__device__ constexpr float kLowB[2] = {0.9990234375f, -0.3025f};
-// Quadratic, |x| <= 1/4: silu(x) = s + s^2 in fp32, off by s^4 / 3 (t / 3 <= 5.2e-3 of the square at the very end, a tenth of that at a third of it).  kQuadS is the largest
-// fp32 logit whose square in fp16 arithmetic is kQuadT2 or less.
-constexpr float kQuadT2 = 0.015625f, kQuadS = 0.125f + 0x1p-14f;
-// Third segment, |x| <= 4 (t <= 4): silu(x) = s + t (B0 + B1 t + B2 t^2 + B3 t^3 + B4 t^4), minimax-weighted fit of
+// Second segment, |x| <= 4 (t <= 4): silu(x) = s + t (B0 + B1 t + B2 t^2 + B3 t^3 + B4 t^4), minimax-weighted fit of
 // (silu(2 s) - s) / t on 0 <= t <= 4 (error of silu below 5.4e-4).
 constexpr float kMidT2 = 4.0f;
 __device__ constexpr float kMidB[5] = {0.9926417973f, -0.3010154918f, 0.0835130618f, -0.0141349725f, 0.0010234216f};
@@ -354,7 +347,6 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
 
   // Two stages: requests one tile ahead, all of them landed at the barrier that opens a tile.  Three or four: two tiles ahead, and past the last tile
   // the requests repeat it (into a free stage), so that "at most REQ requests outstanding" always means "tile t has landed".
-  bool cool = true;                    // the block before was on the quadratic route
   if (BRING && n_tiles > 0) {
     request_tile(0);
 #pragma unroll
@@ -528,90 +520,53 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
 #pragma unroll
               for (int i = 0; i < 8; ++i) fp[2 * j + h][i] = w[4 * h + i / 2][i & 1];
           };
-          bool quadratic = false, low = false, poly = false;
-          if (cool) {
-            // the block before was on the quadratic: its test first, which needs the logits only.  (The test on the squares below asks the same question, so a block's route
-            // depends on its logits alone.)
-            auto max3 = [](float a, float b, float c) {
-              return __builtin_elementwise_maximum(__builtin_elementwise_maximum(__builtin_fabsf(a), __builtin_fabsf(b)), __builtin_fabsf(c));
-            };
-            float m[10];
-#pragma unroll
-            for (int k = 0; k < 10; ++k) {
-              const int e = 3 * k;   // values 0..29 in the order sacc[0][0..15], sacc[1][0..13]
-              m[k] = max3(sacc[e >> 4][e & 15], sacc[(e + 1) >> 4][(e + 1) & 15], sacc[(e + 2) >> 4][(e + 2) & 15]);
-            }
-            const float m0 = max3(m[0], m[1], m[2]), m1 = max3(m[3], m[4], m[5]), m2 = max3(m[6], m[7], m[8]), m3 = max3(m[9], sacc[1][14], sacc[1][15]);
-            quadratic = __builtin_amdgcn_ballot_w64(!(__builtin_elementwise_maximum(max3(m0, m1, m2), m3) <= kQuadS)) == 0;
-          }
           f16x2 th[2][8];
-          half_t mx = (half_t)0.f;
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+              const f16x2 yh = f16x2{(half_t)sacc[j][2 * i], (half_t)sacc[j][2 * i + 1]};
+              th[j][i] = yh * yh;
+            }
+          // maximum of the 16 pairs with the packed three-input maximum (NaN-propagating): 5 + 2 + 1 instructions
+          auto max3 = [](f16x2 a, f16x2 b, f16x2 c) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c); };
+          const f16x2 m0 = max3(th[0][0], th[0][1], th[0][2]), m1 = max3(th[0][3], th[0][4], th[0][5]);
+          const f16x2 m2 = max3(th[0][6], th[0][7], th[1][0]), m3 = max3(th[1][1], th[1][2], th[1][3]);
+          const f16x2 m4 = max3(th[1][4], th[1][5], th[1][6]);
+          const f16x2 m = __builtin_elementwise_maximum(max3(m0, m1, m2), max3(m3, m4, th[1][7]));
+          const half_t mx = __builtin_elementwise_maximum(m[0], m[1]);
           auto all_within = [&](float t2) { return __builtin_amdgcn_ballot_w64(!(mx <= (half_t)t2)) == 0; };     // NaN counts as beyond
-          if (!quadratic) {
+          // s + t (B0 + B1 t + ...), stage by stage over eight independent pairs, so that no instruction waits for the one before
+          auto polynomial = [&](auto... coefficient) {
+            constexpr int N = sizeof...(coefficient);
+            const half_t c[N] = {(half_t)coefficient...};
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < 2; ++j) {
+              f16x2 r[8], w[8];
 #pragma unroll
-              for (int i = 0; i < 8; ++i) {
-                const f16x2 yh = f16x2{(half_t)sacc[j][2 * i], (half_t)sacc[j][2 * i + 1]};
-                th[j][i] = yh * yh;
-              }
-            // maximum of the 16 pairs with the packed three-input maximum (NaN-propagating): 5 + 2 + 1 instructions
-            auto max3 = [](f16x2 a, f16x2 b, f16x2 c) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c); };
-            const f16x2 m0 = max3(th[0][0], th[0][1], th[0][2]), m1 = max3(th[0][3], th[0][4], th[0][5]);
-            const f16x2 m2 = max3(th[0][6], th[0][7], th[1][0]), m3 = max3(th[1][1], th[1][2], th[1][3]);
-            const f16x2 m4 = max3(th[1][4], th[1][5], th[1][6]);
-            const f16x2 m = __builtin_elementwise_maximum(max3(m0, m1, m2), max3(m3, m4, th[1][7]));
-            mx = __builtin_elementwise_maximum(m[0], m[1]);
-            poly = all_within(kPolyT2);
-            low = poly && all_within(kLowT2);
-            quadratic = low && all_within(kQuadT2);
-          }
-          cool = quadratic;
-          if (quadratic) {
+              for (int i = 0; i < 8; ++i) r[i] = __builtin_elementwise_fma(f16x2{c[N - 1], c[N - 1]}, th[j][i], f16x2{c[N - 2], c[N - 2]});
+#pragma unroll
+              for (int n = N - 3; n >= 0; --n)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) r[i] = __builtin_elementwise_fma(r[i], th[j][i], f16x2{c[n], c[n]});
+#pragma unroll
+              for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) w[i][h] = (half_t)__builtin_fmaf((float)th[j][i][h], (float)r[i][h], sacc[j][2 * i + h]);
+              finish(j, w);
+            }
+          };
+          if (all_within(kPolyT2)) {
+            polynomial(4.0f * kPolyA1, 16.0f * kPolyA3, 64.0f * kPolyA5);
+          } else if (all_within(kMidT2)) {
+            polynomial(kMidB[0], kMidB[1], kMidB[2], kMidB[3], kMidB[4]);
+          } else {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
               f16x2 w[8];
 #pragma unroll
-              for (int i = 0; i < 8; ++i)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) w[i][h] = (half_t)__builtin_fmaf(sacc[j][2 * i + h], sacc[j][2 * i + h], sacc[j][2 * i + h]);
+              for (int i = 0; i < 8; ++i) w[i] = f16x2{(half_t)silu_half_domain(sacc[j][2 * i]), (half_t)silu_half_domain(sacc[j][2 * i + 1])};
               finish(j, w);
-            }
-          } else {
-            // s + t (B0 + B1 t + ...), stage by stage over eight independent pairs, so that no instruction waits for the one before
-            auto polynomial = [&](auto... coefficient) {
-              constexpr int N = sizeof...(coefficient);
-              const half_t c[N] = {(half_t)coefficient...};
-#pragma unroll
-              for (int j = 0; j < 2; ++j) {
-                f16x2 r[8], w[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) r[i] = __builtin_elementwise_fma(f16x2{c[N - 1], c[N - 1]}, th[j][i], f16x2{c[N - 2], c[N - 2]});
-#pragma unroll
-                for (int n = N - 3; n >= 0; --n)
-#pragma unroll
-                  for (int i = 0; i < 8; ++i) r[i] = __builtin_elementwise_fma(r[i], th[j][i], f16x2{c[n], c[n]});
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-#pragma unroll
-                  for (int h = 0; h < 2; ++h) w[i][h] = (half_t)__builtin_fmaf((float)th[j][i][h], (float)r[i][h], sacc[j][2 * i + h]);
-                finish(j, w);
-              }
-            };
-            if (low) {
-              polynomial(kLowB[0], kLowB[1]);
-            } else if (poly) {
-              polynomial(4.0f * kPolyA1, 16.0f * kPolyA3, 64.0f * kPolyA5);
-            } else if (all_within(kMidT2)) {
-              polynomial(kMidB[0], kMidB[1], kMidB[2], kMidB[3], kMidB[4]);
-            } else {
-#pragma unroll
-              for (int j = 0; j < 2; ++j) {
-                f16x2 w[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) w[i] = f16x2{(half_t)silu_half_domain(sacc[j][2 * i]), (half_t)silu_half_domain(sacc[j][2 * i + 1])};
-                finish(j, w);
-              }
             }
           }
         }

@@ -28,10 +28,9 @@ def weight_error(x, top):
     """Largest error of a weight at logit x in a block whose largest |logit| is top: that of the approximation (csrc/attn_mfma.hip), four roundings of its fp16 arithmetic on the
     term beside the logit, and the rounding of the weight."""
     t = (x / 2) ** 2
-    if top <= 0.25 + 2.0 ** -12:
-        approx, term = t * t / 3, 0.0
-    elif top <= 4.0 + 2.0 ** -8:
-        approx, term = np.where(top <= 1.001, 1.1e-3 * t, np.where(top <= 2.002, 3.5e-3 * t, 5.4e-4)), np.minimum(t, np.abs(x) / 2)
+    if top <= 4.0 + 2.0 ** -8:
+        # the short polynomial's bracket is off by 3.4e-3 of itself where that is most, at the smallest logits (a1 against 1/4); the long one's weight by 5.4e-4
+        approx, term = np.where(top <= 2.002, 3.5e-3 * t, 5.4e-4), np.minimum(t, np.abs(x) / 2)
     else:
         approx, term = 0.0, 0.0
     return approx + 4 * H16 * term + H16 * np.abs(silu(x)) + 2.0 ** -25
