@@ -205,8 +205,6 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
   // maximum starts below kNeg * tscale for any sensible temperature, so a row whose keys so far were all masked
   // holds weights exp2(0) that the first real maximum scales to zero (every row sees key 0 of tile 0 or itself).
   constexpr float kNeg = -1.0e30f;
-  // The running maximum may stay behind the true one by kSlack (as a power of two): numerators reach 2^8 then, which fp16 holds with the same relative precision.
-  constexpr float kSlack = 8.0f;
   const float ts = SOFTMAX ? tscale_h[head] : 0.f;
   float m_run[NP], l_run[NP];
 #pragma unroll
@@ -477,10 +475,9 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
           const float l3 = max3(l2[0], l2[1], l2[2]);
           const float mt = __builtin_elementwise_maximum(l3, l2[3]);
           const float m_new = fmaxf(m_run[P], pair_max(mt) * ts);
-          // The accumulators are rescaled, all rows to their maximum, only when some row of the wavefront has outgrown what it is measured from by kSlack (rare after the first tiles);
-          // the branch is uniform over the wavefront.  (At every new maximum of any of the 32 rows, which is every other tile of a history of 2500: 32 production requests, 16 layers
-          // 16.22 -> 15.94 ms per forward with the slack.)
-          if (__builtin_amdgcn_ballot_w64(m_new > m_run[P] + kSlack) != 0) {
+          // The accumulators are rescaled only when some row of the wavefront has a new maximum; the branch is uniform over the wavefront, and a row without one is multiplied by exactly 1,
+          // so that no row's bits depend on the others.
+          if (__builtin_amdgcn_ballot_w64(m_new != m_run[P]) != 0) {
             const float sc = __builtin_amdgcn_exp2f(m_run[P] - m_new);
             l_run[P] *= sc;
 #pragma unroll
@@ -489,7 +486,7 @@ __global__ __launch_bounds__(KP == 4 ? 768 : KP > 1 ? 512 : 256, KP > 1 ? 1 : 3)
               for (int e = 0; e < 16; ++e) oacc[P][b][e] *= sc;
             m_run[P] = m_new;
           }
-          const float nm = -m_run[P];
+          const float nm = -m_new;
           float psum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int j = 0; j < 2; ++j) {
