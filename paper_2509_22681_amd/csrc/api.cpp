@@ -207,7 +207,7 @@ void run_group(flame_gr *h, const flame_gr_weights &w, const Group &G, float *sc
   if (pass_n == 0) return;
   const int64_t plane = sh.ws_rows * d;
   // K3 of a layer and K1 of the next as one kernel (not where a layer's planes are to be looked at)
-  const bool fused = dt == FLAME_GR_BF16 && h->capture_layer < 0 && (layer_fused(d, pass_n) || layer_fused_streaming(d, pass_n));
+  const bool fused = dt == FLAME_GR_BF16 && h->capture_layer < 0 && layer_fused(d);
   // one-pass: the four planes of the handle, reused by every layer; two-stage: U and Q there, V and K in the
   // layer's own pair of planes, where the candidate pass finds the history rows that the history pass left
   auto planes_of = [&](int l) {

@@ -129,11 +129,10 @@ void launch_k3_fused(const void *O, const void *U, const void *gamma, const void
                      void *Xh, void *Xl, bool lo_is_zero, const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first,
                      const Shape &sh, hipStream_t s);
 
-// K3 of a layer and K1 of the next in one kernel (layer_mfma.hip), where layer_fused or layer_fused_streaming says so: the rows' planes of the next layer are made from the new
+// K3 of a layer and K1 of the next in one kernel (layer_mfma.hip), for the widths that layer_fused names: the rows' planes of the next layer are made from the new
 // residual rows; all_hist, all_cand: all four planes for history (candidate) blocks, or V and K only.  layer_setup: once per handle (raises the LDS limit).
 // U may be the plane planes.u: a workgroup has read its rows of the one before it writes them to the other.
-bool layer_fused(int d, int n_blk);
-bool layer_fused_streaming(int d, int n_blk);
+bool layer_fused(int d);
 hipError_t layer_setup(int d);
 void launch_layer(const void *O, const void *U, const void *gamma, const void *beta, const void *W2p_layer, const void *b2, void *Xh, void *Xl, bool lo_is_zero,
                   const RowBlock *blocks, const int32_t *blk_list, int n_blk, int blk_first, const void *W1h_next, const void *b1_next, PlanePtrs planes, bool all_hist, bool all_cand,

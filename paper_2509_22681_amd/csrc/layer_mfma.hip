@@ -344,19 +344,12 @@ __global__ __launch_bounds__(512, 4) void layer_kernel(const half_t *__restrict_
 
 }  // namespace
 
-// From the first row block on, d = 128, 192 and 256: forwards of 4 layers on two kernels a layer / on this one (us), by 64-row blocks:
-//   d = 128: 5: 86 / 72, 100: 104 / 86, 320: 150 / 119, 1025: 324 / 268, 8200: 1821 / 1688;  d = 192: 5: 96 / 81, 130: 149 / 127, 510: 262 / 205, 2050: 790 / 710;
-//   d = 256: 5: 90 / 87, 65: 124 / 113, 160: 147 / 136, 510: 302 / 267, 1025: 589 / 515, 8200: 3735 / 3661.
+// At every size of d = 128, 192 and 256: forwards of 4 layers on two kernels a layer / on this one (us), by 64-row blocks (the two kernels stream past 1024, 682 and 512 of them):
+//   d = 128: 5: 86 / 72, 100: 104 / 86, 320: 150 / 119, 1025: 324 / 268, 1140: 347 / 282, 1278: 372 / 309, 8200: 1821 / 1688;
+//   d = 192: 5: 96 / 81, 130: 149 / 127, 510: 262 / 205, 684: 333 / 274, 768: 350 / 287, 852: 398 / 336, 2050: 790 / 710;
+//   d = 256: 5: 90 / 87, 65: 124 / 113, 160: 147 / 136, 510: 302 / 267, 561: 356 / 305, 639: 384 / 325, 1025: 589 / 515, 8200: 3735 / 3661.
 // (Stores and loads past the caches make it slower in launches that stream, too: d = 192, 1280 blocks 454 -> 480 us, d = 256, 640 blocks 330 -> 342.)
-// Between kStreamBytes and kLayerStreamBytes of a plane the two kernels run: the tests hold the two sides of the first line to the same bits.
-constexpr int kLayerFrom192 = 1, kLayerFrom256 = 1;
-constexpr int64_t kLayerStreamBytes = 20 << 20;
-static bool layer_width(int d) { return d == 128 || d == 192 || d == 256; }
-bool layer_fused(int d, int n_blk) {
-  const int from = d == 192 ? kLayerFrom192 : d == 256 ? kLayerFrom256 : 1;
-  return layer_width(d) && n_blk >= from && (int64_t)n_blk * kRowAlign * d * 2 <= kStreamBytes;
-}
-bool layer_fused_streaming(int d, int n_blk) { return layer_width(d) && (int64_t)n_blk * kRowAlign * d * 2 >= kLayerStreamBytes; }
+bool layer_fused(int d) { return d == 128 || d == 192 || d == 256; }
 
 // Row blocks that a workgroup takes whole; each of the others is two workgroups of half of it.  Beyond a multiple of the compute units, blocks that fit them as halves, one each, go
 // as halves: the most rows on a compute unit are then half a block fewer.  (Twice the traffic of weights for those; more of them would not shorten the longest.)

@@ -1,21 +1,21 @@
 """The kernel that makes a layer's output projection and the next layer's projections in one launch, against the two kernels that run
 where a handle's planes are to be looked at: the same instructions in the same order, so the same bits, in each pass that can take it,
-on both sides of the sizes at which it begins and ends (which of them ran is read from the launches that a profiled handle counts); and against the fp64 oracle at the hot bar."""
+from two row blocks to sizes that stream (which of them ran is read from the launches that a profiled handle counts); and against the fp64 oracle at the hot bar."""
 import numpy as np
 import pytest
 
 import oracle
 from paper_2509_22681_amd import workloads as W
 from tests.test_gpu_parity import TOL_HOT, score_err
-from tests.test_routes import LAYER_BLOCKS
 
 pytestmark = pytest.mark.gpu
 
-# (width, heads, 64-row blocks of the batch): sizes between, and both sides of where the rule begins and ends (an even number of blocks)
-SIZES = [(128, 2, 2), (128, 4, 66), (192, 6, 132), (256, 8, 310)]
+# (width, heads, 64-row blocks of the batch, an even number): the smallest, sizes between, and both sides of the 16 MB of a plane past which the two kernels stream
+SIZES = [(128, 2, 2), (192, 3, 2), (256, 4, 2), (128, 4, 66), (192, 6, 132), (256, 8, 310)]
 for width, heads in ((128, 2), (192, 3), (256, 4)):
-    first, last = LAYER_BLOCKS[width]
-    SIZES += [(width, heads, n) for n in (first - 2, first, last // 2 * 2, last // 2 * 2 + 2) if n > 2]
+    last = (16 << 20) // (64 * 2 * width)
+    SIZES += [(width, heads, n) for n in (last // 2 * 2, last // 2 * 2 + 2)]
+SIZES += [(256, 4, 600), (192, 3, 800), (128, 2, 1300)]
 
 
 def batch(blocks):
@@ -59,8 +59,7 @@ def test_one_launch_per_layer_gives_the_same_bits(d, H, blocks, kind):
     want = scores(False, True, launches=two)
     assert np.isfinite(want).all()
     assert np.array_equal(scores(False, False, launches=one), want)
-    first, last = LAYER_BLOCKS[d]
-    assert two["uvqk"] == 3 and one["uvqk"] == (1 if first <= blocks <= last else 3)
+    assert two["uvqk"] == 3 and one["uvqk"] == 1          # (the projections of the first layer)
     assert np.array_equal(scores(False, False, n_streams=2), want)
     assert np.array_equal(scores(True, False), want) and np.array_equal(scores(True, True), want)
     if blocks <= 160:

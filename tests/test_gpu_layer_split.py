@@ -9,8 +9,8 @@ from tests.test_gpu_layer_kernel import batch
 pytestmark = pytest.mark.gpu
 
 UNITS = 256           # compute units: blocks beyond a multiple of them go as halves up to half as many
-# (an even number of blocks); 20 MB of a plane from 640 blocks of d = 256 and 854 of d = 192 on
-SIZES = [(128, 2, n) for n in (UNITS // 2, UNITS // 2 + 2, UNITS, UNITS + 2, 2 * UNITS + 4)] + [(192, 3, n) for n in (UNITS + UNITS // 2, UNITS + UNITS // 2 + 2, 854)] + [(256, 4, n) for n in (UNITS // 2, 640, 900)]
+# (an even number of blocks); the two kernels stream from 16 MB of a plane on: past 512 blocks of d = 256, 682 of d = 192 and 1024 of d = 128
+SIZES = [(128, 2, n) for n in (UNITS // 2, UNITS // 2 + 2, UNITS, UNITS + 2, 2 * UNITS + 4, 5 * UNITS + 2)] + [(192, 3, n) for n in (UNITS + UNITS // 2, UNITS + UNITS // 2 + 2, 854)] + [(256, 4, n) for n in (UNITS // 2, 640, 900)]
 
 
 @pytest.mark.parametrize("d,H,blocks", SIZES)

@@ -16,9 +16,8 @@ def constants(source, pattern):
     return {k: int(v) for k, v in re.findall(pattern + r" = (\d+)(?=[,;])", (CSRC / source).read_text())}
 
 
-# Limits of the rules below, as the sources have them: of the key-ordered attention, and the 64-row blocks from and up to which the layer kernel runs
+# Limits of the key-ordered attention, as the source has them
 KEY_ORDERED = constants("attn_mfma.hip", r"\bkAttnSeq(\w+)")
-LAYER_BLOCKS = {d: (first, (16 << 20) // (64 * 2 * d)) for d, first in {128: 1, **{int(k): v for k, v in constants("layer_mfma.hip", r"\bkLayerFrom(\d+)").items()}}.items()}
 
 
 def library():
@@ -33,18 +32,17 @@ def key_ordered(grid, n_items, n_cand, longest):
     return f(grid, n_items, n_cand, longest)
 
 
-def layer_fused(d, blocks):
-    f = library()._ZN5flame11layer_fusedEii
+def layer_fused(d):
+    f = library()._ZN5flame11layer_fusedEi
     f.restype = ctypes.c_bool
-    return f(d, blocks)
+    return f(d)
 
 
-def test_layer_kernel_runs_between_its_limits():
-    assert set(LAYER_BLOCKS) == {128, 192, 256}
-    for d, (first, last) in LAYER_BLOCKS.items():
-        assert [layer_fused(d, n) for n in (first - 1, first, last, last + 1)] == [False, True, True, False]
-    for d in (64, 96, 320, 384, 512, 1024):
-        assert not any(layer_fused(d, n) for n in (1, 64, 160, 256, 512, 1024))
+def test_layer_kernel_runs_for_its_widths():
+    """By width alone, at every size of a launch: this is the whole rule (test_gpu_layer_kernel.py counts the launches)."""
+    assert [d for d in range(32, 1025, 32) if layer_fused(d)] == [128, 192, 256]
+    call = re.search(r"const bool fused = (.*?);", (CSRC / "api.cpp").read_text()).group(1)
+    assert re.findall(r"\w+_fused\w*\([^)]*\)", call) == ["layer_fused(d)"]
 
 
 # (shortest and longest history of the row, limit where history tiles prevail)
