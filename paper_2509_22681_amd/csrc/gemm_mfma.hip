@@ -576,7 +576,7 @@ static void launch_small(const void *Xh, const void *W1h, const void *b1, PlaneP
 // Up to this many 64-row blocks a launch runs on the small tiles.  The wider the model, the fewer workgroups of the small tile fit a
 // compute unit (its X block is 128 d bytes of LDS) and the more its W traffic, once per 64 rows, weighs against the large
 // tile's, once per 256.  Microseconds per launch, small against large, four planes:
-//   d = 512: 16 blocks 11.2 / 18.5, 48: 16.7 / 19.8, 96: 25.6 / 26.4, 128: 31.6 / 29.3
+//   d = 512: 16 blocks 11.2 / 18.5, 48: 16.7 / 19.8, 96: 25.6 / 26.4, 128: 31.6 / 29.3 (small tiles of 128 columns; of 256: below)
 //   d = 384: 16: 10.1 / 16.3, 128: 21.5 / 23.4, 384: 48 / 52, 512: 61 / 60
 //   d = 256: 16: 8.6 / 13.6, 256: 21.8 / 23.6, 1024: 62 / 63, 2048: 122 / 116
 //   d = 192: 16: 7.9 / 10.1, 256: 16.9 / 19.7, 2048: 84 / 91, 8192: 340 / 345 (the large tile is 64 columns wide there)
@@ -584,10 +584,10 @@ static void launch_small(const void *Xh, const void *W1h, const void *b1, PlaneP
 //   d = 64: 512: 12.9 / 14.8, 2048: 22.2 / 25.3, 8192: 64 / 81, 16384: 143 / 182
 // d = 384 and 512 from these blocks on with eight wavefronts, 64 rows x 256 columns, which halve the traffic of X, once per column tile, where there are enough tiles all the same.
 // Forwards of 8 layers (us), 128 columns wide (or the large tile, from 97 and 385 blocks on) / 256:
-//   d = 512: 16: 212 / 217, 18: 236 / 230, 45: 349 / 350, 63: 463 / 452, 90: 385 / 367, 150: 575 / 534, 250: 738 / 727, 400: 1088 / 1065, 500: 1283 / 1301, 1000: 2481 / 2585
+//   d = 512: 16: 212 / 217, 18: 236 / 230, 45: 349 / 350, 63: 463 / 452, 90: 385 / 367, 150: 575 / 534, 250: 738 / 727, 310: 988 / 956, 350: 1064 / 1022, 400: 1177 / 1125, 480: 1349 / 1302
+//     (64 + 64 from 310 on; 512 + 128: 380: 1102 / 1086, 480: 1389 / 1342, 640: 1786 / 1778; 2048 + 512: 480: 1787 / 1776, 560: 2095 / 2121;  64 + 64: 768: 2041 / 2010, 1000: 2597 / 2671)
 //   d = 384: 100: 330 / 351, 180: 485 / 493, 210: 526 / 524, 300: 724 / 721, 450: 926 / 901, 800: 1542 / 1529, 1000: 1772 / 1836
-// (Stores past the caches: d = 512, 300 blocks 904, 400: 1091; d = 384, 800: 1567.)
-// The line of d = 512 lies at 300, not at 400 where the two cross over: the stage-by-stage oracle case of the large tile has 309 row blocks, and what lies between is 2 %.
+// (Stores past the caches slow the wide tile down: d = 512, 400 blocks 1065 -> 1091; d = 384, 800: 1529 -> 1567.)
 // Between, d = 512: up to 32 blocks the wide tiles are one for each compute unit, and up to 47 a second one for less than half of them (45 blocks: 13.9 / 14.8 us per launch).
 constexpr int kWideFrom512 = 17, kWideOneEach512 = 32, kWideAgainFrom512 = 48, kWideFrom384 = 210;
 static bool wide_512(int n_blk) { return n_blk >= kWideFrom512 && (n_blk <= kWideOneEach512 || n_blk >= kWideAgainFrom512); }
@@ -597,7 +597,7 @@ static int small_tile_blocks(int d) {
     case 128: return 8192;
     case 256: return 1024;
     case 384: return 800;
-    case 512: return 300;
+    case 512: return 480;
     default: return 0;                                          // no instance
   }
 }

@@ -29,10 +29,12 @@ HOT = {
     "d512": dict(L=[3001, 129], M=[333, 65], d=512, H=8, n_layers=2, n_buckets=128, max_rel_dist=4096, seed=11),
     # the long workload's table: 512 buckets, D = 16384, distances reach the log-spaced half (>= 256) and beyond 4096
     "table512": dict(L=[4100], M=[70], d=512, H=8, n_layers=2, n_buckets=512, max_rel_dist=16384, seed=12),
-    # the instances of the large batches: K1's large tile and whole row blocks of K3, all three kernels storing past the caches
-    # (test_many_rows_is_past_the_limits holds the sizes against the limits)
+    # the instances of the large batches: whole row blocks of K3, and K2 and K3 storing past the caches (test_many_rows_is_past_the_limits holds the sizes against the limits)
     "many_rows": dict(L=[1500, 300, 1901] + [197 + 89 * i % 400 for i in range(30)], M=[100, 700, 31] + [17 + 53 * i % 120 for i in range(30)], d=512, H=8,
                       n_layers=2, n_buckets=128, max_rel_dist=2048, seed=13),
+    # and K1's large tile, which more row blocks take: many short requests beside two of some length
+    "many_requests": dict(L=[901, 530] + [1 + 37 * i % 64 for i in range(240)], M=[70, 40] + [1 + 29 * i % 48 for i in range(240)], d=512, H=8, n_layers=2, n_buckets=64,
+                          max_rel_dist=1024, seed=14),
 }
 
 
@@ -49,16 +51,18 @@ def oracle_with_stages(wl, weights=None):
 
 
 def test_many_rows_is_past_the_limits():
-    """The launches of many_rows are past the size of a plane from which K1, K2 and K3 store past the caches (and K3 takes whole row blocks), and past the
-    small tile of K1: the limits in csrc/kernels.h and csrc/gemm_mfma.hip."""
-    c = HOT["many_rows"]
-    blocks = sum(-(-n // 64) for n in c["L"] + c["M"])
-    items = sum(-(-n // 128) for n in c["L"] + c["M"])
+    """The launches of many_rows and many_requests are past the size of a plane from which K1's large tile, K2 and K3 store past the caches (and K3 takes whole row blocks), and those of
+    many_requests past the small tile of K1: the limits in csrc/kernels.h and csrc/gemm_mfma.hip."""
     csrc = Path(W.__file__).parent / "csrc"
     m = re.search(r"kStreamBytes = (\d+) << (\d+);", (csrc / "kernels.h").read_text())
     stream = int(m.group(1)) << int(m.group(2))
     small = int(re.search(r"case 512: return (\d+);", (csrc / "gemm_mfma.hip").read_text()).group(1))
-    assert blocks * 64 * c["d"] * 2 > stream and items * 128 * c["d"] * 2 > stream and blocks > small, (blocks, items, stream, small)
+    for name in ("many_rows", "many_requests"):
+        c = HOT[name]
+        blocks = sum(-(-n // 64) for n in c["L"] + c["M"])
+        items = sum(-(-n // 128) for n in c["L"] + c["M"])
+        assert blocks * 64 * c["d"] * 2 > stream and items * 128 * c["d"] * 2 > stream, (name, blocks, items, stream)
+    assert blocks > small, (blocks, small)
 
 
 @pytest.fixture(scope="module")
