@@ -148,6 +148,12 @@ int retire(flame_dso *d, int idx) {
   return FLAME_GR_OK;
 }
 
+// Gathered rows are uploaded ahead of the flush in pieces of this many bytes or more.  A piece is one or two copies of some 10 us each, which pay where the copying of the next
+// requests into the pinned buffer takes longer.  Eight requests at an idle orchestrator, d = 512, 2 layers (us), no early upload / pieces of 1 / 2 / 3 MB / each request by itself:
+//   64 + 16: 129 / 129 / 129 / 129 / 221;  256 + 64: 205 / 193 / 213 / 205 / 276;  512 + 128: 312 / 295 / 284 / 294 / 354;  1024 + 256: 550 / 517 / 470 / 471 / 517;
+//   2048 + 256: 886 / 766 / 767 / 737 / 769;  3072 + 512: 1592 / 1242 / 1138 / 1137 / 1143;  d = 256, 4 layers, 512 + 128: 264 / 251 / 272 / 263 / 334
+constexpr size_t kUploadBytes = (size_t)3 << 20;
+
 // Jagged mode: upload the gathered rows that are not on their way yet.
 int upload(flame_dso *d, Executor &e) {
   const size_t row = (size_t)d->d * d->elt;
@@ -352,8 +358,8 @@ static int submit_request(flame_dso_t *d, const void *history_emb, int32_t hist_
       if (e.n_req == d->max_batch) {
         int rc = flush(d, d->gathering);
         if (rc) return rc;
-      } else if (d->busy_q.empty()) {
-        // Nothing runs that would hide the upload: each request goes to the GPU under the copying of the next (16 requests in micro-batches of 8, production model:
+      } else if (d->busy_q.empty() && (size_t)(e.n_hist - e.sent_hist + e.n_cand - e.sent_cand) * row >= kUploadBytes) {
+        // Nothing runs that would hide the upload: what has gathered goes to the GPU under the copying of the next requests (16 requests in micro-batches of 8, production model:
         // 12.0 -> 11.5 ms; behind a running batch, 80 batches of 8 x (1024 + 514), 5925 -> 5510 requests/s).  The request has joined its batch: a failure here is not its own,
         // and the flush, which sends what is still missing, reports it if it lasts.
         if (upload(d, e) != FLAME_GR_OK) {

@@ -1,5 +1,6 @@
 """Micro-batches of the request orchestrator without a GPU: the runtime and the forward are stand-ins, "device" memory is host memory.  What reaches the forward is whole and in place
-however a batch was uploaded and whatever flushed it; a failed upload ahead of the flush is not an error of the submit that made it."""
+however a batch was uploaded and whatever flushed it; short requests share their uploads; a failed upload ahead of the flush is not an error of the submit that made it."""
+import re
 import subprocess
 import sys
 
@@ -9,9 +10,10 @@ STAND_INS = r"""
 #include <cstdlib>
 #include <cstring>
 #include <cstdint>
-static int fail = 0, last_error = 0;
+static int copies = 0, fail = 0, last_error = 0;
 extern "C" {
 void stub_fail(int n) { fail = n; }
+int stub_copies() { const int n = copies; copies = 0; return n; }
 int hipGetLastError() { const int e = last_error; last_error = 0; return e; }
 const char *hipGetErrorString(int) { return "made to fail"; }
 int hipMalloc(void **p, size_t n) { *p = calloc(n ? n : 1, 1); return 0; }
@@ -22,6 +24,7 @@ int hipMemset(void *p, int v, size_t n) { memset(p, v, n); return 0; }
 int hipMemcpyAsync(void *d, const void *s, size_t n, int kind, void *) {
   if (kind == 1) {                                   // to the device
     if (fail > 0) { --fail; return last_error = 1; }
+    ++copies;
   }
   memcpy(d, s, n);
   return 0;
@@ -98,6 +101,16 @@ for how in ("wait", "drain", "flush", "full"):
             B.flame_dso_drain(dso)
         check(rs)
 
+# copies of a batch: short requests two, however many they are; long ones two each, of rows there are
+stub.stub_copies()
+for ns, want in (([short] * 5, 2), ([0] * 5, 1), ([long] * 5, 10), ([long, short, short, short, short], 4)):
+    rs = [request(n, 3) for n in ns]
+    for r in rs: submit(r)
+    B.flame_dso_drain(dso)
+    check(rs)
+    got = stub.stub_copies()
+    assert got == want, (ns, got, want)
+
 # an upload ahead of the flush fails: the submit still gives its ticket, nothing is lost, and no error stays behind for the forward
 for n_fail in (1, 2):
     rs = [request(long, 9), request(long, 4), request(short, 2)]
@@ -121,7 +134,9 @@ B.flame_dso_destroy(dso)
 
 
 def test_batches_are_whole_however_they_were_uploaded(tmp_path):
-    piece = 1 << 20
+    with open(f"{build_mod.CSRC}/dso.cpp") as f:
+        m = re.search(r"kUploadBytes = \(size_t\)(\d+) << (\d+);", f.read())
+    piece = int(m.group(1)) << int(m.group(2))
     stub = tmp_path / "libstandin.so"
     subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-x", "c++", "-", "-o", stub], input=STAND_INS, text=True, check=True)
     r = subprocess.run([sys.executable, "-c", DRIVE, stub, build_mod.HERE + "/..", str(piece)], capture_output=True, text=True, timeout=120)
