@@ -585,7 +585,8 @@ static void launch_small(const void *Xh, const void *W1h, const void *b1, PlaneP
 // d = 384 and 512 from these blocks on with eight wavefronts, 64 rows x 256 columns, which halve the traffic of X, once per column tile, where there are enough tiles all the same.
 // Forwards of 8 layers (us), 128 columns wide (or the large tile, from 97 and 385 blocks on) / 256:
 //   d = 512: 16: 212 / 217, 18: 236 / 230, 45: 349 / 350, 63: 463 / 452, 90: 385 / 367, 150: 575 / 534, 250: 738 / 727, 310: 988 / 956, 350: 1064 / 1022, 400: 1177 / 1125, 480: 1349 / 1302
-//     (64 + 64 from 310 on; 512 + 128: 380: 1102 / 1086, 480: 1389 / 1342, 640: 1786 / 1778; 2048 + 512: 480: 1787 / 1776, 560: 2095 / 2121;  64 + 64: 768: 2041 / 2010, 1000: 2597 / 2671)
+//     (64 + 64 from 310 on, 640: 1772 / 1734, 1000: 2597 / 2671; 512 + 128: 380: 1102 / 1086, 640: 1786 / 1778; 2048 + 512: 560: 2095 / 2121).  The line of d = 512 lies where the first
+//     form of call stops to gain: prefill and scores of 4 layers, 1000 + 64, by blocks of the history pass: 288: 752 / 751, 352: 828 / 831, 368: 834 / 850, 448: 909 / 925
 //   d = 384: 100: 330 / 351, 180: 485 / 493, 210: 526 / 524, 300: 724 / 721, 450: 926 / 901, 800: 1542 / 1529, 1000: 1772 / 1836
 // (Stores past the caches slow the wide tile down: d = 512, 400 blocks 1065 -> 1091; d = 384, 800: 1529 -> 1567.)
 // Between, d = 512: up to 32 blocks the wide tiles are one for each compute unit, and up to 47 a second one for less than half of them (45 blocks: 13.9 / 14.8 us per launch).
@@ -597,7 +598,7 @@ static int small_tile_blocks(int d) {
     case 128: return 8192;
     case 256: return 1024;
     case 384: return 800;
-    case 512: return 480;
+    case 512: return 352;
     default: return 0;                                          // no instance
   }
 }

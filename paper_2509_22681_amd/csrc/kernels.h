@@ -147,7 +147,7 @@ constexpr int kK3CutInFour = 22, kK3CutInTwo = 64, kK3OneEach = 128, kK3HalfBloc
 // against nontemporal: 3 MB per plane (one request, d = 512) 1033 against 1078 us, 10 MB (32 x 640 rows, d = 256) 289 against 308 us; 27 MB equal;
 // 100 MB 5.15 against 4.98 ms, 500 MB 65.4 against 63.7 ms.  (At the line the eight arrays of a layer are 128 MB, half of the cache behind the L2s.)
 // K1's large tile and K3 count the rows of the launch, K2 128 rows per tile.  K1's small tile has a line of its own (kSmallStreamBytes) and none for
-// d >= 256, which it leaves at 31 to 39 MB: d = 256, 32 MB, 4 layers of 512 x (64 + 64) 615 us, with the large tile 625.  The
+// d >= 256, which it leaves at 23 to 39 MB: d = 256, 32 MB, 4 layers of 512 x (64 + 64) 615 us, with the large tile 625.  The
 // kernels of widths without a fused K3 (ln_gate, output projection) store through the caches at any size.
 constexpr int64_t kStreamBytes = 16 << 20;
 
