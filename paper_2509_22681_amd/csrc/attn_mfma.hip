@@ -888,10 +888,10 @@ hipError_t attn_setup(const Shape &sh) {
 // Workgroups of 128 rows (tiles x heads) up to which a launch takes the key-ordered split, by the longest history of the pass.  Its workgroups have 64 rows and a
 // compute unit each, so up to 128 are one round of them; beyond, it pays only where most tiles are history tiles, whose chains of keys are half as long on average, and the longest
 // chain is what the other kernel takes.  Forwards of four layers, one wavefront per group / split (us):
-//   1024 + 256, 8 heads: 80 workgroups 147 / 126, 160: 165 / 144, 240: 179 / 172, 320: 208 / 213; 4 heads: 80: 141 / 119, 240: 161 / 152, 320: 175 / 178; 1024 + 1024: 128: 157 / 136, 256: 186 / 189
-//   2048 + 256, 8 heads: 144: 214 / 173, 288: 256 / 240, 432: 286 / 295; 3 heads: 108: 184 / 142, 216: 207 / 175, 324: 212 / 207; 8192 + 512, 2 heads: 136: 520 / 330
-//   512 + 128, 8 heads: 80: 124 / 115, 120: 131 / 124, 160: 141 / 136, 200: 151 / 151; 4 heads: 160: 129 / 123, 240: 137 / 139
-//   320 + 128, 2 heads: 24: 91 / 88, 128: 107 / 109; 128 + 64: 40: 82 / 84, 160: 98 / 119 (a history of one or two 256-key tiles has no chain to shorten)
+//   1024 + 256, 8 heads: 80 workgroups 153 / 128, 160: 167 / 142, 240: 177 / 164, 320: 202 / 204; 4 heads: 80: 145 / 119, 240: 166 / 154, 320: 176 / 178; 1024 + 1024: 128: 156 / 131, 256: 182 / 182
+//   2048 + 256, 8 heads: 144: 222 / 173, 288: 256 / 231, 432: 286 / 291; 3 heads: 108: 196 / 147, 216: 219 / 179, 324: 222 / 210; 8192 + 512, 2 heads: 136: 514 / 300
+//   512 + 128, 8 heads: 80: 127 / 113, 120: 132 / 119, 160: 140 / 132, 200: 146 / 145; 4 heads: 160: 131 / 123, 240: 137 / 139
+//   320 + 128, 2 heads: 24: 79 / 75, 128: 95 / 95; 128 + 64: 40: 69 / 71, 160: 84 / 105 (a history of one or two 256-key tiles has no chain to shorten)
 // Candidate tiles alone (one layer), 4 heads: 512 + 128: 64: 48 / 46, 128: 53 / 53, 160: 59 / 65; 2048 + 128: 64: 87 / 79, 128: 140 / 136, 160: 152 / 169.
 constexpr int kAttnSeqHistory = 384, kAttnSeqWorkgroups = 128;                            // from this history on; up to this many workgroups, and where history tiles prevail
 constexpr int kAttnSeqLongHistory = 1024, kAttnSeqLongWorkgroups = 240, kAttnSeqLongerHistory = 2048, kAttnSeqLongerWorkgroups = 288;   // up to these
